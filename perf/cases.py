@@ -24,6 +24,7 @@ spectrum (features of standard deviation 1/i, rotated).
 """
 import math
 
+import numpy as np
 import torch
 
 import paper_2207_04228_amd as bed
@@ -154,3 +155,49 @@ def tolerance(case):
     if case["decay"]:
         return {"rel": 4e-5, "max": 8e-4}
     return {"rel": 4e-5, "max": 2e-4}
+
+
+def _couplings(lam, degree):
+    """[batch, n, n] antisymmetric K_ij: the series of 1 / (lam_j - lam_i) in the ratio smaller / larger magnitude."""
+    a, b = lam[:, :, None], lam[:, None, :]
+    later = np.triu(np.ones((lam.shape[1],) * 2, dtype=bool), 1)
+    big_b = (np.abs(b) > np.abs(a)) | ((np.abs(b) == np.abs(a)) & later)
+    den, num = np.where(big_b, b, a), np.where(big_b, a, b)
+    K = sum((num / den) ** k for k in range(degree + 1)) / den
+    return np.where(big_b, K, -K) * (1.0 - np.eye(lam.shape[1]))
+
+
+def exact(case, seed):
+    state = prepare(case, seed)
+    host = {k: v.detach().double().cpu().numpy() for k, v in state.items() if isinstance(v, torch.Tensor)}
+    kind, total = state["kind"], case["batch"]
+    parts = []
+    for lo in range(0, total, 2048):
+        A, *rest = (host[k][lo:lo + 2048] for k in ("A", "G", "g_lam", "weight") if k in host)
+        lam, V = np.linalg.eigh(A)
+        if kind == "values":
+            parts.append((lam,))
+            continue
+        Vt = np.ascontiguousarray(V.transpose(0, 2, 1))
+        if kind == "train_eigh":
+            g_lam, weight = rest
+            C = _couplings(lam, 9) * (Vt @ (weight * V))
+            C = 0.5 * (C + C.transpose(0, 2, 1))
+            C[:, range(case["n"]), range(case["n"])] = g_lam
+            parts.append((lam, V @ C @ Vt))
+            continue
+        root = np.sqrt(np.maximum(lam, FLOOR))
+        inverse = kind in ("whiten", "train_inv")
+        out = (V * (1.0 / root if inverse else root)[:, None, :]) @ Vt
+        if kind == "whiten":
+            parts.append((out,))
+            continue
+        # divided differences of f(max(x, floor)); every eigenvalue lies above the floor here
+        assert lam.min() > FLOOR
+        si, sj = root[:, :, None], root[:, None, :]
+        phi = -1.0 / (si * sj * (si + sj)) if inverse else 1.0 / (si + sj)
+        G = rest[0]
+        grad = V @ (phi * (Vt @ (0.5 * (G + G.transpose(0, 2, 1))) @ V)) @ Vt
+        parts.append((lam if kind == "eigh" else out, grad))
+    outs = tuple(torch.from_numpy(np.concatenate(p)) for p in zip(*parts))
+    return outs[0] if kind in ("whiten", "values") else outs
