@@ -17,7 +17,10 @@
  * 3.2.2, App. A.1, A.3), per-matrix deflation of converged rows
  * (Sec. 3.2.3, generalised from the last row to any negligible off-diagonal),
  * and accumulation of all rotations into V = P Q_0 ... Q_k (closing equation
- * of Sec. 3.2.1, Sec. 3.2.5).
+ * of Sec. 3.2.1, Sec. 3.2.5).  Calls that ask for nothing of the rotations
+ * (bed_syevd, bed_spd_fn; bed_syevd_info with rotations = NULL) get the
+ * eigenvalues and eigenvectors of T from divide and conquer instead where that
+ * is faster; results meet the same accuracy bars.
  */
 #ifndef BED_H
 #define BED_H
@@ -69,8 +72,8 @@ typedef enum {
  *   stream hipStream_t or NULL.
  *
  * Numerical non-convergence never aborts: the QR loop is capped (30 sweeps
- * per row), a NaN/Inf input yields NaNs for that matrix only.  Use
- * bed_syevd_info to observe it.
+ * per row; the root finder of divide and conquer is capped too), a NaN/Inf
+ * input yields NaNs for that matrix only.  Use bed_syevd_info to observe it.
  */
 int bed_syevd(const float* A, int batch, int n, float* evals, float* evecs,
               void* stream);
@@ -93,9 +96,12 @@ int bed_syevd(const float* A, int batch, int n, float* evals, float* evecs,
  *                  perturbs the eigenvalues by at most 2e-6 ||A||_2 (a fifth of
  *                  the 1e-5 ||A||_2 accuracy bar), but eigenvalues far below
  *                  ||A||_2 lose their relative accuracy.
+ *              From divide and conquer (rotations = NULL) w is 0 and k counts
+ *              non-finite eigenvalues.
  *   rotations  device, [batch] uint32: number of Givens rotations applied to
  *              this matrix (the R of the flop model R*(6n+20); the paper
- *              reports the related "reduction times" in App. C.4).
+ *              reports the related "reduction times" in App. C.4).  Asking for
+ *              it selects the rotation kernels.
  */
 int bed_syevd_info(const float* A, int batch, int n, float* evals, float* evecs,
                    int* info, unsigned* rotations, void* stream);
@@ -359,8 +365,9 @@ int bed_timing_arm(int on);
 int bed_timing_end(float* microseconds, int max_count, int* count);
 
 /*
- * Name of the kernel that bed_syevd (want_vectors = 1) or its eigenvalues-only form
- * (want_vectors = 0) launches for this batch and n, e.g. "wave_kernel<32>" (one wavefront per
+ * Name of the kernel of Givens rotations for this batch and n, with eigenvectors (want_vectors = 1)
+ * or without (want_vectors = 0): the one bed_syevd_info and bed_syevd_tol launch, and bed_syevd where
+ * it does not use divide and conquer, e.g. "wave_kernel<32>" (one wavefront per
  * matrix, register arrays of 32), "packed_kernel<16>" (several matrices per wavefront),
  * "lane_kernel<4>" (one matrix per lane), "pair_kernel<64>" (two wavefronts per matrix),
  * "block_kernel" (four wavefronts per matrix); static storage, NULL for arguments out of range.

@@ -1,0 +1,683 @@
+// Divide and conquer for the symmetric tridiagonal eigenproblem, one matrix per workgroup.
+//
+// T is torn into blocks of one or two rows: every coupling e between two blocks is taken out as a
+// rank-one term, T = diag(T1', T2') + rho z z^T with rho = 2|e| (Cuppen 1981), and the blocks are
+// merged pairwise, all merges of a level at once.  A merge of m eigenvalues
+//   - deflates components of z that are negligible and pairs of poles that a plane rotation
+//     decouples within the tolerance (Dongarra and Sorensen 1987),
+//   - finds the roots of the secular equation 1/rho + sum z_j^2 / (d_j - lambda) = 0, one root per
+//     thread, from rational interpolation with the two neighbouring poles (Bunch, Nielsen and
+//     Sorensen 1978; Li 1993), inside a bracket and measured from the nearer pole,
+//   - recomputes z from the roots so that the eigenvectors are orthogonal to working precision
+//     whatever the last bits of the roots are (Gu and Eisenstat 1994),
+//   - multiplies the block's eigenvectors with those of the merge on the matrix cores (fp32).
+// The rotation-by-rotation QR iteration is one serial chain of about 1.1 n^2 rotations (188 cycles
+// per pair); here the serial depth is log2(n) merges whose inner loops run over m poles.
+#ifndef BED_DC_HPP
+#define BED_DC_HPP
+#include "bed_wave_kernel.hpp"
+
+namespace bed {
+
+// Matrix instructions in fp32: v_mfma_f32_32x32x2_f32, and v_mfma_f32_16x16x4_f32 for n <= 16.
+// With S the tile size, lane l holds the operands A[l % S][l / S] and B[l / S][l % S]; register v
+// of the result is D[dc_row<S>(v, l)][l % S].
+typedef float dc_acc32 __attribute__((ext_vector_type(16)));
+typedef float dc_acc16 __attribute__((ext_vector_type(4)));
+template <int N>
+struct DcTile {
+    static constexpr int size = 32;
+    using acc = dc_acc32;
+};
+template <>
+struct DcTile<16> {
+    static constexpr int size = 16;
+    using acc = dc_acc16;
+};
+template <int TS>
+__device__ __forceinline__ int dc_row(int v, int lane) {
+    return TS == 16 ? 4 * (lane >> 4) + v : 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+}
+__device__ __forceinline__ dc_acc32 dc_mfma(float a, float b, dc_acc32 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ dc_acc16 dc_mfma(float a, float b, dc_acc16 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+constexpr float kDcTol = 4.7683716e-7f;         // 8 units of rounding (2^-24)
+constexpr float kDcTiny = 5.9604645e-8f;        // blocks below 2^-24 of the pre-scaled matrix deflate at an absolute 3e-14
+constexpr float kDcFar = 1.0e4f;                 // a pole beyond every eigenvalue of the pre-scaled matrix
+constexpr int kDcMaxIter = 60;                  // bisection alone ends a bracket in fewer
+
+// N: rows covered (16, 32, 64, 128); TPE: threads per eigenvalue.
+// The arrays that the inner loops read are laid out per block with the block size rounded up to
+// 4 TPE: trip counts are the same in every lane, each thread takes four poles from 128-bit reads,
+// and the entries behind a block's end (and those of deflated poles) hold kDcFar with z = 0.
+template <int N, int TPE, bool WANT_V>
+struct DcShared {
+    static constexpr int LD = N + 1;
+    static constexpr int NP = N * TPE;   // the smallest merges have 3 or 4 poles in 4 TPE entries
+    alignas(16) float Dp[NP];            // by column: eigenvalues
+    alignas(16) float2 dz[NP];           // by slot (kept poles ascending, then the deflated ones): d, z^2
+    alignas(16) float2 om[NP];           // by slot: the pole the root is measured from, and the distance
+    alignas(16) float2 zs[NP];           // by slot: z, and the offset of its row in U (as an integer)
+    alignas(16) float2 fl[NP];           // by slot: entries of the first and last row
+    float4 rot[N];                       // deflating rotations: two columns (as integers), cosine, sine
+    alignas(16) float V[WANT_V ? N * LD : 1];        // V[r * LD + c]
+    alignas(16) float U[WANT_V ? (N + 1) * LD : 1];  // eigenvectors of the current merges, same layout; row N takes what is not wanted
+    alignas(16) float D[N];              // by column: eigenvalues (the result); +inf from n on
+    float first[N], last[N];             // by column: first and last row of its block's eigenvectors
+    float dS[N], zS[N];                  // sorted by d
+    float dd[N];                         // by slot: d, also of deflated poles
+    float rn[N];                         // reciprocal norm of a column of U
+    int perm[N];                         // sorted position -> column
+    int src[N];                          // slot -> column
+    int nrot[N];                         // rotations of the block that starts here
+};
+
+template <int TPE>
+__device__ __forceinline__ float dc_sum(float x) {
+    if (TPE >= 2) x += dpp0<kQuadXor1>(x);
+    if (TPE >= 4) x += dpp0<kQuadXor2>(x);
+    return x;
+}
+template <int TPE>
+__device__ __forceinline__ float dc_product(float x) {
+    if (TPE >= 2) x *= dpp0<kQuadXor1>(x);
+    if (TPE >= 4) x *= dpp0<kQuadXor2>(x);
+    return x;
+}
+
+// Sets of up to 128 positions, wave-uniform.
+template <int NB>
+struct DcMask {
+    uint64_t w[NB];
+    __device__ __forceinline__ bool has(int p) const { return (w[NB == 1 ? 0 : (p >> 6)] >> (p & 63)) & 1; }
+    __device__ __forceinline__ int below(int p) const {      // members < p, p in 0..64 NB
+        int c = 0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int q = p - 64 * b;
+            const uint64_t m = q >= 64 ? ~0ull : (q <= 0 ? 0ull : ((1ull << q) - 1ull));
+            c += __builtin_popcountll(w[b] & m);
+        }
+        return c;
+    }
+    __device__ __forceinline__ int next(int p) const {       // smallest member > p, or 64 NB
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int q = p - 64 * b;
+            const uint64_t m = q >= 63 ? 0ull : (q < 0 ? ~0ull : ~((2ull << q) - 1ull));
+            if (w[b] & m) return 64 * b + __builtin_ctzll(w[b] & m);
+        }
+        return 64 * NB;
+    }
+};
+
+// Are two neighbouring kept poles with components za, zb decoupled by a rotation within tol?
+// |gap c s| <= tol with c, s = za, zb normalised; as a ratio, so that nothing underflows.
+__device__ __forceinline__ bool dc_close(float gap, float za, float zb, float tol) {
+    const float hi = fmaxf(fabsf(za), fabsf(zb)), lo = fminf(fabsf(za), fabsf(zb));
+    const float q = lo * __builtin_amdgcn_rcpf(hi);
+    return gap * q <= tol * fmaf(q, q, 1.f);
+}
+
+// 1 / sqrt(x) to the last bit or two
+__device__ __forceinline__ float dc_rsqrt(float x) {
+    const float r = __builtin_amdgcn_rsqf(x);
+    return r * fmaf(-0.5f * x * r, r, 1.5f);
+}
+
+// Root of c x^2 - a x + b that interpolates a root between the two poles (s = 1) or right of both (s = -1).
+__device__ __forceinline__ float dc_quadratic(float a, float b, float c, float s) {
+    const float disc = s * __builtin_amdgcn_sqrtf(fmaxf(fmaf(a, a, -4.f * b * c), 0.f));
+    const bool neg = s * a <= 0.f;
+    const float num = neg ? a - disc : 2.f * b;
+    const float den = neg ? 2.f * c : a + disc;
+    return num * __builtin_amdgcn_rcpf(den);
+}
+
+// Eigenvalues (S.D, by column) and eigenvectors (S.V) of the tridiagonal with entries dget(k), eget(k) (coupling k
+// and k+1), k < n, in LDS, visible to all T threads.  The caller has pre-scaled T to a norm of about one.
+// With a non-finite entry in T every output is NaN.
+template <int N, int T, bool WANT_V, typename Dget, typename Eget>
+__device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const int n, const int tid, Dget&& dget, Eget&& eget) {
+    constexpr int TPE = T / N;                      // threads per eigenvalue, neighbours in a wavefront
+    constexpr int LD = DcShared<N, TPE, WANT_V>::LD;
+    constexpr int CH = 4 * TPE;                     // poles per step of an inner loop
+    constexpr int PP = N / TPE;                     // poles of one thread
+    constexpr int NB = (N + 63) / 64;
+    static_assert(T % N == 0 && (TPE == 2 || TPE == 4), "2 or 4 threads per eigenvalue");
+    constexpr int TS = DcTile<N>::size, NTILE = N / TS, NWV = T / 64;
+    constexpr int KT = 64 / TS;                     // columns that one matrix instruction takes
+    constexpr int AR = TS * TS / 64;
+    using Acc = typename DcTile<N>::acc;
+    static_assert(NWV == 1 || NWV % NTILE == 0, "a wavefront owns tiles of one row");
+    constexpr int TI = NWV == 1 ? NTILE : 1;        // tile rows of a wavefront
+    constexpr int JSTEP = NWV == 1 ? 1 : NWV / NTILE;
+    constexpr int TJ = NTILE / JSTEP;               // tile columns of a wavefront
+    const int lane = tid & 63, wv = tid >> 6;
+    const int e = tid / TPE, part = tid % TPE;
+    const bool valid = e < n;
+    auto sync = [&]() {
+        if (T == 64) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            __syncthreads();
+        }
+    };
+
+    int L = 0;
+    while ((2 << L) < n) ++L;       // 2^L leaves of one or two rows
+    // leaf that holds row r: the largest i with floor(i n / 2^L) <= r
+    const float rcp_n = 1.f / (float)n;
+    auto leaf_of = [&](int r) { return (int)(((float)(((r + 1) << L) - 1) + 0.5f) * rcp_n); };
+    const int leaf = valid ? leaf_of(e) : 0;
+    int leafq[NB];
+    bool bad = false;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int q = lane + 64 * b;
+        leafq[b] = q < n ? leaf_of(q) : 0;
+        if (q < n) bad = bad || !(fabsf(dget(q)) < __builtin_inff()) || (q < n - 1 && !(fabsf(eget(q)) < __builtin_inff()));
+    }
+    bad = __ballot(bad) != 0;
+
+    // ---- leaves ----
+    if (WANT_V) {
+        constexpr int Q = N * LD / 4;
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int i = 0; i < (Q + T - 1) / T; ++i) {
+            const int at = tid + i * T;
+            if (at < Q) {
+                reinterpret_cast<float4*>(S.V)[at] = zero;
+                reinterpret_cast<float4*>(S.U)[at] = zero;
+            }
+        }
+        sync();
+    }
+    float lam = __builtin_inff();   // eigenvalue of column e
+    if (part == 0) {
+        S.rn[e] = 1.f;
+        S.perm[e] = e;
+        S.src[e] = e;
+        S.first[e] = 0.f;
+        S.last[e] = 0.f;
+        if (valid) {
+            const int lo = (leaf * n) >> L, hi = ((leaf + 1) * n) >> L;
+            const float el = lo > 0 ? fabsf(eget(lo - 1)) : 0.f, eh = hi < n ? fabsf(eget(hi - 1)) : 0.f;
+            float cc = 1.f, ss = 0.f;
+            if (hi - lo == 1) {
+                lam = dget(lo) - el - eh;
+            } else {
+                const float a = dget(lo) - el, b = eget(lo), c = dget(lo + 1) - eh;
+                float t = 0.f;
+                if (b != 0.f) {
+                    const float th = (c - a) / (2.f * b);
+                    t = copysignf(1.f / (fabsf(th) + sqrtf(fmaf(th, th, 1.f))), th);
+                }
+                cc = 1.f / sqrtf(fmaf(t, t, 1.f));
+                ss = t * cc;
+                lam = e == lo ? fmaf(-t, b, a) : fmaf(t, b, c);
+            }
+            if (bad) lam = cc = __builtin_nanf("");
+            // column e of the leaf: (cc, -ss) for its first row, (ss, cc) for its second
+            if (WANT_V) {
+                S.V[e * LD + e] = cc;
+                if (hi - lo == 2) S.V[(e == lo ? lo + 1 : lo) * LD + e] = e == lo ? -ss : ss;
+            }
+            S.first[e] = e == lo ? cc : ss;
+            S.last[e] = e == hi - 1 ? cc : -ss;
+        }
+    }
+    if (TPE >= 2) lam = part == 0 ? lam : dpp0<kQuadXor1>(lam);
+    if (TPE >= 4) lam = part < 2 ? lam : dpp0<kQuadXor2>(lam);
+    sync();
+    if (bad) {
+        if (part == 0) S.D[e] = lam;
+        sync();
+        return;
+    }
+
+    for (int level = 1; level <= L; ++level) {
+        const int sh = L - level;
+        auto lo_of = [&](int i) { return (i * n) >> sh; };
+        auto mid_of = [&](int i) { return ((2 * i + 1) * n) >> (sh + 1); };
+        const int blk = leaf >> level;
+        const int lo = valid ? lo_of(blk) : 0, hi = valid ? lo_of(blk + 1) : 0;
+        const int mid = valid ? mid_of(blk) : 0;
+        const int m = hi - lo, k = e - lo;
+        const int M = (n + (1 << sh) - 1) >> sh;               // size of the largest block
+        const int Mp = (M + CH - 1) & ~(CH - 1);
+        const int base = blk * Mp;                              // first entry of the block in the padded arrays
+        if (valid && part == 0) {
+            S.Dp[base + e - lo] = lam;
+            for (int i = e - lo + m; i < Mp; i += m) S.Dp[base + i] = __builtin_inff();
+        }
+        sync();
+
+        // ---- z, and the order of the poles ----
+        if (valid) {
+            const float ec = eget(mid - 1);
+            const float zr = e < mid ? S.last[e] : S.first[e];
+            const float ze = 0.70710678f * ((e >= mid && ec < 0.f) ? -zr : zr);
+            const float de = lam;
+            int cnt = 0;
+#pragma unroll
+            for (int c = 0; c < PP; c += 4) {
+                if (c * TPE < M) {
+                    const int j = c * TPE + 4 * part;
+                    const float4 q = *reinterpret_cast<const float4*>(S.Dp + base + j);
+                    const int ahead = k - j;                        // ties: the earlier column first
+                    cnt += (q.x < de || (q.x == de && ahead > 0)) ? 1 : 0;
+                    cnt += (q.y < de || (q.y == de && ahead > 1)) ? 1 : 0;
+                    cnt += (q.z < de || (q.z == de && ahead > 2)) ? 1 : 0;
+                    cnt += (q.w < de || (q.w == de && ahead > 3)) ? 1 : 0;
+                }
+            }
+            const int pos = lo + (int)dc_sum<TPE>((float)cnt);
+            if (part == 0) {
+                S.dS[pos] = de;
+                S.zS[pos] = ze;
+                S.perm[pos] = e;
+                (e < mid ? S.last : S.first)[e] = 0.f;
+            }
+        }
+        sync();
+
+        // ---- deflation; every wavefront looks at all positions, so the masks need no exchange ----
+        DcMask<NB> kept, close;
+        float tolq[NB], rhoq[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int q = lane + 64 * b;
+            bool k = false;
+            tolq[b] = rhoq[b] = 0.f;
+            if (q < n) {
+                const int bq = leafq[b] >> level;
+                rhoq[b] = 2.f * fabsf(eget(mid_of(bq) - 1));
+                const float dmax = fmaxf(fabsf(S.dS[lo_of(bq)]), fabsf(S.dS[lo_of(bq + 1) - 1]));
+                tolq[b] = kDcTol * fmaxf(fmaxf(dmax, rhoq[b]), kDcTiny);
+                k = rhoq[b] * fabsf(S.zS[q]) > tolq[b];
+            }
+            kept.w[b] = __ballot(k);
+        }
+        uint64_t any = 0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int q = lane + 64 * b;
+            bool c = false;
+            if (q < n && kept.has(q)) {
+                const int nx = kept.next(q);
+                if (nx < lo_of((leafq[b] >> level) + 1)) c = dc_close(S.dS[nx] - S.dS[q], S.zS[q], S.zS[nx], tolq[b]);
+            }
+            close.w[b] = __ballot(c);
+            any |= close.w[b];
+        }
+        if (any) {
+            // one thread per block walks its poles in order and rotates close pairs; the lower pole of
+            // the pair loses its component of z
+            sync();
+            if (valid && part == 0 && e == lo) {
+                int nr = 0;
+                if (close.below(hi) != close.below(lo)) {
+                    const float rho = 2.f * fabsf(eget(mid - 1));
+                    const float dmax = fmaxf(fabsf(S.dS[lo]), fabsf(S.dS[hi - 1]));
+                    const float tol = kDcTol * fmaxf(fmaxf(dmax, rho), kDcTiny);
+                    int p = kept.has(lo) ? lo : kept.next(lo);
+                    float dp = p < hi ? S.dS[p] : 0.f, zp = p < hi ? S.zS[p] : 0.f;
+                    while (p < hi) {
+                        const int q = kept.next(p);
+                        if (q >= hi) break;
+                        float dq = S.dS[q], zq = S.zS[q];
+                        if (dc_close(dq - dp, zp, zq, tol)) {
+                            const float big = fmaxf(fabsf(zp), fabsf(zq)), r = fminf(fabsf(zp), fabsf(zq)) / big;
+                            const float tau = big * sqrtf(fmaf(r, r, 1.f));
+                            const float c = zq / tau, s = -zp / tau;
+                            const float np = dp * c * c + dq * s * s, nq = dp * s * s + dq * c * c;
+                            const int cp = S.perm[p], cq = S.perm[q];
+                            S.dS[p] = np;
+                            S.zS[p] = 0.f;
+                            S.dS[q] = dq = nq;
+                            S.zS[q] = zq = tau;
+                            S.rot[lo + nr] = make_float4(__int_as_float(cp), __int_as_float(cq), c, s);
+                            ++nr;
+                            const float fp = S.first[cp], fq = S.first[cq], lp = S.last[cp], lq = S.last[cq];
+                            S.first[cp] = fmaf(c, fp, s * fq);
+                            S.first[cq] = fmaf(c, fq, -s * fp);
+                            S.last[cp] = fmaf(c, lp, s * lq);
+                            S.last[cq] = fmaf(c, lq, -s * lp);
+                        }
+                        p = q;
+                        dp = dq;
+                        zp = zq;
+                    }
+                }
+                S.nrot[lo] = nr;
+            }
+            sync();
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int q = lane + 64 * b;
+                kept.w[b] = __ballot(q < n && rhoq[b] * fabsf(S.zS[q < n ? q : 0]) > tolq[b]);
+            }
+        }
+
+        // ---- slots: kept poles in ascending order, then the deflated ones ----
+        const int K = kept.below(hi) - kept.below(lo);
+        if (valid && part == 0) {
+            const int before = kept.below(e) - kept.below(lo);
+            const bool in = kept.has(e);
+            const int slot = in ? before : K + k - before;
+            const float d = S.dS[e], z = S.zS[e];
+            const int col = S.perm[e];
+            S.dz[base + slot] = in ? make_float2(d, z * z) : make_float2(kDcFar, 0.f);
+            S.zs[base + slot] = make_float2(in ? z : 0.f, __int_as_float(col * LD));
+            S.dd[lo + slot] = d;
+            S.src[lo + slot] = col;
+            S.fl[base + slot] = make_float2(S.first[col], S.last[col]);
+            for (int i = k + m; i < Mp; i += m) {
+                S.dz[base + i] = make_float2(kDcFar, 0.f);
+                S.zs[base + i] = make_float2(0.f, __int_as_float(N * LD));
+                S.fl[base + i] = make_float2(0.f, 0.f);
+            }
+        }
+        sync();
+        // poles that the loops visit: the same count in every lane
+        const int trip = sh == 0 ? __builtin_amdgcn_readfirstlane(kept.below(n)) : M;
+
+        // ---- secular equation: thread e finds root k of its block ----
+        const bool root = valid && k < K;
+        float dorg = 0.f, mu = 0.f;
+        float dl[PP], z2[PP];               // distances from the origin of the root, squares of z
+        {
+            const float2* const pz = S.dz + base;
+            const float rho = valid ? 2.f * fabsf(eget(mid - 1)) : 1.f;
+            const float rinv = __builtin_amdgcn_rcpf(rho);
+            const bool many = root && K > 1;
+            const int i1 = many ? min(k, K - 2) : 0;
+            const bool last = k == K - 1;
+            const float2 pk = pz[root ? k : 0], p1 = pz[i1], p2 = pz[many ? i1 + 1 : 0];
+            const float gap = last ? 1.00001f * rho : p2.x - pk.x;       // |z| <= 1
+            const float half = 0.5f * gap;
+            // this thread's poles stay in registers for all iterations
+            float fm = 0.f;
+#pragma unroll
+            for (int c = 0; c < PP; c += 4) {
+                if (c * TPE < trip) {
+                    const float4* const q = reinterpret_cast<const float4*>(pz + c * TPE + 4 * part);
+                    const float4 q0 = q[0], q1 = q[1];
+                    dl[c] = q0.x, dl[c + 1] = q0.z, dl[c + 2] = q1.x, dl[c + 3] = q1.z;
+                    z2[c] = q0.y, z2[c + 1] = q0.w, z2[c + 2] = q1.y, z2[c + 3] = q1.w;
+#pragma unroll
+                    for (int i = c; i < c + 4; ++i) fm = fmaf(z2[i], __builtin_amdgcn_rcpf((dl[i] - pk.x) - half), fm);
+                } else {
+#pragma unroll
+                    for (int i = c; i < c + 4; ++i) dl[i] = kDcFar;
+                }
+            }
+            fm = dc_sum<TPE>(fm) + rinv;
+            const bool right = !last && fm < 0.f;
+            dorg = right ? p2.x : pk.x;
+#pragma unroll
+            for (int i = 0; i < PP; ++i) dl[i] -= dorg;
+            float lb = last ? (fm < 0.f ? half : 0.f) : (right ? -half : 0.f);
+            float ub = last ? (fm < 0.f ? gap : half) : (right ? 0.f : half);
+            const float D1 = p1.x - dorg, D2 = p2.x - dorg;
+            const float sgn = last ? -1.f : 1.f;
+            {
+                const float at = right ? -half : half;
+                const float c = fm - p1.y * __builtin_amdgcn_rcpf(D1 - at) - p2.y * __builtin_amdgcn_rcpf(D2 - at);
+                const float a = fmaf(c, D1 + D2, p1.y + p2.y);
+                const float b = fmaf(c * D1, D2, fmaf(p1.y, D2, p2.y * D1));
+                const float x = dc_quadratic(a, b, c, sgn);
+                mu = (x > lb && x < ub) ? x : 0.5f * (lb + ub);
+            }
+            bool open = many;
+            for (int it = 0; it < kDcMaxIter && __ballot(open) != 0; ++it) {
+                float F = 0.f, dF = 0.f, N1 = 0.f, dN = 0.f;       // sums over all poles, over the terms below zero
+#pragma unroll
+                for (int c = 0; c < PP; c += 4) {
+                    if (c * TPE < trip) {
+#pragma unroll
+                        for (int i = c; i < c + 4; ++i) {
+                            const float r = __builtin_amdgcn_rcpf(dl[i] - mu);
+                            const float w = z2[i] * r, wn = fminf(w, 0.f);
+                            F += w;
+                            N1 += wn;
+                            dF = fmaf(w, r, dF);
+                            dN = fmaf(wn, r, dN);
+                        }
+                    }
+                }
+                F = dc_sum<TPE>(F);
+                N1 = dc_sum<TPE>(N1);
+                dF = dc_sum<TPE>(dF);
+                dN = dc_sum<TPE>(dN);
+                const float mag = F - 2.f * N1 + rinv;             // sum of the magnitudes
+                F += rinv;
+                const float err = fmaf(4.7683716e-7f, mag, 5.9604645e-8f * fabsf(mu) * dF);
+                const float d1 = D1 - mu, d2 = D2 - mu;
+                // derivative of the part left of the split; for the last root the split is before the last pole
+                const float r2 = __builtin_amdgcn_rcpf(d2);
+                const float dpsi = last ? dF - p2.y * r2 * r2 : dN;
+                const float dphi = dF - dpsi;
+                if (open && !(fabsf(F) <= err)) {
+                    if (F < 0.f) lb = mu;
+                    else ub = mu;
+                    const float c = F - d1 * dpsi - d2 * dphi;
+                    const float a = (d1 + d2) * F - d1 * d2 * dF;
+                    const float b = d1 * d2 * F;
+                    float x = mu + dc_quadratic(a, b, c, sgn);
+                    if (!(x > lb && x < ub)) x = 0.5f * (lb + ub);
+                    const bool inside = x != mu && x > lb && x < ub;
+                    // convergence is quadratic in the step over the distance of the nearer pole: below
+                    // 2^-12 of it the next step would be below the rounding of mu
+                    open = inside && !(fabsf(x - mu) <= 2.4414062e-4f * fminf(fabsf(d1), fabsf(d2)));
+                    if (inside) mu = x;
+                } else {
+                    open = false;
+                }
+            }
+            if (root && !many) {
+                dorg = pk.x;
+                mu = rho * pk.y;
+            }
+            lam = root ? dorg + mu : S.dd[valid ? e : 0];
+            if (valid && part == 0) S.om[base + k] = make_float2(dorg, mu);
+            if (valid && part == 0)
+                for (int i = k + m; i < Mp; i += m) S.om[base + i] = make_float2(0.f, 0.f);
+        }
+        sync();
+
+        // ---- the z of which these are the exact roots, up to a common factor ----
+        {
+            float prod = 1.f;
+            const float dk = S.dz[base + (root ? k : 0)].x;
+            auto ratio = [&](int i, float d, float ox, float oy) {
+                const float x = ((dk - ox) - oy) * __builtin_amdgcn_rcpf(i == k ? 1.f : dk - d);
+                prod *= i < K ? x : 1.f;
+            };
+#pragma unroll
+            for (int c = 0; c < PP; c += 4) {
+                if (c * TPE < trip) {
+                    const int i = c * TPE + 4 * part;
+                    const float4* const q = reinterpret_cast<const float4*>(S.dz + base + i);
+                    const float4* const o = reinterpret_cast<const float4*>(S.om + base + i);
+                    const float4 q0 = q[0], q1 = q[1], o0 = o[0], o1 = o[1];
+                    ratio(i, q0.x, o0.x, o0.y);
+                    ratio(i + 1, q0.z, o0.z, o0.w);
+                    ratio(i + 2, q1.x, o1.x, o1.y);
+                    ratio(i + 3, q1.z, o1.z, o1.w);
+                }
+            }
+            prod = dc_product<TPE>(prod);
+            if (root && part == 0) S.zs[base + k].x = copysignf(__builtin_amdgcn_sqrtf(fabsf(prod)), S.zs[base + k].x);
+        }
+        sync();
+
+        // ---- eigenvectors of the merge ----
+        {
+            // the first and last row follow by dot products, so that eigenvalues only, without any of
+            // the rest, are the same numbers
+            float nrm = 0.f, f = 0.f, l = 0.f;
+            const int visit = WANT_V ? M : trip;
+#pragma unroll
+            for (int c = 0; c < PP; c += 4) {
+                if (c * TPE < visit && valid) {
+                    const int j = c * TPE + 4 * part;
+                    const float4* const w = reinterpret_cast<const float4*>(S.zs + base + j);
+                    const float4* const g = reinterpret_cast<const float4*>(S.fl + base + j);
+                    const float4 w0 = w[0], w1 = w[1], g0 = g[0], g1 = g[1];
+                    const float z[4] = {w0.x, w0.z, w1.x, w1.z}, off[4] = {w0.y, w0.w, w1.y, w1.w};
+                    const float fr[4] = {g0.x, g0.z, g1.x, g1.z}, la[4] = {g0.y, g0.w, g1.y, g1.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float u = z[i] * __builtin_amdgcn_rcpf(dl[c + i] - mu);
+                        nrm = fmaf(u, u, nrm);
+                        f = fmaf(u, fr[i], f);
+                        l = fmaf(u, la[i], l);
+                        if (WANT_V) S.U[__float_as_int(off[i]) + e] = root ? u : (j + i == k ? 1.f : 0.f);
+                    }
+                }
+            }
+            const float rn = root ? dc_rsqrt(dc_sum<TPE>(nrm)) : 1.f;
+            f = dc_sum<TPE>(f) * rn;
+            l = dc_sum<TPE>(l) * rn;
+            if (valid && !root) {
+                const float2 own = S.fl[base + k];
+                f = own.x;
+                l = own.y;
+            }
+            if (valid && part == 0) {
+                S.first[e] = f;
+                S.last[e] = l;
+                if (WANT_V) S.rn[e] = rn;
+            }
+        }
+        if (WANT_V) {
+            if (any) {
+                if (TPE > 1) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                }
+                if (valid && part == 0) {
+                    for (int r = S.nrot[lo] - 1; r >= 0; --r) {
+                        const float4 g = S.rot[lo + r];
+                        float* const up = S.U + __float_as_int(g.x) * LD + e;
+                        float* const uq = S.U + __float_as_int(g.y) * LD + e;
+                        const float a = *up, b = *uq;
+                        *up = fmaf(g.z, a, -g.w * b);
+                        *uq = fmaf(g.w, a, g.z * b);
+                    }
+                }
+            }
+            sync();
+            // ---- V <- V U, block diagonal times block diagonal ----
+            if (M <= 8) {
+                // blocks of at most four rows before the merge: this thread's column from plain FMAs
+                // (the matrix cores would spend a whole tile product on it)
+                const int k0 = part & 1 ? mid : lo, k1 = part & 1 ? hi : mid;      // rows and columns of one half
+                float out[4], u[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = k0 + i < k1 ? S.U[(k0 + i) * LD + e] : 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    out[r] = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) out[r] = fmaf(S.V[min(k0 + r, N - 1) * LD + min(k0 + i, N - 1)], u[i], out[r]);
+                }
+                const float rn = S.rn[e];
+                sync();
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (valid && part < 2 && k0 + r < k1) S.V[(k0 + r) * LD + e] = out[r] * rn;
+            } else {
+                // 32 x 32 tiles (16 x 16 for N = 16), only the columns that a tile's blocks share
+                Acc acc[TI][TJ];
+                const int loT = lane & (TS - 1), hiT = lane / TS;
+#pragma unroll
+                for (int ti = 0; ti < TI; ++ti) {
+                    const int I = NWV == 1 ? ti : wv % NTILE;
+#pragma unroll
+                    for (int tj = 0; tj < TJ; ++tj) {
+                        const int J = NWV == 1 ? tj : wv / NTILE + tj * JSTEP;
+                        int k0 = 0, k1 = n;
+                        if (NTILE > 1) {
+                            const int ri = min(32 * I, n - 1), rj = min(32 * I + 31, n - 1);
+                            const int ci = min(32 * J, n - 1), cj = min(32 * J + 31, n - 1);
+                            // rows: blocks before this merge; columns: after it
+                            const int half_lo = ((leaf_of(ri) >> (level - 1)) * n) >> (sh + 1);
+                            const int half_hi = (((leaf_of(rj) >> (level - 1)) + 1) * n) >> (sh + 1);
+                            k0 = __builtin_amdgcn_readfirstlane(max(half_lo, lo_of(leaf_of(ci) >> level)));
+                            k1 = __builtin_amdgcn_readfirstlane(min(half_hi, lo_of((leaf_of(cj) >> level) + 1)));
+                        }
+                        acc[ti][tj] = Acc{};
+                        const float* const va = S.V + (TS * I + loT) * LD + hiT;
+                        const float* const ub = S.U + hiT * LD + TS * J + loT;
+                        for (int kk = k0 & ~(KT - 1); kk < k1; kk += 4 * KT) {
+                            float a[4], u[4];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                // behind k1 the operands are read at k1's step: in bounds, and dropped
+                                const int at = min(kk + i * KT, N - KT);
+                                a[i] = va[at];
+                                u[i] = kk + i * KT < k1 ? ub[at * LD] : 0.f;
+                            }
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) acc[ti][tj] = dc_mfma(a[i], u[i], acc[ti][tj]);
+                        }
+                    }
+                }
+                sync();
+#pragma unroll
+                for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+                    for (int tj = 0; tj < TJ; ++tj) {
+                        const int I = NWV == 1 ? ti : wv % NTILE;
+                        const int J = NWV == 1 ? tj : wv / NTILE + tj * JSTEP;
+                        const float r = S.rn[TS * J + loT];
+#pragma unroll
+                        for (int v = 0; v < AR; ++v) S.V[(TS * I + dc_row<TS>(v, lane)) * LD + TS * J + loT] = acc[ti][tj][v] * r;
+                    }
+            }
+            sync();
+        }
+    }
+    if (part == 0) S.D[e] = valid ? lam : __builtin_inff();
+    sync();
+}
+
+// Rank of column e's eigenvalue among all n (ties by column): the ascending output order.  With a
+// non-finite eigenvalue among them (`odd`) the columns stay where they are.
+template <int N, int TPE, bool WANT_V>
+__device__ __forceinline__ int dc_rank(const DcShared<N, TPE, WANT_V>& S, int n, int e, bool odd) {
+    const float de = S.D[e];
+    int rank = 0;
+    for (int j = 0; j < n; j += 4) {                        // D is +inf from n on
+        const float4 q = *reinterpret_cast<const float4*>(S.D + j);
+        rank += (q.x < de || (q.x == de && j < e)) ? 1 : 0;
+        rank += (q.y < de || (q.y == de && j + 1 < e)) ? 1 : 0;
+        rank += (q.z < de || (q.z == de && j + 2 < e)) ? 1 : 0;
+        rank += (q.w < de || (q.w == de && j + 3 < e)) ? 1 : 0;
+    }
+    return odd ? e : rank;
+}
+
+// Number of non-finite eigenvalues (the same in every wavefront).
+template <int N, int TPE, bool WANT_V>
+__device__ __forceinline__ int dc_non_finite(const DcShared<N, TPE, WANT_V>& S, int n, int lane) {
+    int count = 0;
+#pragma unroll
+    for (int b = 0; b < (N + 63) / 64; ++b) {
+        const int q = lane + 64 * b;
+        count += (int)__builtin_popcountll(__ballot(q < n && !(fabsf(S.D[q < n ? q : 0]) < __builtin_inff())));
+    }
+    return count;
+}
+
+}  // namespace bed
+#endif

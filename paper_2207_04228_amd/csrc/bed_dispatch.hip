@@ -20,6 +20,7 @@ hipError_t launch_wave_n48(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_wave_n56(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_wave_n64(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_block(const KernelArgs&, int, bool, hipStream_t);
+hipError_t launch_dc_wave(const KernelArgs&, int, bool, hipStream_t);
 
 namespace {
 
@@ -39,7 +40,7 @@ struct Choice {
 
 Choice wave_choice(int n);
 
-// The one place that decides which kernel serves a problem.  `forced` (kFamilyAuto unless a test
+// Which kernel of Givens rotations serves a problem.  `forced` (kFamilyAuto unless a test
 // or a measurement asks for one family) must be able to serve n: the caller has checked.
 Choice choose(int batch, int n, int stage, bool want_v, int forced) {
     if (forced == kFamilyLane) return n <= 4 ? Choice{kLaneFamily, 4, "lane_kernel<4>"} : Choice{kLaneFamily, 8, "lane_kernel<8>"};
@@ -110,6 +111,29 @@ Choice wave_choice(int n) {
     return {kWaveFamily, 64, "wave_kernel<64>"};
 }
 
+// Divide and conquer serves the calls that want a decomposition and nothing of the rotations: no
+// rotation counts, no threshold or sweep cap of the caller, no forced family, no stage hook.
+// It takes one wavefront per matrix whatever the batch; the rule looks at n and batch only, so that
+// eigenvalues alone, eigenvectors and the spectral function of one batch come from one method.
+// Measured (us per launch, rotations as chosen above / divide and conquer, eigenvectors on):
+//   n = 8:  batch 512: 14.0 / 12.5   2048: 17.0 / 14.8   32768: 50 / 113
+//   n = 16: batch 64: 30.7 / 17.4    512: 30.5 / 20.2    4096: 42.6 / 37.7 (eigenvalues 31.4 / 33.3)  16384: 89 / 104
+//   n = 20: batch 1024: 45.6 / 29.7  4096: 75.9 / 74.2   16384: 193 / 217
+//   n = 24: batch 4096: 93.5 / 79.9  16384: 248 / 238 (eigenvalues 159 / 172)
+//   n = 28: batch 4096: 124 / 95     16384: 308 / 276
+//   n = 32: batch 64: 82 / 34        512: 90 / 42        4096: 152 / 85      16384: 390 / 290
+// Up to four rows the rotations need one or two sweeps and win everywhere; where four matrices share
+// a wavefront (packed kernels) small n keeps the rotations.
+bool divide_and_conquer(const KernelArgs& args, int stage, int forced) {
+    if (forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
+    if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;
+    const int n = args.n, batch = args.batch;
+    if (n <= 4 || n > 32) return false;
+    if (n <= 16) return batch < kPackedFromBatch;
+    if (n <= 24) return batch <= kPackedRowsFromBatch;
+    return true;
+}
+
 }  // namespace
 
 const char* kernel_variant(int batch, int n, bool want_v) { return choose(batch, n, kFull, want_v, kFamilyAuto).name; }
@@ -129,6 +153,7 @@ bool family_serves(int family, int n) {
 
 hipError_t launch(const KernelArgs& args, int stage, bool want_v, hipStream_t stream, int forced) {
     if (args.batch == 0) return hipSuccess;
+    if (divide_and_conquer(args, stage, forced)) return launch_dc_wave(args, stage, want_v, stream);
     const Choice c = choose(args.batch, args.n, stage, want_v, forced);
     if (c.family == kPairFamily) {
         if (!want_v || stage != kFull) return hipErrorInvalidValue;     // the pair kernels always form eigenvectors

@@ -586,6 +586,220 @@ __device__ __forceinline__ void qr_iterations(float2* const sP, float* const sV,
 }
 
 // ---------------------------------------------------------------------------
+// Load, power-of-two pre-scaling and Householder tridiagonalisation (Sec. 3.1) in one wavefront.
+// On return sP holds T (sP[k] = (e[k-1], d[k])), sV (column-major, stride LD) the reflector
+// product P when it is wanted, and inv_scale undoes the scaling.  sV is also the staging buffer.
+// ---------------------------------------------------------------------------
+template <int N, int LD>
+__device__ __forceinline__ void tridiag_half(const float* __restrict__ Ab, const int n, const int lane, float* const sV,
+                                             float2* const sP, float& inv_scale, PhaseClock& clk) {
+    // ---- rows fit in half a wavefront and P is wanted: the lower half holds the rows of
+    // the working matrix, the upper half the rows of the accumulated reflector product
+    // P (Eq. (8)).  One instruction stream serves both: the dot product with u gives
+    // p = 2Au/|u|^2 in the lower half and w = 2Pu/|u|^2 in the upper half, and the update
+    // x <- x - q u^T is the first half of the rank-2 update of A (q = p - K u) and the whole
+    // rank-1 update of P (q = w); the second half, x <- x - u q^T, runs with u = 0 in the
+    // upper half.
+    constexpr int W = lanes_for(N);
+    const int row = lane & 31;
+    const bool roleP = lane >= 32;
+    const int arow = roleP ? -1 : row;         // row index for the selections on A; none for the P lanes
+    float x[N];
+    const float rcp_n = 1.0f / (float)n;
+    chunked_copy<copy_chunk(N * N)>(
+        n * n, lane, [&](int idx) { return Ab[idx]; },
+        [&](int idx, float x) {
+            const int i = (int)(((float)idx + 0.5f) * rcp_n);
+            sV[i * LD + (idx - i * n)] = x;
+        });
+    wave_sync();
+    float amax = 0.f;
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        float aval = 0.f;
+        if (row < n && c < n) aval = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
+        amax = fmaxf(amax, fabsf(aval));   // fmaxf drops NaNs; they still reach the output through the arithmetic
+        x[c] = roleP ? ((c == row) ? 1.f : 0.f) : aval;
+    }
+    wave_sync();
+    float scale;
+    pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
+    const float myscale = roleP ? 1.f : scale;
+#pragma unroll
+    for (int c = 0; c < N; ++c) x[c] *= myscale;
+    clk.lap(kPhLoad);
+#pragma unroll
+    for (int J = 0; J < N; ++J) {
+        const float dJ = read_lane(x[J], J);      // final once columns 0..J-1 are reduced
+        float eJ = 0.f;
+        if (J < N - 1) {
+            const float x0 = read_lane(x[J], J + 1);     // A[J+1][J]
+            eJ = x0;                                      // kept as is when no reflector is applied
+            if (J < N - 2) {
+                const float xc = (arow > J) ? x[J] : 0.f; // A[r][J], r > J
+                const float alpha = wave_sum<W>(xc * xc); // |x|^2 (the sum reads the lower half only)
+                const bool active = (J < n - 2) && (alpha > kTinyAlpha);
+                const float nrm = __builtin_amdgcn_sqrtf(alpha);
+                const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
+                float ur = (arow == J + 1) ? (x0 + sigma) : ((arow > J + 1) ? xc : 0.f);
+                ur = active ? ur : 0.f;
+                const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
+                eJ = active ? -sigma : x0;
+                // u and p are broadcast with v_readlane (the entries live in lanes 0..31; the
+                // results are scalars that the FMAs take as operands): no LDS round trip and no
+                // barrier in the whole reduction
+                float u[N];
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) u[c] = read_lane(ur, c);
+                float pp[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) pp[c & 3] = fmaf(x[c], u[c], pp[c & 3]);
+                const float pw = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));     // p (A lanes), w (P lanes)
+                // A - q u^T - u q^T with q = p - K u, K = u^T p / |u|^2, regrouped as
+                // A - (p - 2K u) u^T - u p^T: the broadcast of p does not wait for K.
+                const float K2 = beta * wave_sum<W>(ur * pw);                    // 2K
+                const float sr = fmaf(-K2, ur, pw);       // p - 2K u; stays w in the P lanes (u = 0 there)
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) x[c] = fmaf(-ur, read_lane(pw, c), fmaf(-sr, u[c], x[c]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (lane == 0) {
+            sP[J].y = dJ;
+            sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
+        }
+    }
+    if (lane == 0) sP[0].x = 0.f;
+    // every lane stores the P lanes' row (the upper half's value copied over the lower half)
+#pragma unroll
+    for (int c = 0; c < N; ++c) sV[c * LD + row] = from_upper_half(x[c]);
+    wave_sync();
+}
+
+template <int N, int LD, bool WANT_V>
+__device__ __forceinline__ void tridiag_rows(const float* __restrict__ Ab, const int n, const int lane, float* const sV,
+                                             float2* const sP, float* const svec, float* const sq, float& inv_scale,
+                                             PhaseClock& clk) {
+    constexpr int W = lanes_for(N);
+    const int row = (N <= 32) ? (lane & 31) : lane;
+    float a[N];
+    float v[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) v[c] = (c == row) ? 1.f : 0.f;
+
+    // ---- load: coalesced into LDS, then row `row` (lower triangle mirrored)
+    const float rcp_n = 1.0f / (float)n;
+    chunked_copy<copy_chunk(N * N)>(
+        n * n, lane, [&](int idx) { return Ab[idx]; },
+        [&](int idx, float x) {
+            const int i = (int)(((float)idx + 0.5f) * rcp_n);
+            sV[i * LD + (idx - i * n)] = x;
+        });
+    wave_sync();
+    float amax = 0.f;
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        float x = 0.f;
+        if (row < n && c < n) x = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
+        a[c] = x;
+        amax = fmaxf(amax, fabsf(x));   // fmaxf drops NaNs; they still reach the output through the arithmetic
+    }
+    wave_sync();
+    float scale;
+    pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
+#pragma unroll
+    for (int c = 0; c < N; ++c) a[c] *= scale;
+    clk.lap(kPhLoad);
+
+    // ---- Householder tridiagonalisation, column J reduced at step J ----
+    // Branch-free: a step that has nothing to do (J >= n-2, or the column is
+    // already reduced) runs with u = 0 and beta = 0.
+    // u and q are broadcast through LDS (one write, then 128-bit reads that every lane
+    // issues for the same address); the latency of each round trip is covered by
+    // independent work: the rank-1 update of V is deferred by one step and runs while
+    // the next u is in flight, and the part of the rank-2 update of A that needs only
+    // this lane's q runs while q is in flight.
+    float ud[N];          // u of the previous step (for the deferred update of V)
+    float wd = 0.f;       // its 2 V u / |u|^2
+#pragma unroll
+    for (int c = 0; c < N; ++c) ud[c] = 0.f;
+#pragma unroll
+    for (int J = 0; J < N; ++J) {
+        const float dJ = read_lane(a[J], J);      // final once columns 0..J-1 are reduced
+        float eJ = 0.f;
+        if (J < N - 1) {
+            const float x0 = read_lane(a[J], J + 1);     // A[J+1][J]
+            eJ = x0;                                      // kept as is when no reflector is applied
+            if (J < N - 2) {
+                const float x = (row > J) ? a[J] : 0.f;   // A[r][J], r > J
+                const float alpha = wave_sum<W>(x * x);   // |x|^2
+                const bool active = (J < n - 2) && (alpha > kTinyAlpha);
+                const float nrm = __builtin_amdgcn_sqrtf(alpha);
+                const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
+                float ur = (row == J + 1) ? (x0 + sigma) : ((row > J + 1) ? x : 0.f);
+                ur = active ? ur : 0.f;
+                const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
+                eJ = active ? -sigma : x0;
+                // Up to 32 rows, u and p are broadcast with v_readlane (scalar operands of the
+                // FMAs); beyond, through LDS (one write, then 128-bit reads of one address).
+                constexpr bool RL = (N <= 32);
+                if (!RL) svec[lane] = ur;
+                if (WANT_V && J > 0) {
+                    // deferred: V <- V - w u^T of step J-1 (columns J .. N-1)
+#pragma unroll
+                    for (int c = J; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
+                }
+                if (!RL) __syncthreads();
+                float u[N];
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) u[c] = RL ? read_lane(ur, c) : svec[c];
+                // p = 2 A u / |u|^2, w = 2 V u / |u|^2; four partial sums each
+                float pp[4] = {0.f, 0.f, 0.f, 0.f}, ww[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) {
+                    pp[c & 3] = fmaf(a[c], u[c], pp[c & 3]);
+                    if (WANT_V) ww[c & 3] = fmaf(v[c], u[c], ww[c & 3]);
+                }
+                const float p = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));
+                wd = beta * ((ww[0] + ww[1]) + (ww[2] + ww[3]));
+                // A - q u^T - u q^T with q = p - K u, regrouped as A - (p - 2K u) u^T - u p^T
+                // (p is broadcast before K is known; same arithmetic as the role-lane variant)
+                if (!RL) sq[lane] = p;
+                const float K2 = beta * wave_sum<W>(ur * p);  // 2K
+                const float sr = fmaf(-K2, ur, p);
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) a[c] = fmaf(-sr, u[c], a[c]);
+                if (!RL) __syncthreads();
+#pragma unroll
+                for (int c = J + 1; c < N; ++c) {
+                    a[c] = fmaf(-ur, RL ? read_lane(p, c) : sq[c], a[c]);
+                    ud[c] = u[c];
+                }
+                // keep the steps apart: interleaving them makes the compiler hoist the next
+                // steps' loads and run out of registers
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // sP[J+1].x = e[J], sP[J].y = d[J]
+        if (lane == 0) {
+            sP[J].y = dJ;
+            sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
+        }
+    }
+    if (WANT_V && N > 2) {
+        // the last reflector's deferred update of V
+#pragma unroll
+        for (int c = N - 2; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
+    }
+    if (lane == 0) sP[0].x = 0.f;
+    if (WANT_V) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) sV[c * LD + row] = v[c];
+    }
+    wave_sync();
+}
+
+// ---------------------------------------------------------------------------
 // N      register-array size (4, 8, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64); n <= N at run time
 // WANT_V accumulate eigenvectors
 // STAGE  kFull, kTridiagOnly (stage hook 1), kQrOnly (stage hook 2), kQrPartial (stage hook 3:
@@ -626,203 +840,9 @@ __global__ __launch_bounds__(64) void wave_kernel(KernelArgs args) {
 
     constexpr bool GIVEN_T = (STAGE == kQrOnly || STAGE == kQrPartial);
     if (!GIVEN_T && HALF && WANT_V) {
-        // ---- rows fit in half a wavefront and P is wanted: the lower half holds the rows of
-        // the working matrix, the upper half the rows of the accumulated reflector product
-        // P (Eq. (8)).  One instruction stream serves both: the dot product with u gives
-        // p = 2Au/|u|^2 in the lower half and w = 2Pu/|u|^2 in the upper half, and the update
-        // x <- x - q u^T is the first half of the rank-2 update of A (q = p - K u) and the whole
-        // rank-1 update of P (q = w); the second half, x <- x - u q^T, runs with u = 0 in the
-        // upper half.
-        const bool roleP = lane >= 32;
-        const int arow = roleP ? -1 : row;         // row index for the selections on A; none for the P lanes
-        float x[N];
-        const float* __restrict__ Ab = args.A + (size_t)b * n * n;
-        const float rcp_n = 1.0f / (float)n;
-        chunked_copy<copy_chunk(N * N)>(
-            n * n, lane, [&](int idx) { return Ab[idx]; },
-            [&](int idx, float x) {
-                const int i = (int)(((float)idx + 0.5f) * rcp_n);
-                sV[i * LD + (idx - i * n)] = x;
-            });
-        wave_sync();
-        float amax = 0.f;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-            float aval = 0.f;
-            if (row < n && c < n) aval = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
-            amax = fmaxf(amax, fabsf(aval));   // fmaxf drops NaNs; they still reach the output through the arithmetic
-            x[c] = roleP ? ((c == row) ? 1.f : 0.f) : aval;
-        }
-        wave_sync();
-        float scale;
-        pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
-        const float myscale = roleP ? 1.f : scale;
-#pragma unroll
-        for (int c = 0; c < N; ++c) x[c] *= myscale;
-        clk.lap(kPhLoad);
-#pragma unroll
-        for (int J = 0; J < N; ++J) {
-            const float dJ = read_lane(x[J], J);      // final once columns 0..J-1 are reduced
-            float eJ = 0.f;
-            if (J < N - 1) {
-                const float x0 = read_lane(x[J], J + 1);     // A[J+1][J]
-                eJ = x0;                                      // kept as is when no reflector is applied
-                if (J < N - 2) {
-                    const float xc = (arow > J) ? x[J] : 0.f; // A[r][J], r > J
-                    const float alpha = wave_sum<W>(xc * xc); // |x|^2 (the sum reads the lower half only)
-                    const bool active = (J < n - 2) && (alpha > kTinyAlpha);
-                    const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                    const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
-                    float ur = (arow == J + 1) ? (x0 + sigma) : ((arow > J + 1) ? xc : 0.f);
-                    ur = active ? ur : 0.f;
-                    const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
-                    eJ = active ? -sigma : x0;
-                    // u and p are broadcast with v_readlane (the entries live in lanes 0..31; the
-                    // results are scalars that the FMAs take as operands): no LDS round trip and no
-                    // barrier in the whole reduction
-                    float u[N];
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) u[c] = read_lane(ur, c);
-                    float pp[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) pp[c & 3] = fmaf(x[c], u[c], pp[c & 3]);
-                    const float pw = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));     // p (A lanes), w (P lanes)
-                    // A - q u^T - u q^T with q = p - K u, K = u^T p / |u|^2, regrouped as
-                    // A - (p - 2K u) u^T - u p^T: the broadcast of p does not wait for K.
-                    const float K2 = beta * wave_sum<W>(ur * pw);                    // 2K
-                    const float sr = fmaf(-K2, ur, pw);       // p - 2K u; stays w in the P lanes (u = 0 there)
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) x[c] = fmaf(-ur, read_lane(pw, c), fmaf(-sr, u[c], x[c]));
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (lane == 0) {
-                sP[J].y = dJ;
-                sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
-            }
-        }
-        if (lane == 0) sP[0].x = 0.f;
-        // every lane stores the P lanes' row (the upper half's value copied over the lower half)
-#pragma unroll
-        for (int c = 0; c < N; ++c) sV[c * LD + row] = from_upper_half(x[c]);
-        wave_sync();
+        tridiag_half<N, LD>(args.A + (size_t)b * n * n, n, lane, sV, sP, inv_scale, clk);
     } else if (!GIVEN_T) {
-        float a[N];
-        float v[N];
-#pragma unroll
-        for (int c = 0; c < N; ++c) v[c] = (c == row) ? 1.f : 0.f;
-
-        // ---- load: coalesced into LDS, then row `row` (lower triangle mirrored)
-        const float* __restrict__ Ab = args.A + (size_t)b * n * n;
-        const float rcp_n = 1.0f / (float)n;
-        chunked_copy<copy_chunk(N * N)>(
-            n * n, lane, [&](int idx) { return Ab[idx]; },
-            [&](int idx, float x) {
-                const int i = (int)(((float)idx + 0.5f) * rcp_n);
-                sV[i * LD + (idx - i * n)] = x;
-            });
-        wave_sync();
-        float amax = 0.f;
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-            float x = 0.f;
-            if (row < n && c < n) x = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
-            a[c] = x;
-            amax = fmaxf(amax, fabsf(x));   // fmaxf drops NaNs; they still reach the output through the arithmetic
-        }
-        wave_sync();
-        float scale;
-        pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
-#pragma unroll
-        for (int c = 0; c < N; ++c) a[c] *= scale;
-        clk.lap(kPhLoad);
-
-        // ---- Householder tridiagonalisation, column J reduced at step J ----
-        // Branch-free: a step that has nothing to do (J >= n-2, or the column is
-        // already reduced) runs with u = 0 and beta = 0.
-        // u and q are broadcast through LDS (one write, then 128-bit reads that every lane
-        // issues for the same address); the latency of each round trip is covered by
-        // independent work: the rank-1 update of V is deferred by one step and runs while
-        // the next u is in flight, and the part of the rank-2 update of A that needs only
-        // this lane's q runs while q is in flight.
-        float ud[N];          // u of the previous step (for the deferred update of V)
-        float wd = 0.f;       // its 2 V u / |u|^2
-#pragma unroll
-        for (int c = 0; c < N; ++c) ud[c] = 0.f;
-#pragma unroll
-        for (int J = 0; J < N; ++J) {
-            const float dJ = read_lane(a[J], J);      // final once columns 0..J-1 are reduced
-            float eJ = 0.f;
-            if (J < N - 1) {
-                const float x0 = read_lane(a[J], J + 1);     // A[J+1][J]
-                eJ = x0;                                      // kept as is when no reflector is applied
-                if (J < N - 2) {
-                    const float x = (row > J) ? a[J] : 0.f;   // A[r][J], r > J
-                    const float alpha = wave_sum<W>(x * x);   // |x|^2
-                    const bool active = (J < n - 2) && (alpha > kTinyAlpha);
-                    const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                    const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
-                    float ur = (row == J + 1) ? (x0 + sigma) : ((row > J + 1) ? x : 0.f);
-                    ur = active ? ur : 0.f;
-                    const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
-                    eJ = active ? -sigma : x0;
-                    // Up to 32 rows, u and p are broadcast with v_readlane (scalar operands of the
-                    // FMAs); beyond, through LDS (one write, then 128-bit reads of one address).
-                    constexpr bool RL = (N <= 32);
-                    if (!RL) svec[lane] = ur;
-                    if (WANT_V && J > 0) {
-                        // deferred: V <- V - w u^T of step J-1 (columns J .. N-1)
-#pragma unroll
-                        for (int c = J; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
-                    }
-                    if (!RL) __syncthreads();
-                    float u[N];
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) u[c] = RL ? read_lane(ur, c) : svec[c];
-                    // p = 2 A u / |u|^2, w = 2 V u / |u|^2; four partial sums each
-                    float pp[4] = {0.f, 0.f, 0.f, 0.f}, ww[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) {
-                        pp[c & 3] = fmaf(a[c], u[c], pp[c & 3]);
-                        if (WANT_V) ww[c & 3] = fmaf(v[c], u[c], ww[c & 3]);
-                    }
-                    const float p = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));
-                    wd = beta * ((ww[0] + ww[1]) + (ww[2] + ww[3]));
-                    // A - q u^T - u q^T with q = p - K u, regrouped as A - (p - 2K u) u^T - u p^T
-                    // (p is broadcast before K is known; same arithmetic as the role-lane variant)
-                    if (!RL) sq[lane] = p;
-                    const float K2 = beta * wave_sum<W>(ur * p);  // 2K
-                    const float sr = fmaf(-K2, ur, p);
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) a[c] = fmaf(-sr, u[c], a[c]);
-                    if (!RL) __syncthreads();
-#pragma unroll
-                    for (int c = J + 1; c < N; ++c) {
-                        a[c] = fmaf(-ur, RL ? read_lane(p, c) : sq[c], a[c]);
-                        ud[c] = u[c];
-                    }
-                    // keep the steps apart: interleaving them makes the compiler hoist the next
-                    // steps' loads and run out of registers
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            // sP[J+1].x = e[J], sP[J].y = d[J]
-            if (lane == 0) {
-                sP[J].y = dJ;
-                sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
-            }
-        }
-        if (WANT_V && N > 2) {
-            // the last reflector's deferred update of V
-#pragma unroll
-            for (int c = N - 2; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
-        }
-        if (lane == 0) sP[0].x = 0.f;
-        if (WANT_V) {
-#pragma unroll
-            for (int c = 0; c < N; ++c) sV[c * LD + row] = v[c];
-        }
-        wave_sync();
+        tridiag_rows<N, LD, WANT_V>(args.A + (size_t)b * n * n, n, lane, sV, sP, svec, sq, inv_scale, clk);
     } else {
         // ---- stage hook 2: tridiagonal given ----
         float dv = 0.f, ev = 0.f;

@@ -1,0 +1,80 @@
+"""The divide-and-conquer path of bed_syevd and bed_spd_fn at the sizes where it can go wrong: leaves of
+one and two rows, uneven halves, edges of the tiles, heavy deflation, rotations of close poles.  Same
+bars as the rotation kernels (eigenvalues 1e-5 ||A||_2, residual and orthogonality 1e-5 n)."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _check, _solve_gpu
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [5, 6, 7, 8, 9, 12, 13, 15, 16, 17, 20, 21, 24, 25, 28, 29, 31, 32]
+
+
+def _structured(n, seed):
+    rng = np.random.default_rng(seed)
+    one = np.eye(n, k=1) + np.eye(n, k=-1)
+    wilkinson = np.tile(np.abs(np.arange(21) - 10.0), 1 + n // 21)[:n]
+    weak = np.ones(n - 1)
+    weak[20::21] = 1e-7                                     # glued: pairs equal to rounding
+    split = rng.standard_normal(n - 1)
+    split[::3] = 0.0
+    x = rng.standard_normal(n)
+    Q = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    graded = 10.0 ** -np.linspace(0, 12, n)
+    mats = [np.zeros((n, n)), np.eye(n), np.diag(x), 2 * np.eye(n) - one, np.ones((n, n)), np.eye(n) + 1e-7 * one,
+            np.diag(wilkinson) + np.diag(weak, 1) + np.diag(weak, -1),
+            np.diag(x) + np.diag(split, 1) + np.diag(split, -1),
+            np.outer(x, x) + 0.5 * np.eye(n), -np.outer(x, x) - 0.5 * np.eye(n),
+            np.diag(graded) + 0.5 * np.diag(graded[1:], 1) + 0.5 * np.diag(graded[1:], -1),
+            (Q * np.repeat(x, 5)[:n]) @ Q.T]
+    A = np.stack(mats)
+    return (0.5 * (A + A.transpose(0, 2, 1))).astype(np.float32)
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_decomposition_and_eigenvalues_only(n):
+    from paper_2207_04228_amd import workloads
+    for A, name in ((workloads.covariance(9, n, 4 * n, 1e-4, 6100 + n), "full rank"),
+                    (workloads.covariance(9, n, max(1, n // 2), 1e-2, 6200 + n), "half rank"),
+                    (_structured(n, n), "structured")):
+        _check(A, f"divide and conquer, {name}, n={n}")
+        lam, V = _solve_gpu(A)
+        only, none = _solve_gpu(A, want_vectors=False)
+        assert none is None
+        norm = np.abs(lam).max(axis=1, keepdims=True)
+        assert np.all(np.abs(lam - only) <= 1e-5 * norm)
+
+
+def _solve_raw(A32):
+    """(evals, evecs, info of the spectral function): _solve_gpu compares the input with itself, which NaN fails"""
+    import torch
+    from paper_2207_04228_amd import binding
+    At = torch.from_numpy(A32).cuda()
+    lam, V = binding.bed_syevd(At)
+    return lam, V, binding.bed_spd_fn(At, binding.BED_FN_SQRT, 1e-6)[2]
+
+
+def test_scales_and_non_finite_inputs():
+    from paper_2207_04228_amd import workloads
+    for n in (7, 16, 30):
+        A = workloads.covariance(6, n, 4 * n, 1e-4, 6300 + n)
+        for s in (1e-30, 1e-20, 1e18):
+            _check((A.astype(np.float64) * s).astype(np.float32), f"scaled by {s:g}, n={n}")
+        good, _ = _solve_gpu(A)
+        B = A.copy()
+        B[1, 4, 2] = np.nan
+        B[3, 5, 5] = np.inf
+        lam, V, info = (t.cpu().numpy() for t in _solve_raw(B))
+        keep = [0, 2, 4, 5]
+        assert np.array_equal(lam[keep], good[keep])            # the others are untouched
+        assert np.isnan(lam[[1, 3]]).all() and np.isnan(V[[1, 3]]).all()
+        assert (info[[1, 3]] > 0).all() and (info[keep] == 0).all()
+
+
+@pytest.mark.parametrize("fn", [0, 1])
+def test_spectral_function(fn):
+    from test_gpu_spd_fn import _check as check_fn
+    from paper_2207_04228_amd import workloads
+    for n in (5, 8, 13, 16, 19, 28, 32):
+        check_fn(workloads.covariance(7, n, 4 * n, 1e-3, 6400 + n), fn, 1e-6, f"divide and conquer n={n}")
