@@ -1,10 +1,11 @@
 // Divide and conquer for the symmetric tridiagonal eigenproblem, one matrix per workgroup.
 //
 // T is torn into blocks of one or two rows: every coupling e between two blocks is taken out as a
-// rank-one term, T = diag(T1', T2') + rho z z^T with rho = 2|e| (Cuppen 1981), and the blocks are
+// rank-one term, T = diag(T1', T2') + rho z z^T with |z| = 1 (Cuppen 1981), and the blocks are
 // merged pairwise, all merges of a level at once.  A merge of m eigenvalues
 //   - deflates components of z that are negligible and pairs of poles that a plane rotation
-//     decouples within the tolerance (Dongarra and Sorensen 1987),
+//     decouples (Dongarra and Sorensen 1987), to rounding of the pole itself and not of the largest
+//     one, which keeps small eigenvalues of graded matrices,
 //   - finds the roots of the secular equation 1/rho + sum z_j^2 / (d_j - lambda) = 0, one root per
 //     thread, from rational interpolation with the two neighbouring poles (Bunch, Nielsen and
 //     Sorensen 1978; Li 1993), inside a bracket and measured from the nearer pole,
@@ -46,7 +47,8 @@ __device__ __forceinline__ dc_acc16 dc_mfma(float a, float b, dc_acc16 c) {
 }
 
 constexpr float kDcTol = 4.7683716e-7f;         // 8 units of rounding (2^-24)
-constexpr float kDcTiny = 5.9604645e-8f;        // blocks below 2^-24 of the pre-scaled matrix deflate at an absolute 3e-14
+constexpr float kDcFloor = 9.5367432e-7f;       // poles below 2^-20 of the block's norm deflate by that
+constexpr float kDcTiny = 1.5258789e-5f;        // blocks below 2^-16 of the pre-scaled matrix deflate by that
 constexpr float kDcFar = 1.0e4f;                 // a pole beyond every eigenvalue of the pre-scaled matrix
 constexpr int kDcMaxIter = 60;                  // bisection alone ends a bracket in fewer
 
@@ -70,6 +72,7 @@ struct DcShared {
     float first[N], last[N];             // by column: first and last row of its block's eigenvectors
     float dS[N], zS[N];                  // sorted by d
     float dd[N];                         // by slot: d, also of deflated poles
+    float rho[N], za[N], zb[N];          // per coupling: weight of the rank-one term, its two sides in z
     float rn[N];                         // reciprocal norm of a column of U
     int perm[N];                         // sorted position -> column
     int src[N];                          // slot -> column
@@ -115,12 +118,12 @@ struct DcMask {
     }
 };
 
-// Are two neighbouring kept poles with components za, zb decoupled by a rotation within tol?
-// |gap c s| <= tol with c, s = za, zb normalised; as a ratio, so that nothing underflows.
-__device__ __forceinline__ bool dc_close(float gap, float za, float zb, float tol) {
-    const float hi = fmaxf(fabsf(za), fabsf(zb)), lo = fminf(fabsf(za), fabsf(zb));
+// Are two neighbouring kept poles dp <= dq with components zp, zq decoupled by a rotation?  |gap c s| within
+// the tolerance of the larger pole, c, s = zp, zq normalised; as a ratio, so that nothing underflows.
+__device__ __forceinline__ bool dc_close(float dp, float dq, float zp, float zq, float floor) {
+    const float hi = fmaxf(fabsf(zp), fabsf(zq)), lo = fminf(fabsf(zp), fabsf(zq));
     const float q = lo * __builtin_amdgcn_rcpf(hi);
-    return gap * q <= tol * fmaf(q, q, 1.f);
+    return (dq - dp) * q <= kDcTol * fmaxf(fmaxf(fabsf(dp), fabsf(dq)), floor) * fmaf(q, q, 1.f);
 }
 
 // 1 / sqrt(x) to the last bit or two
@@ -199,6 +202,25 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
         }
         sync();
     }
+    // Couplings.  e is torn out as rho w w^T with w = (a, +-b) on the two rows, which takes |e| tau and
+    // |e| / tau off their diagonal entries.  tau = 1 unless the two diagonal entries differ in size:
+    // then tau ~ sqrt(d_k / d_k+1), and where |e|^2 <= d_k d_k+1 (positive definite T) each side loses no
+    // more than its own size.  With tau = 1 small rows of a graded T would be left with the
+    // rounding of a large e: A^(-1/2) of 128x128 covariances with power-law spectra, condition
+    // 1e3, was off by 9e-5 instead of 5e-6.  tau is a power of two.
+    auto tau_of = [&](int k) {
+        const float a = fabsf(dget(k)), c = fabsf(dget(k + 1)), b = fabsf(eget(k));
+        if (!(b * b <= a * c) || b == 0.f) return 1.f;
+        const int ex = (__builtin_amdgcn_frexp_expf(a) - __builtin_amdgcn_frexp_expf(c)) >> 1;
+        return ldexpf(1.f, min(max(ex, -30), 30));
+    };
+    if (part == 0 && e < n - 1) {
+        const float tau = tau_of(e), ec = eget(e);
+        const float w = 1.f / sqrtf(fmaf(tau, tau, 1.f));
+        S.rho[e] = fabsf(ec) * (tau + 1.f / tau);
+        S.za[e] = tau * w;
+        S.zb[e] = ec < 0.f ? -w : w;
+    }
     float lam = __builtin_inff();   // eigenvalue of column e
     if (part == 0) {
         S.rn[e] = 1.f;
@@ -208,7 +230,8 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
         S.last[e] = 0.f;
         if (valid) {
             const int lo = (leaf * n) >> L, hi = ((leaf + 1) * n) >> L;
-            const float el = lo > 0 ? fabsf(eget(lo - 1)) : 0.f, eh = hi < n ? fabsf(eget(hi - 1)) : 0.f;
+            const float el = lo > 0 ? fabsf(eget(lo - 1)) / tau_of(lo - 1) : 0.f;
+            const float eh = hi < n ? fabsf(eget(hi - 1)) * tau_of(hi - 1) : 0.f;
             float cc = 1.f, ss = 0.f;
             if (hi - lo == 1) {
                 lam = dget(lo) - el - eh;
@@ -261,9 +284,8 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
 
         // ---- z, and the order of the poles ----
         if (valid) {
-            const float ec = eget(mid - 1);
             const float zr = e < mid ? S.last[e] : S.first[e];
-            const float ze = 0.70710678f * ((e >= mid && ec < 0.f) ? -zr : zr);
+            const float ze = zr * (e < mid ? S.za : S.zb)[mid - 1];
             const float de = lam;
             int cnt = 0;
 #pragma unroll
@@ -290,18 +312,19 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
 
         // ---- deflation; every wavefront looks at all positions, so the masks need no exchange ----
         DcMask<NB> kept, close;
-        float tolq[NB], rhoq[NB];
+        float flq[NB], rhoq[NB];        // floor for the size of a pole, weight
+
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int q = lane + 64 * b;
             bool k = false;
-            tolq[b] = rhoq[b] = 0.f;
+            flq[b] = rhoq[b] = 0.f;
             if (q < n) {
                 const int bq = leafq[b] >> level;
-                rhoq[b] = 2.f * fabsf(eget(mid_of(bq) - 1));
+                rhoq[b] = S.rho[mid_of(bq) - 1];
                 const float dmax = fmaxf(fabsf(S.dS[lo_of(bq)]), fabsf(S.dS[lo_of(bq + 1) - 1]));
-                tolq[b] = kDcTol * fmaxf(fmaxf(dmax, rhoq[b]), kDcTiny);
-                k = rhoq[b] * fabsf(S.zS[q]) > tolq[b];
+                flq[b] = kDcFloor * fmaxf(fmaxf(dmax, rhoq[b]), kDcTiny);
+                k = rhoq[b] * fabsf(S.zS[q]) > kDcTol * fmaxf(fabsf(S.dS[q]), flq[b]);
             }
             kept.w[b] = __ballot(k);
         }
@@ -312,7 +335,7 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
             bool c = false;
             if (q < n && kept.has(q)) {
                 const int nx = kept.next(q);
-                if (nx < lo_of((leafq[b] >> level) + 1)) c = dc_close(S.dS[nx] - S.dS[q], S.zS[q], S.zS[nx], tolq[b]);
+                if (nx < lo_of((leafq[b] >> level) + 1)) c = dc_close(S.dS[q], S.dS[nx], S.zS[q], S.zS[nx], flq[b]);
             }
             close.w[b] = __ballot(c);
             any |= close.w[b];
@@ -324,16 +347,15 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
             if (valid && part == 0 && e == lo) {
                 int nr = 0;
                 if (close.below(hi) != close.below(lo)) {
-                    const float rho = 2.f * fabsf(eget(mid - 1));
                     const float dmax = fmaxf(fabsf(S.dS[lo]), fabsf(S.dS[hi - 1]));
-                    const float tol = kDcTol * fmaxf(fmaxf(dmax, rho), kDcTiny);
+                    const float fl = kDcFloor * fmaxf(fmaxf(dmax, S.rho[mid - 1]), kDcTiny);
                     int p = kept.has(lo) ? lo : kept.next(lo);
                     float dp = p < hi ? S.dS[p] : 0.f, zp = p < hi ? S.zS[p] : 0.f;
                     while (p < hi) {
                         const int q = kept.next(p);
                         if (q >= hi) break;
                         float dq = S.dS[q], zq = S.zS[q];
-                        if (dc_close(dq - dp, zp, zq, tol)) {
+                        if (dc_close(dp, dq, zp, zq, fl)) {
                             const float big = fmaxf(fabsf(zp), fabsf(zq)), r = fminf(fabsf(zp), fabsf(zq)) / big;
                             const float tau = big * sqrtf(fmaf(r, r, 1.f));
                             const float c = zq / tau, s = -zp / tau;
@@ -362,7 +384,8 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int q = lane + 64 * b;
-                kept.w[b] = __ballot(q < n && rhoq[b] * fabsf(S.zS[q < n ? q : 0]) > tolq[b]);
+                const float d = S.dS[q < n ? q : 0], z = S.zS[q < n ? q : 0];
+                kept.w[b] = __ballot(q < n && rhoq[b] * fabsf(z) > kDcTol * fmaxf(fabsf(d), flq[b]));
             }
         }
 
@@ -395,7 +418,7 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
         float dl[PP], z2[PP];               // distances from the origin of the root, squares of z
         {
             const float2* const pz = S.dz + base;
-            const float rho = valid ? 2.f * fabsf(eget(mid - 1)) : 1.f;
+            const float rho = valid ? S.rho[mid - 1] : 1.f;
             const float rinv = __builtin_amdgcn_rcpf(rho);
             const bool many = root && K > 1;
             const int i1 = many ? min(k, K - 2) : 0;
@@ -472,11 +495,13 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
                     const float a = (d1 + d2) * F - d1 * d2 * dF;
                     const float b = d1 * d2 * F;
                     float x = mu + dc_quadratic(a, b, c, sgn);
-                    if (!(x > lb && x < ub)) x = 0.5f * (lb + ub);
+                    const bool bisect = !(x > lb && x < ub);
+                    if (bisect) x = 0.5f * (lb + ub);
                     const bool inside = x != mu && x > lb && x < ub;
-                    // convergence is quadratic in the step over the distance of the nearer pole: below
-                    // 2^-12 of it the next step would be below the rounding of mu
-                    open = inside && !(fabsf(x - mu) <= 2.4414062e-4f * fminf(fabsf(d1), fabsf(d2)));
+                    // interpolation converges quadratically in the step over the distance of the nearer
+                    // pole: below 2^-12 of it the next step would be below the rounding of mu
+                    const bool small = fabsf(x - mu) <= 2.4414062e-4f * fminf(fabsf(d1), fabsf(d2));
+                    open = inside && (bisect || !small);
                     if (inside) mu = x;
                 } else {
                     open = false;

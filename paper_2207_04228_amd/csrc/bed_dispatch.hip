@@ -21,6 +21,7 @@ hipError_t launch_wave_n56(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_wave_n64(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_block(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_dc_wave(const KernelArgs&, int, bool, hipStream_t);
+hipError_t launch_dc_block(const KernelArgs&, int, bool, hipStream_t);
 
 namespace {
 
@@ -122,15 +123,24 @@ Choice wave_choice(int n) {
 //   n = 24: batch 4096: 93.5 / 79.9  16384: 248 / 238 (eigenvalues 159 / 172)
 //   n = 28: batch 4096: 124 / 95     16384: 308 / 276
 //   n = 32: batch 64: 82 / 34        512: 90 / 42        4096: 152 / 85      16384: 390 / 290
+// and one workgroup per matrix beyond, three of them on a compute unit for n <= 64 (768 on the chip):
+//   n = 36: batch 256: 114 / 66    768: 124 / 84     2048: 157 / 221
+//   n = 40: batch 512: 127 / 79    4096: 334 / 447
+//   n = 48: batch 512: 166 / 87    1024: 186 / 167   4096: 445 / 495 (eigenvalues 340 / 322)
+//   n = 64: batch 50: 272 / 89     256: 282 / 99     1024: 300 / 199   2048: 575 / 306
+//   n = 100: batch 50: 757 / 209   n = 128: batch 256: 1186 / 260      1024: 4620 / 980
 // Up to four rows the rotations need one or two sweeps and win everywhere; where four matrices share
-// a wavefront (packed kernels) small n keeps the rotations.
+// a wavefront (packed kernels) small n keeps the rotations, and so does n just above 32, where half of
+// the 64-row workgroup works on padding, once more matrices wait than the chip holds.
 bool divide_and_conquer(const KernelArgs& args, int stage, int forced) {
     if (forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
     if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;
     const int n = args.n, batch = args.batch;
-    if (n <= 4 || n > 32) return false;
+    if (n <= 4) return false;
     if (n <= 16) return batch < kPackedFromBatch;
     if (n <= 24) return batch <= kPackedRowsFromBatch;
+    if (n > 32 && n <= 40) return batch <= 768;
+    if (n > 40 && n <= 48) return batch <= 1024;
     return true;
 }
 
@@ -153,7 +163,8 @@ bool family_serves(int family, int n) {
 
 hipError_t launch(const KernelArgs& args, int stage, bool want_v, hipStream_t stream, int forced) {
     if (args.batch == 0) return hipSuccess;
-    if (divide_and_conquer(args, stage, forced)) return launch_dc_wave(args, stage, want_v, stream);
+    if (divide_and_conquer(args, stage, forced)) 
+        return args.n <= 32 ? launch_dc_wave(args, stage, want_v, stream) : launch_dc_block(args, stage, want_v, stream);
     const Choice c = choose(args.batch, args.n, stage, want_v, forced);
     if (c.family == kPairFamily) {
         if (!want_v || stage != kFull) return hipErrorInvalidValue;     // the pair kernels always form eigenvectors

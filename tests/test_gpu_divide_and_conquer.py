@@ -8,7 +8,8 @@ from test_gpu_parity import _check, _solve_gpu
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [5, 6, 7, 8, 9, 12, 13, 15, 16, 17, 20, 21, 24, 25, 28, 29, 31, 32]
+SIZES = [5, 6, 7, 8, 9, 12, 13, 15, 16, 17, 20, 21, 24, 25, 28, 29, 31, 32,
+         33, 36, 47, 48, 49, 63, 64, 65, 95, 96, 97, 100, 127, 128]
 
 
 def _structured(n, seed):
@@ -57,7 +58,7 @@ def _solve_raw(A32):
 
 def test_scales_and_non_finite_inputs():
     from paper_2207_04228_amd import workloads
-    for n in (7, 16, 30):
+    for n in (7, 16, 30, 50, 90):
         A = workloads.covariance(6, n, 4 * n, 1e-4, 6300 + n)
         for s in (1e-30, 1e-20, 1e18):
             _check((A.astype(np.float64) * s).astype(np.float32), f"scaled by {s:g}, n={n}")
@@ -72,9 +73,40 @@ def test_scales_and_non_finite_inputs():
         assert (info[[1, 3]] > 0).all() and (info[keep] == 0).all()
 
 
+@pytest.mark.parametrize("n", [16, 32, 64, 100, 128])
+def test_small_eigenvalues_of_graded_covariances(n):
+    """Power-law spectrum in a rotated basis, condition 1e3: the inverse square root needs the small eigenvalues
+    to a few units of their own size (rounding of the large ones alone would show as 1e-4)."""
+    import torch
+    from paper_2207_04228_amd import binding
+    rng = np.random.default_rng(n)
+    Q = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    X = (rng.standard_normal((6, 4 * n, n)) / np.arange(1, n + 1)) @ Q
+    A = (np.einsum("bki,bkj->bij", X, X) / (4 * n) + 1e-3 * np.eye(n)).astype(np.float32)
+    lam, V = np.linalg.eigh(A.astype(np.float64))
+    ref = (V / np.sqrt(lam)[:, None, :]) @ V.transpose(0, 2, 1)
+    F = binding.bed_spd_fn(torch.from_numpy(A).cuda(), binding.BED_FN_INV_SQRT, 1e-6)[0].cpu().numpy()
+    err = np.linalg.norm(F - ref) / np.linalg.norm(ref)
+    print(f"graded n={n}: relative error of A^(-1/2) {err:.1e}")
+    assert err <= 1e-5          # the rotations reach 2e-6 (n = 16) to 6e-6 (n = 128)
+
+
 @pytest.mark.parametrize("fn", [0, 1])
 def test_spectral_function(fn):
     from test_gpu_spd_fn import _check as check_fn
     from paper_2207_04228_amd import workloads
-    for n in (5, 8, 13, 16, 19, 28, 32):
+    for n in (5, 8, 13, 16, 19, 28, 32, 33, 64, 65, 128):
         check_fn(workloads.covariance(7, n, 4 * n, 1e-3, 6400 + n), fn, 1e-6, f"divide and conquer n={n}")
+
+
+@pytest.mark.parametrize("n, batch", [(8, 2048), (32, 4096), (36, 768), (48, 1024), (64, 2048), (100, 1024), (128, 1024)])
+def test_full_chip_of_copies(n, batch):
+    """Copies of four matrices, several workgroups on every compute unit: all copies come out bit for bit
+    the same whatever their neighbours do (wavefronts of a workgroup that run apart show here)."""
+    import torch
+    from paper_2207_04228_amd import binding, workloads
+    A = torch.from_numpy(workloads.covariance(4, n, 2 * n, 1e-3, 6500 + n)).cuda().repeat(batch // 4, 1, 1)
+    lam, V = binding.bed_syevd(A)
+    only, _ = binding.bed_syevd(A, want_vectors=False)
+    assert torch.equal(lam, lam[:4].repeat(batch // 4, 1)) and torch.equal(V, V[:4].repeat(batch // 4, 1, 1))
+    assert torch.equal(lam, only)
