@@ -6,7 +6,7 @@
  * (one exception, stated there: bed_syevd_lockstep_static works in scratch
  * memory built into the library, which calls on the same GPU share).
  * All entry points are asynchronous: they enqueue their kernels (one, except
- * for the lock-step procedure) on `stream` (a hipStream_t passed as void*;
+ * for the lock-step procedure and some sizes of bed_spd_fn_eigh) on `stream` (a hipStream_t passed as void*;
  * NULL = the default stream) and return.  Argument errors are detected on the
  * host, return a negative bed_status and enqueue nothing.  Entry points are
  * re-entrant and thread-safe (same exception).
@@ -215,6 +215,15 @@ int bed_tridiag_qr_sweeps(const float* d, const float* e, int batch, int n, int 
  */
 int bed_spd_fn(const float* A, int batch, int n, int fn, float floor, float* out,
                float* evals, int* info, void* stream);
+
+/*
+ * bed_spd_fn that also leaves the decomposition it comes from, for callers that need it later
+ * (bed_spd_fn_backward of a training step): evals [batch][n] ascending and evecs [batch][n][n] as
+ * written by bed_syevd, both required; info may be NULL.  One kernel where divide and conquer
+ * decomposes, two elsewhere.
+ */
+int bed_spd_fn_eigh(const float* A, int batch, int n, int fn, float floor, float* out,
+                    float* evals, float* evecs, int* info, void* stream);
 
 typedef enum {
     BED_GRAD_EXACT = 0,  /* K_ij = 1/(lambda_j - lambda_i) where |lambda_j - lambda_i| >= gap_floor, else 0 */

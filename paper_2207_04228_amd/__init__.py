@@ -26,6 +26,7 @@ from .binding import (  # noqa: F401
     bed_spd_fn,
     bed_spd_fn_backward,
     bed_syevd_backward,
+    bed_spd_fn_eigh,
     bed_syevd,
     bed_syevd_info,
     bed_syevd_lockstep,

@@ -31,19 +31,21 @@ def _functions():
 
     class SpdFn(torch.autograd.Function):
         @staticmethod
-        def forward(ctx, A, fn, floor):
+        def forward(ctx, A, fn, floor, training):
             A = A.contiguous()
-            out, _, _ = binding.bed_spd_fn(A, fn, floor)
-            ctx.save_for_backward(A)
+            if not training:
+                return binding.bed_spd_fn(A, fn, floor)[0]
+            # the forward pass leaves the decomposition that the gradient needs; A is saved with it so
+            # that changing it in place before the backward pass is noticed
+            out, evals, evecs = binding.bed_spd_fn_eigh(A, fn, floor)
+            ctx.save_for_backward(A, evals, evecs)
             ctx.fn, ctx.floor = fn, floor
             return out
 
         @staticmethod
         def backward(ctx, g_out):
-            (A,) = ctx.saved_tensors
-            # the fused forward keeps V on chip; the backward needs it, so it is recomputed
-            evals, evecs = binding.bed_syevd(A)
-            return binding.bed_spd_fn_backward(evals, evecs, g_out.contiguous(), ctx.fn, ctx.floor), None, None
+            _, evals, evecs = ctx.saved_tensors
+            return binding.bed_spd_fn_backward(evals, evecs, g_out.contiguous(), ctx.fn, ctx.floor), None, None, None
 
     return Syevd, SpdFn
 
@@ -58,6 +60,12 @@ def _get():
     return _cache
 
 
+def _differentiated(A):
+    """Will a backward pass follow?  (Inside forward() gradients are always off.)"""
+    import torch
+    return torch.is_grad_enabled() and A.requires_grad
+
+
 def eigh(A, degree: int = 9):
     """Differentiable (evals ascending, evecs as columns) of symmetric A [batch, n, n]; the
     gradient uses the truncated series of the given degree for the eigenvalue coupling."""
@@ -66,9 +74,9 @@ def eigh(A, degree: int = 9):
 
 def spd_sqrt(A, floor: float = 0.0):
     """Differentiable A^(1/2) with eigenvalues raised to `floor`."""
-    return _get()[1].apply(A, binding.BED_FN_SQRT, float(floor))
+    return _get()[1].apply(A, binding.BED_FN_SQRT, float(floor), _differentiated(A))
 
 
 def spd_inv_sqrt(A, floor: float = 1e-6):
     """Differentiable A^(-1/2) with eigenvalues raised to `floor` (> 0)."""
-    return _get()[1].apply(A, binding.BED_FN_INV_SQRT, float(floor))
+    return _get()[1].apply(A, binding.BED_FN_INV_SQRT, float(floor), _differentiated(A))

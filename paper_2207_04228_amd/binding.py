@@ -56,6 +56,8 @@ def load_library():
         lib.bed_tridiag_qr_sweeps.restype = ci
         lib.bed_spd_fn.argtypes = [vp, ci, ci, ci, ctypes.c_float, vp, vp, vp, vp]
         lib.bed_spd_fn.restype = ci
+        lib.bed_spd_fn_eigh.argtypes = [vp, ci, ci, ci, ctypes.c_float, vp, vp, vp, vp, vp]
+        lib.bed_spd_fn_eigh.restype = ci
         lib.bed_syevd_backward.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ctypes.c_float, vp, vp]
         lib.bed_syevd_backward.restype = ci
         lib.bed_spd_fn_backward.argtypes = [vp, vp, vp, ci, ci, ci, ctypes.c_float, vp, vp]
@@ -395,6 +397,22 @@ def bed_spd_fn(A, fn, floor, out=None, *, want_evals=False, stream=None):
 
 BED_GRAD_EXACT = 0
 BED_GRAD_TAYLOR = 1
+
+
+def bed_spd_fn_eigh(A, fn, floor, *, stream=None):
+    """bed_spd_fn that also returns the decomposition it comes from: (out [batch, n, n],
+    evals [batch, n] ascending, evecs [batch, n, n] with eigenvectors as columns)."""
+    import torch
+    _check_dev(A, "A", torch.float32)
+    batch, n = _square_batch(A)
+    out = torch.empty((batch, n, n), dtype=torch.float32, device=A.device)
+    evals = torch.empty((batch, n), dtype=torch.float32, device=A.device)
+    evecs = torch.empty((batch, n, n), dtype=torch.float32, device=A.device)
+    st = load_library().bed_spd_fn_eigh(_ptr(A), batch, n, int(fn), float(floor), _ptr(out), _ptr(evals),
+                                        _ptr(evecs), None, _stream(stream))
+    if st != 0:
+        raise BedError(st, "bed_spd_fn_eigh")
+    return out, evals, evecs
 
 
 def bed_syevd_backward(evals, evecs, grad_evals=None, grad_evecs=None, *, mode=BED_GRAD_TAYLOR, degree=9,

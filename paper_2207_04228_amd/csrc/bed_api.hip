@@ -217,18 +217,23 @@ int bed_tridiag_qr_sweeps(const float* d, const float* e, int batch, int n, int 
     return run(args, bed::kQrPartial, true, stream);
 }
 
-int bed_spd_fn(const float* A, int batch, int n, int fn, float floor, float* out, float* evals, int* info,
-               void* stream) {
+}  // extern "C"
+
+namespace {
+
+int spd_fn_checked(const float* A, int batch, int n, int fn, float floor, float* out, float* evals, float* evecs,
+                   int* info, bool want_vectors, void* stream) {
     int st = check_common(batch, n);
     if (st != BED_OK) return st;
     if (fn != BED_FN_SQRT && fn != BED_FN_INV_SQRT) return BED_ERR_ARG;
     if (!(floor >= 0.f) || !(floor < __builtin_inff())) return BED_ERR_ARG;
     if (fn == BED_FN_INV_SQRT && !(floor > 0.f)) return BED_ERR_ARG;
     if (batch == 0) return BED_OK;
-    if (!A || !out) return BED_ERR_NULL;
-    if (misaligned(A) || misaligned(out) || misaligned(evals) || misaligned(info)) return BED_ERR_ALIGN;
+    if (!A || !out || (want_vectors && (!evals || !evecs))) return BED_ERR_NULL;
+    if (misaligned(A) || misaligned(out) || misaligned(evals) || misaligned(evecs) || misaligned(info)) return BED_ERR_ALIGN;
     const size_t mat = (size_t)batch * n * n * sizeof(float), vec = (size_t)batch * n * sizeof(float);
-    if (overlaps(A, mat, out, mat) || overlaps(A, mat, evals, vec) || overlaps(out, mat, evals, vec))
+    if (overlaps(A, mat, out, mat) || overlaps(A, mat, evals, vec) || overlaps(out, mat, evals, vec) ||
+        overlaps(A, mat, evecs, mat) || overlaps(out, mat, evecs, mat) || overlaps(evals, vec, evecs, mat))
         return BED_ERR_ALIAS;
     bed::KernelArgs args{};
     args.A = A;
@@ -236,10 +241,25 @@ int bed_spd_fn(const float* A, int batch, int n, int fn, float floor, float* out
     args.fn = (fn == BED_FN_INV_SQRT) ? bed::kFnInvSqrt : bed::kFnSqrt;
     args.fn_floor = floor;
     args.evals = evals;
+    args.evecs = evecs;
     args.info = info;
     args.batch = batch;
     args.n = n;
     return run(args, bed::kSpectral, true, stream);
+}
+
+}  // namespace
+
+extern "C" {
+
+int bed_spd_fn(const float* A, int batch, int n, int fn, float floor, float* out, float* evals, int* info,
+               void* stream) {
+    return spd_fn_checked(A, batch, n, fn, floor, out, evals, nullptr, info, false, stream);
+}
+
+int bed_spd_fn_eigh(const float* A, int batch, int n, int fn, float floor, float* out, float* evals, float* evecs,
+                    int* info, void* stream) {
+    return spd_fn_checked(A, batch, n, fn, floor, out, evals, evecs, info, true, stream);
 }
 
 int bed_syevd_backward(const float* evals, const float* evecs, const float* grad_evals, const float* grad_evecs,

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
                     acc[tj] = dc_mfma(pa[s], S.V[(2 * s + hi) * LD + 32 * (J0 + tj * JSTEP) + lo], acc[tj]);
             }
         }
-        if (STAGE == kFull) {
+        if (STAGE == kFull || args.evecs) {          // the same in all threads
             __syncthreads();                         // ranks
             float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
 #pragma unroll
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
                     if (r < n && c < n) Vb[r * n + rank] = acc[tj][v];
                 }
             }
-        } else {
+        }
+        if (STAGE == kSpectral) {
             // F = (V f(max(Lambda, floor))) V^T (Sec. 4.2-4.4): both operands are rows of V
 #pragma unroll
             for (int tj = 0; tj < TJ; ++tj)

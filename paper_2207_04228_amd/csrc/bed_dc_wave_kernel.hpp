@@ -64,14 +64,15 @@ __global__ __launch_bounds__(64) void dc_wave_kernel(KernelArgs args) {
         Acc acc{};
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = dc_mfma(pa[s], S.V[(KT * s + hi) * LD + lo], acc);
-        if (STAGE == kFull) {
+        if (STAGE == kFull || args.evecs) {
             float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
 #pragma unroll
             for (int v = 0; v < AR; ++v) {
                 const int r = dc_row<R>(v, lane);
                 if (r < n && lo < n) Vb[r * n + rank] = acc[v];
             }
-        } else {
+        }
+        if (STAGE == kSpectral) {
             // F = (V f(max(Lambda, floor))) V^T (Sec. 4.2-4.4): both operands are the same entry of V
 #pragma unroll
             for (int v = 0; v < AR; ++v) S.U[dc_row<R>(v, lane) * LD + lo] = acc[v];

@@ -22,6 +22,7 @@ hipError_t launch_wave_n64(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_block(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_dc_wave(const KernelArgs&, int, bool, hipStream_t);
 hipError_t launch_dc_block(const KernelArgs&, int, bool, hipStream_t);
+hipError_t launch_spectral(const KernelArgs&, hipStream_t);
 
 namespace {
 
@@ -165,6 +166,12 @@ hipError_t launch(const KernelArgs& args, int stage, bool want_v, hipStream_t st
     if (args.batch == 0) return hipSuccess;
     if (divide_and_conquer(args, stage, forced)) 
         return args.n <= 32 ? launch_dc_wave(args, stage, want_v, stream) : launch_dc_block(args, stage, want_v, stream);
+    if (stage == kSpectral && args.evecs) {
+        // the spectral function and the decomposition it comes from: the rotation kernels keep V on chip
+        // for the former or write it for the latter, so a second kernel forms the function
+        const hipError_t err = launch(args, kFull, true, stream, forced);
+        return err == hipSuccess ? launch_spectral(args, stream) : err;
+    }
     const Choice c = choose(args.batch, args.n, stage, want_v, forced);
     if (c.family == kPairFamily) {
         if (!want_v || stage != kFull) return hipErrorInvalidValue;     // the pair kernels always form eigenvectors

@@ -239,7 +239,77 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
             }
 }
 
+// F = V f(max(Lambda, floor)) V^T from a decomposition in memory, n <= 64 (larger n forms F in the kernel
+// that decomposes).  Same tiles and packing as grad_kernel; one product, so the call is bound by its
+// launch for small batches and by reading V and writing F for large ones.
+template <int NT, int PB>
+__global__ __launch_bounds__(64) void spectral_kernel(KernelArgs args) {
+    static_assert(PB == 0 || (NT == 1 && 32 % PB == 0), "packing needs one 32 x 32 tile");
+    constexpr int NMAT = PB ? 32 / PB : 1;
+    constexpr int NP = 32 * NT, LD = NP + 1;
+    __shared__ float sV[NP * LD];
+    __shared__ float sW[NP * LD];      // V f
+    __shared__ float sf[NP];
+    const int lane = threadIdx.x;
+    const int b = blockIdx.x * NMAT;
+    const int count = min(NMAT, args.batch - b);
+    const int n = args.n;
+    auto blk = [](int p) { return PB ? p / (PB ? PB : 1) : 0; };
+    auto loc = [](int p) { return PB ? p % (PB ? PB : 1) : p; };
+    for (int idx = lane; idx < NP * LD; idx += 64) {
+        sV[idx] = 0.f;
+        sW[idx] = 0.f;
+    }
+    if (lane < NP) {
+        float f = 0.f;
+        if (blk(lane) < count && loc(lane) < n) {
+            const float x = fmaxf(args.evals[(size_t)(b + blk(lane)) * n + loc(lane)], args.fn_floor);
+            f = (args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x);
+        }
+        sf[lane] = f;
+    }
+    wave_sync();
+    const float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
+    const float rcp_n = 1.0f / (float)n;
+    const float rcp_nn = rcp_n * rcp_n;
+    chunked_copy<8>(
+        count * n * n, lane, [&](int idx) { return Vb[idx]; },
+        [&](int idx, float x) {
+            const int m = PB ? (int)(((float)idx + 0.5f) * rcp_nn) : 0;
+            const int r = idx - m * n * n;
+            const int i = (int)(((float)r + 0.5f) * rcp_n);
+            const int j = m * PB + r - i * n;
+            sV[(m * PB + i) * LD + j] = x;
+            sW[(m * PB + i) * LD + j] = x * sf[j];
+        });
+    wave_sync();
+    floatx16 acc[NT][NT];
+    product<NT, NT, false, true>(acc, sW, sV, PB ? 32 : ((n + 1) & ~1), lane, 0);
+    float* __restrict__ Fb = args.fn_out + (size_t)b * n * n;
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int i = 32 * ti + acc_row(v, lane);
+                const int j = 32 * tj + (lane & 31);
+                const bool inside = blk(i) == blk(j) && blk(i) < count && loc(i) < n && loc(j) < n;
+                if (inside) Fb[(size_t)blk(i) * n * n + loc(i) * n + loc(j)] = acc[ti][tj][v];
+            }
+}
+
 }  // namespace
+
+hipError_t launch_spectral(const KernelArgs& args, hipStream_t stream) {
+    const int n = args.n, B = args.batch;
+    if (n <= 4) return enqueue(spectral_kernel<1, 4>, dim3((B + 7) / 8), dim3(64), stream, args);
+    if (n <= 8) return enqueue(spectral_kernel<1, 8>, dim3((B + 3) / 4), dim3(64), stream, args);
+    if (n <= 16) return enqueue(spectral_kernel<1, 16>, dim3((B + 1) / 2), dim3(64), stream, args);
+    if (n <= 32) return enqueue(spectral_kernel<1, 0>, dim3(B), dim3(64), stream, args);
+    if (n <= 64) return enqueue(spectral_kernel<2, 0>, dim3(B), dim3(64), stream, args);
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_grad(const GradArgs& args, hipStream_t stream) {
     if (args.batch == 0) return hipSuccess;

@@ -78,7 +78,7 @@ struct KernelArgs {
     const float* d_in;   // [batch][n]               (kQrOnly)
     const float* e_in;   // [batch][n]               (kQrOnly)
     float* evals;        // [batch][n]               (kFull, kQrOnly)
-    float* evecs;        // [batch][n][n] or P       (when vectors are wanted)
+    float* evecs;        // [batch][n][n] or P       (when vectors are wanted; kSpectral: V too if not null)
     float* d_out;        // [batch][n]               (kTridiagOnly)
     float* e_out;        // [batch][n]               (kTridiagOnly)
     float* fn_out;       // [batch][n][n]            (kSpectral) V f(lambda) V^T

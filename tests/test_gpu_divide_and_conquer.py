@@ -110,3 +110,38 @@ def test_full_chip_of_copies(n, batch):
     only, _ = binding.bed_syevd(A, want_vectors=False)
     assert torch.equal(lam, lam[:4].repeat(batch // 4, 1)) and torch.equal(V, V[:4].repeat(batch // 4, 1, 1))
     assert torch.equal(lam, only)
+
+
+@pytest.mark.parametrize("n, batch", [(1, 5), (2, 67), (4, 1000), (8, 4099), (13, 2561), (16, 40), (20, 5001), (32, 70), (40, 1025), (48, 2048),
+                                      (64, 20), (65, 9), (128, 5)])
+def test_function_with_its_decomposition(n, batch):
+    """bed_spd_fn_eigh on both of its routes: the function as bed_spd_fn gives it, the decomposition as bed_syevd does."""
+    import torch
+    from paper_2207_04228_amd import binding, workloads
+    A = torch.from_numpy(workloads.covariance(batch, n, 4 * n, 1e-3, 6600 + n)).cuda()
+    for fn in (binding.BED_FN_SQRT, binding.BED_FN_INV_SQRT):
+        out, lam, V = binding.bed_spd_fn_eigh(A, fn, 1e-6)
+        ref, _, _ = binding.bed_spd_fn(A, fn, 1e-6)
+        lam1, V1 = binding.bed_syevd(A)
+        assert torch.equal(lam, lam1) and torch.equal(V, V1)
+        err = ((out - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)).max()
+        assert err <= 1e-5, err        # 32-bit sums of n terms, in another order
+
+
+def test_training_step_saves_what_it_needs_and_notices_changes():
+    import torch
+    from paper_2207_04228_amd import autograd, binding, workloads
+    A = torch.from_numpy(workloads.covariance(6, 20, 80, 1e-3, 6700)).cuda()
+    G = torch.randn(6, 20, 20, device="cuda")
+    x = A.clone().requires_grad_(True)
+    out = autograd.spd_sqrt(x, 1e-6)
+    (g,) = torch.autograd.grad(out, x, G)
+    lam, V = binding.bed_syevd(A)
+    assert torch.equal(g, binding.bed_spd_fn_backward(lam, V, G, binding.BED_FN_SQRT, 1e-6))
+    with torch.no_grad():
+        assert torch.equal(autograd.spd_sqrt(x, 1e-6), binding.bed_spd_fn(A, binding.BED_FN_SQRT, 1e-6)[0])
+    out = autograd.spd_sqrt(x, 1e-6)
+    with torch.no_grad():
+        x.add_(1.0)
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(out, x, G)
