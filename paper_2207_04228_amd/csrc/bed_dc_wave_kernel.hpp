@@ -45,7 +45,7 @@ __global__ __launch_bounds__(64) void dc_wave_kernel(KernelArgs args) {
             pa[s] = k < n ? stage[k * SLD + lo] : 0.f;
         }
     } else {
-        tridiag_rows<N, SLD, false>(args.A + (size_t)b * n * n, n, lane, stage, sP, nullptr, nullptr, inv_scale, clk);
+        tridiag_values<N, SLD>(args.A + (size_t)b * n * n, n, lane, stage, sP, inv_scale);
     }
     sync();
 

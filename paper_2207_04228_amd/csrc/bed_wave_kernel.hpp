@@ -676,126 +676,73 @@ __device__ __forceinline__ void tridiag_half(const float* __restrict__ Ab, const
     wave_sync();
 }
 
-template <int N, int LD, bool WANT_V>
-__device__ __forceinline__ void tridiag_rows(const float* __restrict__ Ab, const int n, const int lane, float* const sV,
-                                             float2* const sP, float* const svec, float* const sq, float& inv_scale,
-                                             PhaseClock& clk) {
+// The same reduction without P, n <= 32 (wave_kernel keeps its own copy of these lines: with arrays of 40
+// and more rows the compiler spills 250 registers when they come from a function).
+template <int N, int LD>
+__device__ __forceinline__ void tridiag_values(const float* __restrict__ Ab, const int n, const int lane,
+                                               float* const stage, float2* const sP, float& inv_scale) {
+    static_assert(N <= 32, "rows in half a wavefront");
     constexpr int W = lanes_for(N);
-    const int row = (N <= 32) ? (lane & 31) : lane;
+    const int row = lane & 31;
     float a[N];
-    float v[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) v[c] = (c == row) ? 1.f : 0.f;
-
-    // ---- load: coalesced into LDS, then row `row` (lower triangle mirrored)
     const float rcp_n = 1.0f / (float)n;
     chunked_copy<copy_chunk(N * N)>(
         n * n, lane, [&](int idx) { return Ab[idx]; },
         [&](int idx, float x) {
             const int i = (int)(((float)idx + 0.5f) * rcp_n);
-            sV[i * LD + (idx - i * n)] = x;
+            stage[i * LD + (idx - i * n)] = x;
         });
     wave_sync();
     float amax = 0.f;
 #pragma unroll
     for (int c = 0; c < N; ++c) {
         float x = 0.f;
-        if (row < n && c < n) x = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
+        if (row < n && c < n) x = (c <= row) ? stage[row * LD + c] : stage[c * LD + row];
         a[c] = x;
-        amax = fmaxf(amax, fabsf(x));   // fmaxf drops NaNs; they still reach the output through the arithmetic
+        amax = fmaxf(amax, fabsf(x));
     }
     wave_sync();
     float scale;
     pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
 #pragma unroll
     for (int c = 0; c < N; ++c) a[c] *= scale;
-    clk.lap(kPhLoad);
-
-    // ---- Householder tridiagonalisation, column J reduced at step J ----
-    // Branch-free: a step that has nothing to do (J >= n-2, or the column is
-    // already reduced) runs with u = 0 and beta = 0.
-    // u and q are broadcast through LDS (one write, then 128-bit reads that every lane
-    // issues for the same address); the latency of each round trip is covered by
-    // independent work: the rank-1 update of V is deferred by one step and runs while
-    // the next u is in flight, and the part of the rank-2 update of A that needs only
-    // this lane's q runs while q is in flight.
-    float ud[N];          // u of the previous step (for the deferred update of V)
-    float wd = 0.f;       // its 2 V u / |u|^2
-#pragma unroll
-    for (int c = 0; c < N; ++c) ud[c] = 0.f;
 #pragma unroll
     for (int J = 0; J < N; ++J) {
-        const float dJ = read_lane(a[J], J);      // final once columns 0..J-1 are reduced
+        const float dJ = read_lane(a[J], J);
         float eJ = 0.f;
         if (J < N - 1) {
-            const float x0 = read_lane(a[J], J + 1);     // A[J+1][J]
-            eJ = x0;                                      // kept as is when no reflector is applied
+            const float x0 = read_lane(a[J], J + 1);
+            eJ = x0;
             if (J < N - 2) {
-                const float x = (row > J) ? a[J] : 0.f;   // A[r][J], r > J
-                const float alpha = wave_sum<W>(x * x);   // |x|^2
+                const float x = (row > J) ? a[J] : 0.f;
+                const float alpha = wave_sum<W>(x * x);
                 const bool active = (J < n - 2) && (alpha > kTinyAlpha);
                 const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
+                const float sigma = (x0 < 0.f) ? -nrm : nrm;
                 float ur = (row == J + 1) ? (x0 + sigma) : ((row > J + 1) ? x : 0.f);
                 ur = active ? ur : 0.f;
-                const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
+                const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;
                 eJ = active ? -sigma : x0;
-                // Up to 32 rows, u and p are broadcast with v_readlane (scalar operands of the
-                // FMAs); beyond, through LDS (one write, then 128-bit reads of one address).
-                constexpr bool RL = (N <= 32);
-                if (!RL) svec[lane] = ur;
-                if (WANT_V && J > 0) {
-                    // deferred: V <- V - w u^T of step J-1 (columns J .. N-1)
-#pragma unroll
-                    for (int c = J; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
-                }
-                if (!RL) __syncthreads();
                 float u[N];
 #pragma unroll
-                for (int c = J + 1; c < N; ++c) u[c] = RL ? read_lane(ur, c) : svec[c];
-                // p = 2 A u / |u|^2, w = 2 V u / |u|^2; four partial sums each
-                float pp[4] = {0.f, 0.f, 0.f, 0.f}, ww[4] = {0.f, 0.f, 0.f, 0.f};
+                for (int c = J + 1; c < N; ++c) u[c] = read_lane(ur, c);
+                float pp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int c = J + 1; c < N; ++c) {
-                    pp[c & 3] = fmaf(a[c], u[c], pp[c & 3]);
-                    if (WANT_V) ww[c & 3] = fmaf(v[c], u[c], ww[c & 3]);
-                }
+                for (int c = J + 1; c < N; ++c) pp[c & 3] = fmaf(a[c], u[c], pp[c & 3]);
                 const float p = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));
-                wd = beta * ((ww[0] + ww[1]) + (ww[2] + ww[3]));
-                // A - q u^T - u q^T with q = p - K u, regrouped as A - (p - 2K u) u^T - u p^T
-                // (p is broadcast before K is known; same arithmetic as the role-lane variant)
-                if (!RL) sq[lane] = p;
-                const float K2 = beta * wave_sum<W>(ur * p);  // 2K
+                const float K2 = beta * wave_sum<W>(ur * p);
                 const float sr = fmaf(-K2, ur, p);
 #pragma unroll
-                for (int c = J + 1; c < N; ++c) a[c] = fmaf(-sr, u[c], a[c]);
-                if (!RL) __syncthreads();
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) {
-                    a[c] = fmaf(-ur, RL ? read_lane(p, c) : sq[c], a[c]);
-                    ud[c] = u[c];
-                }
-                // keep the steps apart: interleaving them makes the compiler hoist the next
-                // steps' loads and run out of registers
+                for (int c = J + 1; c < N; ++c) a[c] = fmaf(-ur, read_lane(p, c), fmaf(-sr, u[c], a[c]));
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // sP[J+1].x = e[J], sP[J].y = d[J]
         if (lane == 0) {
             sP[J].y = dJ;
             sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
         }
     }
-    if (WANT_V && N > 2) {
-        // the last reflector's deferred update of V
-#pragma unroll
-        for (int c = N - 2; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
-    }
     if (lane == 0) sP[0].x = 0.f;
-    if (WANT_V) {
-#pragma unroll
-        for (int c = 0; c < N; ++c) sV[c * LD + row] = v[c];
-    }
     wave_sync();
 }
 
@@ -842,7 +789,122 @@ __global__ __launch_bounds__(64) void wave_kernel(KernelArgs args) {
     if (!GIVEN_T && HALF && WANT_V) {
         tridiag_half<N, LD>(args.A + (size_t)b * n * n, n, lane, sV, sP, inv_scale, clk);
     } else if (!GIVEN_T) {
-        tridiag_rows<N, LD, WANT_V>(args.A + (size_t)b * n * n, n, lane, sV, sP, svec, sq, inv_scale, clk);
+        float a[N];
+        float v[N];
+#pragma unroll
+        for (int c = 0; c < N; ++c) v[c] = (c == row) ? 1.f : 0.f;
+
+        // ---- load: coalesced into LDS, then row `row` (lower triangle mirrored)
+        const float* __restrict__ Ab = args.A + (size_t)b * n * n;
+        const float rcp_n = 1.0f / (float)n;
+        chunked_copy<copy_chunk(N * N)>(
+            n * n, lane, [&](int idx) { return Ab[idx]; },
+            [&](int idx, float x) {
+                const int i = (int)(((float)idx + 0.5f) * rcp_n);
+                sV[i * LD + (idx - i * n)] = x;
+            });
+        wave_sync();
+        float amax = 0.f;
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            float x = 0.f;
+            if (row < n && c < n) x = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
+            a[c] = x;
+            amax = fmaxf(amax, fabsf(x));   // fmaxf drops NaNs; they still reach the output through the arithmetic
+        }
+        wave_sync();
+        float scale;
+        pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
+#pragma unroll
+        for (int c = 0; c < N; ++c) a[c] *= scale;
+        clk.lap(kPhLoad);
+
+        // ---- Householder tridiagonalisation, column J reduced at step J ----
+        // Branch-free: a step that has nothing to do (J >= n-2, or the column is
+        // already reduced) runs with u = 0 and beta = 0.
+        // u and q are broadcast through LDS (one write, then 128-bit reads that every lane
+        // issues for the same address); the latency of each round trip is covered by
+        // independent work: the rank-1 update of V is deferred by one step and runs while
+        // the next u is in flight, and the part of the rank-2 update of A that needs only
+        // this lane's q runs while q is in flight.
+        float ud[N];          // u of the previous step (for the deferred update of V)
+        float wd = 0.f;       // its 2 V u / |u|^2
+#pragma unroll
+        for (int c = 0; c < N; ++c) ud[c] = 0.f;
+#pragma unroll
+        for (int J = 0; J < N; ++J) {
+            const float dJ = read_lane(a[J], J);      // final once columns 0..J-1 are reduced
+            float eJ = 0.f;
+            if (J < N - 1) {
+                const float x0 = read_lane(a[J], J + 1);     // A[J+1][J]
+                eJ = x0;                                      // kept as is when no reflector is applied
+                if (J < N - 2) {
+                    const float x = (row > J) ? a[J] : 0.f;   // A[r][J], r > J
+                    const float alpha = wave_sum<W>(x * x);   // |x|^2
+                    const bool active = (J < n - 2) && (alpha > kTinyAlpha);
+                    const float nrm = __builtin_amdgcn_sqrtf(alpha);
+                    const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
+                    float ur = (row == J + 1) ? (x0 + sigma) : ((row > J + 1) ? x : 0.f);
+                    ur = active ? ur : 0.f;
+                    const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
+                    eJ = active ? -sigma : x0;
+                    // Up to 32 rows, u and p are broadcast with v_readlane (scalar operands of the
+                    // FMAs); beyond, through LDS (one write, then 128-bit reads of one address).
+                    constexpr bool RL = (N <= 32);
+                    if (!RL) svec[lane] = ur;
+                    if (WANT_V && J > 0) {
+                        // deferred: V <- V - w u^T of step J-1 (columns J .. N-1)
+#pragma unroll
+                        for (int c = J; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
+                    }
+                    if (!RL) __syncthreads();
+                    float u[N];
+#pragma unroll
+                    for (int c = J + 1; c < N; ++c) u[c] = RL ? read_lane(ur, c) : svec[c];
+                    // p = 2 A u / |u|^2, w = 2 V u / |u|^2; four partial sums each
+                    float pp[4] = {0.f, 0.f, 0.f, 0.f}, ww[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int c = J + 1; c < N; ++c) {
+                        pp[c & 3] = fmaf(a[c], u[c], pp[c & 3]);
+                        if (WANT_V) ww[c & 3] = fmaf(v[c], u[c], ww[c & 3]);
+                    }
+                    const float p = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));
+                    wd = beta * ((ww[0] + ww[1]) + (ww[2] + ww[3]));
+                    // A - q u^T - u q^T with q = p - K u, regrouped as A - (p - 2K u) u^T - u p^T
+                    // (p is broadcast before K is known; same arithmetic as the role-lane variant)
+                    if (!RL) sq[lane] = p;
+                    const float K2 = beta * wave_sum<W>(ur * p);  // 2K
+                    const float sr = fmaf(-K2, ur, p);
+#pragma unroll
+                    for (int c = J + 1; c < N; ++c) a[c] = fmaf(-sr, u[c], a[c]);
+                    if (!RL) __syncthreads();
+#pragma unroll
+                    for (int c = J + 1; c < N; ++c) {
+                        a[c] = fmaf(-ur, RL ? read_lane(p, c) : sq[c], a[c]);
+                        ud[c] = u[c];
+                    }
+                    // keep the steps apart: interleaving them makes the compiler hoist the next
+                    // steps' loads and run out of registers
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            // sP[J+1].x = e[J], sP[J].y = d[J]
+            if (lane == 0) {
+                sP[J].y = dJ;
+                sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
+            }
+        }
+        if (WANT_V && N > 2) {
+            // the last reflector's deferred update of V
+#pragma unroll
+            for (int c = N - 2; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
+        }
+        if (lane == 0) sP[0].x = 0.f;
+        if (WANT_V) {
+#pragma unroll
+            for (int c = 0; c < N; ++c) sV[c * LD + row] = v[c];
+        }
+        wave_sync();
     } else {
         // ---- stage hook 2: tridiagonal given ----
         float dv = 0.f, ev = 0.f;
