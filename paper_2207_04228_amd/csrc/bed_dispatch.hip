@@ -128,6 +128,7 @@ Choice wave_choice(int n) {
 //   n = 36: batch 256: 114 / 66    768: 124 / 84     2048: 157 / 221
 //   n = 40: batch 512: 127 / 79    4096: 334 / 447
 //   n = 48: batch 512: 166 / 87    1024: 186 / 167   4096: 445 / 495 (eigenvalues 340 / 322)
+//   n = 52: batch 1024: 217 / 179  4096: 510 / 529   n = 56: batch 4096: 575 / 559
 //   n = 64: batch 50: 272 / 89     256: 282 / 99     1024: 300 / 199   2048: 575 / 306
 //   n = 100: batch 50: 757 / 209   n = 128: batch 256: 1186 / 260      1024: 4620 / 980
 // Up to four rows the rotations need one or two sweeps and win everywhere; where four matrices share
@@ -141,7 +142,7 @@ bool divide_and_conquer(const KernelArgs& args, int stage, int forced) {
     if (n <= 16) return batch < kPackedFromBatch;
     if (n <= 24) return batch <= kPackedRowsFromBatch;
     if (n > 32 && n <= 40) return batch <= 768;
-    if (n > 40 && n <= 48) return batch <= 1024;
+    if (n > 40 && n <= 52) return batch <= 1024;
     return true;
 }
 
