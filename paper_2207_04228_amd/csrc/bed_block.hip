@@ -24,7 +24,7 @@ constexpr int BT = 256;              // threads per matrix
 
 template <bool WANT_V, int STAGE>
 __global__ __launch_bounds__(BT) void block_kernel(KernelArgs args) {
-    __shared__ float sA[BN * BLD];               // A[r][c] at sA[c * BLD + r]; later V f(Lambda) (kSpectral)
+    __shared__ float sA[BN * BLD];               // A[r][c] at sA[c * BLD + r]
     __shared__ float sV[(BN + 8) * BLD];         // P, then V: V[r][c] at sV[c * BLD + r]
     __shared__ float2 sP_all[4 * BPA];           // one copy of T per wavefront: sP[k] = (e[k-1], d[k])
     __shared__ float sd[BN], se[BN];             // T as produced by the tridiagonalisation
@@ -254,29 +254,6 @@ __global__ __launch_bounds__(BT) void block_kernel(KernelArgs args) {
     qr_iterations<BN, true, WANT_V, BLD>(sP, sV, lane, 32 * wv + (lane & 31), n, rotations, info, d_lane, args, inv_scale, clk);
     __syncthreads();       // all four wavefronts leave after the same iteration; V is complete
 
-    if (STAGE == kSpectral) {
-        // F = V f(max(Lambda, floor)) V^T: W = V diag(f) into the area of A, then F = W V^T
-        if (tid < BN) {
-            float lam = fmaxf(sP_all[tid].y * inv_scale, args.fn_floor);
-            svec[tid] = (args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(lam) : __builtin_amdgcn_sqrtf(lam);
-        }
-        __syncthreads();
-        const int row = tid & (BN - 1);
-        for (int k = tid >> 7; k < n; k += 2) sA[k * BLD + row] = sV[k * BLD + row] * svec[k];
-        __syncthreads();
-        float* __restrict__ Fb = args.fn_out + (size_t)b * n * n;
-        for (int c = tid >> 7; c < n; c += 2) {
-            float acc0 = 0.f, acc1 = 0.f;
-            int k = 0;
-            for (; k + 1 < n; k += 2) {
-                acc0 = fmaf(sA[k * BLD + row], sV[k * BLD + c], acc0);
-                acc1 = fmaf(sA[(k + 1) * BLD + row], sV[(k + 1) * BLD + c], acc1);
-            }
-            if (k < n) acc0 = fmaf(sA[k * BLD + row], sV[k * BLD + c], acc0);
-            if (row < n) Fb[c * n + row] = acc0 + acc1;     // F is symmetric: stored as F[c][row], coalesced
-        }
-    }
-
     // ---- ascending order: rank of d[k] among d[0..n) ----
     if (tid < n) {
         const float dk = sP_all[tid].y;
@@ -289,7 +266,7 @@ __global__ __launch_bounds__(BT) void block_kernel(KernelArgs args) {
         if (args.evals) args.evals[(size_t)b * n + rank] = dk * inv_scale;
         sinv[rank] = tid;                                   // output column `rank` comes from column `tid`
     }
-    if (STAGE != kSpectral && WANT_V) {
+    if (WANT_V) {
         __syncthreads();
         float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
         const float rcp_n = 1.0f / (float)n;
@@ -317,7 +294,7 @@ hipError_t launch_block(const KernelArgs& args, int stage, bool want_v, hipStrea
         return want_v ? launch_block_one<true, kTridiagOnly>(args, stream) : launch_block_one<false, kTridiagOnly>(args, stream);
     if (stage == kQrOnly)
         return want_v ? launch_block_one<true, kQrOnly>(args, stream) : launch_block_one<false, kQrOnly>(args, stream);
-    if (stage == kSpectral) return launch_block_one<true, kSpectral>(args, stream);
+    if (stage != kFull) return hipErrorInvalidValue;      // the spectral function comes from divide and conquer
     return want_v ? launch_block_one<true, kFull>(args, stream) : launch_block_one<false, kFull>(args, stream);
 }
 

@@ -478,7 +478,11 @@ __global__ __launch_bounds__(64) void packed_rows_kernel(KernelArgs args) {
 template <int N>
 static hipError_t launch_packed_rows_n(const KernelArgs& args, int stage, bool want_v, hipStream_t stream) {
     const unsigned blocks = (unsigned)((args.batch + 3) / 4);
-    if (stage == kSpectral) return enqueue(packed_rows_kernel<N, true, kSpectral>, dim3(blocks), dim3(64), stream, args);
+    if (stage == kSpectral) {
+        // beyond 24 rows the spectral function comes from divide and conquer
+        if constexpr (N <= 24) return enqueue(packed_rows_kernel<N, true, kSpectral>, dim3(blocks), dim3(64), stream, args);
+        else return hipErrorInvalidValue;
+    }
     if (want_v) return enqueue(packed_rows_kernel<N, true, kFull>, dim3(blocks), dim3(64), stream, args);
     return enqueue(packed_rows_kernel<N, false, kFull>, dim3(blocks), dim3(64), stream, args);
 }

@@ -1059,7 +1059,11 @@ static hipError_t launch_n(const KernelArgs& args, int stage, bool want_v, hipSt
         return want_v ? launch_one<N, true, kQrOnly>(args, stream)
                       : launch_one<N, false, kQrOnly>(args, stream);
     }
-    if (stage == kSpectral) return launch_one<N, true, kSpectral>(args, stream);
+    if (stage == kSpectral) {
+        // the other sizes' spectral functions come from divide and conquer or the packed kernels
+        if constexpr (N <= 8 || (N >= 40 && N <= 56)) return launch_one<N, true, kSpectral>(args, stream);
+        else return hipErrorInvalidValue;
+    }
     if (stage == kQrPartial) return launch_one<N, true, kQrPartial>(args, stream);
     return want_v ? launch_one<N, true, kFull>(args, stream)
                   : launch_one<N, false, kFull>(args, stream);

@@ -58,7 +58,7 @@ def _solve_raw(A32):
 
 def test_scales_and_non_finite_inputs():
     from paper_2207_04228_amd import workloads
-    for n in (7, 16, 30, 50, 90):
+    for n in (11, 16, 30, 50, 90):
         A = workloads.covariance(6, n, 4 * n, 1e-4, 6300 + n)
         for s in (1e-30, 1e-20, 1e18):
             _check((A.astype(np.float64) * s).astype(np.float32), f"scaled by {s:g}, n={n}")
