@@ -131,15 +131,16 @@ Choice wave_choice(int n) {
 //   n = 52: batch 1024: 217 / 179  4096: 510 / 529   n = 56: batch 4096: 575 / 559
 //   n = 64: batch 50: 272 / 89     256: 282 / 99     1024: 300 / 199   2048: 575 / 306
 //   n = 100: batch 50: 757 / 209   n = 128: batch 256: 1186 / 260      1024: 4620 / 980
-// Up to eight rows the rotations keep the call: one small matrix takes 9 us against 11 (n = 5 to 7), and
-// the gain at n = 8 in a batch of 512 is 1.5 us; where four matrices share
+// Few small matrices keep the rotations, whose launch lasts as long as its slowest matrix: n = 5 to 7: 9 us
+// against 11; n = 9: batch 1: 11.3 / 15.4, 64: 15.2 / 15.8; n = 10: batch 16: 18.9 / 16.2; n = 12: batch 1:
+// 15.7 / 15.6 (eigenvalues 12.7 / 13.4), 512: 21.0 / 17.5; n = 16: batch 1: 24.5 / 16.9.  Where four matrices share
 // a wavefront (packed kernels) small n keeps the rotations, and so does n just above 32, where half of
 // the 64-row workgroup works on padding, once more matrices wait than the chip holds.
 bool divide_and_conquer(const KernelArgs& args, int stage, int forced) {
     if (forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
     if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;
     const int n = args.n, batch = args.batch;
-    if (n <= 8) return false;
+    if (n <= 9 || (n <= 12 && batch < 16)) return false;
     if (n <= 16) return batch < kPackedFromBatch;
     if (n <= 24) return batch <= kPackedRowsFromBatch;
     if (n > 32 && n <= 40) return batch <= 768;

@@ -8,7 +8,7 @@ from test_gpu_parity import _check, _solve_gpu
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [5, 6, 7, 8, 9, 12, 13, 15, 16, 17, 20, 21, 24, 25, 28, 29, 31, 32,
+SIZES = [5, 6, 7, 8, 9, 10, 11, 12, 13, 15, 16, 17, 20, 21, 24, 25, 28, 29, 31, 32,
          33, 36, 47, 48, 49, 63, 64, 65, 95, 96, 97, 100, 127, 128]
 
 
@@ -36,8 +36,8 @@ def _structured(n, seed):
 @pytest.mark.parametrize("n", SIZES)
 def test_decomposition_and_eigenvalues_only(n):
     from paper_2207_04228_amd import workloads
-    for A, name in ((workloads.covariance(9, n, 4 * n, 1e-4, 6100 + n), "full rank"),
-                    (workloads.covariance(9, n, max(1, n // 2), 1e-2, 6200 + n), "half rank"),
+    for A, name in ((workloads.covariance(17, n, 4 * n, 1e-4, 6100 + n), "full rank"),
+                    (workloads.covariance(17, n, max(1, n // 2), 1e-2, 6200 + n), "half rank"),
                     (_structured(n, n), "structured")):
         _check(A, f"divide and conquer, {name}, n={n}")
         lam, V = _solve_gpu(A)
@@ -58,7 +58,7 @@ def _solve_raw(A32):
 
 def test_scales_and_non_finite_inputs():
     from paper_2207_04228_amd import workloads
-    for n in (11, 16, 30, 50, 90):
+    for n in (13, 16, 30, 50, 90):
         A = workloads.covariance(6, n, 4 * n, 1e-4, 6300 + n)
         for s in (1e-30, 1e-20, 1e18):
             _check((A.astype(np.float64) * s).astype(np.float32), f"scaled by {s:g}, n={n}")
