@@ -51,7 +51,7 @@ __device__ __forceinline__ void tridiag_tiles(const float* __restrict__ Ab, cons
                 const int i = (int)(((float)idx + 0.5f) * rcp_n);
                 const int j = idx - i * n;
                 if (idx < n * n && j <= i) {
-                    amax = fmaxf(amax, fabsf(t[k]));   // drops NaNs; they reach the output through the arithmetic
+                    amax = fmaxf(amax, fabsf(t[k]));   // drops NaNs; they reach T through the norm of their column
                     stage[i * LD + j] = t[k];
                     stage[j * LD + i] = t[k];
                 }
@@ -107,7 +107,9 @@ __device__ __forceinline__ void tridiag_tiles(const float* __restrict__ Ab, cons
                 float sq = S.u[lane] * S.u[lane];
                 if (N > 64) sq = fmaf(S.u[(lane + 64) & (N - 1)], S.u[(lane + 64) & (N - 1)], sq);
                 const float alpha = wave_sum<64>(sq);
-                const bool active = J < n - 2 && alpha > kTinyAlpha;
+                // a NaN in the column counts as active and goes into T: an inactive step touches nothing, and
+                // no later step reads the column again
+                const bool active = J < n - 2 && !(alpha <= kTinyAlpha);
                 if (tid == 0) {
                     const float nrm = __builtin_amdgcn_sqrtf(alpha);
                     se[J] = active ? (x0 < 0.f ? nrm : -nrm) : x0;

@@ -73,6 +73,41 @@ def test_scales_and_non_finite_inputs():
         assert (info[[1, 3]] > 0).all() and (info[keep] == 0).all()
 
 
+@pytest.mark.parametrize("n", [10, 16, 17, 32, 33, 48, 64, 65, 100, 128])
+def test_a_nan_that_only_its_own_column_sees(n):
+    """One non-finite entry below the first off-diagonal of a matrix whose other columns need no reflector, or in
+    uncoupled channels in front of a dense block: no later step touches it, so its own column has to carry it into T."""
+    import torch
+    from paper_2207_04228_amd import binding, workloads
+    h = n // 2
+    block = np.diag(np.linspace(1.0, 2.0, n))
+    block[h:, h:] = workloads.covariance(1, n - h, 4 * (n - h), 1e-4, 6800 + n)[0]
+    one = np.eye(n, k=1) + np.eye(n, k=-1)
+    mats = []
+    for base, places in ((np.eye(n), ((5, 0), (n - 1, 0), (n - 1, n - 3))), (np.diag(np.arange(1.0, n + 1)), ((5, 0), (n - 1, n - 4))),
+                         (2.0 * np.eye(n) - one, ((2, 0), (n - 1, n - 3))), (block, ((4, 0), (h - 1, h - 4)))):
+        for i, j in places:
+            for value in (np.nan, np.inf, -np.inf):
+                for x in (base[i, j], value):           # the clean matrix, then the same with the entry
+                    m = base.copy()
+                    m[i, j] = m[j, i] = x
+                    mats.append(m)
+    A = np.stack(mats).astype(np.float32)
+    clean = A.copy()
+    clean[1::2] = A[0::2]
+    At, Ct = torch.from_numpy(A).cuda(), torch.from_numpy(clean).cuda()
+    lam, V = binding.bed_syevd(At)
+    only, _ = binding.bed_syevd(At, want_vectors=False)
+    F, ev, info = binding.bed_spd_fn(At, binding.BED_FN_INV_SQRT, 1e-6, want_evals=True)
+    F2, lam2, V2 = binding.bed_spd_fn_eigh(At, binding.BED_FN_SQRT, 1e-6)
+    for t in (lam, V, only, F, ev, F2, lam2, V2):
+        lost = torch.isfinite(t[1::2].flatten(1)).any(dim=1).nonzero().flatten().tolist()
+        assert not lost, (n, lost)
+    assert (info[1::2] > 0).all() and (info[0::2] == 0).all()
+    lam_c, V_c = binding.bed_syevd(Ct)
+    assert torch.equal(lam[0::2], lam_c[0::2]) and torch.equal(V[0::2], V_c[0::2])      # the others are untouched
+
+
 @pytest.mark.parametrize("n", [16, 32, 64, 100, 128])
 def test_small_eigenvalues_of_graded_covariances(n):
     """Power-law spectrum in a rotated basis, condition 1e3: the inverse square root needs the small eigenvalues
