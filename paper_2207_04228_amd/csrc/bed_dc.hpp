@@ -8,7 +8,8 @@
 //     one, which keeps small eigenvalues of graded matrices,
 //   - finds the roots of the secular equation 1/rho + sum z_j^2 / (d_j - lambda) = 0, one root per
 //     thread, from rational interpolation with the two neighbouring poles (Bunch, Nielsen and
-//     Sorensen 1978; Li 1993), inside a bracket and measured from the nearer pole,
+//     Sorensen 1978; Li 1993: fixed weight and middle way in turn), inside a bracket and measured
+//     from the nearer pole,
 //   - recomputes z from the roots so that the eigenvectors are orthogonal to working precision
 //     whatever the last bits of the roots are (Gu and Eisenstat 1994),
 //   - multiplies the block's eigenvectors with those of the merge on the matrix cores (fp32).
@@ -50,7 +51,7 @@ constexpr float kDcTol = 4.7683716e-7f;         // 8 units of rounding (2^-24)
 constexpr float kDcFloor = 9.5367432e-7f;       // poles below 2^-20 of the block's norm deflate by that
 constexpr float kDcTiny = 1.5258789e-5f;        // blocks below 2^-16 of the pre-scaled matrix deflate by that
 constexpr float kDcFar = 1.0e4f;                 // a pole beyond every eigenvalue of the pre-scaled matrix
-constexpr int kDcMaxIter = 60;                  // bisection alone ends a bracket in fewer
+constexpr int kDcMaxIter = 60;                  // more than three times what any root has been seen to take
 
 // N: rows covered (16, 32, 64, 128); TPE: threads per eigenvalue.
 // The arrays that the inner loops read are laid out per block with the block size rounded up to
@@ -132,12 +133,12 @@ __device__ __forceinline__ float dc_rsqrt(float x) {
     return r * fmaf(-0.5f * x * r, r, 1.5f);
 }
 
-// Root of c x^2 - a x + b that interpolates a root between the two poles (s = 1) or right of both (s = -1).
+// Root of c x^2 - 2 a x + b that interpolates a root between the two poles (s = 1) or right of both (s = -1).
 __device__ __forceinline__ float dc_quadratic(float a, float b, float c, float s) {
-    const float disc = s * __builtin_amdgcn_sqrtf(fmaxf(fmaf(a, a, -4.f * b * c), 0.f));
+    const float disc = s * __builtin_amdgcn_sqrtf(fmaxf(fmaf(a, a, -b * c), 0.f));
     const bool neg = s * a <= 0.f;
-    const float num = neg ? a - disc : 2.f * b;
-    const float den = neg ? 2.f * c : a + disc;
+    const float num = neg ? a - disc : b;
+    const float den = neg ? c : a + disc;
     return num * __builtin_amdgcn_rcpf(den);
 }
 
@@ -439,29 +440,41 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
                     for (int i = c; i < c + 4; ++i) fm = fmaf(z2[i], __builtin_amdgcn_rcpf((dl[i] - pk.x) - half), fm);
                 } else {
 #pragma unroll
-                    for (int i = c; i < c + 4; ++i) dl[i] = kDcFar;
+                    for (int i = c; i < c + 4; ++i) dl[i] = kDcFar, z2[i] = 0.f;
                 }
             }
             fm = dc_sum<TPE>(fm) + rinv;
             const bool right = !last && fm < 0.f;
             dorg = right ? p2.x : pk.x;
+            // the pole at the origin leaves the sums: its term is known exactly, and near a root that almost
+            // touches it would swamp what the other poles contribute
+            const int org = right ? k + 1 : k;
+            const float zo = right ? p2.y : pk.y;
 #pragma unroll
-            for (int i = 0; i < PP; ++i) dl[i] -= dorg;
+            for (int c = 0; c < PP; c += 4) {
+                const int j = c * TPE + 4 * part;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    dl[c + i] -= dorg;
+                    z2[c + i] = j + i == org ? 0.f : z2[c + i];
+                }
+            }
             float lb = last ? (fm < 0.f ? half : 0.f) : (right ? -half : 0.f);
             float ub = last ? (fm < 0.f ? gap : half) : (right ? 0.f : half);
             const float D1 = p1.x - dorg, D2 = p2.x - dorg;
+            const float Do = right || last ? D1 : D2;           // the other pole of the interpolation
             const float sgn = last ? -1.f : 1.f;
             {
                 const float at = right ? -half : half;
                 const float c = fm - p1.y * __builtin_amdgcn_rcpf(D1 - at) - p2.y * __builtin_amdgcn_rcpf(D2 - at);
                 const float a = fmaf(c, D1 + D2, p1.y + p2.y);
                 const float b = fmaf(c * D1, D2, fmaf(p1.y, D2, p2.y * D1));
-                const float x = dc_quadratic(a, b, c, sgn);
+                const float x = dc_quadratic(0.5f * a, b, c, sgn);
                 mu = (x > lb && x < ub) ? x : 0.5f * (lb + ub);
             }
             bool open = many;
             for (int it = 0; it < kDcMaxIter && __ballot(open) != 0; ++it) {
-                float F = 0.f, dF = 0.f, N1 = 0.f, dN = 0.f;       // sums over all poles, over the terms below zero
+                float F = 0.f, dF = 0.f, N1 = 0.f, dN = 0.f;       // sums over all other poles, over the terms below zero
 #pragma unroll
                 for (int c = 0; c < PP; c += 4) {
                     if (c * TPE < trip) {
@@ -480,32 +493,33 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
                 N1 = dc_sum<TPE>(N1);
                 dF = dc_sum<TPE>(dF);
                 dN = dc_sum<TPE>(dN);
-                const float mag = F - 2.f * N1 + rinv;             // sum of the magnitudes
-                F += rinv;
-                const float err = fmaf(4.7683716e-7f, mag, 5.9604645e-8f * fabsf(mu) * dF);
-                const float d1 = D1 - mu, d2 = D2 - mu;
-                // derivative of the part left of the split; for the last root the split is before the last pole
-                const float r2 = __builtin_amdgcn_rcpf(d2);
-                const float dpsi = last ? dF - p2.y * r2 * r2 : dN;
-                const float dphi = dF - dpsi;
-                if (open && !(fabsf(F) <= err)) {
-                    if (F < 0.f) lb = mu;
-                    else ub = mu;
-                    const float c = F - d1 * dpsi - d2 * dphi;
-                    const float a = (d1 + d2) * F - d1 * d2 * dF;
-                    const float b = d1 * d2 * F;
-                    float x = mu + dc_quadratic(a, b, c, sgn);
-                    const bool bisect = !(x > lb && x < ub);
-                    if (bisect) x = 0.5f * (lb + ub);
-                    const bool inside = x != mu && x > lb && x < ub;
-                    // interpolation converges quadratically in the step over the distance of the nearer
-                    // pole: below 2^-12 of it the next step would be below the rounding of mu
-                    const bool small = fabsf(x - mu) <= 2.4414062e-4f * fminf(fabsf(d1), fabsf(d2));
-                    open = inside && (bisect || !small);
-                    if (inside) mu = x;
-                } else {
-                    open = false;
-                }
+                const float own = zo * __builtin_amdgcn_rcpf(mu);
+                const float mag = (F - 2.f * N1) + (fabsf(own) + rinv);    // sum of the magnitudes
+                const float R = F + rinv;
+                F = R - own;
+                const float err = fmaf(2.3841858e-7f, mag, 5.9604645e-8f * fabsf(mu) * dF);
+                lb = F < 0.f ? mu : lb;
+                ub = F < 0.f ? ub : mu;
+                // c + s / (Do - x) - so / x through value and derivative at mu.  Two steps with so = zo, exact,
+                // where Do takes the derivative of all the rest (fixed weight), two where so also takes the poles on
+                // the origin's side (middle way), and so on: each alone has cases in which it halves its
+                // way to the root.  Written in x and with mu for Do - d, so that nothing cancels however
+                // near the root is to the pole: with the equation for x - mu, repeated eigenvalues (24 rows of
+                // rank 18) took up to 19 iterations, now 8; the most for any of 1.1e7 roots emulated on the CPU is 17.
+                const float d = Do - mu;
+                const float side = (it & 2) && !last ? (right ? dF - dN : dN) : 0.f, rest = dF - side;
+                const float so = fmaf(side * mu, mu, zo);
+                const float c = fmaf(side, mu, fmaf(-rest, d, R));
+                const float a = fmaf(Do, fmaf(side, mu, R), fmaf(-rest * d, mu, so));
+                const float x = dc_quadratic(0.5f * a, so * Do, c, sgn);
+                const bool ok = x > lb && x < ub;               // mu is one of the two
+                // interpolation converges quadratically in the step over the distance of the nearer
+                // pole: below 2^-12 of it the next step would be below the rounding of mu
+                const bool small = ok && fabsf(x - mu) <= 2.4414062e-4f * fminf(fabsf(mu), fabsf(d));
+                const float y = ok ? x : 0.5f * (lb + ub);
+                const bool step = open && !(fabsf(F) <= err) && y > lb && y < ub;
+                mu = step ? y : mu;
+                open = step && !small;
             }
             if (root && !many) {
                 dorg = pk.x;
