@@ -342,17 +342,17 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
             any |= close.w[b];
         }
         if (any) {
-            // one thread per block walks its poles in order and rotates close pairs; the lower pole of
+            // one thread per block walks its close pairs in order and rotates them; the lower pole of
             // the pair loses its component of z
             sync();
             if (valid && part == 0 && e == lo) {
                 int nr = 0;
-                if (close.below(hi) != close.below(lo)) {
+                int p = close.has(lo) ? lo : close.next(lo);    // the lower pole of a close pair
+                if (p < hi) {
                     const float dmax = fmaxf(fabsf(S.dS[lo]), fabsf(S.dS[hi - 1]));
                     const float fl = kDcFloor * fmaxf(fmaxf(dmax, S.rho[mid - 1]), kDcTiny);
-                    int p = kept.has(lo) ? lo : kept.next(lo);
-                    float dp = p < hi ? S.dS[p] : 0.f, zp = p < hi ? S.zS[p] : 0.f;
-                    while (p < hi) {
+                    float dp = S.dS[p], zp = S.zS[p];
+                    while (true) {
                         const int q = kept.next(p);
                         if (q >= hi) break;
                         float dq = S.dS[q], zq = S.zS[q];
@@ -373,10 +373,15 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
                             S.first[cq] = fmaf(c, fq, -s * fp);
                             S.last[cp] = fmaf(c, lp, s * lq);
                             S.last[cq] = fmaf(c, lq, -s * lp);
+                            p = q;                              // has moved: its upper neighbour may be close now
+                            dp = dq;
+                            zp = zq;
+                        } else {
+                            p = close.next(p);                  // untouched poles in between stay apart
+                            if (p >= hi) break;
+                            dp = S.dS[p];
+                            zp = S.zS[p];
                         }
-                        p = q;
-                        dp = dq;
-                        zp = zq;
                     }
                 }
                 S.nrot[lo] = nr;

@@ -150,7 +150,8 @@ def test_full_chip_of_copies(n, batch):
 @pytest.mark.parametrize("n", [12, 16, 24, 32])
 def test_repeated_eigenvalues_take_no_longer(n):
     """Kernel time on rank-deficient covariances (three quarters of full rank, the rest of the spectrum at the ridge)
-    against full rank, as in the application's own batches.  It was 1.4 times as long."""
+    against full rank, as in the application's own batches.  It was 1.4 times as long;
+    the slowest matrix of the batch sets the time, and a few close poles must not make it visit all of them."""
     import torch
     from paper_2207_04228_amd import binding, workloads
     us = []
@@ -165,7 +166,7 @@ def test_repeated_eigenvalues_take_no_longer(n):
             binding.bed_syevd(A, lam, V)
         us.append(float(binding.bed_timing_end(30)[0].min()))
     print(f"n={n}: full rank {us[0]:.1f} us, repeated eigenvalues {us[1]:.1f} us")
-    assert us[1] <= 1.35 * us[0]
+    assert us[1] <= 1.2 * us[0]
 
 
 @pytest.mark.parametrize("n, batch", [(1, 5), (2, 67), (4, 1000), (8, 4099), (13, 2561), (16, 40), (20, 5001), (32, 70), (40, 1025), (48, 2048),
