@@ -122,7 +122,7 @@ int bed_syevd_info(const float* A, int batch, int n, float* evals, float* evecs,
  *   sweep_cap    > 0: at most this many QR sweeps per matrix (two per outer iteration; App. B runs
  *                n outer iterations, i.e. 2 n sweeps); off-diagonals still live then are counted in
  *                info.  0: the default cap of 30 n.  < 0: BED_ERR_ARG.
- * Everything else as bed_syevd_info.
+ * Everything else as bed_syevd_info; epsilon_abs > 0 or sweep_cap > 0 selects the rotation kernels too.
  */
 int bed_syevd_tol(const float* A, int batch, int n, float* evals, float* evecs, int* info,
                   unsigned* rotations, float epsilon_abs, int sweep_cap, void* stream);
@@ -132,7 +132,7 @@ int bed_syevd_tol(const float* A, int batch, int n, float* evals, float* evecs, 
  * family at every batch size, and for measuring the batch sizes at which the automatic choice
  * should change).  Same method, arguments and outputs; the families differ in how matrices
  * map onto the machine:
- *   BED_FAMILY_AUTO    what bed_syevd does: chosen from n and batch (see bed_kernel_variant)
+ *   BED_FAMILY_AUTO    what bed_syevd_info does: chosen from n and batch (see bed_kernel_variant)
  *   BED_FAMILY_WAVE    one wavefront per matrix, n <= 64
  *   BED_FAMILY_PACKED  four matrices per wavefront (16 lanes each) for n <= 16, two (32 lanes each)
  *                      for 16 < n <= 32
@@ -374,8 +374,18 @@ int bed_timing_arm(int on);
 int bed_timing_end(float* microseconds, int max_count, int* count);
 
 /*
+ * Name of the kernel that bed_syevd launches for this batch and n, with eigenvectors (want_vectors = 1; also the
+ * kernel of bed_spd_fn, and the first of bed_spd_fn_eigh) or without (want_vectors = 0): "dc_wave_kernel<32>"
+ * (divide and conquer, one wavefront per matrix, register arrays of 32), "dc_block_kernel<64>" (divide and conquer, one
+ * workgroup per matrix) or a kernel of Givens rotations as named by bed_kernel_variant; static storage, NULL
+ * for arguments out of range.
+ */
+const char* bed_syevd_kernel(int batch, int n, int want_vectors);
+
+/*
  * Name of the kernel of Givens rotations for this batch and n, with eigenvectors (want_vectors = 1)
- * or without (want_vectors = 0): the one bed_syevd_info and bed_syevd_tol launch, and bed_syevd where
+ * or without (want_vectors = 0): the one that bed_syevd_info and bed_syevd_tol launch when they are given a
+ * buffer for the rotation counts (bed_syevd_tol also when a threshold or a cap is set), and bed_syevd where
  * it does not use divide and conquer, e.g. "wave_kernel<32>" (one wavefront per
  * matrix, register arrays of 32), "packed_kernel<16>" (several matrices per wavefront),
  * "lane_kernel<4>" (one matrix per lane), "pair_kernel<64>" (two wavefronts per matrix),

@@ -29,6 +29,7 @@ from .binding import (  # noqa: F401
     bed_spd_fn_eigh,
     bed_syevd,
     bed_syevd_info,
+    bed_syevd_kernel,
     bed_syevd_lockstep,
     bed_syevd_tol,
     bed_syevd_lockstep_static,

@@ -82,6 +82,8 @@ def load_library():
         lib.bed_timing_end.restype = ci
         lib.bed_kernel_variant.argtypes = [ci, ci, ci]
         lib.bed_kernel_variant.restype = ctypes.c_char_p
+        lib.bed_syevd_kernel.argtypes = [ci, ci, ci]
+        lib.bed_syevd_kernel.restype = ctypes.c_char_p
         lib.bed_status_string.argtypes = [ci]
         lib.bed_status_string.restype = ctypes.c_char_p
         lib.bed_version.argtypes = []
@@ -90,8 +92,17 @@ def load_library():
     return _lib
 
 
-def bed_kernel_variant(batch: int, n: int, want_vectors: bool = True) -> str:
+def bed_syevd_kernel(batch: int, n: int, want_vectors: bool = True) -> str:
     """Name of the kernel bed_syevd launches for this batch and n."""
+    r = load_library().bed_syevd_kernel(int(batch), int(n), 1 if want_vectors else 0)
+    if r is None:
+        raise ValueError("batch or n out of range")
+    return r.decode()
+
+
+def bed_kernel_variant(batch: int, n: int, want_vectors: bool = True) -> str:
+    """Name of the kernel of Givens rotations for this batch and n: the one bed_syevd_info launches, and
+    bed_syevd where it does not use divide and conquer."""
     r = load_library().bed_kernel_variant(int(batch), int(n), 1 if want_vectors else 0)
     if r is None:
         raise ValueError("batch or n out of range")

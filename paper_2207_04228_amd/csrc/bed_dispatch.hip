@@ -1,4 +1,5 @@
 // Size dispatch: picks the kernel whose register arrays fit n.
+#include "bed.h"
 #include "bed_kernel.h"
 
 namespace bed {
@@ -152,6 +153,14 @@ bool divide_and_conquer(const KernelArgs& args, int stage, int forced) {
 
 const char* kernel_variant(int batch, int n, bool want_v) { return choose(batch, n, kFull, want_v, kFamilyAuto).name; }
 
+// Name of the divide-and-conquer kernel for n: the instantiations of launch_dc_wave and launch_dc_block.
+static const char* divide_and_conquer_name(int n) {
+    static const char* const wave[] = {"dc_wave_kernel<12>", "dc_wave_kernel<16>", "dc_wave_kernel<20>",
+                                       "dc_wave_kernel<24>", "dc_wave_kernel<28>", "dc_wave_kernel<32>"};
+    if (n <= 32) return wave[n <= 12 ? 0 : (n + 3) / 4 - 3];
+    return n <= 64 ? "dc_block_kernel<64>" : "dc_block_kernel<128>";
+}
+
 bool family_serves(int family, int n) {
     switch (family) {
         case kFamilyAuto: return n >= 1 && n <= 128;
@@ -204,3 +213,12 @@ hipError_t launch(const KernelArgs& args, int stage, bool want_v, hipStream_t st
 }
 
 }  // namespace bed
+
+extern "C" const char* bed_syevd_kernel(int batch, int n, int want_vectors) {
+    if (batch < 0 || n < 1 || n > BED_MAX_N) return nullptr;
+    bed::KernelArgs args{};
+    args.batch = batch;
+    args.n = n;
+    return bed::divide_and_conquer(args, bed::kFull, bed::kFamilyAuto) ? bed::divide_and_conquer_name(n)
+                                                                       : bed::kernel_variant(batch, n, want_vectors != 0);
+}

@@ -177,3 +177,19 @@ def test_binding_rejects_mismatched_buffers_before_any_pointer_is_passed():
         chk(good, "evecs", torch.float32, (3, 4, 4))
     with pytest.raises(ValueError, match=r"\[batch, n, n\]"):
         binding._square_batch(torch.zeros((3, 4, 5)))
+
+
+def test_the_kernel_that_runs_is_named(lib):
+    """bed_syevd_kernel follows the rule by which bed_syevd chooses, bed_kernel_variant names the rotations."""
+    name = binding.bed_syevd_kernel
+    for n, kernel in ((14, "dc_wave_kernel<16>"), (16, "dc_wave_kernel<16>"), (20, "dc_wave_kernel<20>"), (21, "dc_wave_kernel<24>"),
+                      (28, "dc_wave_kernel<28>"), (29, "dc_wave_kernel<32>"), (32, "dc_wave_kernel<32>"), (33, "dc_block_kernel<64>"),
+                      (64, "dc_block_kernel<64>"), (65, "dc_block_kernel<128>"), (128, "dc_block_kernel<128>")):
+        assert name(512, n) == kernel and name(512, n, False) == kernel
+        assert "dc_" not in binding.bed_kernel_variant(512, n)
+    for batch, n in ((1, 4), (512, 8), (65536, 4), (4096, 16), (8192, 24), (1, 9), (4096, 40), (4096, 48)):
+        assert name(batch, n) == binding.bed_kernel_variant(batch, n)
+        assert name(batch, n, False) == binding.bed_kernel_variant(batch, n, False)
+    assert lib.bed_syevd_kernel(1, 129, 1) is None and lib.bed_syevd_kernel(-1, 4, 1) is None
+    with pytest.raises(ValueError):
+        name(1, 0)
