@@ -116,36 +116,42 @@ Choice wave_choice(int n) {
 
 // Divide and conquer serves the calls that want a decomposition and nothing of the rotations: no
 // rotation counts, no threshold or sweep cap of the caller, no forced family, no stage hook.
-// It takes one wavefront per matrix whatever the batch; the rule looks at n and batch only, so that
-// eigenvalues alone, eigenvectors and the spectral function of one batch come from one method.
-// Measured (us per launch, rotations as chosen above / divide and conquer, eigenvectors on):
-//   n = 8:  batch 512: 14.0 / 12.5   2048: 17.0 / 14.8   32768: 50 / 113
-//   n = 16: batch 64: 30.7 / 17.4    512: 30.5 / 20.2    4096: 42.6 / 37.7 (eigenvalues 31.4 / 33.3)  16384: 89 / 104
-//   n = 20: batch 1024: 45.6 / 29.7  4096: 75.9 / 74.2   16384: 193 / 217
-//   n = 24: batch 4096: 93.5 / 79.9  16384: 248 / 238 (eigenvalues 159 / 172)
-//   n = 28: batch 4096: 124 / 95     16384: 308 / 276
-//   n = 32: batch 64: 82 / 34        512: 90 / 42        4096: 152 / 85      16384: 390 / 290
-// and one workgroup per matrix beyond, three of them on a compute unit for n <= 64 (768 on the chip):
-//   n = 36: batch 256: 114 / 66    768: 124 / 84     2048: 157 / 221
-//   n = 40: batch 512: 127 / 79    4096: 334 / 447
-//   n = 48: batch 512: 166 / 87    1024: 186 / 167   4096: 445 / 495 (eigenvalues 340 / 322)
-//   n = 52: batch 1024: 217 / 179  4096: 510 / 529   n = 56: batch 4096: 575 / 559
-//   n = 64: batch 50: 272 / 89     256: 282 / 99     1024: 300 / 199   2048: 575 / 306
-//   n = 100: batch 50: 757 / 209   n = 128: batch 256: 1186 / 260      1024: 4620 / 980
-// Few small matrices keep the rotations, whose launch lasts as long as its slowest matrix: n = 5 to 7: 9 us
-// against 11; n = 9: batch 1: 11.3 / 15.4, 64: 15.2 / 15.8; n = 10: batch 16: 18.9 / 16.2; n = 12: batch 1:
-// 15.7 / 15.6 (eigenvalues 12.7 / 13.4), 512: 21.0 / 17.5; n = 16: batch 1: 24.5 / 16.9.  Where four matrices share
-// a wavefront (packed kernels) small n keeps the rotations, and so does n just above 32, where half of
-// the 64-row workgroup works on padding, once more matrices wait than the chip holds.
-bool divide_and_conquer(const KernelArgs& args, int stage, int forced) {
+// What it takes hardly depends on the spectrum; the rotations take fewer sweeps for decaying and
+// rank-deficient ones.  So the lines lie where the geometric mean over full-rank, decaying and rank-deficient (3 n / 4)
+// covariances, in shares of 56, 19 and 25 %, turns.  Measured, time over that of the rotations as chosen
+// above, for the three and their mean (eigenvectors on, and the spectral function within 5 % of it):
+//   n = 10: batch 16: 1.06 1.26 1.29 = 1.15   512: 0.97 1.20 1.32 = 1.09   2048: 0.93 1.12 1.21 = 1.03
+//   n = 11: batch 16: 1.00 1.11 1.32 = 1.09   64: 1.02  256: 0.98  2048: 0.95   (eigenvalues 16: 1.19, 256: 1.07, 2048: 1.04)
+//   n = 12: batch 16: 0.86 1.04 1.13 = 0.95   512: 0.77 0.96 1.10 = 0.88   (eigenvalues 16: 1.03, 512: 0.96)
+//   n = 16: batch 512: 0.61 0.77 0.87 = 0.70  (us at full rank 31.6 / 19.2)
+//   n = 17: batch 512: 0.82 1.03 1.11 = 0.93  2559: 0.81 0.96 1.06 = 0.89  3072: 1.08 1.29 1.41 = 1.19  4095: 1.03 1.25 1.35 = 1.14
+//   n = 18: batch 3072: 1.12  3584: 0.96  4095: 1.09   n = 19: 3072: 1.08  3584: 0.92  4095: 1.03   n = 20: batch 2559: 0.75  3072: 1.02  4095: 0.97  4096: 1.11
+//   n = 22: batch 2559: 0.72  4095: 0.90  4096: 1.04                       n = 24: batch 2559: 0.65  4096: 0.95
+//   n = 25: batch 512: 0.65   6144: 0.98  8192: 1.18  12288: 1.10          n = 27: batch 6144: 0.89  8192: 1.08  12288: 1.00
+//   n = 28: batch 8192: 1.03  16384: 1.01                                  n = 32: batch 512: 0.50   8192: 0.90  16384: 0.88
+// Eigenvalues only, where four matrices share a wavefront from batch 3072 on:
+//   n = 17: batch 3072: 1.01  3584: 1.27   n = 20: 3072: 0.90  3584: 1.10   n = 22: 3072: 0.89  3584: 1.08   n = 24: 4096: 0.97
+//   batch 8192 / 16384: n = 25: 1.34 / 1.15   27: 1.25 / 1.05   28: 1.19 / 1.00   29: 1.23 / 1.23   31: 1.14 / 1.13   32: 1.09 / 1.09
+//   batch 6144 / 10000: n = 25: 1.09 / 0.97   27: 0.99 / 0.89   28: 0.95 / 0.85   29: 0.98 / 0.98   31: 0.91 / 0.90   32: 0.87 / 0.86
+// (its arrays have 28 or 32 rows, so that what n lacks to them counts against it).  Beyond 32 rows one workgroup per
+// matrix, three of them on a compute unit for n <= 64 (768 on the chip; five for eigenvalues only):
+//   n = 36: batch 512: 0.67 0.86 0.94 = 0.76   768: 0.73 0.90 0.97 = 0.82   2048 (full rank, us): 157 / 221
+//   n = 41: batch 768: 0.70  900: 1.11 (eigenvalues 0.83)    n = 44: 768: 0.65  1024: 1.04, the function 1.00 (0.79)    n = 48: 768: 0.62  1024: 0.98
+//   n = 48: 4096 (full rank, us): 445 / 495   n = 52: batch 1024: 0.89   n = 53: batch 1536: 0.85  2048: 1.13  2559: 0.93   n = 56: 2048: 1.06
+//   n = 64: batch 256: 0.37  2048: 0.62       us at full rank: n = 100, batch 64: 784 / 211   n = 128, batch 256: 1195 / 239
+bool divide_and_conquer(const KernelArgs& args, int stage, bool want_v, int forced) {
     if (forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
     if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;
     const int n = args.n, batch = args.batch;
-    if (n <= 9 || (n <= 12 && batch < 16)) return false;
+    if (n <= 10 || (n == 11 && (!want_v || batch < 256)) || (n == 12 && batch < 16)) return false;
     if (n <= 16) return batch < kPackedFromBatch;
+    if (n <= 22 && !want_v) return batch <= kPackedRowsValuesFromBatch;
+    if (n <= 18) return batch <= kPackedFromBatch;
+    if (n <= 22) return batch < kPackedRowsFromBatch;
     if (n <= 24) return batch <= kPackedRowsFromBatch;
-    if (n > 32 && n <= 40) return batch <= 768;
-    if (n > 40 && n <= 52) return batch <= 1024;
+    if (n <= 32) return batch <= 6144 || (want_v ? n > 26 : n % 4 == 0);
+    if (n <= 40) return batch <= 768;
+    if (n <= 52) return batch <= (want_v && n <= 43 ? 768 : 1024);
     return true;
 }
 
@@ -176,7 +182,7 @@ bool family_serves(int family, int n) {
 
 hipError_t launch(const KernelArgs& args, int stage, bool want_v, hipStream_t stream, int forced) {
     if (args.batch == 0) return hipSuccess;
-    if (divide_and_conquer(args, stage, forced)) 
+    if (divide_and_conquer(args, stage, want_v, forced))
         return args.n <= 32 ? launch_dc_wave(args, stage, want_v, stream) : launch_dc_block(args, stage, want_v, stream);
     if (stage == kSpectral && args.evecs) {
         // the spectral function and the decomposition it comes from: the rotation kernels keep V on chip
@@ -219,6 +225,7 @@ extern "C" const char* bed_syevd_kernel(int batch, int n, int want_vectors) {
     bed::KernelArgs args{};
     args.batch = batch;
     args.n = n;
-    return bed::divide_and_conquer(args, bed::kFull, bed::kFamilyAuto) ? bed::divide_and_conquer_name(n)
-                                                                       : bed::kernel_variant(batch, n, want_vectors != 0);
+    const bool want_v = want_vectors != 0;
+    return bed::divide_and_conquer(args, bed::kFull, want_v, bed::kFamilyAuto) ? bed::divide_and_conquer_name(n)
+                                                                               : bed::kernel_variant(batch, n, want_v);
 }

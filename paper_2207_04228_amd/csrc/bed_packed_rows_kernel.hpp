@@ -479,8 +479,8 @@ template <int N>
 static hipError_t launch_packed_rows_n(const KernelArgs& args, int stage, bool want_v, hipStream_t stream) {
     const unsigned blocks = (unsigned)((args.batch + 3) / 4);
     if (stage == kSpectral) {
-        // beyond 24 rows the spectral function comes from divide and conquer
-        if constexpr (N <= 24) return enqueue(packed_rows_kernel<N, true, kSpectral>, dim3(blocks), dim3(64), stream, args);
+        // beyond 26 rows the spectral function comes from divide and conquer
+        if constexpr (N <= 28) return enqueue(packed_rows_kernel<N, true, kSpectral>, dim3(blocks), dim3(64), stream, args);
         else return hipErrorInvalidValue;
     }
     if (want_v) return enqueue(packed_rows_kernel<N, true, kFull>, dim3(blocks), dim3(64), stream, args);

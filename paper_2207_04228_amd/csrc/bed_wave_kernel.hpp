@@ -1061,7 +1061,7 @@ static hipError_t launch_n(const KernelArgs& args, int stage, bool want_v, hipSt
     }
     if (stage == kSpectral) {
         // the other sizes' spectral functions come from divide and conquer or the packed kernels
-        if constexpr (N <= 12 || (N >= 40 && N <= 56)) return launch_one<N, true, kSpectral>(args, stream);
+        if constexpr (N <= 12 || N == 20 || (N >= 40 && N <= 56)) return launch_one<N, true, kSpectral>(args, stream);
         else return hipErrorInvalidValue;
     }
     if (stage == kQrPartial) return launch_one<N, true, kQrPartial>(args, stream);

@@ -193,3 +193,24 @@ def test_the_kernel_that_runs_is_named(lib):
     assert lib.bed_syevd_kernel(1, 129, 1) is None and lib.bed_syevd_kernel(-1, 4, 1) is None
     with pytest.raises(ValueError):
         name(1, 0)
+
+
+def test_lines_between_divide_and_conquer_and_the_rotations(lib):
+    """(n, largest batch with eigenvectors, largest batch without): on both sides of every line of the rule."""
+    for n, vectors, values in ((12, 2559, 2559), (16, 2559, 2559), (17, 2560, 3072), (18, 2560, 3072), (19, 4095, 3072), (22, 4095, 3072),
+                               (23, 4096, 4096), (24, 4096, 4096), (25, 6144, 6144), (26, 6144, 6144), (33, 768, 768), (40, 768, 768),
+                               (41, 768, 1024), (43, 768, 1024), (44, 1024, 1024), (52, 1024, 1024)):
+        for want, most in ((True, vectors), (False, values)):
+            assert binding.bed_syevd_kernel(most, n, want).startswith("dc_"), (n, most, want)
+            assert binding.bed_syevd_kernel(most + 1, n, want) == binding.bed_kernel_variant(most + 1, n, want)
+    for n in (1, 9, 10):
+        for batch in (1, 16, 512, 2048, 4096):
+            assert "dc_" not in binding.bed_syevd_kernel(batch, n) + binding.bed_syevd_kernel(batch, n, False)
+    assert "dc_" not in binding.bed_syevd_kernel(255, 11) + binding.bed_syevd_kernel(512, 11, False) + binding.bed_syevd_kernel(2560, 11)
+    assert binding.bed_syevd_kernel(256, 11) == "dc_wave_kernel<12>"
+    assert "dc_" not in binding.bed_syevd_kernel(15, 12) and binding.bed_syevd_kernel(16, 12) == "dc_wave_kernel<12>"
+    for n in (27, 29, 30, 31):          # eigenvalues alone turn where the arrays have rows to spare
+        assert binding.bed_syevd_kernel(1 << 20, n).startswith("dc_")
+        assert binding.bed_syevd_kernel(6145, n, False) == binding.bed_kernel_variant(6145, n, False)
+    for n in (28, 32, 53, 64, 128):
+        assert binding.bed_syevd_kernel(1 << 20, n).startswith("dc_") and binding.bed_syevd_kernel(1 << 20, n, False).startswith("dc_")
