@@ -73,7 +73,8 @@ typedef enum {
  *
  * Numerical non-convergence never aborts: the QR loop is capped (30 sweeps
  * per row; the root finder of divide and conquer is capped too), a NaN/Inf
- * input yields NaNs for that matrix only.  Use bed_syevd_info to observe it.
+ * input yields NaNs for that matrix only.  bed_syevd_info reports both: with
+ * rotations = NULL it runs the kernel that bed_syevd runs.
  */
 int bed_syevd(const float* A, int batch, int n, float* evals, float* evecs,
               void* stream);
@@ -97,7 +98,8 @@ int bed_syevd(const float* A, int batch, int n, float* evals, float* evecs,
  *                  the 1e-5 ||A||_2 accuracy bar), but eigenvalues far below
  *                  ||A||_2 lose their relative accuracy.
  *              From divide and conquer (rotations = NULL) w is 0 and k counts
- *              non-finite eigenvalues.
+ *              non-finite eigenvalues and roots of the secular equations that the cap of
+ *              60 iterations stopped before their test was met (none is known).
  *   rotations  device, [batch] uint32: number of Givens rotations applied to
  *              this matrix (the R of the flop model R*(6n+20); the paper
  *              reports the related "reduction times" in App. C.4).  Asking for

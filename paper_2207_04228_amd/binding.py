@@ -229,9 +229,11 @@ def bed_syevd(A, evals=None, evecs=None, *, want_vectors=True, stream=None):
 BED_FAMILY_AUTO, BED_FAMILY_WAVE, BED_FAMILY_PACKED, BED_FAMILY_LANE, BED_FAMILY_BLOCK, BED_FAMILY_PAIR, BED_FAMILY_PACKED_ROWS = range(7)
 
 
-def bed_syevd_info(A, evals=None, evecs=None, *, want_vectors=True, stream=None, family=BED_FAMILY_AUTO):
+def bed_syevd_info(A, evals=None, evecs=None, *, want_vectors=True, stream=None, family=BED_FAMILY_AUTO,
+                   want_rotations=True):
     """bed_syevd plus (info int32 [batch], rotations int32-view of uint32 [batch]); `family`
-    forces one kernel family (bed_syevd_family)."""
+    forces one kernel family (bed_syevd_family).  Rotation counts select the kernels of Givens rotations; with
+    want_rotations=False (rotations: None) it is the kernel bed_syevd runs, and its info."""
     import torch
     _check_dev(A, "A", torch.float32)
     batch, n = _square_batch(A)
@@ -245,7 +247,7 @@ def bed_syevd_info(A, evals=None, evecs=None, *, want_vectors=True, stream=None,
     if evecs is not None:
         _check_dev(evecs, "evecs", torch.float32, (batch, n, n), A)
     info = torch.empty((batch,), dtype=torch.int32, device=A.device)
-    rot = torch.empty((batch,), dtype=torch.int32, device=A.device)
+    rot = torch.empty((batch,), dtype=torch.int32, device=A.device) if want_rotations else None
     st = load_library().bed_syevd_family(_ptr(A), batch, n, _ptr(evals), _ptr(evecs),
                                          _ptr(info), _ptr(rot), int(family), _stream(stream))
     if st != 0:

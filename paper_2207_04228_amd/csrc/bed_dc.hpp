@@ -78,6 +78,7 @@ struct DcShared {
     int perm[N];                         // sorted position -> column
     int src[N];                          // slot -> column
     int nrot[N];                         // rotations of the block that starts here
+    int unresolved;                      // T > 64: sum of the wavefronts' counts
 };
 
 template <int TPE>
@@ -144,9 +145,9 @@ __device__ __forceinline__ float dc_quadratic(float a, float b, float c, float s
 
 // Eigenvalues (S.D, by column) and eigenvectors (S.V) of the tridiagonal with entries dget(k), eget(k) (coupling k
 // and k+1), k < n, in LDS, visible to all T threads.  The caller has pre-scaled T to a norm of about one.
-// With a non-finite entry in T every output is NaN.
+// With a non-finite entry in T every output is NaN.  Returns the number of roots that the cap stopped.
 template <int N, int T, bool WANT_V, typename Dget, typename Eget>
-__device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const int n, const int tid, Dget&& dget, Eget&& eget) {
+__device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int n, const int tid, Dget&& dget, Eget&& eget) {
     constexpr int TPE = T / N;                      // threads per eigenvalue, neighbours in a wavefront
     constexpr int LD = DcShared<N, TPE, WANT_V>::LD;
     constexpr int CH = 4 * TPE;                     // poles per step of an inner loop
@@ -177,6 +178,8 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
     while ((2 << L) < n) ++L;       // 2^L leaves of one or two rows
     // leaf that holds row r: the largest i with floor(i n / 2^L) <= r
     const float rcp_n = 1.f / (float)n;
+    int unresolved = 0;
+    if (T > 64 && tid == 0) S.unresolved = 0;
     auto leaf_of = [&](int r) { return (int)(((float)(((r + 1) << L) - 1) + 0.5f) * rcp_n); };
     const int leaf = valid ? leaf_of(e) : 0;
     int leafq[NB];
@@ -263,7 +266,7 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
     if (bad) {
         if (part == 0) S.D[e] = lam;
         sync();
-        return;
+        return 0;
     }
 
     for (int level = 1; level <= L; ++level) {
@@ -478,7 +481,8 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
                 mu = (x > lb && x < ub) ? x : 0.5f * (lb + ub);
             }
             bool open = many;
-            for (int it = 0; it < kDcMaxIter && __ballot(open) != 0; ++it) {
+            int it = 0;
+            for (; it < kDcMaxIter && __ballot(open) != 0; ++it) {
                 float F = 0.f, dF = 0.f, N1 = 0.f, dN = 0.f;       // sums over all other poles, over the terms below zero
 #pragma unroll
                 for (int c = 0; c < PP; c += 4) {
@@ -526,6 +530,7 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
                 mu = step ? y : mu;
                 open = step && !small;
             }
+            if (it == kDcMaxIter) unresolved += (int)__builtin_popcountll(__ballot(open && part == 0));
             if (root && !many) {
                 dorg = pk.x;
                 mu = rho * pk.y;
@@ -692,7 +697,9 @@ __device__ __forceinline__ void dc_solve(DcShared<N, T / N, WANT_V>& S, const in
         }
     }
     if (part == 0) S.D[e] = valid ? lam : __builtin_inff();
+    if (T > 64 && unresolved && lane == 0) atomicAdd(&S.unresolved, unresolved);
     sync();
+    return T > 64 ? S.unresolved : unresolved;
 }
 
 // Rank of column e's eigenvalue among all n (ties by column): the ascending output order.  With a

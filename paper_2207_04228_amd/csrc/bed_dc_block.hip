@@ -39,11 +39,11 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
     }
     __syncthreads();
 
-    dc_solve<N, DT, WANT_V>(
+    const int unresolved = dc_solve<N, DT, WANT_V>(
         S, n, tid, [&](int k) { return sd[k]; }, [&](int k) { return se[k]; });
 
     const int odd = dc_non_finite(S, n, lane);
-    if (tid == 0 && args.info) args.info[b] = odd;
+    if (tid == 0 && args.info) args.info[b] = odd + unresolved;
     if (tid < n) {
         const int rank = dc_rank(S, n, tid, odd != 0);
         S.perm[tid] = rank;

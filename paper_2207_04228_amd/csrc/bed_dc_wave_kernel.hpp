@@ -49,7 +49,7 @@ __global__ __launch_bounds__(64) void dc_wave_kernel(KernelArgs args) {
     }
     sync();
 
-    dc_solve<R, 64, WANT_V>(
+    const int unresolved = dc_solve<R, 64, WANT_V>(
         S, n, lane, [&](int k) { return sP[k].y; }, [&](int k) { return sP[k + 1].x; });
 
     // column `lo` of the result, in every group of R lanes
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(64) void dc_wave_kernel(KernelArgs args) {
     const int odd = dc_non_finite(S, n, lane);
     const int rank = dc_rank(S, n, lo, odd != 0);
     if (args.evals && lane < n) args.evals[(size_t)b * n + rank] = lam;
-    if (lane == 0 && args.info) args.info[b] = odd;
+    if (lane == 0 && args.info) args.info[b] = odd + unresolved;
 
     if constexpr (WANT_V) {
         // V = P V_T

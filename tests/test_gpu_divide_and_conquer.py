@@ -56,6 +56,24 @@ def _solve_raw(A32):
     return lam, V, binding.bed_spd_fn(At, binding.BED_FN_SQRT, 1e-6)[2]
 
 
+@pytest.mark.parametrize("n", [13, 32, 48, 100])
+def test_info_of_the_kernel_that_bed_syevd_runs(n):
+    """Without rotation counts bed_syevd_info is bed_syevd with its diagnostics: 0 where every root was found, the number
+    of non-finite eigenvalues otherwise."""
+    import torch
+    from paper_2207_04228_amd import binding, workloads
+    A = np.concatenate([_structured(n, n), workloads.covariance(8, n, 3 * n // 4, 1e-2, 6950 + n)])
+    A[3, 2, 1] = A[3, 1, 2] = np.nan
+    At = torch.from_numpy(A).cuda()
+    lam, V = binding.bed_syevd(At)
+    lam1, V1, info, rotations = binding.bed_syevd_info(At, want_rotations=False)
+    only, none, info_only, _ = binding.bed_syevd_info(At, want_vectors=False, want_rotations=False)
+    assert rotations is None and none is None
+    keep = [b for b in range(A.shape[0]) if b != 3]
+    assert torch.equal(lam1[keep], lam[keep]) and torch.equal(V1[keep], V[keep]) and torch.equal(only[keep], lam[keep])
+    assert (info[keep] == 0).all() and int(info[3]) == n and torch.equal(info, info_only)
+
+
 def test_scales_and_non_finite_inputs():
     from paper_2207_04228_amd import workloads
     for n in (13, 16, 30, 50, 90):
