@@ -11,9 +11,10 @@ inputs already resident in HBM.  The script prints ONE JSON line:
   per_n        per-call figures for each n (every kernel launched with a start and a stop
                HIP event of its own on the launch stream; the dominant call, n = 32, is
                measured inside the timed region, the others in a second pass)
-  roofline     the dominant kernel (n = 32): algorithmic flops / mean launch
-               duration against the fp32 vector peak (datasheet, packed), the plain-FMA
-               peak, and ceilings measured in this run (plain-FMA kernel, device copy)
+  roofline     the dominant kernel (n = 32): algorithmic flops of the method that ran / mean
+               launch duration against the fp32 peak (datasheet; packed vector and matrix
+               instructions alike), the plain-FMA peak, and ceilings measured in this run
+               (plain-FMA kernel, device copy)
   ceilings     those measured ceilings; environment: clocks, ROCm version, device
   cpu_baseline the float64 Jacobi oracle on the host cores, same inputs
 """
@@ -97,21 +98,21 @@ def environment(torch):
     return env
 
 
-def traffic_from_profile():
+def traffic_from_profile(name="wave_kernel_n32_b512_counters.md"):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3 --pmc summary, but
     only if that summary was taken from exactly the sources this library is built from (it
     records their hash); otherwise None: a counter reading of another kernel is not this one's."""
     import re
     from paper_2207_04228_amd import build
-    tpath = os.path.join(ROOT, "profiles", "wave_kernel_n32_b512_counters.md")
+    tpath = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(tpath):
         return None, None
     text = open(tpath).read()
     m = re.search(r"^hbm_bytes_per_launch:\s*([0-9.]+)", text, flags=re.M)
     h = re.search(r"^source_hash:\s*([0-9a-f]+)", text, flags=re.M)
     if not m or not h or h.group(1) != build.source_hash():
-        return None, "profiles/wave_kernel_n32_b512_counters.md was taken from other sources than this build"
-    return float(m.group(1)), "profiles/wave_kernel_n32_b512_counters.md (same source hash as this build)"
+        return None, f"profiles/{name} was taken from other sources than this build"
+    return float(m.group(1)), f"profiles/{name} (same source hash as this build)"
 
 
 def flops_per_matrix(n: int, rotations: float, vectors: bool = True) -> float:
@@ -121,6 +122,20 @@ def flops_per_matrix(n: int, rotations: float, vectors: bool = True) -> float:
     if vectors:
         f += (4.0 / 3.0) * n ** 3 + rotations * 6.0 * n
     return f
+
+
+def dense_flops_per_matrix(n: int, vectors: bool = True) -> float:
+    """The dense part of divide and conquer: (4/3)n^3 tridiagonalisation, and with eigenvectors (4/3)n^3
+    forming P, (4/3)n^3 for the merges' products (n^3 at the top, a quarter of that on each level below; without
+    deflation) and 2n^3 for V = P V_T.  Roots and vectors of the merges, O(n^2) a level, are not counted."""
+    return (6.0 if vectors else 4.0 / 3.0) * n ** 3
+
+
+def work_of(kernel: str, n: int, rotations: float):
+    """(flops per matrix, what they count) of the kernel that ran."""
+    if kernel.startswith("dc_"):
+        return dense_flops_per_matrix(n), "dense part of divide and conquer, 6 n^3"
+    return flops_per_matrix(n, rotations), "(8/3) n^3 + rotations x (6 n + 20)"
 
 
 def bytes_per_matrix(n: int, vectors: bool = True) -> float:
@@ -197,7 +212,7 @@ def main(argv=None) -> int:
             binding.bed_syevd(A, ev, V)
         torch.cuda.synchronize()
         print(json.dumps({"only_n": n, "launches": a.steps, "batch": int(A.shape[0]),
-                          "kernel": binding.bed_kernel_variant(int(A.shape[0]), n)}))
+                          "kernel": binding.bed_syevd_kernel(int(A.shape[0]), n)}))
         return 0
     bufs = []
     for n, A32 in points:
@@ -207,7 +222,8 @@ def main(argv=None) -> int:
         bufs.append((n, A, ev, V))
     stream = torch.cuda.current_stream()
 
-    # rotation counts (for the flop model), outside the timed region
+    # rotation counts of the rotation kernels (the flop model where they run; the input is converged), outside
+    # the timed region
     rot_mean = {}
     rot_max = {}
     for n, A, ev, V in bufs:
@@ -265,11 +281,13 @@ def main(argv=None) -> int:
             durs = dom_durs                    # the dominant kernel: measured inside the timed region
         mean = float(durs.mean())
         B = int(A.shape[0])
-        fl = B * flops_per_matrix(n, rot_mean[n])
+        kernel = binding.bed_syevd_kernel(B, n)
+        per_matrix, model = work_of(kernel, n, rot_mean[n])
+        fl = B * per_matrix
         by = B * bytes_per_matrix(n)
         per_n[str(n)] = {
             "batch": B,
-            "kernel": binding.bed_kernel_variant(B, n),
+            "kernel": kernel,
             "kernel_us_mean": mean * 1e6,
             "kernel_us_median": float(np.median(durs)) * 1e6,
             "kernel_us_p10": float(np.percentile(durs, 10)) * 1e6,
@@ -278,6 +296,7 @@ def main(argv=None) -> int:
             "rotations_mean": rot_mean[n],
             "rotations_max": rot_max[n],
             "flops_per_launch": fl,
+            "flops_model": model,
             "tflops": fl / mean / 1e12,
             "frac_fp32_valu": fl / mean / 1e12 / PEAK_FP32_TFLOPS,
             "frac_plain_fma": fl / mean / 1e12 / PEAK_FP32_PLAIN_FMA_TFLOPS,
@@ -400,9 +419,11 @@ def main(argv=None) -> int:
         t_ev = timed(lambda: binding.bed_syevd(Ab, evb, None, want_vectors=False), 10)
         t_fn = timed(lambda: binding.bed_spd_fn(Ab, binding.BED_FN_INV_SQRT, 1e-6, out=Vb), 10)
         _, _, _, rotb = binding.bed_syevd_info(Ab, evb, Vb)
-        flb = batch * flops_per_matrix(n, float(rotb.float().mean().item()))
+        kernel = binding.bed_syevd_kernel(batch, n)
+        per_matrix, model = work_of(kernel, n, float(rotb.float().mean().item()))
+        flb = batch * per_matrix
         extras["large_batch"][f"n{n}_b{batch}"] = {
-            "kernel": binding.bed_kernel_variant(batch, n),
+            "kernel": kernel, "flops_model": model,
             "kernel_us": t * 1e6, "matrices_per_s": batch / t,
             "eigenvalues_only_us": t_ev * 1e6,
             "spd_inv_sqrt_us": t_fn * 1e6,
@@ -413,9 +434,11 @@ def main(argv=None) -> int:
 
     dom = per_n["32"]
     ceilings = measure_ceilings(binding, torch, dev, stream)
-    traffic, traffic_source = traffic_from_profile()
+    dc = dom["kernel"].startswith("dc_")
+    traffic, traffic_source = traffic_from_profile(("dc_" if dc else "") + "wave_kernel_n32_b512_counters.md")
     roofline = {
-        "kernel": "bed::wave_kernel<32, true, 0> (n=32, batch 512)",
+        "kernel": f"bed::{dom['kernel']} (n=32, batch 512, with eigenvectors)",
+        "flops_model": dom["flops_model"],
         "bound": "alu",
         "achieved": dom["tflops"],
         "peak": PEAK_FP32_TFLOPS,
@@ -426,7 +449,8 @@ def main(argv=None) -> int:
         "peak_measured": ceilings["plain_fma_tflops"],
         "frac_vs_measured": dom["tflops"] / ceilings["plain_fma_tflops"],
         "launch_shape_ceiling": ceilings["dependent_chain_512_waves_tflops"],
-        "frac_vs_launch_shape_ceiling": dom["tflops"] / ceilings["dependent_chain_512_waves_tflops"],
+        # one dependent FMA chain per wavefront is the rotations' shape; the matrix cores are not bound by it
+        "frac_vs_launch_shape_ceiling": None if dc else dom["tflops"] / ceilings["dependent_chain_512_waves_tflops"],
         "traffic": traffic,
         "traffic_source": traffic_source,
         "hbm_frac": dom["frac_hbm"],

@@ -27,6 +27,19 @@ def test_work_model_matches_its_definition():
     assert bench.PEAK_FP32_PLAIN_FMA_TFLOPS == 78.6      # v_fma_f32 only: what a build without packed fp32 can reach
 
 
+def test_work_is_that_of_the_kernel_that_runs():
+    """Divide and conquer is charged its dense products and no rotations: 2 x (4/3) n^3 for T and P, (4/3) n^3 for the
+    products of the merges, 2 n^3 for V = P V_T."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2207_04228_amd import binding
+    for n in (16, 32, 64, 128):
+        merges = sum((n >> k) ** 3 * (1 << k) for k in range(7) if n >> k)      # m^3 for each merge into m rows
+        assert abs(bench.dense_flops_per_matrix(n) - (8.0 / 3.0 * n ** 3 + merges + 2.0 * n ** 3)) < 0.01 * n ** 3 + 2 * n
+        assert bench.work_of(binding.bed_syevd_kernel(512, n), n, 1e9)[0] == bench.dense_flops_per_matrix(n)
+    assert bench.work_of(binding.bed_syevd_kernel(512, 8), 8, 100.0)[0] == bench.flops_per_matrix(8, 100.0)
+
+
 def test_traffic_is_reported_only_for_the_profiled_sources(tmp_path, monkeypatch):
     """roofline.traffic comes from the committed counter summary only while that summary's
     source hash equals the hash of the sources the library is built from."""
