@@ -109,6 +109,17 @@ int main() {
     EXPECT(bed_spd_fn(A, 8, 16, BED_FN_SQRT, 0.f, A, L, I, nullptr), BED_ERR_ALIAS);
     EXPECT(bed_spd_fn(A, 8, 16, BED_FN_SQRT, 0.f, nullptr, L, I, nullptr), BED_ERR_NULL);
 
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, 0.f, X, L, V, I, nullptr), BED_OK);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_INV_SQRT, 1e-6f, X, L, V, nullptr, nullptr), BED_OK);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, 0.f, X, nullptr, V, I, nullptr), BED_ERR_NULL);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, 0.f, X, L, nullptr, I, nullptr), BED_ERR_NULL);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, nan, X, L, V, I, nullptr), BED_ERR_ARG);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, 0.f, X, L, X, I, nullptr), BED_ERR_ALIAS);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, 0.f, V, L, V + 8 * 16 * 16 - 1, I, nullptr), BED_ERR_ALIAS);
+    EXPECT(bed_spd_fn_eigh(A, 8, 16, BED_FN_SQRT, 0.f, V, L, V + 8 * 16 * 16, I, nullptr), BED_OK);      // adjacent
+    EXPECT(bed_spd_fn_eigh(dev<float>(0x10000002), 8, 16, BED_FN_SQRT, 0.f, X, L, V, I, nullptr), BED_ERR_ALIGN);
+    EXPECT_NOOP(bed_spd_fn_eigh(nullptr, 0, 16, BED_FN_SQRT, 0.f, nullptr, nullptr, nullptr, nullptr, nullptr));
+
     // gradients
     EXPECT(bed_syevd_backward(L, V, W, X, 8, 16, BED_GRAD_TAYLOR, 9, 0.f, A, nullptr), BED_OK);
     EXPECT(bed_syevd_backward(L, V, nullptr, X, 8, 16, BED_GRAD_EXACT, 0, 1e-6f, A, nullptr), BED_OK);

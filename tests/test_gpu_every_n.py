@@ -1,5 +1,7 @@
 """Every size n = 1 .. 128 (all instantiations and both sides of every dispatch boundary)
-with five kinds of spectra each, held to the parity bar against the oracle."""
+with five kinds of spectra each, held to the parity bar against the oracle: through the kernels of
+Givens rotations (bed_syevd_info with rotation counts) and through bed_syevd, which takes divide and
+conquer from n = 12 on."""
 import numpy as np
 import pytest
 
@@ -29,6 +31,13 @@ def test_every_n(first):
             acc = evaluate(A, ev.cpu().numpy(), V.cpu().numpy(), lam_o, V_o)
             w = acc.worst()
             assert acc.passes() and int((info & 0xFFFF).max()) == 0, (n, kind, w)
+            if n >= 12:          # twice the batch: the line of n = 12 lies at 16 matrices
+                A2 = np.concatenate([A, A])
+                assert binding.bed_syevd_kernel(A2.shape[0], n).startswith("dc_") or A2.shape[0] < 16
+                ev, V = binding.bed_syevd(torch.from_numpy(A2).to("cuda:0"))
+                acc = evaluate(A2, ev.cpu().numpy(), V.cpu().numpy(), np.concatenate([lam_o, lam_o]), np.concatenate([V_o, V_o]))
+                assert acc.passes(), (n, kind, "bed_syevd", acc.worst())
+                w = {key: max(w[key], acc.worst()[key]) for key in w}
             if int((info >> 16).sum()):
                 relaxed.append((n, kind, int((info >> 16).sum())))
             for key in worst:

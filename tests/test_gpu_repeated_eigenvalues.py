@@ -1,7 +1,8 @@
 """Heavily repeated eigenvalues.  Inside a cluster the recurrence leaves the off-diagonals at
 the rounding level of the diagonal; with a deflation tolerance of 2^-23 such windows could
 hover around the tolerance until the sweep cap (0.2 % of these matrices did not converge).
-Every matrix must converge (info = 0, no runaway rotation counts) and meet the parity bar."""
+Every matrix must converge (info = 0, no runaway rotation counts) and meet the parity bar, in the
+rotation kernels and in the kernel that bed_syevd runs."""
 import numpy as np
 import pytest
 
@@ -37,6 +38,10 @@ def test_repeated_eigenvalues_converge(n):
             lam_o, V_o = jacobi.syevd(A)
             acc = evaluate(A, ev.cpu().numpy(), V.cpu().numpy(), lam_o, V_o)
             assert acc.passes(), (n, seed, kind, acc.worst())
+            ev, V, info, _ = binding.bed_syevd_info(torch.from_numpy(A).to("cuda:0"), want_rotations=False)
+            assert int((info & 0xFFFF).max()) == 0, (n, seed, kind)
+            acc = evaluate(A, ev.cpu().numpy(), V.cpu().numpy(), lam_o, V_o)
+            assert acc.passes(), (n, seed, kind, binding.bed_syevd_kernel(batch, n), acc.worst())
     print(f"[repeated] n={n}: max rotations / n^2 = {worst_rot:.2f}; fallback deflations: "
           f"{relaxed} in {matrices} matrices", flush=True)
     assert worst_rot <= 4.0

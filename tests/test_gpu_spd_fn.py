@@ -150,14 +150,18 @@ def test_large_batch_small_n():
 @pytest.mark.parametrize("fn", [0, 1])
 def test_where_the_packed_and_lane_kernels_are_dispatched(fn):
     """The fused spectral function at the batch sizes that go to four matrices per wavefront
-    (n <= 16 from batch 2560, 16 < n <= 32 from batch 4096) and to one matrix per lane (n <= 4 from batch 20480, n <= 8 from batch
-    32768), ragged last wavefronts included; 65536 matrices of 4 x 4 are the shape of App. B.3."""
+    (n <= 16 from batch 2560, 16 < n <= 24 from batch 4096, n <= 26 from batch 6145) and to one matrix per lane (n <= 4 from
+    batch 20480, n <= 8 from batch 32768), ragged last wavefronts included, to one wavefront per matrix just below,
+    and to divide and conquer beyond 26 rows; 65536 matrices of 4 x 4 are the shape of App. B.3."""
     from paper_2207_04228_amd import binding, workloads
     cases = [("packed_kernel<16>", workloads.config4()),
              ("packed_kernel<12>", workloads.covariance(2560 + 3, 12, 48, 1e-4, 61)),
              ("packed_kernel<8>", workloads.config3(8, batch=4096 + 1)),
              ("packed_kernel<4>", workloads.config2(4096)),
-             ("packed_rows_kernel<32>", workloads.config3(32, batch=4096 + 5)),
+             ("dc_wave_kernel<32>", workloads.config3(32, batch=4096 + 5)),
+             ("packed_rows_kernel<28>", workloads.covariance(6144 + 3, 26, 104, 1e-4, 67)),
+             ("wave_kernel<20>", workloads.covariance(2561, 18, 72, 1e-4, 68)),
+             ("wave_kernel<48>", workloads.covariance(769, 43, 172, 1e-4, 69)),
              ("packed_rows_kernel<24>", workloads.covariance(4096 + 2, 21, 84, 1e-4, 65)),
              ("packed_rows_kernel<20>", workloads.covariance(4096, 17, 68, 1e-4, 66)),
              ("lane_kernel<4>", workloads.config2(65536)),
@@ -165,7 +169,7 @@ def test_where_the_packed_and_lane_kernels_are_dispatched(fn):
              ("lane_kernel<8>", workloads.config3(8, batch=32768 + 7)),
              ("lane_kernel<8>", workloads.covariance(32768 + 64, 6, 24, 1e-4, 63))]
     for variant, A in cases:
-        assert binding.bed_kernel_variant(A.shape[0], A.shape[-1]) == variant
+        assert binding.bed_syevd_kernel(A.shape[0], A.shape[-1]) == variant
         _check(A, fn, 1e-6, f"{variant} batch {A.shape[0]} n={A.shape[-1]}")
 
 

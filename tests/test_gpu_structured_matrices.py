@@ -1,6 +1,7 @@
 """Parity on matrices whose structure stresses deflation, scaling and clustering (graded and
 paired spectra, scales 1e-30 and 1e+30, Wilkinson and glued Wilkinson matrices, rank-deficient,
-sparse, arrow, nearly scalar, Hilbert ...), in every size class of the kernels."""
+sparse, arrow, nearly scalar, Hilbert ...), in every size class of the kernels: the rotations, and what
+bed_syevd runs."""
 import numpy as np
 import pytest
 
@@ -26,6 +27,11 @@ def test_structured_matrices(n):
         acc = evaluate(A, ev.cpu().numpy(), V.cpu().numpy(), lam_o, V_o)
         w = acc.worst()
         assert acc.passes(), (n, name, w)
+        ev, V, info, _ = binding.bed_syevd_info(torch.from_numpy(A).to("cuda:0"), want_rotations=False)
+        assert int((info & 0xFFFF).max()) == 0, (n, name)
+        acc = evaluate(A, ev.cpu().numpy(), V.cpu().numpy(), lam_o, V_o)
+        assert acc.passes(), (n, name, binding.bed_syevd_kernel(A.shape[0], n), acc.worst())
+        w = {k: max(w[k], acc.worst()[k]) for k in w}
         for k in worst:
             worst[k] = max(worst[k], w[k])
     print(f"[structured] n={n}: eval {worst['eval_err']:.2e} res {worst['residual']:.2e} orth {worst['orth']:.2e}; "

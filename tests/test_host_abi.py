@@ -151,6 +151,33 @@ def test_argument_validation_is_host_side(lib):
     assert lib.bed_syevd_lockstep(A, 0, 16, f(1e-5), 16, 1, L, V, None, None, W, sz(need), None) == 0
 
 
+def test_function_with_decomposition_checks_its_arguments_on_the_host(lib):
+    p, f = ctypes.c_void_p, ctypes.c_float
+    call = lib.bed_spd_fn_eigh
+    A, L, V, O, I = p(0x10000), p(0x20000), p(0x30000), p(0x40000), p(0x50000)
+    assert call(None, 1, 4, 0, f(0.0), O, L, V, I, None) == -1
+    assert call(A, 1, 4, 0, f(0.0), None, L, V, I, None) == -1
+    assert call(A, 1, 4, 0, f(0.0), O, None, V, I, None) == -1          # the decomposition is required
+    assert call(A, 1, 4, 0, f(0.0), O, L, None, I, None) == -1
+    assert call(A, -1, 4, 0, f(0.0), O, L, V, I, None) == -2
+    assert call(A, 1, 0, 0, f(0.0), O, L, V, I, None) == -3
+    assert call(A, 1, 129, 0, f(0.0), O, L, V, I, None) == -3
+    for bad in ((p(0x10002), O, L, V, I), (A, p(0x40001), L, V, I), (A, O, p(0x20003), V, I), (A, O, L, p(0x30002), I), (A, O, L, V, p(0x50001))):
+        assert call(bad[0], 1, 4, 0, f(0.0), bad[1], bad[2], bad[3], bad[4], None) == -4
+    inside = {0x10000: p(0x10020), 0x40000: p(0x40020), 0x30000: p(0x30020)}       # 64 bytes a 4x4 matrix
+    assert call(A, 1, 4, 0, f(0.0), inside[0x10000], L, V, I, None) == -6           # out, evals, evecs inside A
+    assert call(A, 1, 4, 0, f(0.0), O, inside[0x10000], V, I, None) == -6
+    assert call(A, 1, 4, 0, f(0.0), O, L, inside[0x10000], I, None) == -6
+    assert call(A, 1, 4, 0, f(0.0), O, inside[0x40000], V, I, None) == -6           # evals, evecs inside out
+    assert call(A, 1, 4, 0, f(0.0), O, L, inside[0x40000], I, None) == -6
+    assert call(A, 1, 4, 0, f(0.0), O, inside[0x30000], V, I, None) == -6           # evals inside evecs
+    assert call(A, 1, 4, 2, f(1.0), O, L, V, I, None) == -7
+    assert call(A, 1, 4, 1, f(0.0), O, L, V, I, None) == -7
+    for floor in (-1.0, float("nan"), float("inf")):
+        assert call(A, 1, 4, 0, f(floor), O, L, V, I, None) == -7
+    assert call(None, 0, 4, 0, f(0.0), None, None, None, None, None) == 0
+
+
 def test_binding_rejects_cpu_tensors():
     import torch
     with pytest.raises(TypeError):
