@@ -3,7 +3,9 @@
 //
 // P leaves LDS before the divide and conquer and waits in registers as the left operand of the last
 // product V = P V_T (a strip of 32 rows per wavefront, N / 2 registers), so that V_T and the
-// eigenvectors of the merges have the two matrix-sized areas of LDS to themselves.
+// eigenvectors of the merges have the two matrix-sized areas of LDS to themselves.  Beside the poles of the
+// root finder that is the limit at 128 rows: 256 registers and 14 to 16 spilled (none at 64, 168 registers).
+// 256 matrices: 64x64 282 us with the rotations, 90 now; 128x128 1195, 239.
 #include "bed_tile_tridiag.hpp"
 
 namespace bed {

@@ -1,4 +1,4 @@
-// Instantiations of the divide-and-conquer kernels for 8 < n <= 32.
+// Instantiations of the divide-and-conquer kernels for 10 < n <= 32.
 #include "bed_dc_wave_kernel.hpp"
 
 namespace bed {

@@ -86,8 +86,8 @@ Choice choose(int batch, int n, int stage, bool want_v, int forced) {
     //   n = 24: batch 3072: 93.6 / 97.5 / 96.3   4096: 115 / 101 / 95       8192: 193 / 163 / 129   16384: 355 / 288 / 238
     //   n = 28: batch 3072: 119 / 130 / 125      4096: 145 / 131 / 124      8192: 247 / 232 / 165   16384: 456 / 400 / 309
     //   n = 32: batch 3072: 148 / 162 / 152      4096: 180 / 163 / 152      8192: 309 / 275 / 205   16384: 571 / 488 / 379):
-    // four matrices per wavefront, also for the fused spectral function (16384 x 32x32: 529 us with
-    // two per wavefront, 388 us with four); two per wavefront remains for forced-family runs
+    // four matrices per wavefront, also for the fused spectral function up to the 26 rows for which the rotations
+    // give it (divide and conquer beyond); two per wavefront remains for forced-family runs
     // (eigenvalues only, n = 32: batch 3072: 125 / 109 / 95   4096: 149 / 108 / 94   16384: 479 / 379 / 230)
     if (whole && n > 16 && n <= 32 && batch >= (want_v ? kPackedRowsFromBatch : kPackedRowsValuesFromBatch))
         return choose(batch, n, stage, want_v, kFamilyPackedRows);

@@ -136,7 +136,7 @@ hipError_t launch_lockstep(const LockstepArgs& args, hipStream_t stream);
 constexpr size_t kLockstepScratchBytes = 1u << 20;
 hipError_t lockstep_scratch(void** ptr);
 
-// Name of the kernel that serves a full decomposition of this batch and n.
+// Name of the kernel of Givens rotations that serves a full decomposition of this batch and n.
 const char* kernel_variant(int batch, int n, bool want_v);
 
 // Kernel families (values of bed_family in bed.h).
