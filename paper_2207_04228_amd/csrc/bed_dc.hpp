@@ -702,19 +702,21 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
     return T > 64 ? S.unresolved : unresolved;
 }
 
-// Rank of column e's eigenvalue among all n (ties by column): the ascending output order.  With a
-// non-finite eigenvalue among them (`odd`) the columns stay where they are.
+// Rank of column e's eigenvalue among all n (ties by column): the ascending output order; thread `part` of the TPE that
+// share an eigenvalue looks at every TPE-th group of four.  With a non-finite eigenvalue among them (`odd`) the columns
+// stay where they are.
 template <int N, int TPE, bool WANT_V>
-__device__ __forceinline__ int dc_rank(const DcShared<N, TPE, WANT_V>& S, int n, int e, bool odd) {
+__device__ __forceinline__ int dc_rank(const DcShared<N, TPE, WANT_V>& S, int n, int e, int part, bool odd) {
     const float de = S.D[e];
     int rank = 0;
-    for (int j = 0; j < n; j += 4) {                        // D is +inf from n on
+    for (int j = 4 * part; j < n; j += 4 * TPE) {           // D is +inf from n on
         const float4 q = *reinterpret_cast<const float4*>(S.D + j);
         rank += (q.x < de || (q.x == de && j < e)) ? 1 : 0;
         rank += (q.y < de || (q.y == de && j + 1 < e)) ? 1 : 0;
         rank += (q.z < de || (q.z == de && j + 2 < e)) ? 1 : 0;
         rank += (q.w < de || (q.w == de && j + 3 < e)) ? 1 : 0;
     }
+    rank = (int)dc_sum<TPE>((float)rank);
     return odd ? e : rank;
 }
 

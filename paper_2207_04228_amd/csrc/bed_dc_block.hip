@@ -1,11 +1,9 @@
 // 32 < n <= 128: tridiagonalisation in the accumulators of the matrix cores and divide and conquer on
 // the tridiagonal, one workgroup per matrix: four wavefronts for n <= 64, eight beyond.
 //
-// P leaves LDS before the divide and conquer and waits in registers as the left operand of the last
-// product V = P V_T (a strip of 32 rows per wavefront, N / 2 registers), so that V_T and the
-// eigenvectors of the merges have the two matrix-sized areas of LDS to themselves.  Beside the poles of the
-// root finder that is the limit at 128 rows: 256 registers and 14 to 16 spilled (none at 64, 168 registers).
-// 256 matrices: 64x64 282 us with the rotations, 90 now; 128x128 1195, 239.
+// The reflectors of the tridiagonalisation leave LDS before the divide and conquer and wait in registers (N / 4 of
+// them), so that the eigenvectors of T and of the merges have the two matrix-sized areas of LDS to themselves.  Then
+// they come back and are applied to V, sixteen columns per wavefront.  256 matrices, us per launch: 64x64 96 before, 72 now; 128x128 245, 169.
 #include "bed_tile_tridiag.hpp"
 
 namespace bed {
@@ -16,29 +14,43 @@ template <int N, bool WANT_V, int STAGE>
 __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(KernelArgs args) {
     constexpr int DT = 4 * N;                        // threads per matrix
     using Shared = DcShared<N, DT / N, WANT_V>;
-    constexpr int LD = Shared::LD;
-    constexpr int KS = N / 2;                        // steps of a product over N columns
+    constexpr int LD = Shared::LD, LR = kReflectorStride<N>;
     constexpr int NTILE = N / 32, JSTEP = (DT / 64) / NTILE, TJ = NTILE / JSTEP;
     __shared__ Shared S;
-    __shared__ TileShared<N> tiles;
     __shared__ float sd[N], se[N];
-    __shared__ float stage_own[WANT_V ? 1 : N * LD];
-    float* const stage = WANT_V ? S.V : stage_own;
+    __shared__ alignas(16) float stage_own[WANT_V ? 4 : N * LR];
+    // R takes V and the first rows of U, the blocks of T rows of U behind it
+    float* const R = WANT_V ? S.V : stage_own;
+    dc_acc16* const Tb = reinterpret_cast<dc_acc16*>(S.V + N * LR);
+    static_assert(!WANT_V || N * LR + 16 * N <= (int)(sizeof(S.V) + sizeof(S.U)) / 4, "R and T in the matrix areas");
+    // not in use before the divide and conquer
+    ReflectorFactors<N>& factors = *reinterpret_cast<ReflectorFactors<N>*>(S.dz);
+    StripExchange& strips = *reinterpret_cast<StripExchange*>(S.om);
+    static_assert(sizeof(factors) <= sizeof(S.dz) && (N == 64 || sizeof(strips) <= sizeof(S.om)), "");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wv = tid >> 6;
-    const int lo = lane & 31, hi = lane >> 5;
-    const int I = wv % NTILE, J0 = wv / NTILE;       // this wavefront's tile row, its first tile column
     const int b = blockIdx.x;
     const int n = args.n;
     float inv_scale = 1.f;
 
-    tridiag_tiles<N, WANT_V>(args.A + (size_t)b * n * n, n, tid, tiles, stage, sd, se, inv_scale);
-    float pa[WANT_V ? KS : 1];                       // pa[s] = P[32 I + lane % 32][2 s + lane / 32]
-    if constexpr (WANT_V) {
+    {
+        const float seen = load_symmetric<DT>(args.A + (size_t)b * n * n, n, tid, R, LD);
+        if (lane == 0) S.rn[wv] = seen;
+        __syncthreads();
+        float scale, top = S.rn[0];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) pa[s] = stage[(32 * I + lo) * LD + 2 * s + hi];
+        for (int w = 1; w < DT / 64; ++w) top = fmaxf(top, S.rn[w]);
+        pow2_scale(top, scale, inv_scale);
+        if constexpr (N == 64) {
+            if (wv == 0) tridiag_wave<N, LD>(R, R, factors, n, lane, scale, sd, se);
+        } else {
+            tridiag_strips<LD>(R, R, factors, strips, n, tid, scale, sd, se);
+        }
+        __syncthreads();
     }
+    Reflectors<N> H;
+    if constexpr (WANT_V) take_reflectors<N>(H, factors, R, n, tid);
     __syncthreads();
 
     const int unresolved = dc_solve<N, DT, WANT_V>(
@@ -46,57 +58,71 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
 
     const int odd = dc_non_finite(S, n, lane);
     if (tid == 0 && args.info) args.info[b] = odd + unresolved;
-    if (tid < n) {
-        const int rank = dc_rank(S, n, tid, odd != 0);
-        S.perm[tid] = rank;
-        if (args.evals) args.evals[(size_t)b * n + rank] = S.D[tid] * inv_scale;
+    {
+        const int e = tid / 4, part = tid % 4;
+        const int rank = dc_rank(S, n, e, part, odd != 0);
+        if (e < n && part == 0) {
+            S.perm[rank] = e;
+            if (args.evals) args.evals[(size_t)b * n + rank] = S.D[e] * inv_scale;
+        }
     }
     if constexpr (WANT_V) {
-        dc_acc32 acc[TJ];
+        // V = H_0 H_1 ... V_T; this wavefront's columns 16 wv ..
+        const int i = lane & 15, g = lane >> 4;
+        dc_acc16 x[N / 16];
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) acc[tj] = dc_acc32{};
-        // V = P V_T
+        for (int t = 0; t < N / 16; ++t)
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            if (2 * s < n) {
+            for (int v = 0; v < 4; ++v) x[t][v] = S.V[(16 * t + 4 * g + v) * LD + 16 * wv + i];
+        __syncthreads();
 #pragma unroll
-                for (int tj = 0; tj < TJ; ++tj)
-                    acc[tj] = dc_mfma(pa[s], S.V[(2 * s + hi) * LD + 32 * (J0 + tj * JSTEP) + lo], acc[tj]);
-            }
+        for (int k = 0; k < Reflectors<N>::kShare; ++k) {
+            const int at = tid + k * DT;
+            *reinterpret_cast<dc_acc16*>(R + (at / (N / 4)) * LR + 4 * (at % (N / 4))) = H.rows[k];
         }
+        Tb[tid] = H.t;
+        __syncthreads();
+        if (16 * wv < n) apply_reflectors<N>(x, R, Tb, n, lane);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < N / 16; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S.V[(16 * t + 4 * g + v) * LD + 16 * wv + i] = x[t][v];
+        if (STAGE == kSpectral && tid < N) {
+            const float y = fmaxf(S.D[tid] * inv_scale, args.fn_floor);
+            const float f = (args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(y) : __builtin_amdgcn_sqrtf(y);
+            S.rn[tid] = tid < n ? f : 0.f;
+        }
+        __syncthreads();
         if (STAGE == kFull || args.evecs) {          // the same in all threads
-            __syncthreads();                         // ranks
+            // ascending order; the columns of V change places on the way to memory
             float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
+            const float rcp_n = 1.0f / (float)n;
+            for (int base = tid; base < n * n; base += 8 * DT) {
+                float t[8];
 #pragma unroll
-            for (int tj = 0; tj < TJ; ++tj) {
-                const int c = 32 * (J0 + tj * JSTEP) + lo;
-                const int rank = S.perm[c];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int r = 32 * I + dc_row<32>(v, lane);
-                    if (r < n && c < n) Vb[r * n + rank] = acc[tj][v];
+                for (int k = 0; k < 8; ++k) {
+                    const int idx = min(base + k * DT, n * n - 1);
+                    const int r = (int)(((float)idx + 0.5f) * rcp_n);
+                    t[k] = S.V[r * LD + S.perm[idx - r * n]];
                 }
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (base + k * DT < n * n) Vb[base + k * DT] = t[k];
             }
         }
         if (STAGE == kSpectral) {
             // F = (V f(max(Lambda, floor))) V^T (Sec. 4.2-4.4): both operands are rows of V
-#pragma unroll
-            for (int tj = 0; tj < TJ; ++tj)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) S.U[(32 * I + dc_row<32>(v, lane)) * LD + 32 * (J0 + tj * JSTEP) + lo] = acc[tj][v];
-            if (tid < N) {
-                const float x = fmaxf(S.D[tid] * inv_scale, args.fn_floor);
-                const float f = (args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x);
-                S.rn[tid] = tid < n ? f : 0.f;
-            }
-            __syncthreads();
+            const int lo = lane & 31, hi = lane >> 5;
+            const int I = wv % NTILE, J0 = wv / NTILE;       // this wavefront's tile row, its first tile column
+            dc_acc32 acc[TJ];
 #pragma unroll
             for (int tj = 0; tj < TJ; ++tj) acc[tj] = dc_acc32{};
 #pragma unroll 4
             for (int k = 0; k < n; k += 2) {
-                const float a = S.U[(32 * I + lo) * LD + k + hi] * S.rn[k + hi];
+                const float a = S.V[(32 * I + lo) * LD + k + hi] * S.rn[k + hi];
 #pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) acc[tj] = dc_mfma(a, S.U[(32 * (J0 + tj * JSTEP) + lo) * LD + k + hi], acc[tj]);
+                for (int tj = 0; tj < TJ; ++tj) acc[tj] = dc_mfma(a, S.V[(32 * (J0 + tj * JSTEP) + lo) * LD + k + hi], acc[tj]);
             }
             float* __restrict__ Fb = args.fn_out + (size_t)b * n * n;
 #pragma unroll

@@ -55,8 +55,16 @@ __global__ __launch_bounds__(64) void dc_wave_kernel(KernelArgs args) {
     // column `lo` of the result, in every group of R lanes
     const float lam = S.D[lo] * inv_scale;
     const int odd = dc_non_finite(S, n, lane);
-    const int rank = dc_rank(S, n, lo, odd != 0);
-    if (args.evals && lane < n) args.evals[(size_t)b * n + rank] = lam;
+    {
+        const int e = lane / KT, part = lane % KT;
+        const int at = dc_rank(S, n, e, part, odd != 0);
+        if (part == 0) {
+            S.perm[e] = at;
+            if (args.evals && e < n) args.evals[(size_t)b * n + at] = S.D[e] * inv_scale;
+        }
+    }
+    sync();
+    const int rank = S.perm[lo];
     if (lane == 0 && args.info) args.info[b] = odd + unresolved;
 
     if constexpr (WANT_V) {

@@ -1,187 +1,443 @@
-// Load, power-of-two pre-scaling and Householder tridiagonalisation (Sec. 3.1) of one matrix,
-// 32 < n <= 128, with the working matrix and P^T in the accumulators of the matrix cores.
+// Householder tridiagonalisation (Sec. 3.1) of a symmetric matrix held in the accumulators of the matrix cores,
+// and the product with its reflectors.
 //
-// Each wavefront owns a strip of 32 columns of A or of P^T (N / 32 tiles of 32 x 32, 16 registers
-// each).  Both are updated by outer products with the reflector u,
-//   A   <- A   - u p^T - (p - 2K u) u^T      (rank 2: one v_mfma_f32_32x32x2_f32 per tile),
-//   P^T <- P^T - u w^T                       (rank 1: the same instruction with a zero column),
-// and both products p = A u and w = P u are column sums of the strips (A is symmetric), so a lane
-// adds up its own registers and only the two halves of the wavefront have to be combined.  Column J
-// is read off as row J.  Rows up to J are finished: their tiles drop out.
-// The earlier form of this phase, matrix and P in LDS, read and wrote every entry twice per step: 391 us
-// for 256 matrices of 128x128 where the LDS traffic alone took most of it.  Around the same divide and conquer the call
-// took 495 us with it and 260 with this.
+// The matrix is cut into tiles of 32 x 32 (16 x 16 for n <= 16).  Step J applies reflector J - 1 (one matrix instruction per
+// tile, rank 2: A <- A - u p^T - (p - 2K u) u^T) and forms its own p = A u as column sums of the tiles (A is
+// symmetric): a lane adds up its own registers, then the lanes that share a column.  What bounds it is the
+// serial chain of a column, so the chain is cut short: row J + 1 is taken from the tiles BEFORE the update and
+// brought up to date beside the matrix instructions (a - u_J p - (p_J - 2K u_J) u, one or two entries per lane).  Up to 64
+// rows one wavefront does all of it, with one LDS round trip a column (u in the order of the tiles' rows) and no barrier; at
+// 128 rows four wavefronts own a strip of 32 columns each and exchange p and the next row, with ONE barrier a column: u^T p, the
+// row and its norm are formed by each of them, the same bits.
+// Finished rows and columns take part in the updates: what is left of them is T and rounding.
+// The reflectors stay behind as the rows of R and are applied to the eigenvectors of T after the divide and conquer,
+// sixteen at a time (compact WY form I - Y T Y^T, Schreiber and Van Loan 1989).
+// The form before this one updated P beside A, in half of the wavefronts, with two barriers a column.
+// Cycles from load to the end of the reduction, one matrix per compute unit: 64x64 130 k, 128x128 364 k; now 79 k and 194 k, and 5 k and
+// 8 k for the blocks of T.  A column costs 920 cycles with one tile left, 1400 with four (n <= 64) or four strips.
 #ifndef BED_TILE_TRIDIAG_HPP
 #define BED_TILE_TRIDIAG_HPP
 #include "bed_dc.hpp"
 
 namespace bed {
 
+// Row stride of R: rows start on 128 bits, and 16 rows at the same four columns lie in 64 different banks.
 template <int N>
-struct TileShared {
-    alignas(16) float u[N];      // row J right of the diagonal, zero up to J
-    float p[N];
-    float k[N / 32];             // partial sums of u^T p, one per strip
-    float amax[N / 16];
+constexpr int kReflectorStride = N + 4;
+
+// Reflector J: 2/|u|^2, and what is added to entry J + 1 of row J of R to make it u.
+template <int N>
+struct ReflectorFactors {
+    float beta[N], sigma[N];
 };
 
-// stage: N rows of stride N + 1, left with P[r][c] at stage[r * (N + 1) + c] when it is wanted.
-// sd, se: T.  Threads: 4 N (N / 32 wavefronts for A, as many for P).  Ends with a barrier.
-template <int N, bool WANT_P>
-__device__ __forceinline__ void tridiag_tiles(const float* __restrict__ Ab, const int n, const int tid,
-                                              TileShared<N>& S, float* const stage, float* const sd, float* const se,
-                                              float& inv_scale) {
-    constexpr int T = 4 * N, NS = N / 32, LD = N + 1;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int lo = lane & 31, hi = lane >> 5;
-    const bool isA = wv < NS;
-    const int c = 32 * (isA ? wv : wv - NS) + lo;      // this lane's column
-    const bool works = isA || WANT_P;
+// The lower triangle of the matrix mirrored into `stage` (stride LD), T threads; returns the largest magnitude that this
+// wavefront has seen (NaNs drop out; they reach T through the norm of their column).
+template <int T>
+__device__ __forceinline__ float load_symmetric(const float* __restrict__ Ab, const int n, const int tid, float* const stage,
+                                                const int LD) {
+    const float rcp_n = 1.0f / (float)n;
+    float amax = 0.f;
+    for (int base = tid; base < n * n; base += 8 * T) {
+        float t[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) t[k] = base + k * T < n * n ? Ab[base + k * T] : 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int idx = base + k * T;
+            const int i = (int)(((float)idx + 0.5f) * rcp_n);
+            const int j = idx - i * n;
+            if (idx < n * n && j <= i) {
+                amax = fmaxf(amax, fabsf(t[k]));
+                stage[i * LD + j] = t[k];
+                stage[j * LD + i] = t[k];
+            }
+        }
+    }
+    return wave_max_nonneg<64>(amax);
+}
 
-    // ---- lower triangle mirrored into LDS; pre-scaling from its largest entry ----
-    {
-        const float rcp_n = 1.0f / (float)n;
-        float amax = 0.f;
-        for (int base = tid; base < n * n; base += 8 * T) {
-            float t[8];
+// Reflector of a column x with |x|^2 = alpha and first entry x0.
+struct Reflector {
+    float sigma, beta, first;                          // added to the first entry of x, 2/|u|^2, first entry of u
+    bool active;
+    __device__ __forceinline__ Reflector(float alpha, float x0, bool inside) {
+        // a NaN in the column counts as active and goes into T: an inactive step touches nothing, and
+        // no later step reads the column again
+        active = inside && !(alpha <= kTinyAlpha);
+        const float nrm = __builtin_amdgcn_sqrtf(alpha);
+        sigma = active ? (x0 < 0.f ? -nrm : nrm) : 0.f;                             // sign chosen to avoid cancellation
+        // |u|^2/2 for the square root that was taken, and its reciprocal to the last bit: I - beta u u^T is then as
+        // orthogonal as |x|^2 is accurate
+        const float half = fmaf(fabsf(x0), nrm, 0.5f * fmaf(nrm, nrm, alpha));
+        const float r = __builtin_amdgcn_rcpf(half);
+        beta = active ? fmaf(fmaf(-half, r, 1.f), r, r) : 0.f;
+        first = active ? x0 + sigma : 0.f;
+    }
+};
+
+// One wavefront, n <= N = 16, 32 or 64.  stage: the symmetric matrix, stride LD; R may be the same memory and is
+// left with row J of R in row J (columns up to J zero).  sd, se: T.
+template <int N, int LD>
+__device__ __forceinline__ void tridiag_wave(const float* const stage, float* const R, ReflectorFactors<N>& F, const int n,
+                                             const int lane, const float scale, float* const sd, float* const se) {
+    constexpr int TS = N == 16 ? 16 : 32, NS = N / TS, AR = TS * TS / 64, LR = kReflectorStride<N>;
+    using Acc = typename DcTile<N>::acc;
+    const int lo = lane & (TS - 1), hi = lane / TS;
+    const int at = lane & (N - 1);                     // the index whose vector entries this lane holds (copies for N < 64)
+    auto sync = []() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    Acc x[NS][NS];                                     // x[t][j][v]: row TS t + dc_row<TS>(v, lane), column TS j + lo
 #pragma unroll
-            for (int k = 0; k < 8; ++k) t[k] = base + k * T < n * n ? Ab[base + k * T] : 0.f;
+    for (int t = 0; t < NS; ++t)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int idx = base + k * T;
-                const int i = (int)(((float)idx + 0.5f) * rcp_n);
-                const int j = idx - i * n;
-                if (idx < n * n && j <= i) {
-                    amax = fmaxf(amax, fabsf(t[k]));   // drops NaNs; they reach T through the norm of their column
-                    stage[i * LD + j] = t[k];
-                    stage[j * LD + i] = t[k];
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int v = 0; v < AR; ++v) {
+                const int r = TS * t + dc_row<TS>(v, lane), c = TS * j + lo;
+                x[t][j][v] = (r < n && c < n) ? stage[r * LD + c] * scale : 0.f;
+            }
+    float a = at < n ? stage[at] * scale : 0.f;        // row J before reflector J - 1, by index
+    sync();                                            // R may take the place of the matrix
+    float p = 0.f, un = 0.f, beta = 0.f, uJ = 0.f;     // p, -u and 2/|u|^2 of reflector J - 1, u_J
+    float dv = 0.f, av = 0.f, xv = 0.f;                // diagonal of T, |x|^2 and first entry of the columns, by index
+
+    // columns TS t0 and up are not finished
+    auto column = [&](const int J, const int s, const int t0) {
+        const float K2 = -beta * wave_sum<N>(un * p);                               // 2K
+        const float wJ = fmaf(-K2, uJ, read_lane(p, J));
+        const float w = fmaf(K2, un, p);                                            // p - 2K u
+        const float r = fmaf(wJ, un, fmaf(-uJ, p, a));                              // row J, all reflectors before it applied
+        const float row = at > J ? r : 0.f;
+        R[J * LR + at] = row;
+        sync();
+        if (TS == 32) {
+            // lanes 0..31 hold the operands of the first outer product, lanes 32..63 of the second
+            const auto l = __builtin_amdgcn_permlane32_swap(__float_as_uint(un), __float_as_uint(w), false, false);
+            const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(un), false, false);
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+#pragma unroll
+                for (int j = 0; j < NS; ++j)
+                    if (t >= t0 && j >= t0) x[t][j] = dc_mfma(__uint_as_float(l[t]), __uint_as_float(c[j]), x[t][j]);
+        } else {
+            x[0][0] = dc_mfma(hi == 0 ? un : hi == 1 ? w : 0.f, hi == 0 ? p : hi == 1 ? un : 0.f, x[0][0]);
+        }
+        const float alpha = wave_sum<N>(row * row), x0 = J + 1 < N ? read_lane(row, (J + 1) & (N - 1)) : 0.f;
+        const Reflector H(alpha, x0, J < n - 2);
+        dv = at == J ? r : dv;
+        av = at == J ? alpha : av;
+        xv = at == J ? x0 : xv;
+        // column sums and row J + 1 (s, the step's place in the unrolled loop, names the register)
+        const int tile = (J + 1) / TS, sub = (s + 1) & 3, group = ((J + 1) >> 3) & 3;
+        float part[NS][4], next[NS];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            next[j] = 0.f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[j][v] = 0.f;
+        }
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+            if (t >= t0) {
+#pragma unroll
+                for (int q = 0; q < AR / 4; ++q) {
+                    const dc_acc16 u = *reinterpret_cast<const dc_acc16*>(R + J * LR + TS * t + dc_row<TS>(4 * q, lane));
+#pragma unroll
+                    for (int j = 0; j < NS; ++j)
+                        if (j >= t0)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) part[j][v] = fmaf(x[t][j][4 * q + v], u[v], part[j][v]);
                 }
             }
         }
-        amax = wave_max_nonneg<64>(amax);
-        if (lane == 0) S.amax[wv] = amax;
-    }
-    __syncthreads();
-    float scale, top = S.amax[0];
 #pragma unroll
-    for (int w = 1; w < T / 64; ++w) top = fmaxf(top, S.amax[w]);
-    pow2_scale(top, scale, inv_scale);
+        for (int j = 0; j < NS; ++j) {
+            if (j >= t0) {
+                next[j] = x[t0][j][sub];
+#pragma unroll
+                for (int t = t0; t < NS; ++t)
+#pragma unroll
+                    for (int q = 0; q < AR / 4; ++q) next[j] = (t == tile && q == group) ? x[t][j][4 * q + sub] : next[j];
+            }
+        }
+        un = H.active ? -(row + (at == J + 1 ? H.sigma : 0.f)) : 0.f;
+        beta = H.beta;
+        uJ = H.first;
+        float sum[NS];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) sum[j] = (part[j][0] + part[j][1]) + (part[j][2] + part[j][3]);
+        if (TS == 32) {
+            // the halves of a column; by index at the same time for two strips
+            const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(next[0]), __float_as_uint(next[NS - 1]), false, false);
+            a = __uint_as_float(y[((s + 1) >> 2) & 1]);
+            const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[0]), __float_as_uint(sum[NS - 1]), false, false);
+            p = __uint_as_float(z[0]) + __uint_as_float(z[1]);
+        } else {
+            float y = hi == (((J + 1) >> 2) & 3) ? next[0] : 0.f, z = sum[0];
+            auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+            y = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);
+            s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+            z = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);
+            auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+            a = __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
+            s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+            p = __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
+        }
+        p = beta * fmaf(H.sigma, a, p);                // u is row J of R with sigma added to entry J + 1
+    };
+    const int first = min(n, 32);
+    for (int J0 = 0; J0 < first; J0 += 8) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            if (J0 + s < first) column(J0 + s, s, 0);
+    }
+    if (NS > 1) {
+        for (int J0 = 32; J0 < n; J0 += 8) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                if (J0 + s < n) column(J0 + s, s, 1);
+        }
+    }
+    if (lane < n) {
+        const Reflector H(av, xv, lane < n - 2);       // the same bits as in the loop
+        sd[lane] = dv;
+        se[lane] = H.active ? -H.sigma : xv;
+        F.beta[lane] = H.beta;
+        F.sigma[lane] = H.sigma;
+    }
+    sync();
+}
 
-    dc_acc32 x[NS];                                    // x[t][v]: row 32 t + dc_row<32>(v, lane), column c
+// 64 < n <= 128: four wavefronts, a strip of 32 columns each; lanes hold the entries `lane` and `lane + 64` of a vector.
+struct StripExchange {
+    float p[2][128];             // [step parity]: A u by column
+    float row[2][128];           // [step parity]: the next row
+};
+template <int LD>
+__device__ __forceinline__ void tridiag_strips(const float* const stage, float* const R, ReflectorFactors<128>& F,
+                                               StripExchange& S, const int n, const int tid, const float scale,
+                                               float* const sd, float* const se) {
+    constexpr int NS = 4, LR = kReflectorStride<128>;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lo = lane & 31, hi = lane >> 5;
+    const int c = 32 * wv + lo;                        // this lane's column
+
+    if (wv >= NS) {                                    // the same number of barriers
+        __syncthreads();
+        for (int J = 0; J < n; ++J) __syncthreads();
+        return;
+    }
+    dc_acc32 x[NS];
 #pragma unroll
     for (int t = 0; t < NS; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = 32 * t + dc_row<32>(v, lane);
-            const float a = (isA && r < n && c < n) ? stage[r * LD + c] * scale : 0.f;
-            x[t][v] = isA ? a : ((r == c && c < n) ? 1.f : 0.f);
+            x[t][v] = (r < n && c < n) ? stage[r * LD + c] * scale : 0.f;
         }
-    if (tid < N) S.p[tid] = 0.f;
+    if (hi == 0) {
+        S.p[0][c] = 0.f;
+        S.row[0][c] = x[0][0];
+    }
+    __syncthreads();                                   // R may take the place of the matrix
 
-    // entry of row `row` in this lane's column (one half of the wavefront holds it): registers are
-    // indexed by compile-time constants, so `sub` = row % 4 comes from an unrolled loop
-    auto pick = [&](int row, int sub) {
-        const int tile = row >> 5, group = (row >> 3) & 3;
-        float val = 0.f;
-#pragma unroll
-        for (int t = 0; t < NS; ++t)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) val = (t == tile && g == group) ? x[t][4 * g + sub] : val;
-        return val;
-    };
+    float un[2] = {0.f, 0.f}, beta = 0.f, uJ = 0.f;    // -u and 2/|u|^2 of reflector J - 1, u_J
+    float dv[2] = {0.f, 0.f}, av[2] = {0.f, 0.f}, xv[2] = {0.f, 0.f};   // diagonal of T, |x|^2 and first entry of the columns
+    const bool odd = wv & 1, upper = wv >> 1;
 
-    for (int J0 = 0; J0 < n; J0 += 4) {
+    // rows and columns 32 t0 and up are not finished
+    auto column = [&](const int J, const int s, const int t0) {
+        const int par = s & 1;
+        float p[2], a[2], r[2], w[2], row[2];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int J = J0 + s;
-            if (J < n) {                               // the same in all threads
-                const int first = J >> 5;              // tiles above are finished
-                if (isA) {
-                    const float row = pick(J, s);
-                    if (hi == ((J >> 2) & 1)) {
-                        S.u[c] = c > J ? row : 0.f;
-                        if (c == J) sd[J] = row;
-                    }
-                }
-                __syncthreads();
-                const float x0 = J + 1 < n ? S.u[J + 1 < N ? J + 1 : 0] : 0.f;
-                float sq = S.u[lane] * S.u[lane];
-                if (N > 64) sq = fmaf(S.u[(lane + 64) & (N - 1)], S.u[(lane + 64) & (N - 1)], sq);
-                const float alpha = wave_sum<64>(sq);
-                // a NaN in the column counts as active and goes into T: an inactive step touches nothing, and
-                // no later step reads the column again
-                const bool active = J < n - 2 && !(alpha <= kTinyAlpha);
-                if (tid == 0) {
-                    const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                    se[J] = active ? (x0 < 0.f ? nrm : -nrm) : x0;
-                }
-                if (active) {                          // the same in all threads
-                    const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                    const float sigma = (x0 < 0.f) ? -nrm : nrm;       // sign chosen to avoid cancellation
-                    const float beta = __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha));    // 2/|u|^2
-                    // u is the row in LDS with sigma added to entry J + 1
-                    float pc = 0.f;
-                    // entries of u that this lane needs after the second barrier: by then a wavefront that is
-                    // ahead may write the next row over it
-                    float ur[NS];
+        for (int q = 0; q < 2; ++q) {
+            p[q] = beta * S.p[par][lane + 64 * q];
+            a[q] = S.row[par][lane + 64 * q];
+        }
+        const float K2 = -beta * wave_sum<64>(fmaf(un[0], p[0], un[1] * p[1]));     // 2K
+        const float wJ = fmaf(-K2, uJ, read_lane(t0 >= 2 ? p[1] : p[0], J & 63));
 #pragma unroll
-                    for (int t = 0; t < NS; ++t) ur[t] = S.u[32 * t + lo] + (32 * t + lo == J + 1 ? sigma : 0.f);
-                    if (works) {
-                        float part[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < 2; ++q) {
+            w[q] = fmaf(K2, un[q], p[q]);
+            r[q] = fmaf(wJ, un[q], fmaf(-uJ, p[q], a[q]));
+            row[q] = lane + 64 * q > J ? r[q] : 0.f;
+            // every wavefront writes the row, the same bits, and reads back what it wrote itself
+            R[J * LR + lane + 64 * q] = row[q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        {
+            const auto cc = __builtin_amdgcn_permlane32_swap(__float_as_uint(upper ? p[1] : p[0]),
+                                                             __float_as_uint(upper ? un[1] : un[0]), false, false);
+            const float right = __uint_as_float(odd ? cc[1] : cc[0]);
 #pragma unroll
-                        for (int t = 0; t < NS; ++t) {
-                            if (t >= first && 32 * t < n) {
+            for (int q = 0; q < 2; ++q) {
+                if (2 * q + 1 >= t0) {
+                    const auto l = __builtin_amdgcn_permlane32_swap(__float_as_uint(un[q]), __float_as_uint(w[q]), false, false);
 #pragma unroll
-                                for (int g = 0; g < 4; ++g) {
-                                    const float4 w = *reinterpret_cast<const float4*>(S.u + 32 * t + 8 * g + 4 * hi);
-                                    part[0] = fmaf(x[t][4 * g + 0], w.x, part[0]);
-                                    part[1] = fmaf(x[t][4 * g + 1], w.y, part[1]);
-                                    part[2] = fmaf(x[t][4 * g + 2], w.z, part[2]);
-                                    part[3] = fmaf(x[t][4 * g + 3], w.w, part[3]);
-                                }
-                            }
-                        }
-                        const float next = hi == (((J + 1) >> 2) & 1) ? pick(J + 1, (s + 1) & 3) : 0.f;
-                        float sum = fmaf(sigma, next, (part[0] + part[1]) + (part[2] + part[3]));
-                        const unsigned bits = __float_as_uint(sum);
-                        const auto both = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
-                        pc = beta * (__uint_as_float(both[0]) + __uint_as_float(both[1]));
-                    }
-                    const float uc = S.u[c] + (c == J + 1 ? sigma : 0.f);
-                    if (isA) {
-                        if (hi == 0) S.p[c] = pc;
-                        const float dot = wave_sum<32>(uc * pc);
-                        if (lane == 0) S.k[wv] = dot;
-                    }
-                    __syncthreads();
-                    if (works) {
-                        float K2 = S.k[0];
-#pragma unroll
-                        for (int w = 1; w < NS; ++w) K2 += S.k[w];
-                        K2 *= beta;                                    // 2K
-                        const float right = hi == 0 ? pc : (isA ? uc : 0.f);
-#pragma unroll
-                        for (int t = 0; t < NS; ++t) {
-                            if (t >= first && 32 * t < n) {
-                                const float left = hi == 0 ? ur[t] : fmaf(-K2, ur[t], S.p[32 * t + lo]);
-                                x[t] = dc_mfma(-left, right, x[t]);
-                            }
-                        }
-                    }
-                } else {
-                    __syncthreads();                   // all have read the row
+                    for (int k = 0; k < 2; ++k)
+                        if (2 * q + k >= t0) x[2 * q + k] = dc_mfma(__uint_as_float(l[k]), right, x[2 * q + k]);
                 }
             }
         }
-    }
-    __syncthreads();
-    if (WANT_P && !isA) {
+        const int J1 = min(J + 1, 127);
+        const float x0 = J + 1 < 128 ? read_lane(J1 >= 64 ? row[1] : row[0], J1 & 63) : 0.f;
+        const float alpha = wave_sum<64>(fmaf(row[0], row[0], row[1] * row[1]));
+        const Reflector H(alpha, x0, J < n - 2);
+        {
+            constexpr int kBank[4] = {0, 0, 1, 1};
+            const int q = kBank[t0];
+            const bool here = lane == (J & 63);
+            dv[q] = here ? r[q] : dv[q];
+            av[q] = here ? alpha : av[q];
+            xv[q] = here ? x0 : xv[q];
+        }
 #pragma unroll
-        for (int t = 0; t < NS; ++t)
+        for (int q = 0; q < 2; ++q) un[q] = H.active ? -(row[q] + (lane + 64 * q == J + 1 ? H.sigma : 0.f)) : 0.f;
+        beta = H.beta;
+        uJ = H.first;
+        const int tile = (J + 1) >> 5, sub = (s + 1) & 3, group = ((J + 1) >> 3) & 3;
+        float part[4] = {0.f, 0.f, 0.f, 0.f}, next = x[t0][sub];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) stage[c * LD + 32 * t + dc_row<32>(v, lane)] = x[t][v];
+        for (int t = 0; t < NS; ++t) {
+            if (t >= t0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const dc_acc16 u = *reinterpret_cast<const dc_acc16*>(R + J * LR + 32 * t + 8 * q + 4 * hi);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) part[v] = fmaf(x[t][4 * q + v], u[v], part[v]);
+                    if (t <= t0 + 1) next = (t == tile && q == group) ? x[t][4 * q + sub] : next;
+                }
+            }
+        }
+        const unsigned bits = __float_as_uint(next);
+        const auto y = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+        const float up = __uint_as_float(y[((s + 1) >> 2) & 1]);
+        const unsigned half = __float_as_uint((part[0] + part[1]) + (part[2] + part[3]));
+        const auto z = __builtin_amdgcn_permlane32_swap(half, half, false, false);
+        const float sum = __uint_as_float(z[0]) + __uint_as_float(z[1]);
+        if (hi == 0) {
+            S.p[par ^ 1][c] = fmaf(H.sigma, up, sum);  // u is row J of R with sigma added to entry J + 1
+            S.row[par ^ 1][c] = up;
+        }
+        __syncthreads();
+    };
+#pragma unroll
+    for (int t0 = 0; t0 < NS; ++t0) {
+        const int end = min(n, 32 * (t0 + 1));
+        for (int J0 = 32 * t0; J0 < end; J0 += 8) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                if (J0 + s < end) column(J0 + s, s, t0);
+        }
     }
+    if (wv == 0) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int l = lane + 64 * q;
+            if (l < n) {
+                const Reflector H(av[q], xv[q], l < n - 2);    // the same bits as in the loop
+                sd[l] = dv[q];
+                se[l] = H.active ? -H.sigma : xv[q];
+                F.beta[l] = H.beta;
+                F.sigma[l] = H.sigma;
+            }
+        }
+    }
+}
+
+// The reflectors in the form in which they wait for the divide and conquer to end: T of this wavefront's block
+// of sixteen as the left operand of X = T Z, and this thread's share of R.
+template <int N>
+struct Reflectors {
+    static constexpr int kShare = N / 16;              // vectors of four entries of R per thread
+    dc_acc16 rows[kShare];
+    dc_acc16 t;
+};
+
+// R in LDS as the tridiagonalisation leaves it, visible to all threads.  Ends without a barrier.
+template <int N>
+__device__ __forceinline__ void take_reflectors(Reflectors<N>& H, const ReflectorFactors<N>& S, float* const R, const int n,
+                                                const int tid) {
+    constexpr int T = 4 * N, LR = kReflectorStride<N>;
+    const int lane = tid & 63, wv = tid >> 6;
+    const int i = lane & 15, g = lane >> 4;
+    if (tid < n - 2) R[tid * LR + tid + 1] += S.sigma[tid];
+    for (int k = n * N + tid; k < ((n + 13) & ~15) * N; k += T) R[(k / N) * LR + k % N] = 0.f;   // rows that fill the last block
     __syncthreads();
+    const int J0 = 16 * wv;
+    H.t = dc_acc16{};
+    if (J0 < n - 2) {                                  // the same in all lanes of a wavefront
+        // S = Y^T Y in 64 bits (both operands are the same entry of R, register v of the result is row 4 v + lane / 16):
+        // the block is only as orthogonal as T fits Y.  With S in 32 bits V^T V - I was 10 % larger than
+        // with P accumulated reflector by reflector, with this it is smaller.
+        typedef double acc64 __attribute__((ext_vector_type(4)));
+        acc64 s = acc64{};
+        for (int k = J0; k < n; k += 16) {
+            const dc_acc16 y = *reinterpret_cast<const dc_acc16*>(R + (J0 + i) * LR + k + 4 * g);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s = __builtin_amdgcn_mfma_f64_16x16x4f64((double)y[v], (double)y[v], s, 0, 0, 0);
+        }
+        // T = (diag(1/beta) + strictly upper part of S)^-1 with beta = 2 / S_jj; lane i has row i, from left to right
+        const float f[4] = {(float)s[0], (float)s[1], (float)s[2], (float)s[3]};
+        const float own_diag = i < 4 ? f[0] : i < 8 ? f[1] : i < 12 ? f[2] : f[3];      // S_ii where lane / 16 = i % 4
+        const float b = S.beta[J0 + i] > 0.f ? 2.f / own_diag : 0.f;
+        float t[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            float sum = i == j ? -1.f : 0.f;
+#pragma unroll
+            for (int k = 0; k < j; ++k) sum = fmaf(t[k], read_lane(f[k >> 2], 16 * (k & 3) + j), sum);
+            t[j] = J0 + j < n - 2 ? -read_lane(b, 16 * (j & 3) + j) * sum : 0.f;
+        }
+        auto own = [&](int v) { return g == 0 ? t[v] : g == 1 ? t[4 + v] : g == 2 ? t[8 + v] : t[12 + v]; };
+        H.t = dc_acc16{own(0), own(1), own(2), own(3)};
+    }
+#pragma unroll
+    for (int k = 0; k < Reflectors<N>::kShare; ++k) {
+        const int at = tid + k * T;
+        H.rows[k] = *reinterpret_cast<const dc_acc16*>(R + (at / (N / 4)) * LR + 4 * (at % (N / 4)));
+    }
+}
+
+// V <- H_0 H_1 ... V for this wavefront's columns 16 wv .. 16 wv + 15 of V, in accumulators: x[t][v] is row
+// 16 t + 4 (lane / 16) + v.  R and the blocks of T (64 vectors each, by lane) in LDS.
+template <int N>
+__device__ __forceinline__ void apply_reflectors(dc_acc16 (&x)[N / 16], const float* const R, const dc_acc16* const T,
+                                                 const int n, const int lane) {
+    constexpr int LR = kReflectorStride<N>;
+    const int i = lane & 15, g = lane >> 4;
+    for (int blk = (n + 13) / 16 - 1; blk >= 0; --blk) {
+        const dc_acc16 t = T[64 * blk + lane];
+        dc_acc16 z[4] = {};                            // Z = Y^T V, four partial sums
+#pragma unroll
+        for (int k = 0; k < N / 16; ++k) {
+            if (k >= blk && 16 * k < n) {
+                const dc_acc16 y = *reinterpret_cast<const dc_acc16*>(R + (16 * blk + i) * LR + 16 * k + 4 * g);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) z[v] = dc_mfma(y[v], x[k][v], z[v]);
+            }
+        }
+        const dc_acc16 zz = (z[0] + z[1]) + (z[2] + z[3]);
+        dc_acc16 w = dc_acc16{};                       // T Z
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w = dc_mfma(t[v], zz[v], w);
+#pragma unroll
+        for (int k = 0; k < N / 16; ++k) {
+            if (k >= blk && 16 * k < n) {
+                // the sixteen products are summed before they meet V: one rounding at the size of V a block
+                const float* const y = R + (16 * blk + 4 * g) * LR + 16 * k + i;
+                dc_acc16 d = dc_acc16{};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) d = dc_mfma(y[v * LR], w[v], d);
+                x[k] -= d;
+            }
+        }
+    }
 }
 
 }  // namespace bed

@@ -232,3 +232,16 @@ def test_training_step_saves_what_it_needs_and_notices_changes():
         x.add_(1.0)
     with pytest.raises(RuntimeError):
         torch.autograd.grad(out, x, G)
+
+
+@pytest.mark.parametrize("n", [34, 35, 50, 51, 66, 67, 82, 83, 98, 99, 114, 115, 126])
+def test_edges_of_the_blocks_of_reflectors(n):
+    """n - 2 reflectors are applied in blocks of sixteen; the structured matrices leave some of them out (zero columns)."""
+    from paper_2207_04228_amd import workloads
+    perm = np.random.default_rng(6990 + n).permutation(n)
+    gaps = workloads.covariance(4, n, 4 * n, 1e-4, 6991 + n)
+    gaps[:, ::5, :] *= np.eye(n, dtype=np.float32)[::5]         # every fifth row and column decoupled, anywhere in the order
+    gaps[:, :, ::5] *= np.eye(n, dtype=np.float32)[:, ::5]
+    for A, name in ((_structured(n, n + 1), "structured"), (gaps, "gaps"), (np.ascontiguousarray(gaps[:, perm][:, :, perm]), "shuffled")):
+        assert _runs(A)
+        _check(A, f"blocks of reflectors, {name}, n={n}")
