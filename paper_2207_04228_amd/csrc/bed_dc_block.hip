@@ -43,7 +43,7 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
         for (int w = 1; w < DT / 64; ++w) top = fmaxf(top, S.rn[w]);
         pow2_scale(top, scale, inv_scale);
         if constexpr (N == 64) {
-            if (wv == 0) tridiag_wave<N, LD>(R, R, factors, n, lane, scale, sd, se);
+            if (wv == 0) tridiag_wave<LD>(R, R, factors, n, lane, scale, sd, se);
         } else {
             tridiag_strips<LD>(R, R, factors, strips, n, tid, scale, sd, se);
         }

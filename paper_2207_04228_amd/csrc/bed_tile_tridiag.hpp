@@ -1,7 +1,7 @@
-// Householder tridiagonalisation (Sec. 3.1) of a symmetric matrix held in the accumulators of the matrix cores,
+// Householder tridiagonalisation (Sec. 3.1) of a symmetric matrix, 32 < n <= 128, held in the accumulators of the matrix cores,
 // and the product with its reflectors.
 //
-// The matrix is cut into tiles of 32 x 32 (16 x 16 for n <= 16).  Step J applies reflector J - 1 (one matrix instruction per
+// The matrix is cut into tiles of 32 x 32.  Step J applies reflector J - 1 (one matrix instruction per
 // tile, rank 2: A <- A - u p^T - (p - 2K u) u^T) and forms its own p = A u as column sums of the tiles (A is
 // symmetric): a lane adds up its own registers, then the lanes that share a column.  What bounds it is the
 // serial chain of a column, so the chain is cut short: row J + 1 is taken from the tiles BEFORE the update and
@@ -32,18 +32,18 @@ struct ReflectorFactors {
 };
 
 // The lower triangle of the matrix mirrored into `stage` (stride LD), T threads; returns the largest magnitude that this
-// wavefront has seen (NaNs drop out; they reach T through the norm of their column).
-template <int T>
+// wavefront has seen (NaNs drop out; they reach T through the norm of their column).  CH loads per thread are in flight.
+template <int T, int CH = 8>
 __device__ __forceinline__ float load_symmetric(const float* __restrict__ Ab, const int n, const int tid, float* const stage,
                                                 const int LD) {
     const float rcp_n = 1.0f / (float)n;
     float amax = 0.f;
-    for (int base = tid; base < n * n; base += 8 * T) {
-        float t[8];
+    for (int base = tid; base < n * n; base += CH * T) {
+        float t[CH];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t[k] = base + k * T < n * n ? Ab[base + k * T] : 0.f;
+        for (int k = 0; k < CH; ++k) t[k] = base + k * T < n * n ? Ab[base + k * T] : 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < CH; ++k) {
             const int idx = base + k * T;
             const int i = (int)(((float)idx + 0.5f) * rcp_n);
             const int j = idx - i * n;
@@ -57,136 +57,118 @@ __device__ __forceinline__ float load_symmetric(const float* __restrict__ Ab, co
     return wave_max_nonneg<64>(amax);
 }
 
-// Reflector of a column x with |x|^2 = alpha and first entry x0.
+// Reflector of a column x with |x|^2 = alpha and first entry x0; left out (beta = 0: then p and all that follows from it are
+// zero, whatever u is) where alpha is not above `limit`.  A NaN in the column counts as active and goes into T: an inactive step
+// touches nothing, and no later step reads the column again.
 struct Reflector {
     float sigma, beta, first;                          // added to the first entry of x, 2/|u|^2, first entry of u
     bool active;
-    __device__ __forceinline__ Reflector(float alpha, float x0, bool inside) {
-        // a NaN in the column counts as active and goes into T: an inactive step touches nothing, and
-        // no later step reads the column again
-        active = inside && !(alpha <= kTinyAlpha);
+    __device__ __forceinline__ Reflector(float alpha, float x0, float limit) {
+        active = !(alpha <= limit);
         const float nrm = __builtin_amdgcn_sqrtf(alpha);
-        sigma = active ? (x0 < 0.f ? -nrm : nrm) : 0.f;                             // sign chosen to avoid cancellation
+        sigma = copysignf(nrm, x0);                    // no cancellation
         // |u|^2/2 for the square root that was taken, and its reciprocal to the last bit: I - beta u u^T is then as
         // orthogonal as |x|^2 is accurate
         const float half = fmaf(fabsf(x0), nrm, 0.5f * fmaf(nrm, nrm, alpha));
         const float r = __builtin_amdgcn_rcpf(half);
         beta = active ? fmaf(fmaf(-half, r, 1.f), r, r) : 0.f;
-        first = active ? x0 + sigma : 0.f;
+        first = x0 + sigma;
     }
+    static __device__ __forceinline__ float limit(int J, int n) { return J < n - 2 ? kTinyAlpha : __builtin_inff(); }
 };
 
-// One wavefront, n <= N = 16, 32 or 64.  stage: the symmetric matrix, stride LD; R may be the same memory and is
+// What the loops leave per column, by index l: T, and the reflector.
+template <int N>
+__device__ __forceinline__ void finish_column(const float* const R, ReflectorFactors<N>& F, const int n, const int l,
+                                              const float diagonal, const float alpha, float* const sd, float* const se) {
+    const float x0 = l + 1 < n ? R[l * kReflectorStride<N> + l + 1] : 0.f;
+    const Reflector H(alpha, x0, Reflector::limit(l, n));      // the same bits as in the loop
+    sd[l] = diagonal;
+    se[l] = H.active ? -H.sigma : x0;
+    F.beta[l] = H.beta;
+    F.sigma[l] = H.active ? H.sigma : 0.f;
+}
+
+// One wavefront, n <= 64, a vector entry per lane.  stage: the symmetric matrix, stride LD; R may be the same memory and is
 // left with row J of R in row J (columns up to J zero).  sd, se: T.
-template <int N, int LD>
-__device__ __forceinline__ void tridiag_wave(const float* const stage, float* const R, ReflectorFactors<N>& F, const int n,
+template <int LD>
+__device__ __forceinline__ void tridiag_wave(const float* const stage, float* const R, ReflectorFactors<64>& F, const int n,
                                              const int lane, const float scale, float* const sd, float* const se) {
-    constexpr int TS = N == 16 ? 16 : 32, NS = N / TS, AR = TS * TS / 64, LR = kReflectorStride<N>;
-    using Acc = typename DcTile<N>::acc;
-    const int lo = lane & (TS - 1), hi = lane / TS;
-    const int at = lane & (N - 1);                     // the index whose vector entries this lane holds (copies for N < 64)
+    constexpr int NS = 2, LR = kReflectorStride<64>;
+    const int lo = lane & 31, hi = lane >> 5;
     auto sync = []() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
 
-    Acc x[NS][NS];                                     // x[t][j][v]: row TS t + dc_row<TS>(v, lane), column TS j + lo
+    dc_acc32 x[NS][NS];                                // x[t][j][v]: row 32 t + dc_row<32>(v, lane), column 32 j + lo
 #pragma unroll
     for (int t = 0; t < NS; ++t)
 #pragma unroll
         for (int j = 0; j < NS; ++j)
 #pragma unroll
-            for (int v = 0; v < AR; ++v) {
-                const int r = TS * t + dc_row<TS>(v, lane), c = TS * j + lo;
-                x[t][j][v] = (r < n && c < n) ? stage[r * LD + c] * scale : 0.f;
+            for (int v = 0; v < 16; ++v) {
+                const int r = 32 * t + dc_row<32>(v, lane), c = 32 * j + lo;
+                const float entry = stage[r * LD + c];          // within the buffer also from n on
+                x[t][j][v] = (r < n && c < n) ? entry * scale : 0.f;
             }
-    float a = at < n ? stage[at] * scale : 0.f;        // row J before reflector J - 1, by index
+    const float top = stage[lane];
+    float a = lane < n ? top * scale : 0.f;            // row J before reflector J - 1
     sync();                                            // R may take the place of the matrix
     float p = 0.f, un = 0.f, beta = 0.f, uJ = 0.f;     // p, -u and 2/|u|^2 of reflector J - 1, u_J
-    float dv = 0.f, av = 0.f, xv = 0.f;                // diagonal of T, |x|^2 and first entry of the columns, by index
+    float dv = 0.f, av = 0.f;                          // diagonal of T, |x|^2 of the columns
 
-    // columns TS t0 and up are not finished
+    // columns 32 t0 and up are not finished; s, the step's place in the unrolled loop, names registers
     auto column = [&](const int J, const int s, const int t0) {
-        const float K2 = -beta * wave_sum<N>(un * p);                               // 2K
+        const float K2 = -beta * wave_sum<64>(un * p);                              // 2K
         const float wJ = fmaf(-K2, uJ, read_lane(p, J));
         const float w = fmaf(K2, un, p);                                            // p - 2K u
         const float r = fmaf(wJ, un, fmaf(-uJ, p, a));                              // row J, all reflectors before it applied
-        const float row = at > J ? r : 0.f;
-        R[J * LR + at] = row;
+        const float row = lane > J ? r : 0.f;
+        R[J * LR + lane] = row;
         sync();
-        if (TS == 32) {
-            // lanes 0..31 hold the operands of the first outer product, lanes 32..63 of the second
-            const auto l = __builtin_amdgcn_permlane32_swap(__float_as_uint(un), __float_as_uint(w), false, false);
-            const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(un), false, false);
+        // lanes 0..31 hold the operands of the first outer product, lanes 32..63 of the second
+        const auto l = __builtin_amdgcn_permlane32_swap(__float_as_uint(un), __float_as_uint(w), false, false);
+        const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(un), false, false);
 #pragma unroll
-            for (int t = 0; t < NS; ++t)
+        for (int t = t0; t < NS; ++t)
 #pragma unroll
-                for (int j = 0; j < NS; ++j)
-                    if (t >= t0 && j >= t0) x[t][j] = dc_mfma(__uint_as_float(l[t]), __uint_as_float(c[j]), x[t][j]);
-        } else {
-            x[0][0] = dc_mfma(hi == 0 ? un : hi == 1 ? w : 0.f, hi == 0 ? p : hi == 1 ? un : 0.f, x[0][0]);
-        }
-        const float alpha = wave_sum<N>(row * row), x0 = J + 1 < N ? read_lane(row, (J + 1) & (N - 1)) : 0.f;
-        const Reflector H(alpha, x0, J < n - 2);
-        dv = at == J ? r : dv;
-        av = at == J ? alpha : av;
-        xv = at == J ? x0 : xv;
-        // column sums and row J + 1 (s, the step's place in the unrolled loop, names the register)
-        const int tile = (J + 1) / TS, sub = (s + 1) & 3, group = ((J + 1) >> 3) & 3;
-        float part[NS][4], next[NS];
+            for (int j = t0; j < NS; ++j) x[t][j] = dc_mfma(__uint_as_float(l[t]), __uint_as_float(c[j]), x[t][j]);
+        const float alpha = wave_sum<64>(row * row);
+        const Reflector H(alpha, J < 63 ? read_lane(row, (J + 1) & 63) : 0.f, Reflector::limit(J, n));
+        dv = lane == J ? r : dv;
+        av = lane == J ? alpha : av;
+        // column sums and row J + 1
+        const int tile = (J + 1) >> 5, sub = (s + 1) & 3, group = ((J + 1) >> 3) & 3;
+        float part[NS][4] = {}, next[NS] = {0.f, 0.f}, sum[NS];
 #pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            next[j] = 0.f;
+        for (int t = t0; t < NS; ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) part[j][v] = 0.f;
-        }
+            for (int q = 0; q < 4; ++q) {
+                const dc_acc16 u = *reinterpret_cast<const dc_acc16*>(R + J * LR + 32 * t + 8 * q + 4 * hi);
 #pragma unroll
-        for (int t = 0; t < NS; ++t) {
-            if (t >= t0) {
+                for (int j = t0; j < NS; ++j)
 #pragma unroll
-                for (int q = 0; q < AR / 4; ++q) {
-                    const dc_acc16 u = *reinterpret_cast<const dc_acc16*>(R + J * LR + TS * t + dc_row<TS>(4 * q, lane));
-#pragma unroll
-                    for (int j = 0; j < NS; ++j)
-                        if (j >= t0)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) part[j][v] = fmaf(x[t][j][4 * q + v], u[v], part[j][v]);
-                }
+                    for (int v = 0; v < 4; ++v) part[j][v] = fmaf(x[t][j][4 * q + v], u[v], part[j][v]);
             }
+#pragma unroll
+        for (int j = t0; j < NS; ++j) {
+            next[j] = x[t0][j][sub];
+#pragma unroll
+            for (int t = t0; t < NS; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) next[j] = (t == tile && q == group) ? x[t][j][4 * q + sub] : next[j];
         }
-#pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            if (j >= t0) {
-                next[j] = x[t0][j][sub];
-#pragma unroll
-                for (int t = t0; t < NS; ++t)
-#pragma unroll
-                    for (int q = 0; q < AR / 4; ++q) next[j] = (t == tile && q == group) ? x[t][j][4 * q + sub] : next[j];
-            }
-        }
-        un = H.active ? -(row + (at == J + 1 ? H.sigma : 0.f)) : 0.f;
+        un = lane == J + 1 ? -H.first : -row;
         beta = H.beta;
         uJ = H.first;
-        float sum[NS];
 #pragma unroll
         for (int j = 0; j < NS; ++j) sum[j] = (part[j][0] + part[j][1]) + (part[j][2] + part[j][3]);
-        if (TS == 32) {
-            // the halves of a column; by index at the same time for two strips
-            const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(next[0]), __float_as_uint(next[NS - 1]), false, false);
-            a = __uint_as_float(y[((s + 1) >> 2) & 1]);
-            const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[0]), __float_as_uint(sum[NS - 1]), false, false);
-            p = __uint_as_float(z[0]) + __uint_as_float(z[1]);
-        } else {
-            float y = hi == (((J + 1) >> 2) & 3) ? next[0] : 0.f, z = sum[0];
-            auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-            y = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);
-            s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(z), __float_as_uint(z), false, false);
-            z = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);
-            auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-            a = __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
-            s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
-            p = __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
-        }
+        // the halves of a column, and at the same time from strips to lanes
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(next[0]), __float_as_uint(next[1]), false, false);
+        a = __uint_as_float(y[((s + 1) >> 2) & 1]);
+        const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[0]), __float_as_uint(sum[1]), false, false);
+        p = __uint_as_float(z[0]) + __uint_as_float(z[1]);
         p = beta * fmaf(H.sigma, a, p);                // u is row J of R with sigma added to entry J + 1
     };
     const int first = min(n, 32);
@@ -195,20 +177,12 @@ __device__ __forceinline__ void tridiag_wave(const float* const stage, float* co
         for (int s = 0; s < 8; ++s)
             if (J0 + s < first) column(J0 + s, s, 0);
     }
-    if (NS > 1) {
-        for (int J0 = 32; J0 < n; J0 += 8) {
+    for (int J0 = 32; J0 < n; J0 += 8) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s)
-                if (J0 + s < n) column(J0 + s, s, 1);
-        }
+        for (int s = 0; s < 8; ++s)
+            if (J0 + s < n) column(J0 + s, s, 1);
     }
-    if (lane < n) {
-        const Reflector H(av, xv, lane < n - 2);       // the same bits as in the loop
-        sd[lane] = dv;
-        se[lane] = H.active ? -H.sigma : xv;
-        F.beta[lane] = H.beta;
-        F.sigma[lane] = H.sigma;
-    }
+    if (lane < n) finish_column<64>(R, F, n, lane, dv, av, sd, se);
     sync();
 }
 
@@ -237,7 +211,8 @@ __device__ __forceinline__ void tridiag_strips(const float* const stage, float* 
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = 32 * t + dc_row<32>(v, lane);
-            x[t][v] = (r < n && c < n) ? stage[r * LD + c] * scale : 0.f;
+            const float entry = stage[r * LD + c];              // within the buffer also from n on
+            x[t][v] = (r < n && c < n) ? entry * scale : 0.f;
         }
     if (hi == 0) {
         S.p[0][c] = 0.f;
@@ -246,7 +221,7 @@ __device__ __forceinline__ void tridiag_strips(const float* const stage, float* 
     __syncthreads();                                   // R may take the place of the matrix
 
     float un[2] = {0.f, 0.f}, beta = 0.f, uJ = 0.f;    // -u and 2/|u|^2 of reflector J - 1, u_J
-    float dv[2] = {0.f, 0.f}, av[2] = {0.f, 0.f}, xv[2] = {0.f, 0.f};   // diagonal of T, |x|^2 and first entry of the columns
+    float dv[2] = {0.f, 0.f}, av[2] = {0.f, 0.f};      // diagonal of T, |x|^2 of the columns
     const bool odd = wv & 1, upper = wv >> 1;
 
     // rows and columns 32 t0 and up are not finished
@@ -287,17 +262,16 @@ __device__ __forceinline__ void tridiag_strips(const float* const stage, float* 
         const int J1 = min(J + 1, 127);
         const float x0 = J + 1 < 128 ? read_lane(J1 >= 64 ? row[1] : row[0], J1 & 63) : 0.f;
         const float alpha = wave_sum<64>(fmaf(row[0], row[0], row[1] * row[1]));
-        const Reflector H(alpha, x0, J < n - 2);
+        const Reflector H(alpha, x0, Reflector::limit(J, n));
         {
             constexpr int kBank[4] = {0, 0, 1, 1};
             const int q = kBank[t0];
             const bool here = lane == (J & 63);
             dv[q] = here ? r[q] : dv[q];
             av[q] = here ? alpha : av[q];
-            xv[q] = here ? x0 : xv[q];
         }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) un[q] = H.active ? -(row[q] + (lane + 64 * q == J + 1 ? H.sigma : 0.f)) : 0.f;
+        for (int q = 0; q < 2; ++q) un[q] = lane + 64 * q == J + 1 ? -H.first : -row[q];
         beta = H.beta;
         uJ = H.first;
         const int tile = (J + 1) >> 5, sub = (s + 1) & 3, group = ((J + 1) >> 3) & 3;
@@ -339,13 +313,7 @@ __device__ __forceinline__ void tridiag_strips(const float* const stage, float* 
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int l = lane + 64 * q;
-            if (l < n) {
-                const Reflector H(av[q], xv[q], l < n - 2);    // the same bits as in the loop
-                sd[l] = dv[q];
-                se[l] = H.active ? -H.sigma : xv[q];
-                F.beta[l] = H.beta;
-                F.sigma[l] = H.sigma;
-            }
+            if (l < n) finish_column<128>(R, F, n, l, dv[q], av[q], sd, se);
         }
     }
 }
