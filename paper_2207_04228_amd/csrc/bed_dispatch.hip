@@ -33,6 +33,7 @@ constexpr int kPackedRowsValuesFromBatch = 3072;   // eigenvalues only
 constexpr int kPairUpToBatch = 512;
 constexpr int kLane4FromBatch = 20480;
 constexpr int kLane8FromBatch = 32768;
+constexpr int kLaneBeatsJacobi = 196608;
 
 enum Family { kLaneFamily, kPackedFamily, kWaveFamily, kPairFamily, kBlockFamily, kPackedRowsFamily };
 struct Choice {
@@ -155,6 +156,18 @@ bool divide_and_conquer(const KernelArgs& args, int stage, bool want_v, int forc
     return true;
 }
 
+// Up to 4 rows the same calls take the Jacobi form of the kernel that choose() names, in one launch also for the spectral function
+// with its decomposition.  In very large batches one matrix per lane needs fewer instructions, and for two rows it
+// has a single rotation to do (us per launch, rotations / Jacobi, eigenvectors on, eigenvalues only):
+//   n = 4: batch 65536: 15.4 / 9.6, 11.6 / 7.4   262144: 27.7 / 27.6, 19.4 / 20.4   393216: 35.7 / 37.7, 24.3 / 27.5
+//   n = 3: batch 65536: 11.9 / 7.6, 9.3 / 6.4    n = 2: 65536: 5.1 / 5.0, 4.1 / 4.3
+bool jacobi_form(const KernelArgs& args, int stage, int forced) {
+    if (args.n > 4 || forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
+    if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;
+    if (stage == kSpectral && args.evecs) return true;
+    return args.batch < (args.n > 2 ? kLaneBeatsJacobi : kLane4FromBatch);
+}
+
 }  // namespace
 
 const char* kernel_variant(int batch, int n, bool want_v) { return choose(batch, n, kFull, want_v, kFamilyAuto).name; }
@@ -184,13 +197,14 @@ hipError_t launch(const KernelArgs& args, int stage, bool want_v, hipStream_t st
     if (args.batch == 0) return hipSuccess;
     if (divide_and_conquer(args, stage, want_v, forced))
         return args.n <= 32 ? launch_dc_wave(args, stage, want_v, stream) : launch_dc_block(args, stage, want_v, stream);
-    if (stage == kSpectral && args.evecs) {
+    if (stage == kSpectral && args.evecs && !jacobi_form(args, stage, forced)) {
         // the spectral function and the decomposition it comes from: the rotation kernels keep V on chip
         // for the former or write it for the latter, so a second kernel forms the function
         const hipError_t err = launch(args, kFull, true, stream, forced);
         return err == hipSuccess ? launch_spectral(args, stream) : err;
     }
     const Choice c = choose(args.batch, args.n, stage, want_v, forced);
+    if (jacobi_form(args, stage, forced)) stage = stage == kSpectral ? kJacobiSpectral : kJacobi;
     if (c.family == kPairFamily) {
         if (!want_v || stage != kFull) return hipErrorInvalidValue;     // the pair kernels always form eigenvectors
         return launch_pair(args, stream);

@@ -1,0 +1,194 @@
+// n <= 4: Jacobi's method (two-sided plane rotations of the full matrix, Jacobi 1846) in registers, four lanes per
+// matrix, 16 matrices per wavefront, no LDS.
+//
+// Lane j of four holds column j of A and of V, skewed: register k is row j ^ k.  Step s = 1, 2, 3 of a sweep rotates
+// both pairs (j, j ^ s) at once, so a sweep is three steps without any data movement between them, and
+// everything a step needs sits in a register that the compiler can name: the diagonal in register 0, the pair's entry in register s,
+// the partner's column in lane j ^ s at register k ^ s, the rotation of row j ^ k in lane j ^ k.  All exchanges are DPP quad
+// permutes.
+// For calls that ask nothing of the shifted QR rotations (counts, thresholds, caps); those reduce to a tridiagonal first and pay
+// for the boundary between two iterations more than for the rotations.  Bound by the chain of a step (angle, then two
+// rotations; 4 to 5 sweeps) for small batches, by instruction issue for large ones.  us per launch, rotations / this: 16 matrices of
+// 4x4 5.6 / 4.0, 4096 8.2 / 4.2, 65536 15.4 / 9.6, 262144 27.7 / 27.6; with the spectral function and the decomposition (two
+// launches there) 65536 28.1 / 10.5.  Distance from 64-bit results a quarter to a half of the rotations'.
+// The same with eight lanes for 5 to 8 rows was measured and left out: 42 steps of 110 instructions, 13.3 us at 512 x 8x8
+// (rotations 14.5, of rank 6 11.8), 13.4 at 512 x 6x6 (10.2).
+#ifndef BED_JACOBI_HPP
+#define BED_JACOBI_HPP
+#include "bed_kernel.h"
+
+namespace bed {
+namespace jacobi {
+
+constexpr int G = 4;                  // lanes per matrix
+constexpr int kMaxSweeps = 15;        // more than twice what any matrix has been seen to take
+constexpr float kAngle = 1.2207031e-4f;         // 2^-13: a sweep of rotations below it leaves entries of the square of it
+constexpr float kNegligible = 1.1920929e-7f;    // 2^-23, of the larger diagonal entry of the pair
+constexpr float kNothing = 1.0e-18f;            // of the pre-scaled matrix
+
+// The value of lane (lane ^ S): quad_perm [1,0,3,2], [2,3,0,1] or [3,2,1,0]
+template <int S>
+__device__ __forceinline__ float from_lane_xor(float x) {
+    if constexpr (S == 0) return x;
+    else return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), S == 1 ? 0xB1 : S == 2 ? 0x4E : 0x1B, 0xF, 0xF, false));
+}
+
+__device__ __forceinline__ float group_max(float x) {
+    x = fmaxf(x, from_lane_xor<1>(x));
+    return fmaxf(x, from_lane_xor<2>(x));
+}
+
+template <bool WANT_V, int S>
+struct Step {
+    // x, v: the lane's columns; d: its diagonal entry (x[0] is not used); work: the matrix still iterates; open: a rotation
+    // of this sweep was not negligible
+    static __device__ __forceinline__ void run(float (&x)[G], float (&v)[G], float& d, const bool work, bool& open,
+                                               const float side) {
+        // both lanes of a pair get the same a and c and opposite delta, t and s, to the last bit
+        const float a = 0.5f * (x[S] + from_lane_xor<S>(x[S]));
+        const float dp = from_lane_xor<S>(d);
+        const float delta = (dp - d) + side;                     // side: +-1e-30, the sign where the two are equal
+        const float a2 = a + a;
+        const float h = __builtin_amdgcn_sqrtf(fmaf(delta, delta, fmaf(a2, a2, 1e-36f)));    // never zero
+        float t = a2 * __builtin_amdgcn_rcpf(delta + copysignf(h, delta));
+        open = open || (fabsf(t) > kAngle && fabsf(a) > fmaxf(kNegligible * fmaxf(fabsf(d), fabsf(dp)), kNothing));
+        t = work ? t : 0.f;
+        const float q = fmaf(t, t, 1.f);
+        const float r = __builtin_amdgcn_rsqf(q);
+        const float c = r * fmaf(-0.5f * q * r, r, 1.5f);
+        const float s = t * c;
+        d = fmaf(-t, a, d);
+        // columns
+        float y[G];
+#pragma unroll
+        for (int k = 1; k < G; ++k)
+            if (k != S) y[k] = fmaf(-s, from_lane_xor<S>(x[k ^ S]), c * x[k]);
+        if (WANT_V) {
+            float w[G];
+#pragma unroll
+            for (int k = 0; k < G; ++k) w[k] = fmaf(-s, from_lane_xor<S>(v[k ^ S]), c * v[k]);
+#pragma unroll
+            for (int k = 0; k < G; ++k) v[k] = w[k];
+        }
+        // rows: the one pair (k, k ^ S) without the diagonal; the rotation of row j ^ k is that of lane j ^ k
+        constexpr int K = S == 1 ? 2 : 1, L = K ^ S;
+        const float ck = from_lane_xor<K>(c), sk = from_lane_xor<K>(s);
+        x[K] = fmaf(-sk, y[L], ck * y[K]);
+        x[L] = fmaf(sk, y[K], ck * y[L]);
+        x[S] = work ? 0.f : x[S];
+    }
+};
+
+template <bool WANT_V, int S = 1>
+__device__ __forceinline__ void sweep(float (&x)[G], float (&v)[G], float& d, const bool work, bool& open, const int j) {
+    if constexpr (S < G) {
+        Step<WANT_V, S>::run(x, v, d, work, open, j < (j ^ S) ? 1e-30f : -1e-30f);
+        sweep<WANT_V, S + 1>(x, v, d, work, open, j);
+    }
+}
+
+template <int K = 1>
+__device__ __forceinline__ int rank_of(const float d, const int j) {
+    if constexpr (K == G) return 0;
+    else {
+        const float other = from_lane_xor<K>(d);
+        return ((other < d || (other == d && (j ^ K) < j)) ? 1 : 0) + rank_of<K + 1>(d, j);
+    }
+}
+
+template <int STAGE>
+constexpr bool is_stage = STAGE == kJacobi || STAGE == kJacobiSpectral;
+
+// Workgroups of one wavefront for a batch.
+inline unsigned blocks(int batch) { return (unsigned)(((long long)batch + 64 / G - 1) / (64 / G)); }
+
+// The whole kernel; the entry points are the kernels that the dispatch names.  kJacobiSpectral: V f(max(Lambda, floor)) V^T,
+// and V too where the caller wants it.
+template <bool WANT_V, int STAGE>
+__device__ __forceinline__ void solve(const KernelArgs& args) {
+    constexpr bool SPECTRAL = STAGE == kJacobiSpectral;
+    constexpr int PER = 64 / G;
+    const int lane = threadIdx.x;
+    const int j = lane & (G - 1);
+    const int n = args.n;
+    const long long b = (long long)blockIdx.x * PER + lane / G;
+    const bool mine = b < args.batch && j < n;
+    const size_t at = (size_t)(b < args.batch ? b : args.batch - 1);
+
+    float x[G], v[G];
+    {
+        const float* __restrict__ Ab = args.A + at * n * n;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            const int i = j ^ k;                                 // the lower triangle is read
+            x[k] = (i < n && j < n) ? Ab[max(i, j) * n + min(i, j)] : 0.f;
+        }
+    }
+    float amax = 0.f;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        amax = fmaxf(amax, fabsf(x[k]));
+        bad = bad || !(fabsf(x[k]) < __builtin_inff());
+    }
+    bad = group_max(bad ? 1.f : 0.f) > 0.f;
+    // power-of-two pre-scaling to a largest entry in [0.5, 1)
+    amax = group_max(amax);
+    const int ex = !bad && amax > 0.f ? min(max(__builtin_amdgcn_frexp_expf(amax), -125), 126) : 0;
+    const float scale = ldexpf(1.f, -ex), inv_scale = ldexpf(1.f, ex);
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        x[k] = bad ? 0.f : x[k] * scale;
+        v[k] = k == 0 ? 1.f : 0.f;
+    }
+    float d = x[0];
+
+    // a matrix that is done keeps its bits however long its neighbours in the wavefront take
+    bool work = true;
+    for (int it = 0; it < kMaxSweeps; ++it) {
+        bool open = false;
+        sweep<WANT_V>(x, v, d, work, open, j);
+        work = work && group_max(open ? 1.f : 0.f) > 0.f;
+        if (__ballot(work) == 0) break;
+    }
+
+    const int rank = bad ? j : rank_of(j < n ? d : __builtin_inff(), j);
+    const float lam = bad ? __builtin_nanf("") : d * inv_scale;
+    if (mine) {
+        if (args.evals) args.evals[at * n + rank] = lam;
+        if (args.info && j == 0) args.info[at] = bad ? n : (work ? n - 1 : 0);
+    }
+    if constexpr (WANT_V) {
+        if (bad) {
+#pragma unroll
+            for (int k = 0; k < G; ++k) v[k] = __builtin_nanf("");
+        }
+        if (!SPECTRAL || args.evecs) {
+            float* __restrict__ Vb = args.evecs + at * n * n;
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+                if (mine && (j ^ k) < n) Vb[(j ^ k) * n + rank] = v[k];
+        }
+        if constexpr (SPECTRAL) {
+            const float y = fmaxf(lam, args.fn_floor);
+            const float f = j < n ? ((args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(y) : __builtin_amdgcn_sqrtf(y)) : 0.f;
+            float w[G];
+#pragma unroll
+            for (int k = 0; k < G; ++k) w[k] = f * v[k];
+            // F[j ^ k][j] = sum over columns m of f_m V[j ^ k][m] V[j][m]
+            float* __restrict__ Fb = args.fn_out + at * n * n;
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                float F = w[0] * v[k];
+                F += from_lane_xor<1>(w[1] * v[1 ^ k]);
+                F += from_lane_xor<2>(w[2] * v[2 ^ k]);
+                F += from_lane_xor<3>(w[3] * v[3 ^ k]);
+                if (mine && (j ^ k) < n) Fb[(j ^ k) * n + j] = F;
+            }
+        }
+    }
+}
+
+}  // namespace jacobi
+}  // namespace bed
+#endif

@@ -70,7 +70,8 @@ constexpr int copy_chunk(int elements_per_wavefront) {
 // 1 / x for x an exact power of two in [2^-125, 2^126] (the pre-scaling factors), bit-exact.
 __device__ __forceinline__ float pow2_reciprocal(float x) { return __uint_as_float(0x7F000000u - __float_as_uint(x)); }
 
-enum Stage { kFull = 0, kTridiagOnly = 1, kQrOnly = 2, kSpectral = 3, kQrPartial = 4 };
+// kJacobi, kJacobiSpectral: kFull and kSpectral by Jacobi's method (n <= 4, bed_jacobi.hpp)
+enum Stage { kFull = 0, kTridiagOnly = 1, kQrOnly = 2, kSpectral = 3, kQrPartial = 4, kJacobi = 5, kJacobiSpectral = 6 };
 enum SpectralFn { kFnSqrt = 0, kFnInvSqrt = 1 };
 
 struct KernelArgs {

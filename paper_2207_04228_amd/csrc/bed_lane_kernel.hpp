@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bed_jacobi.hpp"
 #include "bed_kernel.h"
 
 namespace bed {
@@ -51,6 +52,10 @@ __device__ __forceinline__ uint32_t sort_key(float x) {
 // B.1-B.3: formed in registers from V and lambda, eigenvectors never written).
 template <int N, bool WANT_V, int STAGE>
 __global__ __launch_bounds__(64) void lane_kernel(KernelArgs args) {
+    if constexpr (jacobi::is_stage<STAGE>) {
+        jacobi::solve<WANT_V, STAGE>(args);
+        return;
+    }
     using namespace lanek;
     constexpr int NN = N * N;
     constexpr int MS = NN + 1;                 // staging stride per matrix (odd: conflict-free per-lane reads)
@@ -396,6 +401,13 @@ __global__ __launch_bounds__(64) void lane_kernel(KernelArgs args) {
 
 template <int N>
 static hipError_t launch_lane_n(const KernelArgs& args, int stage, bool want_v, hipStream_t stream) {
+    if constexpr (N == 4) {
+        const unsigned jblocks = jacobi::blocks(args.batch);
+        if (stage == kJacobiSpectral) return enqueue(lane_kernel<N, true, kJacobiSpectral>, dim3(jblocks), dim3(64), stream, args);
+        if (stage == kJacobi)
+            return want_v ? enqueue(lane_kernel<N, true, kJacobi>, dim3(jblocks), dim3(64), stream, args)
+                          : enqueue(lane_kernel<N, false, kJacobi>, dim3(jblocks), dim3(64), stream, args);
+    }
     const unsigned blocks = (unsigned)((args.batch + 63) / 64);
     if (stage == kSpectral) return enqueue(lane_kernel<N, true, kSpectral>, dim3(blocks), dim3(64), stream, args);
     if (want_v) return enqueue(lane_kernel<N, true, kFull>, dim3(blocks), dim3(64), stream, args);

@@ -28,6 +28,7 @@
 
 #include <type_traits>
 
+#include "bed_jacobi.hpp"
 #include "bed_kernel.h"
 
 namespace bed {
@@ -191,6 +192,10 @@ __device__ __forceinline__ void chain_rotate(Chain& S, float ek, float dk1, floa
 // Sec. 4.2-4.4 / App. B.1-B.3, eigenvectors never written).
 template <int GW, int N, bool WANT_V, int STAGE>
 __global__ __launch_bounds__(64) void packed_kernel(KernelArgs args) {
+    if constexpr (jacobi::is_stage<STAGE>) {
+        jacobi::solve<WANT_V, STAGE>(args);
+        return;
+    }
     using namespace packed;
     using G = Group<GW>;
     static_assert(N <= GW, "a matrix must fit its group of lanes");
@@ -594,6 +599,13 @@ template <int GW, int N>
 static hipError_t launch_packed_n(const KernelArgs& args, int stage, bool want_v, hipStream_t stream) {
     constexpr int per_wave = 64 / GW;
     const unsigned blocks = (unsigned)((args.batch + per_wave - 1) / per_wave);
+    if constexpr (N == 4) {
+        const unsigned jblocks = jacobi::blocks(args.batch);
+        if (stage == kJacobiSpectral) return enqueue(packed_kernel<GW, N, true, kJacobiSpectral>, dim3(jblocks), dim3(64), stream, args);
+        if (stage == kJacobi)
+            return want_v ? enqueue(packed_kernel<GW, N, true, kJacobi>, dim3(jblocks), dim3(64), stream, args)
+                          : enqueue(packed_kernel<GW, N, false, kJacobi>, dim3(jblocks), dim3(64), stream, args);
+    }
     if (stage == kSpectral)
         return enqueue(packed_kernel<GW, N, true, kSpectral>, dim3(blocks), dim3(64), stream, args);
     if (want_v) return enqueue(packed_kernel<GW, N, true, kFull>, dim3(blocks), dim3(64), stream, args);

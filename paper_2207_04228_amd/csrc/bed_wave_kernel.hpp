@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bed_jacobi.hpp"
 #include "bed_kernel.h"
 
 namespace bed {
@@ -756,6 +757,10 @@ __device__ __forceinline__ void tridiag_values(const float* __restrict__ Ab, con
 // ---------------------------------------------------------------------------
 template <int N, bool WANT_V, int STAGE>
 __global__ __launch_bounds__(64) void wave_kernel(KernelArgs args) {
+    if constexpr (jacobi::is_stage<STAGE>) {
+        jacobi::solve<WANT_V, STAGE>(args);
+        return;
+    }
     constexpr int W = lanes_for(N);
     // When the rows fit in half a wavefront (N <= 32), lane 32 + r works on the same row r as
     // lane r from load to store: in the tridiagonalisation the upper half holds the rows of P
@@ -1051,6 +1056,13 @@ static hipError_t launch_one(const KernelArgs& args, hipStream_t stream) {
 
 template <int N>
 static hipError_t launch_n(const KernelArgs& args, int stage, bool want_v, hipStream_t stream) {
+    if constexpr (N == 4) {
+        const unsigned jblocks = jacobi::blocks(args.batch);
+        if (stage == kJacobiSpectral) return enqueue(wave_kernel<N, true, kJacobiSpectral>, dim3(jblocks), dim3(64), stream, args);
+        if (stage == kJacobi)
+            return want_v ? enqueue(wave_kernel<N, true, kJacobi>, dim3(jblocks), dim3(64), stream, args)
+                          : enqueue(wave_kernel<N, false, kJacobi>, dim3(jblocks), dim3(64), stream, args);
+    }
     if (stage == kTridiagOnly) {
         return want_v ? launch_one<N, true, kTridiagOnly>(args, stream)
                       : launch_one<N, false, kTridiagOnly>(args, stream);

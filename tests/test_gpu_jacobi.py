@@ -1,0 +1,68 @@
+"""Jacobi's method for n <= 4: sizes below the four lanes, wavefronts that are not full, equal and opposite diagonal entries,
+clusters, scales, non-finite entries, the switch to one matrix per lane.  Same bars as the rotation kernels."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _check, _solve_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _structured(n):
+    one = np.eye(n, k=1) + np.eye(n, k=-1)
+    x = np.arange(1.0, n + 1.0)
+    mats = [np.zeros((n, n)), np.eye(n), -np.eye(n), np.ones((n, n)), one, np.eye(n) + 1e-7 * one, np.diag(10.0 ** -np.arange(0, 4 * n, 4)),
+            np.diag(10.0 ** -np.arange(0, 4 * n, 4)) + 1e-9 * one, np.outer(x, x) - 3.0 * np.eye(n), np.fliplr(np.diag(x)),
+            1e-30 * (np.diag(x) + one), 1e30 * (np.diag(x) + one)]
+    return np.stack(mats).astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+def test_decomposition_function_and_values(n):
+    import torch
+    from oracle import spectral
+    from paper_2207_04228_amd import binding, workloads
+    for batch in (1, 15, 16, 17, 1000, 20479):
+        A = workloads.covariance(batch, n, 4 * n, 1e-4, 7100 + n)
+        _check(A, f"covariances, n={n}, batch {batch}")
+        lam, V = _solve_gpu(A)
+        assert np.array_equal(_solve_gpu(A, want_vectors=False)[0], lam)
+        out, ev, evecs = (t.cpu().numpy() for t in binding.bed_spd_fn_eigh(torch.from_numpy(A).cuda(), binding.BED_FN_SQRT, 1e-6))
+        assert np.array_equal(ev, lam) and np.array_equal(evecs, V)
+        assert np.array_equal(binding.bed_spd_fn(torch.from_numpy(A).cuda(), binding.BED_FN_SQRT, 1e-6)[0].cpu().numpy(), out)
+        F = spectral.spd_fn(A, spectral.FN_SQRT, 1e-6)
+        # r (1 + sqrt(cond) / 2) for a backward error of r = 1e-6 n, capped by sqrt(r) (see test_gpu_spd_fn)
+        assert np.abs(out - F).max() <= np.sqrt(1e-6 * n) * np.abs(F).max()
+    for A in (_structured(n), np.tile(_structured(n), (7, 1, 1))):
+        _check(A, f"structured, n={n}, batch {A.shape[0]}")
+
+
+@pytest.mark.parametrize("n", [3, 4])
+def test_both_sides_of_the_switch_to_one_matrix_per_lane(n):
+    from paper_2207_04228_amd import workloads
+    A = workloads.covariance(64, n, 4 * n, 1e-4, 7200 + n)
+    small = _solve_gpu(A)[0]
+    for batch in (196607, 196608):
+        lam, V = _solve_gpu(np.tile(A, (batch // 64 + 1, 1, 1))[:batch])
+        want = np.tile(small, (batch // 64 + 1, 1))[:batch]
+        assert np.abs(lam - want).max() <= 1e-5 * np.abs(small).max()
+        assert batch >= 196608 or np.array_equal(lam, want)         # whoever shares the wavefront, the same bits
+
+
+def test_non_finite_entries_stay_with_their_matrix():
+    import torch
+    from paper_2207_04228_amd import binding, workloads
+    for n in (2, 3, 4):
+        A = workloads.covariance(40, n, 4 * n, 1e-4, 7300 + n)
+        good, Vg = _solve_gpu(A)
+        B = A.copy()
+        B[3, n - 1, 0] = np.nan
+        B[17, 0, 0] = np.inf
+        B[18, n - 1, n - 1] = -np.inf
+        B[19, 0, n - 1] = np.nan                    # the upper triangle is not read
+        At = torch.from_numpy(B).cuda()
+        lam, V, info, _ = binding.bed_syevd_info(At, want_rotations=False)
+        lam, V, info = lam.cpu().numpy(), V.cpu().numpy(), info.cpu().numpy()
+        keep = [b for b in range(40) if b not in (3, 17, 18)]
+        assert np.array_equal(lam[keep], good[keep]) and np.array_equal(V[keep], Vg[keep]) and (info[keep] == 0).all()
+        assert np.isnan(lam[[3, 17, 18]]).all() and np.isnan(V[[3, 17, 18]]).all() and (info[[3, 17, 18]] == n).all()
