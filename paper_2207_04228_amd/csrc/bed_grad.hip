@@ -10,13 +10,10 @@
 // differences of f in place of K:
 //   g_A = V ( Phi o (V^T sym(G) V) ) V^T.
 //
-// One wavefront owns one matrix (four wavefronts for n > 32, eight for n > 64).
-// The three (four) n x n x n products are dense
-// contractions and run on v_mfma_f32_32x32x2_f32 (full fp32 operands and
-// accumulation); operands are staged in LDS with an odd row stride so that row
-// and column (transposed) operand reads are both conflict-free, and every
-// product's result is written back to LDS in row-major order to become an
-// operand of the next one.
+// The three (four) n x n x n products are dense contractions and run on the fp32 matrix instructions (full fp32
+// operands and accumulation).  Up to 32 rows one wavefront owns a matrix (or several) and every intermediate product
+// stays in the accumulators (tile_grad_kernel); beyond, four or eight wavefronts exchange them through LDS
+// (grad_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,6 +24,7 @@ namespace bed {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
@@ -105,25 +103,37 @@ __device__ __forceinline__ float reciprocal(float x) {
     return fmaf(fmaf(-x, r, 1.f), r, r);
 }
 
-// Coupling of the pair (a, b) = (lambda_i, lambda_j), i != j; ra, rb their reciprocals.
-__device__ __forceinline__ float coupling(float a, float b, float ra, float rb, bool j_later, int mode, int degree,
-                                          float gap_floor) {
+// Couplings K of the pairs (a_v, b) = (lambda_i, lambda_j), i != j; ra, rb their reciprocals.  Exact with a gap floor, or the
+// truncated series: with b the larger in magnitude, 1/(b - a) ~ (1/b) sum_{k<=degree} (a/b)^k; mirrored otherwise.  Equal
+// magnitudes: the later index counts as the larger (later(v): is it j's?), which keeps K antisymmetric.  The
+// recurrences of all V pairs run side by side: one after the other they took 2.3 us of a 10 us call (16 pairs a lane).
+template <int V, typename Later>
+__device__ __forceinline__ void couplings(float (&K)[V], const float (&a)[V], const float b, const float (&ra)[V], const float rb,
+                                          Later&& later, int mode, int degree, float gap_floor) {
     if (mode == kGradExact) {
-        const float d = b - a;
-        return (fabsf(d) >= gap_floor && d != 0.f) ? 1.0f / d : 0.f;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const float d = b - a[v];
+            K[v] = (fabsf(d) >= gap_floor && d != 0.f) ? 1.0f / d : 0.f;
+        }
+        return;
     }
-    // truncated series: with b the larger in magnitude, 1/(b - a) ~ (1/b) sum_{k<=degree} (a/b)^k;
-    // mirrored otherwise.  Equal magnitudes: the later index counts as the larger, which keeps
-    // K antisymmetric.
-    const bool big_b = fabsf(b) > fabsf(a) || (fabsf(b) == fabsf(a) && j_later);
-    const float num = big_b ? a : b, den = big_b ? b : a;
-    if (den == 0.f) return 0.f;
-    const float rden = big_b ? rb : ra;
-    const float rho = num * rden;
-    float s = 1.f;
-    for (int k = 0; k < degree; ++k) s = fmaf(s, rho, 1.f);
-    const float kk = s * rden;
-    return big_b ? kk : -kk;
+    float rho[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const bool big_b = fabsf(b) > fabsf(a[v]) || (fabsf(b) == fabsf(a[v]) && later(v));
+        rho[v] = big_b ? a[v] * rb : b * ra[v];
+        K[v] = 1.f;
+    }
+    for (int k = 0; k < degree; ++k)
+#pragma unroll
+        for (int v = 0; v < V; ++v) K[v] = fmaf(K[v], rho[v], 1.f);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const bool big_b = fabsf(b) > fabsf(a[v]) || (fabsf(b) == fabsf(a[v]) && later(v));
+        const float kk = big_b ? K[v] * rb : -(K[v] * ra[v]);
+        K[v] = (big_b ? b : a[v]) == 0.f ? 0.f : kk;
+    }
 }
 
 // Divided difference of f~(x) = f(max(x, floor)) at (lambda_i, lambda_j); the derivative when they coincide.
@@ -139,19 +149,240 @@ __device__ __forceinline__ float divided_difference(float li, float lj, int mode
     return phi;
 }
 
-// NT tiles of 32 per side (1: n <= 32, 2: n <= 64, 4: n <= 128); NWV wavefronts per matrix.
-// PB > 0 (n <= PB <= 16, NT = NWV = 1): 32 / PB matrices share the wavefront as the diagonal
-// blocks of one 32 x 32 operand; products of block-diagonal matrices are block diagonal, so
-// the same instruction stream serves all of them.
+// ---- n <= 32: everything in registers ----
+// Tiles of TS x TS on v_mfma_f32_32x32x2, 16x16x4 and 4x4x1 (16 blocks).  Lane l holds, in register v, the entry of row
+// Tile::row(v, l) and column l % TS of a result; taken as it stands that is also a right operand (rows as the contracted
+// index) and, for a symmetric matrix, a left one, as long as the other operand names its entries in the same
+// order.  So with V by columns, vc[v] = V[row(v)][lo], and by rows, vr[v] = V[lo][row(v)],
+//   C = V^T (sym(G) V):  T = mfma(gs, vc), C = mfma(vc, T);     C - C^T = V^T g_V - g_V^T V:  mfma(vc, gc), mfma(-gc, vc)
+//   g_A = V (M V^T):     W = mfma(M, vr), g_A = mfma(vr, W)
+// need no exchange at all; LDS only turns V (and G, for its symmetric part) once.
+// Bound by the launch and one pass through the chain of products for small batches, by memory (three matrices) and the
+// matrix cores for large ones.  us per launch of the spectral function's gradient, with every product through LDS (four and two
+// matrices of up to 8 and 16 rows in a 32 x 32 tile) / this: 512 x 16x16 7.7 / 4.1 (4.0 is an empty launch), 512 x 32x32 8.8 / 5.7,
+// 65536 x 4x4 33 / 4.6, 65536 x 16x16 120 / 36, 4096 x 24x24 16.6 / 13.2, 16384 x 32x32 70 / 49 (its bytes take 39 at the copy
+// rate).  Four wavefronts on a SIMD are asked for: with three, 4096 x 27x27 took 19.8 instead of 15.6.
+template <int TS>
+struct Tile;
+template <>
+struct Tile<32> {
+    using acc = floatx16;
+    static constexpr int regs = 16;
+    static __device__ __forceinline__ int row(int v, int lane) { return acc_row(v, lane); }
+    static __device__ __forceinline__ acc mfma(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+};
+template <>
+struct Tile<16> {
+    using acc = floatx4;
+    static constexpr int regs = 4;
+    static __device__ __forceinline__ int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+    static __device__ __forceinline__ acc mfma(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+// sixteen matrices of 4 x 4: lanes 4 m .. 4 m + 3 hold the columns of matrix m
+template <>
+struct Tile<4> {
+    using acc = floatx4;
+    static constexpr int regs = 4;
+    static __device__ __forceinline__ int row(int v, int) { return v; }
+    static __device__ __forceinline__ acc mfma(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
+};
+
+// One wavefront's matrices.  PB = 8 (TS = 16): two matrices of n <= 8 as the diagonal blocks of one tile.  N < TS: registers
+// that only hold rows from N on stay out (R of them are in use).
+template <int TS, int PB, int N = TS>
+struct Lanes {
+    using T = Tile<TS>;
+    static constexpr int R = TS == 32 ? (N + 7) / 8 * 4 : T::regs;
+    static constexpr int kMatrices = TS == 4 ? 16 : PB ? TS / PB : 1;
+    static constexpr int kPositions = TS == 4 ? 64 : TS;       // columns of all tiles
+    static constexpr int kStride = TS + 4;                      // of a row in LDS (128-bit reads of rows)
+    int lane, lo, first, count, n;
+    __device__ __forceinline__ Lanes(int batch, int n_)
+        : lane(threadIdx.x), lo(threadIdx.x % TS), first(blockIdx.x * kMatrices), count(min(kMatrices, batch - first)), n(n_) {}
+    __device__ __forceinline__ int matrix_of(int position) const { return PB ? position / (PB ? PB : 1) : 0; }
+    __device__ __forceinline__ int index_of(int position) const { return PB ? position % (PB ? PB : 1) : position; }
+    __device__ __forceinline__ int matrix() const { return TS == 4 ? lane / 4 : matrix_of(lo); }
+    // is register v an entry of a matrix?
+    __device__ __forceinline__ bool inside(int v) const {
+        const int r = T::row(v, lane);
+        return (TS == 4 || matrix_of(r) == matrix_of(lo)) && matrix() < count && index_of(r) < n && index_of(lo) < n;
+    }
+    // every register of every lane is one (the same in all lanes)
+    __device__ __forceinline__ bool full() const { return PB == 0 && N == TS && n == TS && count == kMatrices; }
+    // its place in bytes, counted from this wavefront's first matrix (at most 64 KB on)
+    __device__ __forceinline__ unsigned offset(int v) const {
+        return 4u * (unsigned)(matrix() * n * n + index_of(T::row(v, lane)) * n + index_of(lo));
+    }
+    // this lane's entries of a matrix in memory, zero outside; all loads go out before the first is used
+    __device__ __forceinline__ void load(float (&x)[R], const float* __restrict__ M) const {
+        const char* const base = reinterpret_cast<const char*>(M + (size_t)first * n * n);
+        if (full()) {
+#pragma unroll
+            for (int v = 0; v < R; ++v) x[v] = *reinterpret_cast<const float*>(base + 4u * (unsigned)(matrix() * TS * TS + T::row(v, lane) * TS + lo));
+        } else {
+            const unsigned last = 4u * (unsigned)(count * n * n - 1);
+#pragma unroll
+            for (int v = 0; v < R; ++v) x[v] = *reinterpret_cast<const float*>(base + min(offset(v), last));
+#pragma unroll
+            for (int v = 0; v < R; ++v) x[v] = inside(v) ? x[v] : 0.f;
+        }
+    }
+    __device__ __forceinline__ void store(float* __restrict__ M, const typename T::acc& x) const {
+        char* const base = reinterpret_cast<char*>(M + (size_t)first * n * n);
+        if (full()) {
+#pragma unroll
+            for (int v = 0; v < R; ++v) *reinterpret_cast<float*>(base + 4u * (unsigned)(matrix() * TS * TS + T::row(v, lane) * TS + lo)) = x[v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < R; ++v)
+                if (inside(v)) *reinterpret_cast<float*>(base + offset(v)) = x[v];
+        }
+    }
+    // x[v] = X[row(v)][lo] -> y[v] = X[lo][row(v)]
+    __device__ __forceinline__ void transpose(float (&y)[R], const float (&x)[R], float* const S) const {
+        float* const own = S + (TS == 4 ? (lane / 4) * 20 : 0);
+        constexpr int LD = TS == 4 ? 4 : kStride;
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < R; ++v) own[T::row(v, lane) * LD + lo] = x[v];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < R; q += 4) {
+            const floatx4 t = *reinterpret_cast<const floatx4*>(own + lo * LD + T::row(q, lane));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[q + k] = t[k];
+        }
+    }
+    static constexpr int kBuffer = TS == 4 ? 16 * 20 : TS * kStride;
+    // entries of a vector in LDS (one per position) at the rows of this lane's registers
+    __device__ __forceinline__ void rows_of(float (&y)[R], const float* const S) const {
+        const float* const own = S + (TS == 4 ? 4 * (lane / 4) : 0);
+#pragma unroll
+        for (int q = 0; q < R; q += 4) {
+            const floatx4 t = *reinterpret_cast<const floatx4*>(own + T::row(q, lane));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[q + k] = t[k];
+        }
+    }
+    // position of a vector entry (lane < kPositions) -> its place in memory, or not one
+    __device__ __forceinline__ bool vector_inside() const {
+        return lane < kPositions && (TS == 4 ? lane / 4 : matrix_of(lane)) < count && index_of(TS == 4 ? lane % 4 : lane) < n;
+    }
+    __device__ __forceinline__ size_t vector_offset() const {
+        return (size_t)(first + (TS == 4 ? lane / 4 : matrix_of(lane))) * n + index_of(TS == 4 ? lane % 4 : lane);
+    }
+    __device__ __forceinline__ int own_position() const { return TS == 4 ? lane : lo; }
+};
+
+template <int TS, int PB, int N = TS>
+__global__ __launch_bounds__(64, 4) void tile_grad_kernel(GradArgs args) {
+    using L = Lanes<TS, PB, N>;
+    using T = Tile<TS>;
+    constexpr int R = L::R;
+    __shared__ __align__(16) float buffer[L::kBuffer];
+    __shared__ __align__(16) float sL[L::kPositions];     // eigenvalues
+    __shared__ __align__(16) float sR[L::kPositions];     // their reciprocals; for a spectral function sqrt(max(lambda, floor))
+    __shared__ __align__(16) float sGl[L::kPositions];    // upstream gradient of the eigenvalues
+    const L own(args.batch, args.n);
+    const bool ed = (args.mode == kGradExact || args.mode == kGradTaylor);
+
+    float vc[R], gc[R];
+    own.load(vc, args.evecs);
+    if (args.g_mat) own.load(gc, args.g_mat);             // the same in all lanes
+    bool low = false;                                      // an eigenvalue below the floor
+    if (own.lane < L::kPositions) {
+        const bool ok = own.vector_inside();
+        const float l = ok ? args.evals[own.vector_offset()] : 0.f;
+        sL[own.lane] = l;
+        sR[own.lane] = ed ? (l != 0.f ? 1.0f / l : 0.f) : sqrtf(fmaxf(l, args.param));
+        sGl[own.lane] = (ok && args.g_evals) ? args.g_evals[own.vector_offset()] : 0.f;
+        low = ok && !(l >= args.param);
+    }
+    low = __ballot(low) != 0;
+
+    typename T::acc c{};
+    if (ed) {
+        if (args.g_mat) {
+#pragma unroll
+            for (int v = 0; v < R; ++v) c = T::mfma(vc[v], gc[v], c);
+#pragma unroll
+            for (int v = 0; v < R; ++v) c = T::mfma(-gc[v], vc[v], c);
+        }
+    } else {
+        float gr[R];
+        own.transpose(gr, gc, buffer);
+        typename T::acc t{};
+#pragma unroll
+        for (int v = 0; v < R; ++v) t = T::mfma(0.5f * (gc[v] + gr[v]), vc[v], t);
+#pragma unroll
+        for (int v = 0; v < R; ++v) c = T::mfma(vc[v], t[v], c);
+    }
+    float vr[R];
+    own.transpose(vr, vc, buffer);                         // and makes sL, sR, sGl visible
+    float li[R], ri[R];
+    own.rows_of(li, sL);
+    own.rows_of(ri, sR);
+    const int jp = own.own_position();
+    const float lj = sL[jp], rj = sR[jp];
+    float m[R];
+    if (ed) {
+        couplings(m, li, lj, ri, rj, [&](int v) { return own.lo > T::row(v, own.lane); }, args.mode, args.degree, args.param);
+#pragma unroll
+        for (int v = 0; v < R; ++v) m[v] = T::row(v, own.lane) == own.lo ? sGl[jp] : 0.5f * m[v] * c[v];
+    } else if (low) {
+#pragma unroll
+        for (int v = 0; v < R; ++v) m[v] = divided_difference(li[v], lj, args.mode, args.param) * c[v];
+    } else {
+        // every eigenvalue at or above the floor: the form without cancellation, from the roots
+#pragma unroll
+        for (int v = 0; v < R; ++v)
+            m[v] = ((args.mode == kGradSqrt) ? reciprocal(ri[v] + rj) : -reciprocal(ri[v] * rj * (ri[v] + rj))) * c[v];
+    }
+#pragma unroll
+    for (int v = 0; v < R; ++v) m[v] = own.inside(v) ? m[v] : 0.f;
+    typename T::acc w{}, g{};
+#pragma unroll
+    for (int v = 0; v < R; ++v) w = T::mfma(m[v], vr[v], w);
+#pragma unroll
+    for (int v = 0; v < R; ++v) g = T::mfma(vr[v], w[v], g);
+    own.store(args.g_A, g);
+}
+
+// F = V f(max(Lambda, floor)) V^T from a decomposition in memory, 4 < n <= 32, the same way (up to 4 rows the decomposition forms it).
+template <int TS, int PB>
+__global__ __launch_bounds__(64) void tile_spectral_kernel(KernelArgs args) {
+    using L = Lanes<TS, PB>;
+    using T = Tile<TS>;
+    constexpr int R = T::regs;
+    __shared__ __align__(16) float buffer[L::kBuffer];
+    __shared__ __align__(16) float sf[L::kPositions];
+    const L own(args.batch, args.n);
+    float vc[R], vr[R], f[R];
+    own.load(vc, args.evecs);
+    if (own.lane < L::kPositions) {
+        const bool ok = own.vector_inside();
+        const float x = fmaxf(ok ? args.evals[own.vector_offset()] : 0.f, args.fn_floor);
+        sf[own.lane] = ok ? ((args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x)) : 0.f;
+    }
+    own.transpose(vr, vc, buffer);
+    own.rows_of(f, sf);
+    typename T::acc F{};
+#pragma unroll
+    for (int v = 0; v < R; ++v) F = T::mfma(vr[v] * f[v], vr[v], F);
+    own.store(args.fn_out, F);
+}
+
+// ---- n > 32 ----
+// NT tiles of 32 per side (2: n <= 64, 4: n <= 128); NWV wavefronts per matrix.  Operands are staged in LDS with an odd
+// row stride so that row and column (transposed) operand reads are both conflict-free, and every product's result is
+// written back to LDS in row-major order to become an operand of the next one.
 // The floor of a large batch is the matrix cores' fp32 rate (n = 128: 16 tiles x 64 steps x 64 cycles x 4
 // products on four of them = 27 us a matrix and compute unit); a small one is bound by the
 // serial path of loads, four products and the exchange between them, which is why operands are read four steps
 // ahead, the inputs eight loads at a time, and a matrix of n > 32 gets four or eight wavefronts.
-template <int NT, int NWV, int PB>
+template <int NT, int NWV>
 __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
-    static_assert(PB == 0 || (NT == 1 && NWV == 1 && 32 % PB == 0), "packing needs one 32 x 32 tile");
     using Own = Tiles<NT, NWV>;
-    constexpr int NMAT = PB ? 32 / PB : 1;       // matrices per workgroup
     constexpr int NP = 32 * NT;
     constexpr int LD = NP + 1;
     constexpr int TI = Own::TI, TJ = Own::TJ;
@@ -165,19 +396,11 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const Own own{tid >> 6};
-    const int b = blockIdx.x * NMAT;           // first matrix of this workgroup
-    const int count = min(NMAT, args.batch - b);
+    const int b = blockIdx.x;
     const int n = args.n;
-    const int kdim = PB ? 32 : ((n + 7) & ~7);
+    const int kdim = (n + 7) & ~7;
     const bool ed = (args.mode == kGradExact || args.mode == kGradTaylor);
-    // position p of the (padded) operand -> matrix p / PB, local index p % PB
-    auto blk = [](int p) { return PB ? p / (PB ? PB : 1) : 0; };
-    auto loc = [](int p) { return PB ? p % (PB ? PB : 1) : p; };
-    // LDS written by one wavefront and read by another needs a workgroup barrier
-    auto sync = [&]() {
-        if (NWV == 1) wave_sync();
-        else __syncthreads();
-    };
+    auto sync = []() { __syncthreads(); };
 
     {
         const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -188,8 +411,8 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
     }
     bool low = false;                  // an eigenvalue below the floor
     if (tid < NP) {
-        const bool ok = blk(tid) < count && loc(tid) < n;
-        const size_t at = (size_t)(b + blk(tid)) * n + loc(tid);
+        const bool ok = tid < n;
+        const size_t at = (size_t)b * n + tid;
         const float l = ok ? args.evals[at] : 0.f;
         sL[tid] = l;
         sR[tid] = ed ? (l != 0.f ? 1.0f / l : 0.f) : sqrtf(fmaxf(l, args.param));
@@ -198,12 +421,10 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
     }
     sync();
     {
-        // the workgroup's matrices are contiguous in memory: one coalesced pass over all of them
         const float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
         const float* __restrict__ Gb = args.g_mat ? args.g_mat + (size_t)b * n * n : nullptr;
         const float rcp_n = 1.0f / (float)n;
-        const float rcp_nn = rcp_n * rcp_n;
-        const int total = count * n * n;
+        const int total = n * n;
         for (int base = tid; base < total; base += 8 * NTH) {
             float v[8], g[8];
 #pragma unroll
@@ -215,10 +436,8 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int idx = base + k * NTH;
-                const int m = PB ? (int)(((float)idx + 0.5f) * rcp_nn) : 0;
-                const int r = idx - m * n * n;
-                const int i = (int)(((float)r + 0.5f) * rcp_n);
-                const int at = (m * PB + i) * LD + m * PB + r - i * n;
+                const int i = (int)(((float)idx + 0.5f) * rcp_n);
+                const int at = i * LD + idx - i * n;
                 if (idx < total) {
                     sV[at] = v[k];
                     sW[at] = g[k];
@@ -226,12 +445,7 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
             }
         }
     }
-    if (NWV == 1) {
-        low = __ballot(low) != 0;
-        sync();
-    } else {
-        low = __syncthreads_or(low);
-    }
+    low = __syncthreads_or(low);
 
     floatx16 acc[TI][TJ];
     if (!ed) {
@@ -253,25 +467,30 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
         for (int tj = 0; tj < TJ; ++tj) {
             const int j = 32 * own.col(tj) + (lane & 31);
             const float lj = sL[j], rj = sR[j];
+            float li[16], ri[16], m[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int i = 32 * own.row(ti) + acc_row(v, lane);
+                li[v] = sL[i];
+                ri[v] = sR[i];
+            }
+            if (ed)
+                couplings(m, li, lj, ri, rj, [&](int v) { return j > 32 * own.row(ti) + acc_row(v, lane); }, args.mode, args.degree, args.param);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int i = 32 * own.row(ti) + acc_row(v, lane);
                 const float cij = acc[ti][tj][v];
                 const float cji = sW[j * LD + i];
-                const float li = sL[i], ri = sR[i];
-                float m;
                 if (ed) {
-                    m = (i == j) ? sGl[i]
-                                 : 0.5f * coupling(li, lj, ri, rj, j > i, args.mode, args.degree, args.param) * (cij - cji);
+                    m[v] = (i == j) ? sGl[i] : 0.5f * m[v] * (cij - cji);
                 } else if (low) {
-                    m = 0.5f * divided_difference(li, lj, args.mode, args.param) * (cij + cji);
+                    m[v] = 0.5f * divided_difference(li[v], lj, args.mode, args.param) * (cij + cji);
                 } else {
                     // every eigenvalue at or above the floor: the form without cancellation, from the roots
-                    const float phi = (args.mode == kGradSqrt) ? reciprocal(ri + rj) : -reciprocal(ri * rj * (ri + rj));
-                    m = 0.5f * phi * (cij + cji);
+                    const float phi = (args.mode == kGradSqrt) ? reciprocal(ri[v] + rj) : -reciprocal(ri[v] * rj * (ri[v] + rj));
+                    m[v] = 0.5f * phi * (cij + cji);
                 }
-                const bool inside = blk(i) == blk(j) && blk(i) < count && loc(i) < n && loc(j) < n;
-                acc[ti][tj][v] = inside ? m : 0.f;
+                acc[ti][tj][v] = i < n && j < n ? m[v] : 0.f;
             }
         }
     sync();
@@ -293,57 +512,41 @@ __global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
             for (int v = 0; v < 16; ++v) {
                 const int i = 32 * own.row(ti) + acc_row(v, lane);
                 const int j = 32 * own.col(tj) + (lane & 31);
-                const bool inside = blk(i) == blk(j) && blk(i) < count && loc(i) < n && loc(j) < n;
-                if (inside) Ob[(size_t)blk(i) * n * n + loc(i) * n + loc(j)] = acc[ti][tj][v];
+                if (i < n && j < n) Ob[i * n + j] = acc[ti][tj][v];
             }
 }
 
-// F = V f(max(Lambda, floor)) V^T from a decomposition in memory, n <= 64 (larger n forms F in the kernel
-// that decomposes).  Same tiles and packing as grad_kernel; one product, so the call is bound by its
-// launch for small batches and by reading V and writing F for large ones.
-template <int NT, int PB>
+// The same for 32 < n <= 64 (larger n forms F in the kernel that decomposes), one wavefront per matrix.
 __global__ __launch_bounds__(64) void spectral_kernel(KernelArgs args) {
-    static_assert(PB == 0 || (NT == 1 && 32 % PB == 0), "packing needs one 32 x 32 tile");
-    constexpr int NMAT = PB ? 32 / PB : 1;
-    constexpr int NP = 32 * NT, LD = NP + 1;
+    constexpr int NT = 2, NP = 32 * NT, LD = NP + 1;
     __shared__ float sV[NP * LD];
     __shared__ float sW[NP * LD];      // V f
     __shared__ float sf[NP];
     const int lane = threadIdx.x;
-    const int b = blockIdx.x * NMAT;
-    const int count = min(NMAT, args.batch - b);
+    const int b = blockIdx.x;
     const int n = args.n;
-    auto blk = [](int p) { return PB ? p / (PB ? PB : 1) : 0; };
-    auto loc = [](int p) { return PB ? p % (PB ? PB : 1) : p; };
     for (int idx = lane; idx < NP * LD; idx += 64) {
         sV[idx] = 0.f;
         sW[idx] = 0.f;
     }
-    if (lane < NP) {
-        float f = 0.f;
-        if (blk(lane) < count && loc(lane) < n) {
-            const float x = fmaxf(args.evals[(size_t)(b + blk(lane)) * n + loc(lane)], args.fn_floor);
-            f = (args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x);
-        }
-        sf[lane] = f;
+    {
+        const float x = fmaxf(lane < n ? args.evals[(size_t)b * n + lane] : 0.f, args.fn_floor);
+        sf[lane] = lane < n ? ((args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x)) : 0.f;
     }
     wave_sync();
     const float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
     const float rcp_n = 1.0f / (float)n;
-    const float rcp_nn = rcp_n * rcp_n;
     chunked_copy<8>(
-        count * n * n, lane, [&](int idx) { return Vb[idx]; },
+        n * n, lane, [&](int idx) { return Vb[idx]; },
         [&](int idx, float x) {
-            const int m = PB ? (int)(((float)idx + 0.5f) * rcp_nn) : 0;
-            const int r = idx - m * n * n;
-            const int i = (int)(((float)r + 0.5f) * rcp_n);
-            const int j = m * PB + r - i * n;
-            sV[(m * PB + i) * LD + j] = x;
-            sW[(m * PB + i) * LD + j] = x * sf[j];
+            const int i = (int)(((float)idx + 0.5f) * rcp_n);
+            const int j = idx - i * n;
+            sV[i * LD + j] = x;
+            sW[i * LD + j] = x * sf[j];
         });
     wave_sync();
     floatx16 acc[NT][NT];
-    Tiles<NT, 1>{0}.template product<false, true>(acc, sW, sV, PB ? 32 : ((n + 7) & ~7), lane);
+    Tiles<NT, 1>{0}.template product<false, true>(acc, sW, sV, (n + 7) & ~7, lane);
     float* __restrict__ Fb = args.fn_out + (size_t)b * n * n;
 #pragma unroll
     for (int ti = 0; ti < NT; ++ti)
@@ -353,8 +556,7 @@ __global__ __launch_bounds__(64) void spectral_kernel(KernelArgs args) {
             for (int v = 0; v < 16; ++v) {
                 const int i = 32 * ti + acc_row(v, lane);
                 const int j = 32 * tj + (lane & 31);
-                const bool inside = blk(i) == blk(j) && blk(i) < count && loc(i) < n && loc(j) < n;
-                if (inside) Fb[(size_t)blk(i) * n * n + loc(i) * n + loc(j)] = acc[ti][tj][v];
+                if (i < n && j < n) Fb[i * n + j] = acc[ti][tj][v];
             }
 }
 
@@ -362,29 +564,23 @@ __global__ __launch_bounds__(64) void spectral_kernel(KernelArgs args) {
 
 hipError_t launch_spectral(const KernelArgs& args, hipStream_t stream) {
     const int n = args.n, B = args.batch;
-    if (n <= 4) return enqueue(spectral_kernel<1, 4>, dim3((B + 7) / 8), dim3(64), stream, args);
-    if (n <= 8) return enqueue(spectral_kernel<1, 8>, dim3((B + 3) / 4), dim3(64), stream, args);
-    if (n <= 16) return enqueue(spectral_kernel<1, 16>, dim3((B + 1) / 2), dim3(64), stream, args);
-    if (n <= 32) return enqueue(spectral_kernel<1, 0>, dim3(B), dim3(64), stream, args);
-    if (n <= 64) return enqueue(spectral_kernel<2, 0>, dim3(B), dim3(64), stream, args);
+    if (n <= 8) return enqueue(tile_spectral_kernel<16, 8>, dim3((B + 1) / 2), dim3(64), stream, args);
+    if (n <= 16) return enqueue(tile_spectral_kernel<16, 0>, dim3(B), dim3(64), stream, args);
+    if (n <= 32) return enqueue(tile_spectral_kernel<32, 0>, dim3(B), dim3(64), stream, args);
+    if (n <= 64) return enqueue(spectral_kernel, dim3(B), dim3(64), stream, args);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_grad(const GradArgs& args, hipStream_t stream) {
     if (args.batch == 0) return hipSuccess;
     const int n = args.n, B = args.batch;
-    if (n <= 4)
-        return enqueue(grad_kernel<1, 1, 4>, dim3((B + 7) / 8), dim3(64), stream, args);
-    else if (n <= 8)
-        return enqueue(grad_kernel<1, 1, 8>, dim3((B + 3) / 4), dim3(64), stream, args);
-    else if (n <= 16)
-        return enqueue(grad_kernel<1, 1, 16>, dim3((B + 1) / 2), dim3(64), stream, args);
-    else if (n <= 32)
-        return enqueue(grad_kernel<1, 1, 0>, dim3(B), dim3(64), stream, args);
-    else if (n <= 64)
-        return enqueue(grad_kernel<2, 4, 0>, dim3(B), dim3(256), stream, args);
-    else
-        return enqueue(grad_kernel<4, 8, 0>, dim3(B), dim3(512), stream, args);
+    if (n <= 4) return enqueue(tile_grad_kernel<4, 0>, dim3((B + 15) / 16), dim3(64), stream, args);
+    if (n <= 8) return enqueue(tile_grad_kernel<16, 8>, dim3((B + 1) / 2), dim3(64), stream, args);
+    if (n <= 16) return enqueue(tile_grad_kernel<16, 0>, dim3(B), dim3(64), stream, args);
+    if (n <= 24) return enqueue(tile_grad_kernel<32, 0, 24>, dim3(B), dim3(64), stream, args);
+    if (n <= 32) return enqueue(tile_grad_kernel<32, 0>, dim3(B), dim3(64), stream, args);
+    if (n <= 64) return enqueue(grad_kernel<2, 4>, dim3(B), dim3(256), stream, args);
+    return enqueue(grad_kernel<4, 8>, dim3(B), dim3(512), stream, args);
 }
 
 }  // namespace bed

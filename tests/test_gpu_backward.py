@@ -213,3 +213,16 @@ def test_batch_edges_and_argument_errors():
         binding.bed_syevd_backward(lam, V, None, g, grad_A=V)                # output aliases an input
     with pytest.raises(binding.BedError):
         binding.bed_spd_fn_backward(lam, V, g, 1, 0.0)                       # inverse square root needs floor > 0
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 6, 8, 9, 12, 15, 16, 17, 20, 23, 24, 25, 28, 31, 32])
+def test_tiles_and_the_matrices_that_share_a_wavefront(n):
+    """Sixteen matrices a wavefront up to 4 rows, two up to 8: batches that leave the last one with a single
+    matrix and with all but one; n below, at and above the edges of the tiles."""
+    from paper_2207_04228_amd import workloads
+    for batch in (1, 15, 17, 33):
+        A = workloads.covariance(batch, n, 4 * n, 1e-2, 7400 + n)
+        for mode in (0, 1):
+            _check_ed(A, mode, f"tiles n={n} batch {batch}", gap_floor=1e-4, seed=n + batch)
+        for fn in (0, 1):
+            _check_fn(A, fn, 1e-3, f"tiles n={n} batch {batch} fn={fn}", seed=n + batch)
