@@ -2,7 +2,10 @@
 kernels (bed_syevd / bed_spd_fn and bed_syevd_backward / bed_spd_fn_backward); this module only
 saves tensors and routes gradients.  The paper uses the decomposition as a differentiable layer
 (Sec. 2: gradients by the truncated series of degree 9; Sec. 4.2-4.4: whitening, covariance
-pooling, colouring)."""
+pooling, colouring).
+
+A plain GPU tensor that requires a gradient goes through the same functions in C++ (csrc/bed_torch.cpp); everything else,
+and every error, through the ones here."""
 from __future__ import annotations
 
 from . import binding
@@ -66,17 +69,28 @@ def _differentiated(A):
     return torch.is_grad_enabled() and A.requires_grad
 
 
+def _layer(A, fn, floor):
+    out = binding.native().spd_layer(A, fn, floor)
+    if out is not None:
+        return out
+    return _get()[1].apply(A, fn, floor, _differentiated(A))
+
+
 def eigh(A, degree: int = 9):
     """Differentiable (evals ascending, evecs as columns) of symmetric A [batch, n, n]; the
     gradient uses the truncated series of the given degree for the eigenvalue coupling."""
+    if isinstance(degree, int):
+        result = binding.native().eigh_layer(A, degree)
+        if result is not None:
+            return result
     return _get()[0].apply(A, degree)
 
 
 def spd_sqrt(A, floor: float = 0.0):
     """Differentiable A^(1/2) with eigenvalues raised to `floor`."""
-    return _get()[1].apply(A, binding.BED_FN_SQRT, float(floor), _differentiated(A))
+    return _layer(A, binding.BED_FN_SQRT, float(floor))
 
 
 def spd_inv_sqrt(A, floor: float = 1e-6):
     """Differentiable A^(-1/2) with eigenvalues raised to `floor` (> 0)."""
-    return _get()[1].apply(A, binding.BED_FN_INV_SQRT, float(floor), _differentiated(A))
+    return _layer(A, binding.BED_FN_INV_SQRT, float(floor))

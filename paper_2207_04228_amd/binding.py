@@ -1,4 +1,4 @@
-"""ctypes binding over libbed.so -- argument marshalling only.
+"""Binding over libbed.so (ctypes, and bed_torch.so for the common calls) -- argument marshalling only.
 
 Every function takes torch CUDA tensors (used purely as device buffers),
 passes their raw pointers and the current HIP stream to the C ABI declared in
@@ -90,6 +90,30 @@ def load_library():
         lib.bed_version.restype = ci
         _lib = lib
     return _lib
+
+
+_native_path = os.path.join(_HERE, "bed_torch.so")
+_native = None
+
+
+def native():
+    """bed_torch.so (built in-tree beside libbed.so): the common calls as C++ functions on torch tensors.  A function returns
+    None for a call that it does not take; the general way below then serves it, or raises."""
+    global _native
+    if _native is None:
+        if not os.path.exists(_native_path):
+            raise FileNotFoundError(
+                f"{_native_path} not found: build it with "
+                "`python -m paper_2207_04228_amd.build` (needs g++)")
+        import importlib.machinery
+        import importlib.util
+        load_library()
+        spec = importlib.util.spec_from_file_location(
+            "bed_torch", _native_path, loader=importlib.machinery.ExtensionFileLoader("bed_torch", _native_path))
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _native = module
+    return _native
 
 
 def bed_syevd_kernel(batch: int, n: int, want_vectors: bool = True) -> str:
@@ -208,6 +232,10 @@ def bed_syevd(A, evals=None, evecs=None, *, want_vectors=True, stream=None):
     """Eigendecomposition of A [batch, n, n] (float32, CUDA, symmetric; the
     lower triangle is read).  Returns (evals [batch, n] ascending,
     evecs [batch, n, n] with eigenvectors as columns, or None)."""
+    if evals is None and evecs is None and stream is None:
+        result = (_native or native()).syevd(A, 1 if want_vectors else 0)
+        if result is not None:
+            return result
     import torch
     _check_dev(A, "A", torch.float32)
     batch, n = _square_batch(A)
@@ -395,6 +423,10 @@ BED_FN_INV_SQRT = 1
 def bed_spd_fn(A, fn, floor, out=None, *, want_evals=False, stream=None):
     """out_b = V_b f(max(Lambda_b, floor)) V_b^T for fn in {BED_FN_SQRT, BED_FN_INV_SQRT}.
     Returns (out [batch, n, n], evals or None, info int32 [batch])."""
+    if out is None and not want_evals and stream is None:
+        result = (_native or native()).spd_fn(A, int(fn), float(floor))
+        if result is not None:
+            return result
     import torch
     _check_dev(A, "A", torch.float32)
     batch, n = _square_batch(A)
@@ -455,6 +487,10 @@ def bed_syevd_backward(evals, evecs, grad_evals=None, grad_evecs=None, *, mode=B
 
 def bed_spd_fn_backward(evals, evecs, grad_out, fn, floor, *, grad_A=None, stream=None):
     """Gradient of <grad_out, V f(max(Lambda, floor)) V^T> with respect to A."""
+    if grad_A is None and stream is None:
+        result = (_native or native()).spd_fn_backward(evals, evecs, grad_out, int(fn), float(floor))
+        if result is not None:
+            return result
     import torch
     _check_dev(evals, "evals", torch.float32)
     _check_dev(evecs, "evecs", torch.float32)

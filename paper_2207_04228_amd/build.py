@@ -1,4 +1,4 @@
-"""Build libbed.so in-tree with hipcc for gfx950.
+"""Build libbed.so in-tree with hipcc for gfx950, and bed_torch.so (host code on torch's C++ interface) with g++.
 
     python -m paper_2207_04228_amd.build [--force] [--remarks]
 
@@ -20,6 +20,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbed.so")
+NATIVE = os.path.join(HERE, "bed_torch.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -95,6 +96,29 @@ def build(force: bool = False, remarks: bool = False, jobs: int = 8) -> str:
     return LIB
 
 
+def build_native(force: bool = False) -> str:
+    """bed_torch.so: csrc/bed_torch.cpp against the installed torch and libbed.so, which it finds beside itself."""
+    import sysconfig
+
+    import torch
+    source = os.path.join(CSRC, "bed_torch.cpp")
+    header = os.path.join(ROOT, "include", "bed.h")
+    if not force and _newer(NATIVE, [source, header]):
+        return NATIVE
+    base = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I" + os.path.join(ROOT, "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(base, "include"),
+           "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+           source, "-o", NATIVE, "-L" + HERE, "-l:libbed.so", "-Wl,-rpath,$ORIGIN",
+           "-L" + os.path.join(base, "lib"), "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on {source}:\n{r.stderr[-4000:]}")
+    return NATIVE
+
+
 def main(argv=None):
     ap = argparse.ArgumentParser()
     ap.add_argument("--force", action="store_true")
@@ -106,6 +130,7 @@ def main(argv=None):
         print(source_hash())
         return 0
     print(build(a.force, a.remarks, a.jobs))
+    print(build_native(a.force))
 
 
 if __name__ == "__main__":

@@ -1,0 +1,264 @@
+// The calls that a program makes once per layer and step, as C++ functions on torch tensors: what binding.py and autograd.py
+// do around the C ABI (checks, output buffers, the current stream, the saved tensors of a training step) without
+// the interpreter.  us a call from Python before / here: bed_syevd of 8 x 8x8 8.6 / 4.5, spd_inv_sqrt forward under grad 15 / 9, a training step
+// 90 / 50 (a multiplication by two and its gradient 42 on the same host: autograd's own path).
+//
+// Every function returns None for a call that it does not take (another kind of tensor, a wrapper of vmap or of
+// forward-mode differentiation, arguments the library refuses): binding.py and autograd.py then go their general way, which also
+// raises the errors.  No state is kept between calls.
+#include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/DeviceGuard.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/pybind.h>
+
+#include "bed.h"
+
+namespace {
+
+using at::Tensor;
+
+PyObject* tensor_type = nullptr;        // torch.Tensor and torch.nn.Parameter, set once when the module is made
+PyObject* parameter_type = nullptr;
+
+void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+
+// A plain dense float32 tensor on a GPU, with memory of its own that may be handed to a kernel.
+bool plain(const Tensor& t) {
+    return t.defined() && t.is_cuda() && t.scalar_type() == at::kFloat && t.layout() == at::kStrided && t.has_storage() && !t.is_neg() &&
+           !t.key_set().has_any(c10::DispatchKeySet({c10::DispatchKey::Python, c10::DispatchKey::FuncTorchBatched,
+                                                     c10::DispatchKey::FuncTorchGradWrapper, c10::DispatchKey::Functionalize}));
+}
+// A batch of square matrices that the library takes.
+bool square_batch(const Tensor& t) {
+    return plain(t) && t.dim() == 3 && t.size(1) == t.size(2) && t.size(1) >= 1 && t.size(1) <= BED_MAX_N && t.size(0) <= INT_MAX;
+}
+bool vector_of(const Tensor& t, const Tensor& M) { return plain(t) && t.dim() == 2 && t.size(0) == M.size(0) && t.size(1) == M.size(1); }
+bool usable(const Tensor& t, const Tensor& like) { return t.is_contiguous() && t.device() == like.device(); }
+
+// The tensor behind a Python object, undefined if it is not exactly a torch.Tensor or a Parameter or if a mode wants to see
+// every call.
+Tensor unpack(PyObject* object) {
+    if ((PyObject*)Py_TYPE(object) != tensor_type && (PyObject*)Py_TYPE(object) != parameter_type) return {};
+    if (at::impl::torch_function_mode_enabled()) return {};
+    return THPVariable_Unpack(object);
+}
+
+float* data(const Tensor& t) { return t.defined() ? t.mutable_data_ptr<float>() : nullptr; }
+const float* const_data(const Tensor& t) { return t.defined() ? t.const_data_ptr<float>() : nullptr; }
+
+bool decompose(const Tensor& A, Tensor& evals, Tensor& evecs, bool want_vectors) {
+    const c10::DeviceGuard guard(A.device());
+    const int batch = (int)A.size(0), n = (int)A.size(1);
+    evals = at::empty({batch, n}, A.options());
+    if (want_vectors) evecs = at::empty({batch, n, n}, A.options());
+    return bed_syevd(const_data(A), batch, n, data(evals), data(evecs), stream_of(A)) == BED_OK;
+}
+
+bool function(const Tensor& A, int fn, float floor, Tensor& out, Tensor& info) {
+    const c10::DeviceGuard guard(A.device());
+    const int batch = (int)A.size(0), n = (int)A.size(1);
+    out = at::empty({batch, n, n}, A.options());
+    info = at::empty({batch}, A.options().dtype(at::kInt));
+    return bed_spd_fn(const_data(A), batch, n, fn, floor, data(out), nullptr, info.mutable_data_ptr<int>(), stream_of(A)) == BED_OK;
+}
+
+bool function_and_decomposition(const Tensor& A, int fn, float floor, Tensor& out, Tensor& evals, Tensor& evecs) {
+    const c10::DeviceGuard guard(A.device());
+    const int batch = (int)A.size(0), n = (int)A.size(1);
+    out = at::empty({batch, n, n}, A.options());
+    evals = at::empty({batch, n}, A.options());
+    evecs = at::empty({batch, n, n}, A.options());
+    return bed_spd_fn_eigh(const_data(A), batch, n, fn, floor, data(out), data(evals), data(evecs), nullptr, stream_of(A)) == BED_OK;
+}
+
+bool function_backward(const Tensor& evals, const Tensor& evecs, const Tensor& g, int fn, float floor, Tensor& gA) {
+    const c10::DeviceGuard guard(evecs.device());
+    const int batch = (int)evecs.size(0), n = (int)evecs.size(1);
+    gA = at::empty({batch, n, n}, evecs.options());
+    return bed_spd_fn_backward(const_data(evals), const_data(evecs), const_data(g), batch, n, fn, floor, data(gA),
+                               stream_of(evecs)) == BED_OK;
+}
+
+// ---- layers ----
+void check_upstream(const Tensor& g, const Tensor& like) {
+    TORCH_CHECK(plain(g) && g.sizes() == like.sizes() && g.device() == like.device(), "bed: upstream gradient of another kind");
+}
+
+struct SpdFn : torch::autograd::Function<SpdFn> {
+    static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& input, int64_t fn, double floor) {
+        const Tensor A = input.contiguous();
+        Tensor out, evals, evecs;
+        TORCH_CHECK(function_and_decomposition(A, (int)fn, (float)floor, out, evals, evecs), "bed_spd_fn_eigh failed");
+        // A is saved with the decomposition so that changing it in place before the backward pass is noticed
+        ctx->save_for_backward({A, evals, evecs});
+        ctx->saved_data["fn"] = fn;
+        ctx->saved_data["floor"] = floor;
+        return out;
+    }
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads) {
+        const auto saved = ctx->get_saved_variables();
+        check_upstream(grads[0], saved[2]);
+        Tensor gA;
+        TORCH_CHECK(function_backward(saved[1], saved[2], grads[0].contiguous(), (int)ctx->saved_data["fn"].toInt(),
+                                      (float)ctx->saved_data["floor"].toDouble(), gA), "bed_spd_fn_backward failed");
+        return {gA, Tensor(), Tensor()};
+    }
+};
+
+struct Syevd : torch::autograd::Function<Syevd> {
+    static torch::autograd::variable_list forward(torch::autograd::AutogradContext* ctx, const Tensor& input, int64_t degree) {
+        const Tensor A = input.contiguous();
+        Tensor evals, evecs;
+        TORCH_CHECK(decompose(A, evals, evecs, true), "bed_syevd failed");
+        ctx->save_for_backward({evals, evecs});
+        ctx->saved_data["degree"] = degree;
+        return {evals, evecs};
+    }
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads) {
+        const auto saved = ctx->get_saved_variables();
+        const Tensor &evals = saved[0], &evecs = saved[1];
+        check_upstream(grads[0], evals);
+        check_upstream(grads[1], evecs);
+        const c10::DeviceGuard guard(evecs.device());
+        const int batch = (int)evecs.size(0), n = (int)evecs.size(1);
+        const Tensor g_evals = grads[0].contiguous(), g_evecs = grads[1].contiguous();
+        Tensor gA = at::empty({batch, n, n}, evecs.options());
+        TORCH_CHECK(bed_syevd_backward(const_data(evals), const_data(evecs), const_data(g_evals), const_data(g_evecs), batch, n,
+                                       BED_GRAD_TAYLOR, (int)ctx->saved_data["degree"].toInt(), 0.f, data(gA), stream_of(evecs)) == BED_OK,
+                    "bed_syevd_backward failed");
+        return {gA, Tensor()};
+    }
+};
+
+// ---- Python ----
+PyObject* none() { Py_RETURN_NONE; }
+PyObject* not_taken() {
+    PyErr_Clear();
+    Py_RETURN_NONE;
+}
+
+// Runs `work` without the interpreter's lock (a full queue makes a launch wait).
+template <typename Work>
+bool unlocked(Work&& work) {
+    const pybind11::gil_scoped_release release;
+    return work();
+}
+
+PyObject* wrapped(std::initializer_list<Tensor> tensors) {
+    PyObject* tuple = PyTuple_New((Py_ssize_t)tensors.size());
+    if (!tuple) return nullptr;
+    Py_ssize_t i = 0;
+    for (const Tensor& t : tensors) {
+        PyObject* item = t.defined() ? THPVariable_Wrap(t) : none();
+        if (!item) {
+            Py_DECREF(tuple);
+            return nullptr;
+        }
+        PyTuple_SET_ITEM(tuple, i++, item);
+    }
+    return tuple;
+}
+
+bool takes(int fn, double floor) {
+    const float f = (float)floor;
+    return (fn == BED_FN_SQRT || fn == BED_FN_INV_SQRT) && f >= 0.f && f < INFINITY && (fn == BED_FN_SQRT || f > 0.f);
+}
+
+bool differentiated(const Tensor& A) { return at::GradMode::is_enabled() && A.requires_grad() && !A._fw_grad(0).defined(); }
+
+PyObject* syevd(PyObject*, PyObject* args) {
+    HANDLE_TH_ERRORS
+    PyObject* object;
+    int want_vectors;
+    if (!PyArg_ParseTuple(args, "Op", &object, &want_vectors)) return not_taken();
+    const Tensor A = unpack(object);
+    if (!square_batch(A) || !A.is_contiguous()) return none();
+    Tensor evals, evecs;
+    if (!unlocked([&] { return decompose(A, evals, evecs, want_vectors); })) return none();
+    return wrapped({evals, evecs});
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject* spd_fn(PyObject*, PyObject* args) {
+    HANDLE_TH_ERRORS
+    PyObject* object;
+    int fn;
+    double floor;
+    if (!PyArg_ParseTuple(args, "Oid", &object, &fn, &floor)) return not_taken();
+    const Tensor A = unpack(object);
+    if (!square_batch(A) || !A.is_contiguous() || !takes(fn, floor)) return none();
+    Tensor out, info;
+    if (!unlocked([&] { return function(A, fn, (float)floor, out, info); })) return none();
+    return wrapped({out, Tensor(), info});
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject* spd_fn_backward(PyObject*, PyObject* args) {
+    HANDLE_TH_ERRORS
+    PyObject *o_evals, *o_evecs, *o_grad;
+    int fn;
+    double floor;
+    if (!PyArg_ParseTuple(args, "OOOid", &o_evals, &o_evecs, &o_grad, &fn, &floor)) return not_taken();
+    const Tensor evecs = unpack(o_evecs), evals = unpack(o_evals), g = unpack(o_grad);
+    if (!square_batch(evecs) || !vector_of(evals, evecs) || !square_batch(g) || g.sizes() != evecs.sizes() || !usable(evecs, evecs) ||
+        !usable(evals, evecs) || !usable(g, evecs) || !takes(fn, floor))
+        return none();
+    Tensor gA;
+    if (!unlocked([&] { return function_backward(evals, evecs, g, fn, (float)floor, gA); })) return none();
+    return THPVariable_Wrap(gA);
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject* spd_layer(PyObject*, PyObject* args) {
+    HANDLE_TH_ERRORS
+    PyObject* object;
+    int fn;
+    double floor;
+    if (!PyArg_ParseTuple(args, "Oid", &object, &fn, &floor)) return not_taken();
+    const Tensor A = unpack(object);
+    if (!square_batch(A) || !takes(fn, floor) || !differentiated(A)) return none();
+    Tensor out;
+    unlocked([&] { out = SpdFn::apply(A, (int64_t)fn, floor); return true; });
+    return THPVariable_Wrap(out);
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject* eigh_layer(PyObject*, PyObject* args) {
+    HANDLE_TH_ERRORS
+    PyObject* object;
+    int degree;
+    if (!PyArg_ParseTuple(args, "Oi", &object, &degree)) return not_taken();
+    const Tensor A = unpack(object);
+    if (!square_batch(A) || degree < 0 || degree > 64 || !differentiated(A)) return none();
+    torch::autograd::variable_list out;
+    unlocked([&] { out = Syevd::apply(A, (int64_t)degree); return true; });
+    return wrapped({out[0], out[1]});
+    END_HANDLE_TH_ERRORS
+}
+
+PyMethodDef methods[] = {{"syevd", syevd, METH_VARARGS, "(A, want_vectors) -> (evals, evecs or None) or None"},
+                         {"spd_fn", spd_fn, METH_VARARGS, "(A, fn, floor) -> (out, None, info) or None"},
+                         {"spd_fn_backward", spd_fn_backward, METH_VARARGS, "(evals, evecs, grad_out, fn, floor) -> grad_A or None"},
+                         {"spd_layer", spd_layer, METH_VARARGS, "(A, fn, floor) -> differentiable out, or None"},
+                         {"eigh_layer", eigh_layer, METH_VARARGS, "(A, degree) -> differentiable (evals, evecs), or None"},
+                         {nullptr, nullptr, 0, nullptr}};
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "bed_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit_bed_torch() {
+    PyObject* torch = PyImport_ImportModule("torch");
+    if (!torch) return nullptr;
+    tensor_type = PyObject_GetAttrString(torch, "Tensor");
+    PyObject* nn = PyObject_GetAttrString(torch, "nn");
+    parameter_type = nn ? PyObject_GetAttrString(nn, "Parameter") : nullptr;
+    Py_XDECREF(nn);
+    Py_DECREF(torch);
+    if (!tensor_type || !parameter_type) return nullptr;
+    return PyModule_Create(&module);
+}

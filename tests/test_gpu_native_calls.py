@@ -1,0 +1,144 @@
+"""The calls that bed_torch.so takes give the same bits as the general way, on every kind of input both take; what they leave
+to the general way ends as it did."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _input(batch, n, seed=0):
+    import torch
+    from paper_2207_04228_amd import workloads
+    return torch.from_numpy(workloads.covariance(batch, n, 4 * n, 1e-2, 7500 + seed)).cuda()
+
+
+def _general(monkeypatch):
+    """Everything through ctypes and the Python functions."""
+    from paper_2207_04228_amd import binding
+
+    class Nothing:
+        def __getattr__(self, name):
+            return lambda *args: None
+    monkeypatch.setattr(binding, "_native", Nothing())
+
+
+@pytest.mark.parametrize("batch, n", [(0, 4), (1, 1), (5, 4), (17, 9), (3, 32), (2, 65)])
+def test_same_bits_as_the_general_way(batch, n, monkeypatch):
+    import torch
+    import paper_2207_04228_amd as bed
+    A = _input(max(batch, 1), n)[:batch].contiguous()
+    G = torch.randn(batch, n, n, device="cuda")
+    w = torch.randn(batch, n, device="cuda")
+
+    def everything():
+        out = list(bed.bed_syevd(A)) + [bed.bed_syevd(A, want_vectors=False)[0]]
+        out += [t for t in bed.bed_spd_fn(A, bed.BED_FN_INV_SQRT, 1e-6) if t is not None]
+        out.append(bed.bed_spd_fn_backward(out[0], out[1], G, bed.BED_FN_SQRT, 1e-6))
+        kinds = [A.clone().requires_grad_(), torch.nn.Parameter(A.clone()), A.transpose(1, 2).clone().transpose(1, 2).requires_grad_()]
+        for X in kinds:
+            for layer in (bed.autograd.spd_sqrt, bed.autograd.spd_inv_sqrt):
+                F = layer(X, 1e-6)
+                assert F.requires_grad
+                out += [F.detach(), torch.autograd.grad(F, X, G)[0], torch.autograd.grad(layer(X, 1e-6).sum(), X)[0]]
+            lam, V = bed.autograd.eigh(X)
+            out += [lam.detach(), V.detach(), torch.autograd.grad((lam, V), X, (w, G))[0]]
+            out.append(torch.autograd.grad(bed.autograd.eigh(X)[0], X, w)[0])
+            out.append(torch.autograd.grad(bed.autograd.eigh(X, 3)[1], X, G)[0])
+        return out
+
+    native = everything()
+    _general(monkeypatch)
+    for a, b in zip(native, everything(), strict=True):
+        assert a.dtype == b.dtype and torch.equal(a, b)
+
+
+def test_what_autograd_promises():
+    import torch
+    import paper_2207_04228_amd as bed
+    A = _input(4, 6).requires_grad_()
+    G = torch.randn(4, 6, 6, device="cuda")
+    F = bed.autograd.spd_sqrt(A, 1e-6)
+    with torch.no_grad():
+        A.mul_(1.0)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        torch.autograd.grad(F, A, G)
+    F = bed.autograd.spd_sqrt(A, 1e-6)
+    torch.autograd.grad(F, A, G)
+    with pytest.raises(RuntimeError, match="second time"):
+        torch.autograd.grad(F, A, G)
+    seen = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: seen.append(t.shape) or t, lambda t: t):
+        F = bed.autograd.spd_inv_sqrt(A, 1e-6)
+        lam, V = bed.autograd.eigh(A)
+    assert len(seen) == 5 and torch.autograd.grad(F, A, G)[0].isfinite().all()
+    with torch.no_grad():
+        assert not bed.autograd.spd_sqrt(A, 1e-6).requires_grad
+    assert not bed.bed_syevd(A)[0].requires_grad
+    with torch.inference_mode():
+        assert bed.bed_syevd(A.detach())[0].is_inference()
+
+
+def test_what_was_refused_is_refused():
+    import torch
+    import paper_2207_04228_amd as bed
+    A = _input(4, 6)
+    with pytest.raises(TypeError, match="CUDA"):
+        bed.autograd.spd_sqrt(A.cpu().requires_grad_(), 1e-6)
+    with pytest.raises(TypeError, match="float32"):
+        bed.bed_syevd(A.double())
+    with pytest.raises(TypeError, match="torch.Tensor"):
+        bed.bed_syevd([[1.0]])
+    with pytest.raises(ValueError, match="contiguous"):
+        bed.bed_syevd(A.transpose(1, 2))
+    with pytest.raises(ValueError, match="shape"):
+        bed.bed_spd_fn_backward(*bed.bed_syevd(A), A[:2].contiguous(), 0, 1e-6)
+    for bad in (dict(fn=2, floor=1e-6), dict(fn=1, floor=0.0), dict(fn=0, floor=-1.0), dict(fn=0, floor=float("nan"))):
+        with pytest.raises(bed.BedError):
+            bed.bed_spd_fn(A, **bad)
+    with pytest.raises(bed.BedError):
+        bed.bed_syevd(torch.zeros(1, 129, 129, device="cuda"))
+    with pytest.raises(bed.BedError):
+        bed.autograd.spd_inv_sqrt(A.clone().requires_grad_(), 0.0)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda X: bed.autograd.spd_sqrt(X, 1e-6))(A.expand(2, 4, 6, 6).contiguous().requires_grad_())
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda X: bed.autograd.spd_sqrt(X, 1e-6).sum())(A)
+    with torch.autograd.forward_ad.dual_level():
+        dual = torch.autograd.forward_ad.make_dual(A.clone().requires_grad_(), torch.ones_like(A))
+        with pytest.raises((RuntimeError, NotImplementedError)):
+            bed.autograd.spd_sqrt(dual, 1e-6)
+
+
+def test_a_side_stream_and_threads():
+    """Launches go to the current stream of the calling thread; the backward pass to the stream of the forward pass."""
+    import threading
+    import torch
+    import paper_2207_04228_amd as bed
+    A = _input(512, 32)
+    G = torch.randn(512, 32, 32, device="cuda")
+    lam = bed.bed_syevd(A)[0]
+    want = torch.autograd.grad(bed.autograd.spd_sqrt(A.requires_grad_(), 1e-6), A, G)[0]
+    A = A.detach()
+    results = {}
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            X = torch.zeros_like(A)
+            for _ in range(20):
+                torch.matmul(X, X)
+            X.copy_(A)                                   # the calls must wait for this, on this stream only
+            got = bed.bed_syevd(X)[0]
+            X.requires_grad_()
+            grad = torch.autograd.grad(bed.autograd.spd_sqrt(X, 1e-6), X, G)[0]
+        stream.synchronize()
+        results[k] = (got, grad)
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k in range(4):
+        assert torch.equal(results[k][0], lam) and torch.equal(results[k][1], want)
