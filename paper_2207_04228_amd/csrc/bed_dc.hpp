@@ -1,6 +1,6 @@
 // Divide and conquer for the symmetric tridiagonal eigenproblem, one matrix per workgroup.
 //
-// T is torn into blocks of one or two rows: every coupling e between two blocks is taken out as a
+// T is torn into blocks of at most four rows, which Jacobi's method solves (four lanes each): every coupling e between two blocks is taken out as a
 // rank-one term, T = diag(T1', T2') + rho z z^T with |z| = 1 (Cuppen 1981), and the blocks are
 // merged pairwise, all merges of a level at once.  A merge of m eigenvalues
 //   - deflates components of z that are negligible and pairs of poles that a plane rotation
@@ -60,7 +60,7 @@ constexpr int kDcMaxIter = 60;                  // more than three times what an
 template <int N, int TPE, bool WANT_V>
 struct DcShared {
     static constexpr int LD = N + 1;
-    static constexpr int NP = N * TPE;   // the smallest merges have 3 or 4 poles in 4 TPE entries
+    static constexpr int NP = N * TPE / 2;   // the smallest merges have 5 to 8 poles in 4 TPE entries (8 for TPE = 2)
     alignas(16) float Dp[NP];            // by column: eigenvalues
     alignas(16) float2 dz[NP];           // by slot (kept poles ascending, then the deflated ones): d, z^2
     alignas(16) float2 om[NP];           // by slot: the pole the root is measured from, and the distance
@@ -98,7 +98,7 @@ __device__ __forceinline__ float dc_product(float x) {
 template <int NB>
 struct DcMask {
     uint64_t w[NB];
-    __device__ __forceinline__ bool has(int p) const { return (w[NB == 1 ? 0 : (p >> 6)] >> (p & 63)) & 1; }
+    __device__ __forceinline__ bool has(int p) const { return ((NB > 1 && p >= 64 ? w[NB - 1] : w[0]) >> (p & 63)) & 1; }
     __device__ __forceinline__ int below(int p) const {      // members < p, p in 0..64 NB
         int c = 0;
 #pragma unroll
@@ -175,7 +175,7 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
     };
 
     int L = 0;
-    while ((2 << L) < n) ++L;       // 2^L leaves of one or two rows
+    while ((4 << L) < n) ++L;       // 2^L leaves of at most four rows
     // leaf that holds row r: the largest i with floor(i n / 2^L) <= r
     const float rcp_n = 1.f / (float)n;
     int unresolved = 0;
@@ -212,57 +212,60 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
     // more than its own size.  With tau = 1 small rows of a graded T would be left with the
     // rounding of a large e: A^(-1/2) of 128x128 covariances with power-law spectra, condition
     // 1e3, was off by 9e-5 instead of 5e-6.  tau is a power of two.
-    auto tau_of = [&](int k) {
-        const float a = fabsf(dget(k)), c = fabsf(dget(k + 1)), b = fabsf(eget(k));
-        if (!(b * b <= a * c) || b == 0.f) return 1.f;
-        const int ex = (__builtin_amdgcn_frexp_expf(a) - __builtin_amdgcn_frexp_expf(c)) >> 1;
-        return ldexpf(1.f, min(max(ex, -30), 30));
-    };
     if (part == 0 && e < n - 1) {
-        const float tau = tau_of(e), ec = eget(e);
-        const float w = 1.f / sqrtf(fmaf(tau, tau, 1.f));
-        S.rho[e] = fabsf(ec) * (tau + 1.f / tau);
+        const float a = fabsf(dget(e)), c = fabsf(dget(e + 1)), ec = eget(e), b = fabsf(ec);
+        int ex = 0;
+        if (b * b <= a * c && b != 0.f) ex = min(max((__builtin_amdgcn_frexp_expf(a) - __builtin_amdgcn_frexp_expf(c)) >> 1, -30), 30);
+        const float tau = ldexpf(1.f, ex), taken = ldexpf(b, -ex);
+        const float w = dc_rsqrt(fmaf(tau, tau, 1.f));
+        S.dd[e] = b * tau;                              // what the rows e and e + 1 lose where the coupling is torn out
+        S.dS[e] = taken;
+        S.rho[e] = fmaf(b, tau, taken);
         S.za[e] = tau * w;
         S.zb[e] = ec < 0.f ? -w : w;
     }
-    float lam = __builtin_inff();   // eigenvalue of column e
     if (part == 0) {
         S.rn[e] = 1.f;
         S.perm[e] = e;
         S.src[e] = e;
-        S.first[e] = 0.f;
-        S.last[e] = 0.f;
-        if (valid) {
-            const int lo = (leaf * n) >> L, hi = ((leaf + 1) * n) >> L;
-            const float el = lo > 0 ? fabsf(eget(lo - 1)) / tau_of(lo - 1) : 0.f;
-            const float eh = hi < n ? fabsf(eget(hi - 1)) * tau_of(hi - 1) : 0.f;
-            float cc = 1.f, ss = 0.f;
-            if (hi - lo == 1) {
-                lam = dget(lo) - el - eh;
-            } else {
-                const float a = dget(lo) - el, b = eget(lo), c = dget(lo + 1) - eh;
-                float t = 0.f;
-                if (b != 0.f) {
-                    const float th = (c - a) / (2.f * b);
-                    t = copysignf(1.f / (fabsf(th) + sqrtf(fmaf(th, th, 1.f))), th);
-                }
-                cc = 1.f / sqrtf(fmaf(t, t, 1.f));
-                ss = t * cc;
-                lam = e == lo ? fmaf(-t, b, a) : fmaf(t, b, c);
-            }
-            if (bad) lam = cc = __builtin_nanf("");
-            // column e of the leaf: (cc, -ss) for its first row, (ss, cc) for its second
+        if (!valid) S.first[e] = S.last[e] = 0.f;
+    }
+    sync();
+    // Four lanes solve a leaf (bed_jacobi.hpp: lane j has column j, register k row j ^ k).  Leaves of two rows took 3 k cycles and the
+    // merge that these save 8 to 14 k (16 to 128 rows); these take 7.3 k.
+    if (tid < (4 << L)) {
+        const int j = tid & 3, lo = ((tid >> 2) * n) >> L, hi = (((tid >> 2) + 1) * n) >> L, m = hi - lo;
+        const bool in = j < m;
+        auto coupling = [&](int k) { return k < m - 1 ? eget(min(lo + k, n - 1)) : 0.f; };      // of rows k and k + 1 of the leaf
+        float d = in ? dget(lo + j) : 0.f;
+        const float before = S.dS[max(lo - 1, 0)], behind = S.dd[hi - 1];
+        d -= j == 0 && lo > 0 ? before : 0.f;
+        d -= j == m - 1 && hi < n ? behind : 0.f;
+        const float e01 = coupling(j & 2), e12 = coupling(1);
+        float x[4] = {d, e01, 0.f, j == 1 || j == 2 ? e12 : 0.f}, v[4] = {1.f, 0.f, 0.f, 0.f};
+        bool work = !bad;
+        for (int it = 0; it < jacobi::kMaxSweeps; ++it) {
+            bool open = false;
+            jacobi::sweep<true>(x, v, d, work, open, j);
+            work = work && jacobi::group_max(open ? 1.f : 0.f) > 0.f;
+            if (__ballot(work) == 0) break;
+        }
+        jacobi::orthonormalise(v);
+        if (bad) d = v[0] = __builtin_nanf("");
+        auto entry = [&](int r) { const int k = j ^ r; return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3]; };
+        if (in) {
+            S.D[lo + j] = d;
+            S.first[lo + j] = entry(0);
+            S.last[lo + j] = entry(m - 1);
             if (WANT_V) {
-                S.V[e * LD + e] = cc;
-                if (hi - lo == 2) S.V[(e == lo ? lo + 1 : lo) * LD + e] = e == lo ? -ss : ss;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if ((j ^ k) < m) S.V[(lo + (j ^ k)) * LD + lo + j] = v[k];
             }
-            S.first[e] = e == lo ? cc : ss;
-            S.last[e] = e == hi - 1 ? cc : -ss;
         }
     }
-    if (TPE >= 2) lam = part == 0 ? lam : dpp0<kQuadXor1>(lam);
-    if (TPE >= 4) lam = part < 2 ? lam : dpp0<kQuadXor2>(lam);
     sync();
+    float lam = valid ? S.D[e] : __builtin_inff();      // eigenvalue of column e
     if (bad) {
         if (part == 0) S.D[e] = lam;
         sync();

@@ -53,9 +53,8 @@ struct Step {
         float t = a2 * __builtin_amdgcn_rcpf(delta + copysignf(h, delta));
         open = open || (fabsf(t) > kAngle && fabsf(a) > fmaxf(kNegligible * fmaxf(fabsf(d), fabsf(dp)), kNothing));
         t = work ? t : 0.f;
-        const float q = fmaf(t, t, 1.f);
-        const float r = __builtin_amdgcn_rsqf(q);
-        const float c = r * fmaf(-0.5f * q * r, r, 1.5f);
+        // c^2 + s^2 = 1 to two units in the last place; what that and the roundings of all rotations do to V is taken out at the end
+        const float c = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f));
         const float s = t * c;
         d = fmaf(-t, a, d);
         // columns
@@ -85,6 +84,27 @@ __device__ __forceinline__ void sweep(float (&x)[G], float (&v)[G], float& d, co
         Step<WANT_V, S>::run(x, v, d, work, open, j < (j ^ S) ? 1e-30f : -1e-30f);
         sweep<WANT_V, S + 1>(x, v, d, work, open, j);
     }
+}
+
+// V <- V + V (I - V^T V) / 2: the columns orthonormal to rounding again (V^T V - I from 1e-6 to 2e-7 for four rows; the
+// vectors of 32 rows built on leaves without it were 10 % less orthogonal than on leaves of two rows).
+template <int K = 0>
+__device__ __forceinline__ void add_correction(float (&w)[G], const float (&v)[G]) {
+    if constexpr (K < G) {
+        float g = K == 0 ? -1.f : 0.f;              // (V^T V - I) [j][j ^ K]
+#pragma unroll
+        for (int m = 0; m < G; ++m) g = fmaf(v[m], from_lane_xor<K>(v[m ^ K]), g);
+        g *= -0.5f;
+#pragma unroll
+        for (int m = 0; m < G; ++m) w[m] = fmaf(g, from_lane_xor<K>(v[m ^ K]), w[m]);
+        add_correction<K + 1>(w, v);
+    }
+}
+__device__ __forceinline__ void orthonormalise(float (&v)[G]) {
+    float w[G] = {0.f, 0.f, 0.f, 0.f};
+    add_correction(w, v);
+#pragma unroll
+    for (int m = 0; m < G; ++m) v[m] += w[m];
 }
 
 template <int K = 1>
@@ -152,6 +172,7 @@ __device__ __forceinline__ void solve(const KernelArgs& args) {
         if (__ballot(work) == 0) break;
     }
 
+    if (WANT_V) orthonormalise(v);
     const int rank = bad ? j : rank_of(j < n ? d : __builtin_inff(), j);
     const float lam = bad ? __builtin_nanf("") : d * inv_scale;
     if (mine) {

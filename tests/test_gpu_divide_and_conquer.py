@@ -245,3 +245,20 @@ def test_edges_of_the_blocks_of_reflectors(n):
     for A, name in ((_structured(n, n + 1), "structured"), (gaps, "gaps"), (np.ascontiguousarray(gaps[:, perm][:, :, perm]), "shuffled")):
         assert _runs(A)
         _check(A, f"blocks of reflectors, {name}, n={n}")
+
+
+@pytest.mark.parametrize("n", [12, 13, 19, 25, 33, 41, 52, 66, 72, 75, 85, 104, 113])
+def test_leaves_of_two_to_four_rows_and_blocks_that_straddle_tiles(n):
+    """Every split of n into leaves, with tridiagonal inputs (nothing to reduce: T is the matrix) that are graded, constant, split and
+    have equal, zero and opposite diagonal entries next to each other."""
+    rng = np.random.default_rng(6970 + n)
+    off = rng.standard_normal(n - 1)
+    small = 10.0 ** -rng.uniform(0, 8, n - 1)
+    cases = [(2 * np.ones(n), -np.ones(n - 1)), (np.zeros(n), np.ones(n - 1)), (np.tile([1.0, -1.0], n)[:n], off), (np.ones(n), 1e-4 * off),
+             (np.repeat(rng.standard_normal(n), 4)[:n], off * (np.arange(n - 1) % 4 != 3)), (10.0 ** -np.linspace(0, 10, n), small * 1e-6),
+             (rng.standard_normal(n), small), (1e-20 * np.ones(n), 1e-20 * off)]
+    A = np.stack([np.diag(d) + np.diag(e, 1) + np.diag(e, -1) for d, e in cases] * 2).astype(np.float32)
+    assert _runs(A)
+    _check(A, f"leaves, n={n}")
+    lam, V = _solve_gpu(A)
+    assert np.array_equal(_solve_gpu(A, want_vectors=False)[0], lam)
