@@ -3,7 +3,8 @@
 //
 // The reflectors of the tridiagonalisation leave LDS before the divide and conquer and wait in registers (N / 4 of
 // them), so that the eigenvectors of T and of the merges have the two matrix-sized areas of LDS to themselves.  Then
-// they come back and are applied to V, sixteen columns per wavefront.  256 matrices, us per launch: 64x64 96 before, 72 now; 128x128 245, 169.
+// they come back and are applied to V, sixteen columns per wavefront.  256 matrices, us per launch: 64x64 96 with P accumulated and leaves of
+// two rows, 65 now; 128x128 245, 160.
 #include "bed_tile_tridiag.hpp"
 
 namespace bed {
