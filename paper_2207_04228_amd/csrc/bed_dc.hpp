@@ -8,8 +8,7 @@
 //     one, which keeps small eigenvalues of graded matrices,
 //   - finds the roots of the secular equation 1/rho + sum z_j^2 / (d_j - lambda) = 0, one root per
 //     thread, from rational interpolation with the two neighbouring poles (Bunch, Nielsen and
-//     Sorensen 1978; Li 1993: fixed weight and middle way in turn), inside a bracket and measured
-//     from the nearer pole,
+//     Sorensen 1978) through two derivatives, inside a bracket and measured from the nearer pole,
 //   - recomputes z from the roots so that the eigenvectors are orthogonal to working precision
 //     whatever the last bits of the roots are (Gu and Eisenstat 1994),
 //   - multiplies the block's eigenvectors with those of the merge on the matrix cores (fp32).
@@ -434,7 +433,7 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
             const float gap = last ? 1.00001f * rho : p2.x - pk.x;       // |z| <= 1
             const float half = 0.5f * gap;
             // this thread's poles stay in registers for all iterations
-            float fm = 0.f;
+            float fm = 0.f, dm = 0.f, hm = 0.f;     // at the middle of the gap: value, first and half the second derivative
 #pragma unroll
             for (int c = 0; c < PP; c += 4) {
                 if (c * TPE < trip) {
@@ -443,13 +442,20 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
                     dl[c] = q0.x, dl[c + 1] = q0.z, dl[c + 2] = q1.x, dl[c + 3] = q1.z;
                     z2[c] = q0.y, z2[c + 1] = q0.w, z2[c + 2] = q1.y, z2[c + 3] = q1.w;
 #pragma unroll
-                    for (int i = c; i < c + 4; ++i) fm = fmaf(z2[i], __builtin_amdgcn_rcpf((dl[i] - pk.x) - half), fm);
+                    for (int i = c; i < c + 4; ++i) {
+                        const float r = __builtin_amdgcn_rcpf((dl[i] - pk.x) - half), w = z2[i] * r, wr = w * r;
+                        fm += w;
+                        dm += wr;
+                        hm = fmaf(wr, r, hm);
+                    }
                 } else {
 #pragma unroll
                     for (int i = c; i < c + 4; ++i) dl[i] = kDcFar, z2[i] = 0.f;
                 }
             }
             fm = dc_sum<TPE>(fm) + rinv;
+            dm = dc_sum<TPE>(dm);
+            hm = dc_sum<TPE>(hm);
             const bool right = !last && fm < 0.f;
             dorg = right ? p2.x : pk.x;
             // the pole at the origin leaves the sums: its term is known exactly, and near a root that almost
@@ -467,62 +473,71 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
             }
             float lb = last ? (fm < 0.f ? half : 0.f) : (right ? -half : 0.f);
             float ub = last ? (fm < 0.f ? gap : half) : (right ? 0.f : half);
-            const float D1 = p1.x - dorg, D2 = p2.x - dorg;
-            const float Do = right || last ? D1 : D2;           // the other pole of the interpolation
+            const float Do = (right || last ? p1.x : p2.x) - dorg;      // the other pole of the interpolation
+            const float rDo = __builtin_amdgcn_rcpf(Do);
             const float sgn = last ? -1.f : 1.f;
+            // The root of c + s / (Do - x) - so / x = 0, where c + s / (Do - x) - (so - zo) / x has the value R, the derivative dR and half
+            // the second derivative hR that 1/rho and the terms of all poles but the origin have at `at` (Gragg 1965 for two poles;
+            // third order).  Every pole's share of s and of so - zo is positive, right of all poles excepted, where so = zo, exact,
+            // and Do takes the whole derivative.  Written in x and with `at` for Do - d, so that nothing cancels however near the
+            // root is to the origin.  Evaluations, largest of a level's roots, added over the levels, in float32 on the CPU, full-rank, decaying and
+            // rank-deficient covariances of 8 / 16 / 32 / 64 / 128 rows: fixed weight and middle way in turn (second order), from a start
+            // without derivatives, 4.1 / 8.3 / 13.9 / 19.1 / 25.8, this 2.8 / 5.8 / 9.2 / 13.5 / 17.7; of 6000 merges with random poles and weights
+            // down to 1e-12 none took more than 8 (before: 11).  us per launch: 512 x 32x32 35.1 -> 33.3, 16384 x 32x32 273 -> 261,
+            // 256 x 64x64 66.2 -> 64.1, 256 x 128x128 155 -> 151.
+            // From the start, where x is far from a root next to an origin of small weight, so - zo is left out if it swamps zo (24 rows of rank 18
+            // took 13.1 evaluations with it, 9.0 without, 12.6 before).
+            auto interpolate = [&](bool start, float at, float R, float dR, float hR) {
+                const float d = Do - at;
+                float side = fmaxf(at * fmaf(-d, hR, dR) * rDo, 0.f);                  // (so - zo) / at^2
+                if (start) side = side * at * at > 128.f * zo ? 0.f : side;
+                const float rest = fmaxf(dR - side, 0.f);
+                const float sa = side * at, rd = rest * d;
+                const float so = fmaf(sa, at, zo);
+                const float c = sa + (R - rd);
+                const float a = fmaf(Do, sa + R, fmaf(-rd, at, so));
+                return dc_quadratic(0.5f * a, so * Do, c, sgn);
+            };
             {
                 const float at = right ? -half : half;
-                const float c = fm - p1.y * __builtin_amdgcn_rcpf(D1 - at) - p2.y * __builtin_amdgcn_rcpf(D2 - at);
-                const float a = fmaf(c, D1 + D2, p1.y + p2.y);
-                const float b = fmaf(c * D1, D2, fmaf(p1.y, D2, p2.y * D1));
-                const float x = dc_quadratic(0.5f * a, b, c, sgn);
+                const float r = __builtin_amdgcn_rcpf(at), w = zo * r;              // less the term of the origin, -zo / at
+                const float x = interpolate(true, at, fm + w, fmaf(-w, r, dm), fmaf(w * r, r, hm));
                 mu = (x > lb && x < ub) ? x : 0.5f * (lb + ub);
             }
             bool open = many;
             int it = 0;
             for (; it < kDcMaxIter && __ballot(open) != 0; ++it) {
-                float F = 0.f, dF = 0.f, N1 = 0.f, dN = 0.f;       // sums over all other poles, over the terms below zero
+                float F = 0.f, mag = 0.f, dF = 0.f, hF = 0.f;       // over all poles but the origin
 #pragma unroll
                 for (int c = 0; c < PP; c += 4) {
                     if (c * TPE < trip) {
 #pragma unroll
                         for (int i = c; i < c + 4; ++i) {
                             const float r = __builtin_amdgcn_rcpf(dl[i] - mu);
-                            const float w = z2[i] * r, wn = fminf(w, 0.f);
+                            const float w = z2[i] * r, wr = w * r;
                             F += w;
-                            N1 += wn;
-                            dF = fmaf(w, r, dF);
-                            dN = fmaf(wn, r, dN);
+                            mag += fabsf(w);
+                            dF += wr;
+                            hF = fmaf(wr, r, hF);
                         }
                     }
                 }
                 F = dc_sum<TPE>(F);
-                N1 = dc_sum<TPE>(N1);
+                mag = dc_sum<TPE>(mag);
                 dF = dc_sum<TPE>(dF);
-                dN = dc_sum<TPE>(dN);
+                hF = dc_sum<TPE>(hF);
                 const float own = zo * __builtin_amdgcn_rcpf(mu);
-                const float mag = (F - 2.f * N1) + (fabsf(own) + rinv);    // sum of the magnitudes
+                mag += fabsf(own) + rinv;
                 const float R = F + rinv;
                 F = R - own;
                 const float err = fmaf(2.3841858e-7f, mag, 5.9604645e-8f * fabsf(mu) * dF);
                 lb = F < 0.f ? mu : lb;
                 ub = F < 0.f ? ub : mu;
-                // c + s / (Do - x) - so / x through value and derivative at mu.  Two steps with so = zo, exact,
-                // where Do takes the derivative of all the rest (fixed weight), two where so also takes the poles on
-                // the origin's side (middle way), and so on: each alone has cases in which it halves its
-                // way to the root.  Written in x and with mu for Do - d, so that nothing cancels however
-                // near the root is to the pole: with the equation for x - mu, repeated eigenvalues (24 rows of
-                // rank 18) took up to 19 iterations, now 8; the most for any of 1.1e7 roots emulated on the CPU is 17.
-                const float d = Do - mu;
-                const float side = (it & 2) && !last ? (right ? dF - dN : dN) : 0.f, rest = dF - side;
-                const float so = fmaf(side * mu, mu, zo);
-                const float c = fmaf(side, mu, fmaf(-rest, d, R));
-                const float a = fmaf(Do, fmaf(side, mu, R), fmaf(-rest * d, mu, so));
-                const float x = dc_quadratic(0.5f * a, so * Do, c, sgn);
+                const float x = interpolate(false, mu, R, dF, hF);
                 const bool ok = x > lb && x < ub;               // mu is one of the two
-                // interpolation converges quadratically in the step over the distance of the nearer
-                // pole: below 2^-12 of it the next step would be below the rounding of mu
-                const bool small = ok && fabsf(x - mu) <= 2.4414062e-4f * fminf(fabsf(mu), fabsf(d));
+                // the next error is of the order of the cube of this step over the distance of the nearer pole: below 2^-9 of
+                // it the next step would be below the rounding of mu
+                const bool small = ok && fabsf(x - mu) <= 1.953125e-3f * fminf(fabsf(mu), fabsf(Do - mu));
                 const float y = ok ? x : 0.5f * (lb + ub);
                 const bool step = open && !(fabsf(F) <= err) && y > lb && y < ub;
                 mu = step ? y : mu;
