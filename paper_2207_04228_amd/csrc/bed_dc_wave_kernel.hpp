@@ -35,17 +35,27 @@ __global__ __launch_bounds__(64) void dc_wave_kernel(KernelArgs args) {
         __builtin_amdgcn_wave_barrier();
     };
 
-    // P stays in registers as the left operand of the last product: pa[s] = P[lane % R][KT s + lane / R]
+    // P stays in registers as the left operand of the last product: pa[s] = P[lane % R][KT s + lane / R].  The columns from n on meet
+    // rows of V that are zero.
     float pa[WANT_V ? KS : 1];
-    if constexpr (WANT_V) {
-        tridiag_half<N, SLD>(args.A + (size_t)b * n * n, n, lane, stage, sP, inv_scale, clk);
+    {
+        float x[N];
+        tridiag_rows<N, SLD, WANT_V>(args.A + (size_t)b * n * n, n, lane, stage, sP, inv_scale, x, clk);
+        if constexpr (WANT_V) {
+            // row r of P is in lane 32 + r
+            auto upper = [](float a, float c) {          // of a below, of c above
+                return __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false, false)[1];
+            };
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const int k = KT * s + hi;
-            pa[s] = k < n ? stage[k * SLD + lo] : 0.f;
+            for (int s = 0; s < KS; ++s) {
+                if constexpr (KT == 2) {
+                    pa[s] = __uint_as_float(upper(x[2 * s], x[2 * s + 1]));
+                } else {
+                    const unsigned even = upper(x[4 * s], x[4 * s + 2]), odd = upper(x[4 * s + 1], x[4 * s + 3]);
+                    pa[s] = __uint_as_float(__builtin_amdgcn_permlane16_swap(even, odd, false, false)[0]);
+                }
+            }
         }
-    } else {
-        tridiag_values<N, SLD>(args.A + (size_t)b * n * n, n, lane, stage, sP, inv_scale);
     }
     sync();
 

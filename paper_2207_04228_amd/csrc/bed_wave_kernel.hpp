@@ -20,155 +20,11 @@
 
 #include "bed_jacobi.hpp"
 #include "bed_kernel.h"
+#include "bed_row_tridiag.hpp"
 
 namespace bed {
 
-// Cycle counts per phase of one wavefront's work, for the phase-resolved profile
-// (paper_2207_04228_amd/phase_profile.py builds a separate library with BED_PHASE_CLOCKS defined).
-// In the product build every member is an empty inline function and the object holds nothing.
-enum Phase { kPhLoad = 0, kPhTridiag, kPhBoundary, kPhFill, kPhSteady, kPhDrain, kPhStore, kPhIterations, kPhCount };
-struct PhaseClock {
-#ifdef BED_PHASE_CLOCKS
-    unsigned long long last;
-    unsigned long long acc[kPhCount];
-    __device__ __forceinline__ void start() {
-        for (int i = 0; i < kPhCount; ++i) acc[i] = 0;
-        last = __builtin_readcyclecounter();
-    }
-    __device__ __forceinline__ void lap(int phase) {
-        const unsigned long long t = __builtin_readcyclecounter();
-        acc[phase] += t - last;
-        last = t;
-    }
-    __device__ __forceinline__ void count(int phase) { acc[phase] += 1; }
-    __device__ __forceinline__ void write(unsigned long long* out, int b, int lane) const {
-        if (out && lane == 0)
-            for (int i = 0; i < kPhCount; ++i) out[(size_t)b * kPhCount + i] = acc[i];
-    }
-#else
-    __device__ __forceinline__ void start() {}
-    __device__ __forceinline__ void lap(int) {}
-    __device__ __forceinline__ void count(int) {}
-    __device__ __forceinline__ void write(unsigned long long*, int, int) const {}
-#endif
-};
-
 namespace {
-
-// Relative deflation tolerance: |e_k| <= kEps (|d_k| + |d_k+1|), kEps = 4 * 2^-23.  Inside a
-// cluster of (nearly) equal eigenvalues the recurrence leaves off-diagonals at the rounding
-// level of the diagonal, one to two units in the last place of d; a tolerance of 2^-23 is only
-// two such units when d is just above a power of two, and windows of repeated eigenvalues then
-// hover around it without ever deflating.
-constexpr float kEps = 4.7683716e-7f;
-// The pair of sweeps with both eigenvalues of the trailing block has fixed points (the 3x3
-// matrix with diagonal 1, 0, 1 and off-diagonals 1 is mapped onto itself up to signs), as the
-// double-shift QR step has in general.  After this many iterations without any deflation both
-// sweeps use the eigenvalue closer to the last diagonal entry, which leaves such a point.
-constexpr uint32_t kExceptionalAfter = 5;
-constexpr uint32_t kStallIterations = 12;   // iterations without any deflation before the absolute threshold applies
-constexpr float kAbsTol1 = 2.3841858e-7f;   // 2^-22 of the pre-scaled matrix
-constexpr float kAbsTol2 = 9.5367432e-7f;   // 2^-20
-constexpr float kTinyE = 1.0e-18f;      // absolute floor for |e| (matrix is pre-scaled to max|a| in [0.5,1))
-constexpr float kTinyG = 1.0e-18f;      // floor for |g| in a rotation (keeps f^2+g^2 a normal number)
-constexpr float kTinyAlpha = 1.0e-35f;  // |x|^2 below this: column already reduced, reflector skipped
-
-// ---- cross-lane helpers ---------------------------------------------------
-
-template <int CTRL, int ROW_MASK = 0xF>
-__device__ __forceinline__ float dpp0(float x) {
-    // lanes not selected by ROW_MASK (or reading out of range) receive 0
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xF, false));
-}
-
-constexpr int kQuadXor1 = 0xB1;       // quad_perm [1,0,3,2]
-constexpr int kQuadXor2 = 0x4E;       // quad_perm [2,3,0,1]
-constexpr int kRowHalfMirror = 0x141;
-constexpr int kRowMirror = 0x140;
-constexpr int kRowBcast15 = 0x142;    // lane 15 of each row -> every lane of the next row
-constexpr int kRowBcast31 = 0x143;    // lane 31 -> every lane of rows 2 and 3
-
-// A workgroup is one wavefront, and a wavefront's LDS operations complete in
-// program order, so data written to LDS by one lane is visible to a later read
-// by another lane without a hardware barrier.  This only stops the compiler
-// from moving memory operations across the point.
-__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
-
-__device__ __forceinline__ float read_lane(float x, int lane_uniform) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane_uniform));
-}
-
-// Lanes 0..31 keep `keep`; lane 32 + i receives the value lane i holds in `src`
-// (v_permlane32_swap exchanges the upper half of its first operand with the lower half of
-// its second; the first result is the first operand after the exchange).
-__device__ __forceinline__ float upper_from_lower(float keep, float src) {
-    return __uint_as_float(
-        __builtin_amdgcn_permlane32_swap(__float_as_uint(keep), __float_as_uint(src), false, false)[0]);
-}
-
-// Every lane receives the value lane 32 + (i & 31) holds: the second result of the same
-// exchange applied to two copies of x is x with its upper half copied over its lower half.
-__device__ __forceinline__ float from_upper_half(float x) {
-    const unsigned u = __float_as_uint(x);
-    return __uint_as_float(__builtin_amdgcn_permlane32_swap(u, u, false, false)[1]);
-}
-
-// Lanes 0..31 keep `keep`; lanes 32..63 receive the value lane 31 holds in `src`
-// (DPP row_bcast31 restricted to rows 2 and 3): one instruction hands a value that is
-// uniform over the lower half to the upper half.
-__device__ __forceinline__ float upper_from_lane31(float keep, float src) {
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(__float_as_int(keep), __float_as_int(src), kRowBcast31, 0xC, 0xF, false));
-}
-
-// Sum over lanes [0, W) of the wave (W = 8, 16, 32 or 64, lanes outside must
-// hold 0 or are ignored), returned as a wave-uniform value.  Quad butterflies,
-// then mirrors (which act as xor 4 / xor 8 on quad-uniform values), then row
-// broadcasts; no LDS traffic.
-template <int W>
-__device__ __forceinline__ float wave_sum(float x) {
-    x += dpp0<kQuadXor1>(x);
-    x += dpp0<kQuadXor2>(x);
-    x += dpp0<kRowHalfMirror>(x);
-    if (W >= 16) x += dpp0<kRowMirror>(x);
-    if (W <= 16) return read_lane(x, 0);
-    x += dpp0<kRowBcast15, 0xA>(x);
-    if (W == 32) return read_lane(x, 31);
-    x += dpp0<kRowBcast31, 0xC>(x);
-    return read_lane(x, 63);
-}
-
-// Same for max of non-negative values.
-template <int W>
-__device__ __forceinline__ float wave_max_nonneg(float x) {
-    x = fmaxf(x, dpp0<kQuadXor1>(x));
-    x = fmaxf(x, dpp0<kQuadXor2>(x));
-    x = fmaxf(x, dpp0<kRowHalfMirror>(x));
-    if (W >= 16) x = fmaxf(x, dpp0<kRowMirror>(x));
-    if (W <= 16) return read_lane(x, 0);
-    x = fmaxf(x, dpp0<kRowBcast15, 0xA>(x));
-    if (W == 32) return read_lane(x, 31);
-    x = fmaxf(x, dpp0<kRowBcast31, 0xC>(x));
-    return read_lane(x, 63);
-}
-
-constexpr int lanes_for(int n) { return n <= 8 ? 8 : (n <= 16 ? 16 : (n <= 32 ? 32 : 64)); }
-
-// Monotone map float -> uint32 (total order; NaNs land at the ends).
-__device__ __forceinline__ uint32_t sort_key(float x) {
-    uint32_t u = __float_as_uint(x);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// exact power-of-two scale bringing amax into [0.5, 1); 1 for 0 / non-finite
-__device__ __forceinline__ void pow2_scale(float amax, float& scale, float& inv_scale) {
-    int ex = 0;
-    if (amax > 0.f && amax < __builtin_inff()) ex = __builtin_amdgcn_frexp_expf(amax);
-    ex = min(max(ex, -125), 126);
-    scale = ldexpf(1.0f, -ex);
-    inv_scale = ldexpf(1.0f, ex);
-}
-
 
 // ---- one sweep's running state (all values are wave-uniform except x) ------
 // Implicit shifted QR step written as a chain of Givens rotations (App. A.1):
@@ -587,167 +443,6 @@ __device__ __forceinline__ void qr_iterations(float2* const sP, float* const sV,
 }
 
 // ---------------------------------------------------------------------------
-// Load, power-of-two pre-scaling and Householder tridiagonalisation (Sec. 3.1) in one wavefront.
-// On return sP holds T (sP[k] = (e[k-1], d[k])), sV (column-major, stride LD) the reflector
-// product P when it is wanted, and inv_scale undoes the scaling.  sV is also the staging buffer.
-// ---------------------------------------------------------------------------
-template <int N, int LD>
-__device__ __forceinline__ void tridiag_half(const float* __restrict__ Ab, const int n, const int lane, float* const sV,
-                                             float2* const sP, float& inv_scale, PhaseClock& clk) {
-    // ---- rows fit in half a wavefront and P is wanted: the lower half holds the rows of
-    // the working matrix, the upper half the rows of the accumulated reflector product
-    // P (Eq. (8)).  One instruction stream serves both: the dot product with u gives
-    // p = 2Au/|u|^2 in the lower half and w = 2Pu/|u|^2 in the upper half, and the update
-    // x <- x - q u^T is the first half of the rank-2 update of A (q = p - K u) and the whole
-    // rank-1 update of P (q = w); the second half, x <- x - u q^T, runs with u = 0 in the
-    // upper half.
-    constexpr int W = lanes_for(N);
-    const int row = lane & 31;
-    const bool roleP = lane >= 32;
-    const int arow = roleP ? -1 : row;         // row index for the selections on A; none for the P lanes
-    float x[N];
-    const float rcp_n = 1.0f / (float)n;
-    chunked_copy<copy_chunk(N * N)>(
-        n * n, lane, [&](int idx) { return Ab[idx]; },
-        [&](int idx, float x) {
-            const int i = (int)(((float)idx + 0.5f) * rcp_n);
-            sV[i * LD + (idx - i * n)] = x;
-        });
-    wave_sync();
-    float amax = 0.f;
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-        float aval = 0.f;
-        if (row < n && c < n) aval = (c <= row) ? sV[row * LD + c] : sV[c * LD + row];
-        amax = fmaxf(amax, fabsf(aval));   // fmaxf drops NaNs; they still reach the output through the arithmetic
-        x[c] = roleP ? ((c == row) ? 1.f : 0.f) : aval;
-    }
-    wave_sync();
-    float scale;
-    pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
-    const float myscale = roleP ? 1.f : scale;
-#pragma unroll
-    for (int c = 0; c < N; ++c) x[c] *= myscale;
-    clk.lap(kPhLoad);
-#pragma unroll
-    for (int J = 0; J < N; ++J) {
-        const float dJ = read_lane(x[J], J);      // final once columns 0..J-1 are reduced
-        float eJ = 0.f;
-        if (J < N - 1) {
-            const float x0 = read_lane(x[J], J + 1);     // A[J+1][J]
-            eJ = x0;                                      // kept as is when no reflector is applied
-            if (J < N - 2) {
-                const float xc = (arow > J) ? x[J] : 0.f; // A[r][J], r > J
-                const float alpha = wave_sum<W>(xc * xc); // |x|^2 (the sum reads the lower half only)
-                const bool active = (J < n - 2) && (alpha > kTinyAlpha);
-                const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                const float sigma = (x0 < 0.f) ? -nrm : nrm;   // sign chosen to avoid cancellation
-                float ur = (arow == J + 1) ? (x0 + sigma) : ((arow > J + 1) ? xc : 0.f);
-                ur = active ? ur : 0.f;
-                const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
-                eJ = active ? -sigma : x0;
-                // u and p are broadcast with v_readlane (the entries live in lanes 0..31; the
-                // results are scalars that the FMAs take as operands): no LDS round trip and no
-                // barrier in the whole reduction
-                float u[N];
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) u[c] = read_lane(ur, c);
-                float pp[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) pp[c & 3] = fmaf(x[c], u[c], pp[c & 3]);
-                const float pw = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));     // p (A lanes), w (P lanes)
-                // A - q u^T - u q^T with q = p - K u, K = u^T p / |u|^2, regrouped as
-                // A - (p - 2K u) u^T - u p^T: the broadcast of p does not wait for K.
-                const float K2 = beta * wave_sum<W>(ur * pw);                    // 2K
-                const float sr = fmaf(-K2, ur, pw);       // p - 2K u; stays w in the P lanes (u = 0 there)
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) x[c] = fmaf(-ur, read_lane(pw, c), fmaf(-sr, u[c], x[c]));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        if (lane == 0) {
-            sP[J].y = dJ;
-            sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
-        }
-    }
-    if (lane == 0) sP[0].x = 0.f;
-    // every lane stores the P lanes' row (the upper half's value copied over the lower half)
-#pragma unroll
-    for (int c = 0; c < N; ++c) sV[c * LD + row] = from_upper_half(x[c]);
-    wave_sync();
-}
-
-// The same reduction without P, n <= 32 (wave_kernel keeps its own copy of these lines: with arrays of 40
-// and more rows the compiler spills 250 registers when they come from a function).
-template <int N, int LD>
-__device__ __forceinline__ void tridiag_values(const float* __restrict__ Ab, const int n, const int lane,
-                                               float* const stage, float2* const sP, float& inv_scale) {
-    static_assert(N <= 32, "rows in half a wavefront");
-    constexpr int W = lanes_for(N);
-    const int row = lane & 31;
-    float a[N];
-    const float rcp_n = 1.0f / (float)n;
-    chunked_copy<copy_chunk(N * N)>(
-        n * n, lane, [&](int idx) { return Ab[idx]; },
-        [&](int idx, float x) {
-            const int i = (int)(((float)idx + 0.5f) * rcp_n);
-            stage[i * LD + (idx - i * n)] = x;
-        });
-    wave_sync();
-    float amax = 0.f;
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-        float x = 0.f;
-        if (row < n && c < n) x = (c <= row) ? stage[row * LD + c] : stage[c * LD + row];
-        a[c] = x;
-        amax = fmaxf(amax, fabsf(x));
-    }
-    wave_sync();
-    float scale;
-    pow2_scale(wave_max_nonneg<W>(amax), scale, inv_scale);
-#pragma unroll
-    for (int c = 0; c < N; ++c) a[c] *= scale;
-#pragma unroll
-    for (int J = 0; J < N; ++J) {
-        const float dJ = read_lane(a[J], J);
-        float eJ = 0.f;
-        if (J < N - 1) {
-            const float x0 = read_lane(a[J], J + 1);
-            eJ = x0;
-            if (J < N - 2) {
-                const float x = (row > J) ? a[J] : 0.f;
-                const float alpha = wave_sum<W>(x * x);
-                const bool active = (J < n - 2) && (alpha > kTinyAlpha);
-                const float nrm = __builtin_amdgcn_sqrtf(alpha);
-                const float sigma = (x0 < 0.f) ? -nrm : nrm;
-                float ur = (row == J + 1) ? (x0 + sigma) : ((row > J + 1) ? x : 0.f);
-                ur = active ? ur : 0.f;
-                const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;
-                eJ = active ? -sigma : x0;
-                float u[N];
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) u[c] = read_lane(ur, c);
-                float pp[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) pp[c & 3] = fmaf(a[c], u[c], pp[c & 3]);
-                const float p = beta * ((pp[0] + pp[1]) + (pp[2] + pp[3]));
-                const float K2 = beta * wave_sum<W>(ur * p);
-                const float sr = fmaf(-K2, ur, p);
-#pragma unroll
-                for (int c = J + 1; c < N; ++c) a[c] = fmaf(-ur, read_lane(p, c), fmaf(-sr, u[c], a[c]));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        if (lane == 0) {
-            sP[J].y = dJ;
-            sP[J + 1].x = (J < n - 1) ? eJ : 0.f;
-        }
-    }
-    if (lane == 0) sP[0].x = 0.f;
-    wave_sync();
-}
-
-// ---------------------------------------------------------------------------
 // N      register-array size (4, 8, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64); n <= N at run time
 // WANT_V accumulate eigenvectors
 // STAGE  kFull, kTridiagOnly (stage hook 1), kQrOnly (stage hook 2), kQrPartial (stage hook 3:
@@ -791,9 +486,16 @@ __global__ __launch_bounds__(64) void wave_kernel(KernelArgs args) {
     clk.start();
 
     constexpr bool GIVEN_T = (STAGE == kQrOnly || STAGE == kQrPartial);
-    if (!GIVEN_T && HALF && WANT_V) {
-        tridiag_half<N, LD>(args.A + (size_t)b * n * n, n, lane, sV, sP, inv_scale, clk);
-    } else if (!GIVEN_T) {
+    if constexpr (!GIVEN_T && HALF) {
+        float x[N];
+        tridiag_rows<N, LD, WANT_V>(args.A + (size_t)b * n * n, n, lane, sV, sP, inv_scale, x, clk);
+        if (WANT_V) {
+            // every lane stores the P lanes' row (the upper half's value copied over the lower half)
+#pragma unroll
+            for (int c = 0; c < N; ++c) sV[c * LD + row] = from_upper_half(x[c]);
+            wave_sync();
+        }
+    } else if constexpr (!GIVEN_T) {
         float a[N];
         float v[N];
 #pragma unroll
@@ -853,19 +555,16 @@ __global__ __launch_bounds__(64) void wave_kernel(KernelArgs args) {
                     ur = active ? ur : 0.f;
                     const float beta = active ? __builtin_amdgcn_rcpf(fmaf(fabsf(x0), nrm, alpha)) : 0.f;  // 2/|u|^2
                     eJ = active ? -sigma : x0;
-                    // Up to 32 rows, u and p are broadcast with v_readlane (scalar operands of the
-                    // FMAs); beyond, through LDS (one write, then 128-bit reads of one address).
-                    constexpr bool RL = (N <= 32);
-                    if (!RL) svec[lane] = ur;
+                    svec[lane] = ur;
                     if (WANT_V && J > 0) {
                         // deferred: V <- V - w u^T of step J-1 (columns J .. N-1)
 #pragma unroll
                         for (int c = J; c < N; ++c) v[c] = fmaf(-wd, ud[c], v[c]);
                     }
-                    if (!RL) __syncthreads();
+                    __syncthreads();
                     float u[N];
 #pragma unroll
-                    for (int c = J + 1; c < N; ++c) u[c] = RL ? read_lane(ur, c) : svec[c];
+                    for (int c = J + 1; c < N; ++c) u[c] = svec[c];
                     // p = 2 A u / |u|^2, w = 2 V u / |u|^2; four partial sums each
                     float pp[4] = {0.f, 0.f, 0.f, 0.f}, ww[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -877,15 +576,15 @@ __global__ __launch_bounds__(64) void wave_kernel(KernelArgs args) {
                     wd = beta * ((ww[0] + ww[1]) + (ww[2] + ww[3]));
                     // A - q u^T - u q^T with q = p - K u, regrouped as A - (p - 2K u) u^T - u p^T
                     // (p is broadcast before K is known; same arithmetic as the role-lane variant)
-                    if (!RL) sq[lane] = p;
+                    sq[lane] = p;
                     const float K2 = beta * wave_sum<W>(ur * p);  // 2K
                     const float sr = fmaf(-K2, ur, p);
 #pragma unroll
                     for (int c = J + 1; c < N; ++c) a[c] = fmaf(-sr, u[c], a[c]);
-                    if (!RL) __syncthreads();
+                    __syncthreads();
 #pragma unroll
                     for (int c = J + 1; c < N; ++c) {
-                        a[c] = fmaf(-ur, RL ? read_lane(p, c) : sq[c], a[c]);
+                        a[c] = fmaf(-ur, sq[c], a[c]);
                         ud[c] = u[c];
                     }
                     // keep the steps apart: interleaving them makes the compiler hoist the next
