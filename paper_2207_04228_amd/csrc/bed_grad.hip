@@ -12,8 +12,8 @@
 //
 // The three (four) n x n x n products are dense contractions and run on the fp32 matrix instructions (full fp32
 // operands and accumulation).  Up to 32 rows one wavefront owns a matrix (or several) and every intermediate product
-// stays in the accumulators (tile_grad_kernel); beyond, four or eight wavefronts exchange them through LDS
-// (grad_kernel).
+// stays in the accumulators (tile_grad_kernel); beyond, a wavefront owns 16 columns of every product and LDS holds the other
+// operand (grad_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,72 +28,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
-// Operand and result layout of v_mfma_f32_32x32x2_f32 (A is 32x2, B is 2x32, D is 32x32):
-//   A: lane l holds A[l % 32][l / 32]
-//   B: lane l holds B[l / 32][l % 32]
-//   D: register v (0..15) of lane l holds D[8 * (v / 4) + 4 * (l / 32) + v % 4][l % 32]
+// Register v of lane l of a result of v_mfma_f32_32x32x2_f32 is in row acc_row(v, l), column l % 32.
 __device__ __forceinline__ int acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
-
-// Tiles of one wavefront: all NT x NT of them when it works alone, else one tile row and every JSTEP-th
-// tile column.
-template <int NT, int NWV>
-struct Tiles {
-    static_assert(NWV == 1 || NWV % NT == 0, "a wavefront owns tiles of one row");
-    static constexpr int TI = NWV == 1 ? NT : 1;
-    static constexpr int JSTEP = NWV == 1 ? 1 : NWV / NT;
-    static constexpr int TJ = NT / JSTEP;
-    static constexpr int LD = 32 * NT + 1;
-    int wv;
-    __device__ __forceinline__ int row(int ti) const { return NWV == 1 ? ti : wv % NT; }
-    __device__ __forceinline__ int col(int tj) const { return NWV == 1 ? tj : wv / NT + tj * JSTEP; }
-
-    // acc = sum_k X[i][k] * Y[k][j] over k < kdim (a multiple of 8; entries from n on are zero).
-    // XT / YT: the operand is stored transposed in its LDS buffer.  Four k steps of operands are read
-    // before their matrix instructions: one at a time, every instruction waits for LDS.
-    template <bool XT, bool YT>
-    __device__ __forceinline__ void product(floatx16 (&acc)[TI][TJ], const float* X, const float* Y, int kdim,
-                                            int lane) const {
-        const int lo = lane & 31, hi = lane >> 5;
-#pragma unroll
-        for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-            for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = floatx16{};
-        for (int k0 = 0; k0 < kdim; k0 += 8) {
-            float a[TI][4], b[TJ][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = k0 + 2 * u + hi;
-#pragma unroll
-                for (int t = 0; t < TI; ++t) {
-                    const int r = 32 * row(t) + lo;
-                    a[t][u] = XT ? X[k * LD + r] : X[r * LD + k];
-                }
-#pragma unroll
-                for (int t = 0; t < TJ; ++t) {
-                    const int r = 32 * col(t) + lo;
-                    b[t][u] = YT ? Y[r * LD + k] : Y[k * LD + r];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < TJ; ++tj)
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ti][u], b[tj][u], acc[ti][tj], 0, 0, 0);
-        }
-    }
-
-    __device__ __forceinline__ void spill(const floatx16 (&acc)[TI][TJ], float* dst, int lane) const {
-#pragma unroll
-        for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-            for (int tj = 0; tj < TJ; ++tj)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    dst[(32 * row(ti) + acc_row(v, lane)) * LD + 32 * col(tj) + (lane & 31)] = acc[ti][tj][v];
-    }
-};
 
 // 1 / x: the hardware reciprocal (one unit in the last place) and one Newton step; the division itself
 // where one of the two would leave the normal range
@@ -376,191 +312,269 @@ __global__ __launch_bounds__(64) void tile_spectral_kernel(KernelArgs args) {
 }
 
 // ---- n > 32 ----
-// NT tiles of 32 per side (2: n <= 64, 4: n <= 128); NWV wavefronts per matrix.  Operands are staged in LDS with an odd
-// row stride so that row and column (transposed) operand reads are both conflict-free, and every product's result is
-// written back to LDS in row-major order to become an operand of the next one.
-// The floor of a large batch is the matrix cores' fp32 rate (n = 128: 16 tiles x 64 steps x 64 cycles x 4
-// products on four of them = 27 us a matrix and compute unit); a small one is bound by the
-// serial path of loads, four products and the exchange between them, which is why operands are read four steps
-// ahead, the inputs eight loads at a time, and a matrix of n > 32 gets four or eight wavefronts.
-template <int NT, int NWV>
-__global__ __launch_bounds__(64 * NWV) void grad_kernel(GradArgs args) {
-    using Own = Tiles<NT, NWV>;
-    constexpr int NP = 32 * NT;
-    constexpr int LD = NP + 1;
-    constexpr int TI = Own::TI, TJ = Own::TJ;
-    constexpr int NTH = 64 * NWV;
-    __shared__ __align__(16) float sV[NP * LD];      // V, row-major, zero padded
-    __shared__ __align__(16) float sW[NP * LD];      // G, then the intermediate products
-    __shared__ float sL[NP];           // eigenvalues
-    __shared__ float sR[NP];           // their reciprocals; for a spectral function sqrt(max(lambda, floor))
-    __shared__ float sGl[NP];          // upstream gradient of the eigenvalues
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const Own own{tid >> 6};
-    const int b = blockIdx.x;
-    const int n = args.n;
-    const int kdim = (n + 7) & ~7;
-    const bool ed = (args.mode == kGradExact || args.mode == kGradTaylor);
-    auto sync = []() { __syncthreads(); };
-
-    {
-        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int idx = tid; idx < NP * LD / 4; idx += NTH) {
-            reinterpret_cast<float4*>(sV)[idx] = zero;
-            reinterpret_cast<float4*>(sW)[idx] = zero;
+// One workgroup per matrix, NT = ceil(n / 16) wavefronts: wavefront w owns columns 16 w .. 16 w + 15 of every product, in tiles of
+// v_mfma_f32_16x16x4.  Register v of lane l of tile t is the entry of row 16 t + 4 (l / 16) + v and column 16 w + l % 16, and as it stands
+// a right operand, so that a product's result is the next one's right operand without leaving the registers; the left operands
+// are rows in LDS, four contracted indices to a 128-bit read, which serves four matrix instructions.  With sym(G) formed before the
+// products, C = V^T (sym(G) V) is symmetric and nothing is exchanged before the last product, g_A = (V M) V^T: there the
+// wavefronts need each other's columns of V M.  It is symmetric too: a tile of it is formed once and stored twice.
+// Bound by the matrix cores for many large matrices (n = 128: 3.5 n^3 multiply-adds, 24 us a matrix and compute unit, after the
+// 10 us in which its bytes arrive), else by the chain of loads, products and barriers.
+// us per launch with 32 x 32 tiles, every product through LDS and up to 64 or 128 rows in one instantiation / this, the function's gradient
+// and the decomposition's: 256 x 36x36 9.4 / 7.2 and 8.6 / 7.7, 2048 x 48x48 43 / 27 and 37 / 26, 256 x 64x64 12.3 / 9.6 and 11.0 / 8.7,
+// 256 x 80x80 33.9 / 18.0 and 30.3 / 17.1, 8 x 100x100 37.7 / 29 and 34.6 / 27, 256 x 128x128 51 / 39.5 and 43 / 34.
+template <int NT>
+struct Strip {
+    static constexpr int NP = 16 * NT;
+    static constexpr int LD = NP + 4;     // rows start on 128 bits; 16 rows at the same four columns lie in 64 different banks
+    int w, i, g, n;
+    __device__ __forceinline__ explicit Strip(int n_)
+        : w(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)), i(threadIdx.x & 15), g((threadIdx.x >> 4) & 3), n(n_) {}
+    __device__ __forceinline__ int row(int t, int v) const { return 16 * t + 4 * g + v; }
+    __device__ __forceinline__ int col() const { return 16 * w + i; }
+    __device__ __forceinline__ bool inside(int t, int v) const { return row(t, v) < n && col() < n; }
+    // does n cut into tile t (the same in all lanes)?  Into the last of a row or column only.
+    __device__ __forceinline__ bool edge(int t) const { return (t == NT - 1 || w == NT - 1) && n < NP; }
+    // this lane's entries of a matrix in memory, zero outside
+    __device__ __forceinline__ void load(floatx4 (&x)[NT], const float* __restrict__ M) const {
+        const int at = 4 * g * n + col();
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[t][v] = M[min(at + (16 * t + v) * n, n * n - 1)];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            if (edge(t))
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[t][v] = inside(t, v) ? x[t][v] : 0.f;
+    }
+    // S[r][c] = X[r][c], and S[c][r] = X[r][c]
+    __device__ __forceinline__ void put(float* S, const floatx4 (&x)[NT]) const {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[row(t, v) * LD + col()] = x[t][v];
+    }
+    __device__ __forceinline__ void put_transposed(float* S, const floatx4 (&x)[NT]) const {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<floatx4*>(S + col() * LD + row(t, 0)) = x[t];
+    }
+    // S[16 r + i][the rows of tile t]: the left operand of its four steps
+    __device__ __forceinline__ floatx4 left(const float* S, int r, int t) const {
+        return *reinterpret_cast<const floatx4*>(S + (16 * r + i) * LD + row(t, 0));
+    }
+    static __device__ __forceinline__ floatx4 mfma(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    // out += S x
+    __device__ __forceinline__ void product(floatx4 (&out)[NT], const float* S, const floatx4 (&x)[NT]) const {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            floatx4 a[NT];
+#pragma unroll
+            for (int r = 0; r < NT; ++r) a[r] = left(S, r, t);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int r = 0; r < NT; ++r) out[r] = mfma(a[r][v], x[t][v], out[r]);
         }
     }
-    bool low = false;                  // an eigenvalue below the floor
+    // M = S x, which is symmetric: tile rows w, w + 1, ... (cyclic), every pair of strips once, and their mirror images (which turn in
+    // `turn`, rows 16 w .. 16 w + 15 of it, where they cannot be stored four columns at a time)
+    __device__ __forceinline__ void store_symmetric(float* __restrict__ M, const float* S, const floatx4 (&x)[NT], float* turn) const {
+        // rows start on 128 bits
+        const bool aligned = n % 4 == 0 && (reinterpret_cast<uintptr_t>(M) & 15) == 0;
+        constexpr int ND = NT / 2 + 1;
+        const bool opposite = NT % 2 || w < NT / 2;                // of a pair half way round, the first
+        floatx4 out[ND] = {};
+        int rows[ND];
+#pragma unroll
+        for (int d = 0; d < ND; ++d) rows[d] = w + d < NT ? w + d : w + d - NT;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            floatx4 a[ND];
+#pragma unroll
+            for (int d = 0; d < ND; ++d) a[d] = left(S, rows[d], t);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+                    if (d < ND - 1 || opposite) out[d] = mfma(a[d][v], x[t][v], out[d]);
+        }
+        auto formed = [&](int d) { return d < ND - 1 || opposite; };
+        const int c = col();
+        if (!aligned) {
+#pragma unroll
+            for (int d = 1; d < ND; ++d)
+                if (formed(d)) *reinterpret_cast<floatx4*>(turn + c * LD + row(rows[d], 0)) = out[d];
+            wave_sync();
+        }
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            if (!formed(d)) continue;
+            const int r = row(rows[d], 0), at = 4 * g * n + c + 16 * rows[d] * n;       // r n + c
+            if (!edge(rows[d])) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) M[at + v * n] = out[d][v];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (r + v < n && c < n) M[at + v * n] = out[d][v];
+            }
+            // four columns at a time are inside or not
+            if (d > 0 && aligned && r < n && c < n) *reinterpret_cast<floatx4*>(M + c * n + r) = out[d];
+        }
+        if (!aligned) {
+#pragma unroll
+            for (int d = 1; d < ND; ++d) {
+                if (!formed(d)) continue;
+                const int mirrored = (16 * w + 4 * g) * n + 16 * rows[d] + i;
+                float m[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) m[v] = turn[row(w, v) * LD + 16 * rows[d] + i];
+                if (!edge(rows[d])) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) M[mirrored + v * n] = m[v];
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (row(w, v) < n && 16 * rows[d] + i < n) M[mirrored + v * n] = m[v];
+                }
+            }
+        }
+    }
+};
+
+// Wavefronts asked for on a SIMD: as many as LDS has room for up to 64 rows (with three, 2048 x 64x64 took 48.6 instead of 43.2 us).
+template <int NT>
+__global__ __launch_bounds__(64 * NT, NT == 3 ? 5 : NT == 4 ? 4 : 2) void grad_kernel(GradArgs args) {
+    using S = Strip<NT>;
+    constexpr int NP = S::NP;
+    __shared__ __align__(16) float sA[NP * S::LD];   // V^T, then V
+    __shared__ __align__(16) float sB[NP * S::LD];   // C^T; for a spectral function G^T and sym(G); then V M
+    __shared__ __align__(16) float sL[NP];           // eigenvalues
+    __shared__ __align__(16) float sR[NP];           // their reciprocals; for a spectral function sqrt(max(lambda, floor))
+    __shared__ float sGl[NP];                        // upstream gradient of the eigenvalues
+
+    const int tid = threadIdx.x, n = args.n;
+    const S own(n);
+    const size_t base = (size_t)blockIdx.x * n * n;
+    const bool ed = (args.mode == kGradExact || args.mode == kGradTaylor);
+
+    floatx4 vc[NT], gc[NT] = {}, c[NT] = {};
+    own.load(vc, args.evecs + base);
+    if (args.g_mat) own.load(gc, args.g_mat + base);  // the same in all lanes
+    bool low = false;                                 // an eigenvalue below the floor
     if (tid < NP) {
         const bool ok = tid < n;
-        const size_t at = (size_t)b * n + tid;
+        const size_t at = (size_t)blockIdx.x * n + tid;
         const float l = ok ? args.evals[at] : 0.f;
         sL[tid] = l;
         sR[tid] = ed ? (l != 0.f ? 1.0f / l : 0.f) : sqrtf(fmaxf(l, args.param));
         sGl[tid] = (ok && args.g_evals) ? args.g_evals[at] : 0.f;
         low = ok && !(l >= args.param);
     }
-    sync();
-    {
-        const float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
-        const float* __restrict__ Gb = args.g_mat ? args.g_mat + (size_t)b * n * n : nullptr;
-        const float rcp_n = 1.0f / (float)n;
-        const int total = n * n;
-        for (int base = tid; base < total; base += 8 * NTH) {
-            float v[8], g[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int idx = base + k * NTH;
-                v[k] = idx < total ? Vb[idx] : 0.f;
-                g[k] = (Gb && idx < total) ? Gb[idx] : 0.f;
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int idx = base + k * NTH;
-                const int i = (int)(((float)idx + 0.5f) * rcp_n);
-                const int at = i * LD + idx - i * n;
-                if (idx < total) {
-                    sV[at] = v[k];
-                    sW[at] = g[k];
-                }
-            }
-        }
-    }
+    own.put_transposed(sA, vc);
+    if (!ed) own.put_transposed(sB, gc);
     low = __syncthreads_or(low);
-
-    floatx16 acc[TI][TJ];
-    if (!ed) {
-        // spectral function: T = G V first, so that C = V^T G V
-        own.template product<false, false>(acc, sW, sV, kdim, lane);
-        sync();
-        own.spill(acc, sW, lane);
-        sync();
+    if (ed) {
+        if (args.g_mat) {
+            // C - C^T
+            own.product(c, sA, gc);
+            own.put_transposed(sB, c);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[t][v] -= sB[own.row(t, v) * S::LD + own.col()];
+        }
+    } else {
+        floatx4 T[NT] = {};
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gc[t][v] = 0.5f * (gc[t][v] + sB[own.row(t, v) * S::LD + own.col()]);
+        __syncthreads();
+        own.put_transposed(sB, gc);
+        __syncthreads();
+        own.product(T, sB, vc);
+        own.product(c, sA, T);
     }
-    // C = V^T T  (T = g_V for the eigendecomposition itself)
-    own.template product<true, false>(acc, sV, sW, kdim, lane);
-    sync();
-    own.spill(acc, sW, lane);
-    sync();
-    // M: element (i, j) needs C_ij (own register), C_ji, lambda_i, lambda_j
+    {
+        const int j = own.col();
+        const float lj = sL[j], rj = sR[j];
+        // two to four tiles side by side: their chains of dependent instructions overlap
+        constexpr int V = NT % 4 == 0 ? 16 : NT % 3 == 0 ? 12 : 4 * ((NT + 1) / 2);
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
+        for (int t0 = 0; t0 < NT; t0 += V / 4) {
+            float li[V], ri[V], m[V];
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) {
-            const int j = 32 * own.col(tj) + (lane & 31);
-            const float lj = sL[j], rj = sR[j];
-            float li[16], ri[16], m[16];
+            for (int k = 0; k < V; k += 4) {
+                const floatx4 l4 = *reinterpret_cast<const floatx4*>(sL + own.row(min(t0 + k / 4, NT - 1), 0));
+                const floatx4 r4 = *reinterpret_cast<const floatx4*>(sR + own.row(min(t0 + k / 4, NT - 1), 0));
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = 32 * own.row(ti) + acc_row(v, lane);
-                li[v] = sL[i];
-                ri[v] = sR[i];
+                for (int v = 0; v < 4; ++v) li[k + v] = l4[v], ri[k + v] = r4[v];
             }
-            if (ed)
-                couplings(m, li, lj, ri, rj, [&](int v) { return j > 32 * own.row(ti) + acc_row(v, lane); }, args.mode, args.degree, args.param);
+            auto row = [&](int k) { return own.row(t0 + k / 4, k % 4); };
+            if (ed) couplings(m, li, lj, ri, rj, [&](int k) { return j > row(k); }, args.mode, args.degree, args.param);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = 32 * own.row(ti) + acc_row(v, lane);
-                const float cij = acc[ti][tj][v];
-                const float cji = sW[j * LD + i];
+            for (int k = 0; k < V; ++k) {
+                if (t0 + k / 4 >= NT) continue;
+                float x = c[t0 + k / 4][k % 4];
                 if (ed) {
-                    m[v] = (i == j) ? sGl[i] : 0.5f * m[v] * (cij - cji);
+                    x = row(k) == j ? sGl[j] : 0.5f * m[k] * x;
                 } else if (low) {
-                    m[v] = 0.5f * divided_difference(li[v], lj, args.mode, args.param) * (cij + cji);
+                    x *= divided_difference(li[k], lj, args.mode, args.param);
                 } else {
                     // every eigenvalue at or above the floor: the form without cancellation, from the roots
-                    const float phi = (args.mode == kGradSqrt) ? reciprocal(ri[v] + rj) : -reciprocal(ri[v] * rj * (ri[v] + rj));
-                    m[v] = 0.5f * phi * (cij + cji);
+                    x *= (args.mode == kGradSqrt) ? reciprocal(ri[k] + rj) : -reciprocal(ri[k] * rj * (ri[k] + rj));
                 }
-                acc[ti][tj][v] = i < n && j < n ? m[v] : 0.f;
+                c[t0 + k / 4][k % 4] = x;
             }
         }
-    sync();
-    own.spill(acc, sW, lane);
-    sync();
-    // U = V M
-    own.template product<false, false>(acc, sV, sW, kdim, lane);
-    sync();
-    own.spill(acc, sW, lane);
-    sync();
-    // g_A = U V^T
-    own.template product<false, true>(acc, sW, sV, kdim, lane);
-    float* __restrict__ Ob = args.g_A + (size_t)b * n * n;
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
+        for (int t = 0; t < NT; ++t)
+            if (own.edge(t))
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj)
+                for (int v = 0; v < 4; ++v) c[t][v] = own.inside(t, v) ? c[t][v] : 0.f;
+    }
+    __syncthreads();
+    own.put(sA, vc);
+    __syncthreads();
+    {
+        floatx4 u[NT] = {};
+        own.product(u, sA, c);
+        own.put(sB, u);
+    }
+    floatx4 vr[NT];                                   // V^T, this wavefront's columns
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = 32 * own.row(ti) + acc_row(v, lane);
-                const int j = 32 * own.col(tj) + (lane & 31);
-                if (i < n && j < n) Ob[i * n + j] = acc[ti][tj][v];
-            }
+    for (int t = 0; t < NT; ++t) vr[t] = own.left(sA, own.w, t);
+    __syncthreads();
+    own.store_symmetric(args.g_A + base, sB, vr, sA);
 }
 
-// The same for 32 < n <= 64 (larger n forms F in the kernel that decomposes), one wavefront per matrix.
-__global__ __launch_bounds__(64) void spectral_kernel(KernelArgs args) {
-    constexpr int NT = 2, NP = 32 * NT, LD = NP + 1;
-    __shared__ float sV[NP * LD];
-    __shared__ float sW[NP * LD];      // V f
-    __shared__ float sf[NP];
-    const int lane = threadIdx.x;
-    const int b = blockIdx.x;
-    const int n = args.n;
-    for (int idx = lane; idx < NP * LD; idx += 64) {
-        sV[idx] = 0.f;
-        sW[idx] = 0.f;
+// The same for 32 < n <= 64 (larger n forms F in the kernel that decomposes).
+template <int NT>
+__global__ __launch_bounds__(64 * NT, 2) void spectral_kernel(KernelArgs args) {
+    using S = Strip<NT>;
+    __shared__ __align__(16) float sV[S::NP * S::LD], turn[S::NP * S::LD];
+    __shared__ float sf[S::NP];
+    const int tid = threadIdx.x, n = args.n;
+    const S own(n);
+    const size_t base = (size_t)blockIdx.x * n * n;
+    floatx4 vc[NT], vr[NT];
+    own.load(vc, args.evecs + base);
+    if (tid < S::NP) {
+        const float x = fmaxf(tid < n ? args.evals[(size_t)blockIdx.x * n + tid] : 0.f, args.fn_floor);
+        sf[tid] = tid < n ? ((args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x)) : 0.f;
     }
-    {
-        const float x = fmaxf(lane < n ? args.evals[(size_t)b * n + lane] : 0.f, args.fn_floor);
-        sf[lane] = lane < n ? ((args.fn == kFnInvSqrt) ? __builtin_amdgcn_rsqf(x) : __builtin_amdgcn_sqrtf(x)) : 0.f;
+    own.put(sV, vc);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        vr[t] = own.left(sV, own.w, t);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) vr[t][v] *= sf[own.row(t, v)];
     }
-    wave_sync();
-    const float* __restrict__ Vb = args.evecs + (size_t)b * n * n;
-    const float rcp_n = 1.0f / (float)n;
-    chunked_copy<8>(
-        n * n, lane, [&](int idx) { return Vb[idx]; },
-        [&](int idx, float x) {
-            const int i = (int)(((float)idx + 0.5f) * rcp_n);
-            const int j = idx - i * n;
-            sV[i * LD + j] = x;
-            sW[i * LD + j] = x * sf[j];
-        });
-    wave_sync();
-    floatx16 acc[NT][NT];
-    Tiles<NT, 1>{0}.template product<false, true>(acc, sW, sV, (n + 7) & ~7, lane);
-    float* __restrict__ Fb = args.fn_out + (size_t)b * n * n;
-#pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < NT; ++tj)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = 32 * ti + acc_row(v, lane);
-                const int j = 32 * tj + (lane & 31);
-                if (i < n && j < n) Fb[i * n + j] = acc[ti][tj][v];
-            }
+    own.store_symmetric(args.fn_out + base, sV, vr, turn);
 }
 
 }  // namespace
@@ -570,7 +584,8 @@ hipError_t launch_spectral(const KernelArgs& args, hipStream_t stream) {
     if (n <= 8) return enqueue(tile_spectral_kernel<16, 8>, dim3((B + 1) / 2), dim3(64), stream, args);
     if (n <= 16) return enqueue(tile_spectral_kernel<16, 0>, dim3(B), dim3(64), stream, args);
     if (n <= 32) return enqueue(tile_spectral_kernel<32, 0>, dim3(B), dim3(64), stream, args);
-    if (n <= 64) return enqueue(spectral_kernel, dim3(B), dim3(64), stream, args);
+    if (n <= 48) return enqueue(spectral_kernel<3>, dim3(B), dim3(192), stream, args);
+    if (n <= 64) return enqueue(spectral_kernel<4>, dim3(B), dim3(256), stream, args);
     return hipErrorInvalidValue;
 }
 
@@ -583,8 +598,14 @@ hipError_t launch_grad(const GradArgs& args, hipStream_t stream) {
     if (n <= 16) return enqueue(tile_grad_kernel<16, 0>, dim3(B), dim3(64), stream, args);
     if (n <= 24) return enqueue(tile_grad_kernel<32, 0, 24>, dim3(B), dim3(64), stream, args);
     if (n <= 32) return enqueue(tile_grad_kernel<32, 0>, dim3(B), dim3(64), stream, args);
-    if (n <= 64) return enqueue(grad_kernel<2, 4>, dim3(B), dim3(256), stream, args);
-    return enqueue(grad_kernel<4, 8>, dim3(B), dim3(512), stream, args);
+    switch ((n + 15) / 16) {
+        case 3: return enqueue(grad_kernel<3>, dim3(B), dim3(192), stream, args);
+        case 4: return enqueue(grad_kernel<4>, dim3(B), dim3(256), stream, args);
+        case 5: return enqueue(grad_kernel<5>, dim3(B), dim3(320), stream, args);
+        case 6: return enqueue(grad_kernel<6>, dim3(B), dim3(384), stream, args);
+        case 7: return enqueue(grad_kernel<7>, dim3(B), dim3(448), stream, args);
+        default: return enqueue(grad_kernel<8>, dim3(B), dim3(512), stream, args);
+    }
 }
 
 }  // namespace bed
