@@ -11,6 +11,12 @@ namespace bed {
 
 namespace {
 
+// Up to 64 rows the first 32 columns of the reduction, by four wavefronts up to this batch, by one beyond: as many matrices as there are
+// compute units.  Then each SIMD has one of the four to itself; with more workgroups on a compute unit what all four repeat
+// competes with the other matrices.  us per launch, one wavefront / four: 256 x 64x64 64.2 / 60.0, eigenvalues 52.6 / 48.1, 256 x 36x36 eigenvalues
+// 41.1 / 36.5; 384 x 64x64 71.0 / 72.0, 512 x 36x36 55.6 / 56.7, 768 x 36x36 61.6 / 71.4, 768 x 64x64 79.1 / 89.7.
+constexpr int kTilesUpToBatch = 256;
+
 template <int N, bool WANT_V, int STAGE>
 __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(KernelArgs args) {
     constexpr int DT = 4 * N;                        // threads per matrix
@@ -27,6 +33,9 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
     // not in use before the divide and conquer
     ReflectorFactors<N>& factors = *reinterpret_cast<ReflectorFactors<N>*>(S.dz);
     StripExchange& strips = *reinterpret_cast<StripExchange*>(S.om);
+    TileExchange& tiles = *reinterpret_cast<TileExchange*>(S.om);
+    float (&tile_rows)[2][64] = *reinterpret_cast<float (*)[2][64]>(S.zs);
+    static_assert(sizeof(tiles) <= sizeof(S.om) && sizeof(tile_rows) <= sizeof(S.zs), "");
     static_assert(sizeof(factors) <= sizeof(S.dz) && (N == 64 || sizeof(strips) <= sizeof(S.om)), "");
 
     const int tid = threadIdx.x;
@@ -44,7 +53,10 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
         for (int w = 1; w < DT / 64; ++w) top = fmaxf(top, S.rn[w]);
         pow2_scale(top, scale, inv_scale);
         if constexpr (N == 64) {
-            if (wv == 0) tridiag_wave<LD>(R, R, factors, n, lane, scale, sd, se);
+            const bool tiled = args.batch <= kTilesUpToBatch;
+            TileState state;
+            if (tiled) tridiag_tiles<LD>(R, R, tiles, tile_rows, state, n, lane, __builtin_amdgcn_readfirstlane(wv), scale);
+            if (wv == (tiled ? 3 : 0)) tridiag_wave<LD>(R, R, factors, n, lane, scale, sd, se, tiled, state);
         } else {
             tridiag_strips<LD>(R, R, factors, strips, n, tid, scale, sd, se);
         }

@@ -6,9 +6,11 @@
 // symmetric): a lane adds up its own registers, then the lanes that share a column.  What bounds it is the
 // serial chain of a column, so the chain is cut short: row J + 1 is taken from the tiles BEFORE the update and
 // brought up to date beside the matrix instructions (a - u_J p - (p_J - 2K u_J) u, one or two entries per lane).  Up to 64
-// rows one wavefront does all of it, with one LDS round trip a column (u in the order of the tiles' rows) and no barrier; at
-// 128 rows four wavefronts own a strip of 32 columns each and exchange p and the next row, with ONE barrier a column: u^T p, the
-// row and its norm are formed by each of them, the same bits.
+// rows one wavefront does all of it, with one LDS round trip a column (u in the order of the tiles' rows) and no barrier, or, where the chip
+// has room, four wavefronts a tile each until one tile is left; at 128 rows four wavefronts own a strip of 32 columns each.  They exchange
+// p and the next row, with ONE barrier a column: u^T p, the row and its norm are formed by each of them, the same bits.
+// Matrix instructions in fp32 and multiply-adds of a wavefront do not overlap (64 cycles of a tile's update and 64 of its share of A u add up:
+// with the update one step late and off the chain, 64x64 took as long), so what shortens a column is fewer of both in a wavefront.
 // Finished rows and columns take part in the updates: what is left of them is T and rounding.
 // The reflectors stay behind as the rows of R and are applied to the eigenvectors of T after the divide and conquer,
 // sixteen at a time (compact WY form I - Y T Y^T, Schreiber and Van Loan 1989).
@@ -90,11 +92,100 @@ __device__ __forceinline__ void finish_column(const float* const R, ReflectorFac
     F.sigma[l] = H.active ? H.sigma : 0.f;
 }
 
+// 32 < n <= 64, the first 32 columns by four wavefronts, a tile each (tile row wv / 2, tile column wv % 2); lanes hold the entry `lane` of a
+// vector.  All four form u^T p, the row and its norm, the same bits, and exchange column sums and the next row, with one barrier a column.
+struct TileExchange {
+    float p[2][2][64];           // [step parity][tile row]: its share of A u by column
+};
+struct TileState {
+    dc_acc32 x{};                // the last tile
+    float a = 0.f, p = 0.f, un = 0.f, beta = 0.f, uJ = 0.f, dv = 0.f, av = 0.f;      // as in tridiag_wave
+};
+template <int LD>
+__device__ __forceinline__ void tridiag_tiles(const float* const stage, float* const R, TileExchange& S, float (&rows)[2][64],
+                                              TileState& out, const int n, const int lane, const int wv, const float scale) {
+    constexpr int LR = kReflectorStride<64>;
+    const int lo = lane & 31, hi = lane >> 5;
+    const int t = wv >> 1, j = wv & 1, c = 32 * j + lo;
+    dc_acc32 x;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = 32 * t + dc_row<32>(v, lane);
+        const float entry = stage[r * LD + c];                  // within the buffer also from n on
+        x[v] = (r < n && c < n) ? entry * scale : 0.f;
+    }
+    if (hi == 0) {
+        S.p[0][t][c] = 0.f;
+        if (t == 0) rows[0][c] = x[0];
+    }
+    __syncthreads();                                   // R may take the place of the matrix
+    float p = 0.f, a = 0.f, un = 0.f, beta = 0.f, uJ = 0.f;     // as in tridiag_wave
+    float dv = 0.f, av = 0.f;
+    for (int J0 = 0; J0 < 32; J0 += 8) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int J = J0 + s, par = s & 1;
+            p = beta * (S.p[par][0][lane] + S.p[par][1][lane]);
+            a = rows[par][lane];
+            const float K2 = -beta * wave_sum<64>(un * p);
+            const float wJ = fmaf(-K2, uJ, read_lane(p, J));
+            const float w = fmaf(K2, un, p);
+            const float r = fmaf(wJ, un, fmaf(-uJ, p, a));
+            const float row = lane > J ? r : 0.f;
+            // every wavefront writes the row, the same bits, and reads back what it wrote itself
+            R[J * LR + lane] = row;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const auto left = __builtin_amdgcn_permlane32_swap(__float_as_uint(un), __float_as_uint(w), false, false);
+            const auto right = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(un), false, false);
+            x = dc_mfma(__uint_as_float(t ? left[1] : left[0]), __uint_as_float(j ? right[1] : right[0]), x);
+            const float alpha = wave_sum<64>(row * row);
+            const Reflector H(alpha, read_lane(row, J + 1), Reflector::limit(J, n));
+            dv = lane == J ? r : dv;
+            av = lane == J ? alpha : av;
+            un = lane == J + 1 ? -H.first : -row;
+            beta = H.beta;
+            uJ = H.first;
+            const int sub = (s + 1) & 3, group = ((J + 1) >> 3) & 3;
+            float part[4] = {0.f, 0.f, 0.f, 0.f}, next = x[sub];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const dc_acc16 u = *reinterpret_cast<const dc_acc16*>(R + J * LR + 32 * t + 8 * q + 4 * hi);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) part[v] = fmaf(x[4 * q + v], u[v], part[v]);
+                next = q == group ? x[4 * q + sub] : next;
+            }
+            const unsigned bits = __float_as_uint(next);
+            const auto y = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+            const float up = __uint_as_float(y[((s + 1) >> 2) & 1]);
+            const unsigned half = __float_as_uint((part[0] + part[1]) + (part[2] + part[3]));
+            const auto z = __builtin_amdgcn_permlane32_swap(half, half, false, false);
+            const float sum = __uint_as_float(z[0]) + __uint_as_float(z[1]);
+            const bool here = ((J + 1) >> 5) == t;     // row J + 1 is one of this tile's
+            if (hi == 0) {
+                S.p[par ^ 1][t][c] = here ? fmaf(H.sigma, up, sum) : sum;    // u is row J of R with sigma added to entry J + 1
+                if (here) rows[par ^ 1][c] = up;
+            }
+            __syncthreads();
+        }
+    }
+    out.x = x;
+    out.p = beta * (S.p[0][0][lane] + S.p[0][1][lane]);
+    out.a = rows[0][lane];
+    out.un = un;
+    out.beta = beta;
+    out.uJ = uJ;
+    out.dv = dv;
+    out.av = av;
+}
+
 // One wavefront, n <= 64, a vector entry per lane.  stage: the symmetric matrix, stride LD; R may be the same memory and is
-// left with row J of R in row J (columns up to J zero).  sd, se: T.
+// left with row J of R in row J (columns up to J zero).  sd, se: T.  tiled: columns 32 and up only, from the state
+// that tridiag_tiles has left in the wavefront of the last tile.
 template <int LD>
 __device__ __forceinline__ void tridiag_wave(const float* const stage, float* const R, ReflectorFactors<64>& F, const int n,
-                                             const int lane, const float scale, float* const sd, float* const se) {
+                                             const int lane, const float scale, float* const sd, float* const se,
+                                             const bool tiled, const TileState& state) {
     constexpr int NS = 2, LR = kReflectorStride<64>;
     const int lo = lane & 31, hi = lane >> 5;
     auto sync = []() {
@@ -103,21 +194,27 @@ __device__ __forceinline__ void tridiag_wave(const float* const stage, float* co
     };
 
     dc_acc32 x[NS][NS];                                // x[t][j][v]: row 32 t + dc_row<32>(v, lane), column 32 j + lo
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-        for (int j = 0; j < NS; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 32 * t + dc_row<32>(v, lane), c = 32 * j + lo;
-                const float entry = stage[r * LD + c];          // within the buffer also from n on
-                x[t][j][v] = (r < n && c < n) ? entry * scale : 0.f;
-            }
-    const float top = stage[lane];
-    float a = lane < n ? top * scale : 0.f;            // row J before reflector J - 1
-    sync();                                            // R may take the place of the matrix
+    float a = 0.f;                                     // row J before reflector J - 1
     float p = 0.f, un = 0.f, beta = 0.f, uJ = 0.f;     // p, -u and 2/|u|^2 of reflector J - 1, u_J
     float dv = 0.f, av = 0.f;                          // diagonal of T, |x|^2 of the columns
+    if (tiled) {
+        x[1][1] = state.x;
+        a = state.a, p = state.p, un = state.un, beta = state.beta, uJ = state.uJ, dv = state.dv, av = state.av;
+    } else {
+#pragma unroll
+        for (int t = 0; t < NS; ++t)
+#pragma unroll
+            for (int j = 0; j < NS; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = 32 * t + dc_row<32>(v, lane), c = 32 * j + lo;
+                    const float entry = stage[r * LD + c];      // within the buffer also from n on
+                    x[t][j][v] = (r < n && c < n) ? entry * scale : 0.f;
+                }
+        const float top = stage[lane];
+        a = lane < n ? top * scale : 0.f;
+        sync();                                        // R may take the place of the matrix
+    }
 
     // columns 32 t0 and up are not finished; s, the step's place in the unrolled loop, names registers
     auto column = [&](const int J, const int s, const int t0) {
@@ -172,11 +269,13 @@ __device__ __forceinline__ void tridiag_wave(const float* const stage, float* co
         p = __uint_as_float(z[0]) + __uint_as_float(z[1]);
         p = beta * fmaf(H.sigma, a, p);                // u is row J of R with sigma added to entry J + 1
     };
-    const int first = min(n, 32);
-    for (int J0 = 0; J0 < first; J0 += 8) {
+    if (!tiled) {
+        const int first = min(n, 32);
+        for (int J0 = 0; J0 < first; J0 += 8) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-            if (J0 + s < first) column(J0 + s, s, 0);
+            for (int s = 0; s < 8; ++s)
+                if (J0 + s < first) column(J0 + s, s, 0);
+        }
     }
     for (int J0 = 32; J0 < n; J0 += 8) {
 #pragma unroll

@@ -1,0 +1,61 @@
+"""33 to 64 rows: the first columns of the reduction by four wavefronts up to batch 256, by one beyond."""
+import numpy as np
+import pytest
+
+from oracle import jacobi
+from oracle.acceptance import evaluate
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrices(n):
+    """Full rank, rank 3 n / 4, decaying, columns that are reduced already (diagonal, tridiagonal, blocks of the tiles), a last coupling across the tiles."""
+    rng = np.random.default_rng(n)
+    out = []
+    for samples, decay in ((4 * n, False), (3 * n // 4, False), (4 * n, True)):
+        X = rng.standard_normal((7, samples, n))
+        if decay:
+            X = X / np.arange(1, n + 1) @ np.linalg.qr(rng.standard_normal((n, n)))[0]
+        out += list(X.transpose(0, 2, 1) @ X / samples + 1e-3 * np.eye(n))
+    full = out[0]
+    r, c = np.indices((n, n))
+    out += [np.diag(np.diag(full)), np.where(abs(r - c) < 2, full, 0), np.where((r < 32) == (c < 32), full, 0),
+            np.where((r == c) | ((r == 31) & (c == 32)) | ((r == 32) & (c == 31)), full, 0), np.where((r < 32) & (c < 32), full, 0)]
+    return np.stack(out).astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [33, 34, 40, 47, 48, 63, 64])
+def test_both_ways_of_the_reduction(n):
+    import torch
+
+    import paper_2207_04228_amd as bed
+
+    A = _matrices(n)
+    lam_o, V_o = jacobi.syevd(A)
+    for batch in (256, 257):
+        many = np.resize(A, (batch, n, n))
+        assert bed.binding.bed_syevd_kernel(batch, n) == "dc_block_kernel<64>"
+        At = torch.from_numpy(many).cuda()
+        lam, V = bed.bed_syevd(At)
+        alone, _ = bed.bed_syevd(At, want_vectors=False)
+        lam, V, alone = lam.cpu().numpy(), V.cpu().numpy(), alone.cpu().numpy()
+        assert (lam == alone).all()                    # the same numbers without eigenvectors
+        acc = evaluate(A, lam[:len(A)], V[:len(A)], lam_o, V_o)
+        assert acc.passes(), (n, batch, acc.worst())
+        copies = batch // len(A) * len(A)              # every copy of a matrix is treated alike
+        assert (lam[:copies].reshape(-1, len(A), n) == lam[:len(A)]).all() and (V[:copies].reshape(-1, len(A), n, n) == V[:len(A)]).all()
+
+
+@pytest.mark.parametrize("n", [33, 64])
+def test_non_finite_entries(n):
+    """A matrix with a NaN or an infinity is all NaN, its neighbours are untouched."""
+    import torch
+
+    import paper_2207_04228_amd as bed
+
+    A = np.repeat(_matrices(n)[:1], 4, axis=0)
+    A[1, n - 1, 0] = np.nan
+    A[2, 33 if n > 33 else 32, 32] = np.inf
+    lam, V = (x.cpu().numpy() for x in bed.bed_syevd(torch.from_numpy(A).cuda()))
+    assert np.isnan(lam[1:3]).all() and np.isnan(V[1:3]).all()
+    assert np.isfinite(lam[[0, 3]]).all() and (lam[0] == lam[3]).all() and (V[0] == V[3]).all()
