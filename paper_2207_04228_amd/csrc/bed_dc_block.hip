@@ -4,7 +4,7 @@
 // The reflectors of the tridiagonalisation leave LDS before the divide and conquer and wait in registers (N / 4 of
 // them), so that the eigenvectors of T and of the merges have the two matrix-sized areas of LDS to themselves.  Then
 // they come back and are applied to V, sixteen columns per wavefront.  256 matrices, us per launch: 64x64 96 with P accumulated and leaves of
-// two rows, 65 now; 128x128 245, 160.
+// two rows, 60 now; 128x128 245, 148.
 #include "bed_tile_tridiag.hpp"
 
 namespace bed {
@@ -58,7 +58,10 @@ __global__ __launch_bounds__(4 * N, N == 64 ? 3 : 2) void dc_block_kernel(Kernel
             if (tiled) tridiag_tiles<LD>(R, R, tiles, tile_rows, state, n, lane, __builtin_amdgcn_readfirstlane(wv), scale);
             if (wv == (tiled ? 3 : 0)) tridiag_wave<LD>(R, R, factors, n, lane, scale, sd, se, tiled, state);
         } else {
-            tridiag_strips<LD>(R, R, factors, strips, n, tid, scale, sd, se);
+            if (n <= 96)
+                tridiag_strips<LD, 3>(R, R, factors, strips, n, tid, scale, sd, se);
+            else
+                tridiag_strips<LD, 4>(R, R, factors, strips, n, tid, scale, sd, se);
         }
         __syncthreads();
     }

@@ -151,6 +151,11 @@ Choice wave_choice(int n) {
 //   n = 43: batch 768: 0.42 0.55 0.60   n = 48: batch 1024: 0.64 0.83 0.94 (184 / 117)   n = 52: batch 1024: 0.60 0.78 0.84   n = 53: batch 1536: 0.55 0.74 0.82
 //   n = 56: batch 2048: 0.69 0.90 1.01   n = 64: batch 256: 0.24 0.32 0.35 (277 / 65)   2048: 0.39 0.51 0.56   n = 100: batch 64: 0.17 0.22 0.25 (761 / 133)
 //   n = 128: batch 256: 0.13 0.17 0.19 (1172 / 153)
+// With roots of third order, the reduction's factors as DPP operands and the tiles of the reduction shared, beyond the lines (event-bracketed loops):
+//   n = 12: batch 2560: 0.78 0.96 0.99   4096: 0.95 1.15 1.20   n = 14: batch 4096: 0.86 1.05 1.13   n = 16: batch 2560: 0.59 0.73 0.77 (41.3 / 24.5)
+//   4096: 0.70 0.90 0.95   6144: 0.78 0.96 1.07   16384: 1.07 1.36 1.42   n = 18: batch 4096: 0.84 1.00 1.07   n = 20: batch 4096: 0.74 0.91 0.93
+//   n = 24: batch 6144: 0.62 0.78 0.82   8192: 0.79 0.99 1.04   n = 26: batch 16384: 0.82 0.99 1.06   n = 40: batch 1536: 0.75 0.96 1.06
+//   n = 48: batch 1536: 0.58 0.78 0.84   2048: 0.78 1.01 1.13   n = 8 (registers for 8 rows): batch 512: 0.77 0.95 1.00   2560: 0.89 1.06 1.09
 bool divide_and_conquer(const KernelArgs& args, int stage, bool want_v, int forced) {
     if (forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
     if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;

@@ -7,7 +7,7 @@
 // serial chain of a column, so the chain is cut short: row J + 1 is taken from the tiles BEFORE the update and
 // brought up to date beside the matrix instructions (a - u_J p - (p_J - 2K u_J) u, one or two entries per lane).  Up to 64
 // rows one wavefront does all of it, with one LDS round trip a column (u in the order of the tiles' rows) and no barrier, or, where the chip
-// has room, four wavefronts a tile each until one tile is left; at 128 rows four wavefronts own a strip of 32 columns each.  They exchange
+// has room, four wavefronts a tile each until one tile is left; beyond 64 rows three or four wavefronts own a strip of 32 columns each.  They exchange
 // p and the next row, with ONE barrier a column: u^T p, the row and its norm are formed by each of them, the same bits.
 // Matrix instructions in fp32 and multiply-adds of a wavefront do not overlap (64 cycles of a tile's update and 64 of its share of A u add up:
 // with the update one step late and off the chain, 64x64 took as long), so what shortens a column is fewer of both in a wavefront.
@@ -286,21 +286,24 @@ __device__ __forceinline__ void tridiag_wave(const float* const stage, float* co
     sync();
 }
 
-// 64 < n <= 128: four wavefronts, a strip of 32 columns each; lanes hold the entries `lane` and `lane + 64` of a vector.
+// 64 < n <= 32 NS: NS = 3 or 4 wavefronts, a strip of 32 columns each; lanes hold the entries `lane` and `lane + 64` of a vector.  Up to 96
+// rows a fourth strip and tile row of zeros would cost 64 cycles of matrix instructions and 64 of multiply-adds a column: us per launch
+// with four / three strips, 256 x 80x80 110.9 / 102.6, 256 x 96x96 125 / 115, eigenvalues of 256 x 80x80 87.5 / 77.5.
 struct StripExchange {
     float p[2][128];             // [step parity]: A u by column
     float row[2][128];           // [step parity]: the next row
 };
-template <int LD>
+template <int LD, int NS>
 __device__ __forceinline__ void tridiag_strips(const float* const stage, float* const R, ReflectorFactors<128>& F,
                                                StripExchange& S, const int n, const int tid, const float scale,
                                                float* const sd, float* const se) {
-    constexpr int NS = 4, LR = kReflectorStride<128>;
+    constexpr int LR = kReflectorStride<128>;
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = lane & 31, hi = lane >> 5;
     const int c = 32 * wv + lo;                        // this lane's column
 
     if (wv >= NS) {                                    // the same number of barriers
+        if (wv == 3 && hi == 0) S.p[0][c] = S.p[1][c] = S.row[0][c] = S.row[1][c] = 0.f;       // the entries that nobody owns
         __syncthreads();
         for (int J = 0; J < n; ++J) __syncthreads();
         return;
@@ -351,11 +354,11 @@ __device__ __forceinline__ void tridiag_strips(const float* const stage, float* 
             const float right = __uint_as_float(odd ? cc[1] : cc[0]);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                if (2 * q + 1 >= t0) {
+                if (2 * q + 1 >= t0 && 2 * q < NS) {
                     const auto l = __builtin_amdgcn_permlane32_swap(__float_as_uint(un[q]), __float_as_uint(w[q]), false, false);
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
-                        if (2 * q + k >= t0) x[2 * q + k] = dc_mfma(__uint_as_float(l[k]), right, x[2 * q + k]);
+                        if (2 * q + k >= t0 && 2 * q + k < NS) x[2 * q + k] = dc_mfma(__uint_as_float(l[k]), right, x[2 * q + k]);
                 }
             }
         }

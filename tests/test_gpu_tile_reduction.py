@@ -1,4 +1,4 @@
-"""33 to 64 rows: the first columns of the reduction by four wavefronts up to batch 256, by one beyond."""
+"""The reduction of 33 to 128 rows in tiles: up to 64 rows the first columns by four wavefronts up to batch 256, by one beyond; more rows in strips."""
 import numpy as np
 import pytest
 
@@ -59,3 +59,20 @@ def test_non_finite_entries(n):
     lam, V = (x.cpu().numpy() for x in bed.bed_syevd(torch.from_numpy(A).cuda()))
     assert np.isnan(lam[1:3]).all() and np.isnan(V[1:3]).all()
     assert np.isfinite(lam[[0, 3]]).all() and (lam[0] == lam[3]).all() and (V[0] == V[3]).all()
+
+
+@pytest.mark.parametrize("n", [65, 79, 95, 96, 97, 127])
+def test_strips(n):
+    """65 to 96 rows in three strips of 32 columns, more in four."""
+    import torch
+
+    import paper_2207_04228_amd as bed
+
+    A = _matrices(n)
+    lam_o, V_o = jacobi.syevd(A)
+    At = torch.from_numpy(A).cuda()
+    lam, V = (x.cpu().numpy() for x in bed.bed_syevd(At))
+    alone = bed.bed_syevd(At, want_vectors=False)[0].cpu().numpy()
+    assert (lam == alone).all()
+    acc = evaluate(A, lam, V, lam_o, V_o)
+    assert acc.passes(), (n, acc.worst())
