@@ -17,6 +17,7 @@
 #ifndef BED_DC_HPP
 #define BED_DC_HPP
 #include "bed_wave_kernel.hpp"
+#include "bed_secular.hpp"
 
 namespace bed {
 
@@ -137,15 +138,6 @@ __device__ __forceinline__ bool dc_close(float dp, float dq, float zp, float zq,
 __device__ __forceinline__ float dc_rsqrt(float x) {
     const float r = __builtin_amdgcn_rsqf(x);
     return r * fmaf(-0.5f * x * r, r, 1.5f);
-}
-
-// Root of c x^2 - 2 a x + b that interpolates a root between the two poles (s = 1) or right of both (s = -1).
-__device__ __forceinline__ float dc_quadratic(float a, float b, float c, float s) {
-    const float disc = s * __builtin_amdgcn_sqrtf(fmaxf(fmaf(a, a, -b * c), 0.f));
-    const bool neg = s * a <= 0.f;
-    const float num = neg ? a - disc : b;
-    const float den = neg ? c : a + disc;
-    return num * __builtin_amdgcn_rcpf(den);
 }
 
 // Eigenvalues (S.D, by column) and eigenvectors (S.V) of the tridiagonal with entries dget(k), eget(k) (coupling k
@@ -478,39 +470,8 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
                     z2[c + i] = j + i == org ? 0.f : z2[c + i];
                 }
             }
-            float lb = last ? (fm < 0.f ? half : 0.f) : (right ? -half : 0.f);
-            float ub = last ? (fm < 0.f ? gap : half) : (right ? 0.f : half);
-            const float Do = (right || last ? p1.x : p2.x) - dorg;      // the other pole of the interpolation
-            const float rDo = __builtin_amdgcn_rcpf(Do);
-            const float sgn = last ? -1.f : 1.f;
-            // The root of c + s / (Do - x) - so / x = 0, where c + s / (Do - x) - (so - zo) / x has the value R, the derivative dR and half
-            // the second derivative hR that 1/rho and the terms of all poles but the origin have at `at` (Gragg 1965 for two poles;
-            // third order).  Every pole's share of s and of so - zo is positive, right of all poles excepted, where so = zo, exact,
-            // and Do takes the whole derivative.  Written in x and with `at` for Do - d, so that nothing cancels however near the
-            // root is to the origin.  Evaluations, largest of a level's roots, added over the levels, in float32 on the CPU, full-rank, decaying and
-            // rank-deficient covariances of 8 / 16 / 32 / 64 / 128 rows: fixed weight and middle way in turn (second order), from a start
-            // without derivatives, 4.1 / 8.3 / 13.9 / 19.1 / 25.8, this 2.8 / 5.8 / 9.2 / 13.5 / 17.7; of 6000 merges with random poles and weights
-            // down to 1e-12 none took more than 8 (before: 11).  us per launch: 512 x 32x32 35.1 -> 33.3, 16384 x 32x32 273 -> 261,
-            // 256 x 64x64 66.2 -> 64.1, 256 x 128x128 155 -> 151.
-            // From the start, where x is far from a root next to an origin of small weight, so - zo is left out if it swamps zo (24 rows of rank 18
-            // took 13.1 evaluations with it, 9.0 without, 12.6 before).
-            auto interpolate = [&](bool start, float at, float R, float dR, float hR) {
-                const float d = Do - at;
-                float side = fmaxf(at * fmaf(-d, hR, dR) * rDo, 0.f);                  // (so - zo) / at^2
-                if (start) side = side * at * at > 128.f * zo ? 0.f : side;
-                const float rest = fmaxf(dR - side, 0.f);
-                const float sa = side * at, rd = rest * d;
-                const float so = fmaf(sa, at, zo);
-                const float c = sa + (R - rd);
-                const float a = fmaf(Do, sa + R, fmaf(-rd, at, so));
-                return dc_quadratic(0.5f * a, so * Do, c, sgn);
-            };
-            {
-                const float at = right ? -half : half;
-                const float r = __builtin_amdgcn_rcpf(at), w = zo * r;              // less the term of the origin, -zo / at
-                const float x = interpolate(true, at, fm + w, fmaf(-w, r, dm), fmaf(w * r, r, hm));
-                mu = (x > lb && x < ub) ? x : 0.5f * (lb + ub);
-            }
+            // Do: the other pole of the interpolation
+            SecularRoot x(last, right, zo, (right || last ? p1.x : p2.x) - dorg, gap, fm, dm, hm);
             bool open = many;
             int it = 0;
             for (; it < kDcMaxIter && __ballot(open) != 0; ++it) {
@@ -520,7 +481,7 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
                     if (c * TPE < trip) {
 #pragma unroll
                         for (int i = c; i < c + 4; ++i) {
-                            const float r = __builtin_amdgcn_rcpf(dl[i] - mu);
+                            const float r = __builtin_amdgcn_rcpf(dl[i] - x.mu);
                             const float w = z2[i] * r, wr = w * r;
                             F += w;
                             mag += fabsf(w);
@@ -533,24 +494,10 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
                 mag = dc_sum<TPE>(mag);
                 dF = dc_sum<TPE>(dF);
                 hF = dc_sum<TPE>(hF);
-                const float own = zo * __builtin_amdgcn_rcpf(mu);
-                mag += fabsf(own) + rinv;
-                const float R = F + rinv;
-                F = R - own;
-                const float err = fmaf(2.3841858e-7f, mag, 5.9604645e-8f * fabsf(mu) * dF);
-                lb = F < 0.f ? mu : lb;
-                ub = F < 0.f ? ub : mu;
-                const float x = interpolate(false, mu, R, dF, hF);
-                const bool ok = x > lb && x < ub;               // mu is one of the two
-                // the next error is of the order of the cube of this step over the distance of the nearer pole: below 2^-9 of
-                // it the next step would be below the rounding of mu
-                const bool small = ok && fabsf(x - mu) <= 1.953125e-3f * fminf(fabsf(mu), fabsf(Do - mu));
-                const float y = ok ? x : 0.5f * (lb + ub);
-                const bool step = open && !(fabsf(F) <= err) && y > lb && y < ub;
-                mu = step ? y : mu;
-                open = step && !small;
+                open = x.step(open, rinv, F, mag, dF, hF);
             }
             if (it == kDcMaxIter) unresolved += (int)__builtin_popcountll(__ballot(open && part == 0));
+            mu = x.mu;
             if (root && !many) {
                 dorg = pk.x;
                 mu = rho * pk.y;
