@@ -50,7 +50,7 @@ __device__ __forceinline__ dc_acc16 dc_mfma(float a, float b, dc_acc16 c) {
 constexpr float kDcTol = 4.7683716e-7f;         // 8 units of rounding (2^-24)
 constexpr float kDcFloor = 9.5367432e-7f;       // poles below 2^-20 of the block's norm deflate by that
 constexpr float kDcTiny = 1.5258789e-5f;        // blocks below 2^-16 of the pre-scaled matrix deflate by that
-constexpr float kDcFar = 1.0e4f;                 // a pole beyond every eigenvalue of a block of norm one
+constexpr float kDcFar = 1.0e10f;               // a pole beyond every eigenvalue of a block, in units of its rho (poles stay below 1 / kDcTol)
 constexpr int kDcMaxIter = 60;                  // seven times what any root has been seen to take
 
 // N: rows covered (16, 32, 64, 128); TPE: threads per eigenvalue.
@@ -64,8 +64,8 @@ struct DcShared {
     // its 2^(L-1) merges has 5 to 8 poles (others 4, n = 17 .. 19, 33 .. 39, 65 .. 79), so 4 TPE entries each.
     static constexpr int NP = N * TPE / 2;
     alignas(16) float Dp[NP];            // by column: eigenvalues
-    alignas(16) float2 dz[NP];           // by slot (kept poles ascending, then the deflated ones): d in units of the block, z^2
-    alignas(16) float2 om[NP];           // by slot: the pole the root is measured from, and the distance, in units of the block
+    alignas(16) float2 dz[NP];           // by slot (kept poles ascending, then the deflated ones): d in units of the merge, z^2
+    alignas(16) float2 om[NP];           // by slot: the pole the root is measured from, and the distance, in units of the merge
     alignas(16) float2 zs[NP];           // by slot: z, and the offset of its row in U (as an integer)
     alignas(16) float2 fl[NP];           // by slot: entries of the first and last row
     float4 rot[N];                       // deflating rotations: two columns (as integers), cosine, sine
@@ -79,7 +79,7 @@ struct DcShared {
     float first[N], last[N];             // by column: first and last row of its block's eigenvectors
     float dS[N], zS[N];                  // sorted by d
     float dd[N];                         // by slot: d, also of deflated poles
-    float rho[N], za[N], zb[N];          // per coupling: weight of the rank-one term, its two sides in z (za from then on: the exponent of the merged block's unit, as an integer)
+    float rho[N], za[N], zb[N];          // per coupling: weight of the rank-one term, its two sides in z
     float rn[N + 2 * kTail];             // reciprocal norm of a column of U
     int perm[N];                         // sorted position -> column
     int src[N];                          // slot -> column
@@ -388,8 +388,8 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
         }
 
         // ---- slots: kept poles in ascending order, then the deflated ones ----
-        // From here to the eigenvalues the block is in units of a power of two that takes its norm to [0.5, 1): the poles that deflation
-        // leaves are then at least 2e-13 apart, and the third power of a distance is a number.  In units of the matrix they may be
+        // From here to the eigenvalues the merge is in units of a power of two that takes rho to [0.5, 1): the poles that deflation leaves are
+        // then below 2.1e6 and at least 4e-13 apart, and the third power of a distance is a number.  In units of the matrix they may be
         // 1e-17 apart; merges of blocks of 1e-9 to 1e-12 of it, whose third powers overflowed, took up to 50 evaluations of bisections instead of 6
         // (256 matrices, us per launch: 32x32 with such a block 42.6, 64x64 81.7; without 26, 57).
         const int K = kept.below(hi) - kept.below(lo);
@@ -399,8 +399,7 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
             const int slot = in ? before : K + k - before;
             const float d = S.dS[e], z = S.zS[e];
             const int col = S.perm[e];
-            const int unit = __builtin_amdgcn_frexp_expf(fmaxf(fmaxf(fabsf(S.dS[lo]), fabsf(S.dS[hi - 1])), S.rho[mid - 1]));
-            S.za[mid - 1] = __int_as_float(unit);
+            const int unit = __builtin_amdgcn_frexp_expf(S.rho[mid - 1]);
             S.dz[base + slot] = in ? make_float2(ldexpf(d, -unit), z * z) : make_float2(kDcFar, 0.f);
             S.zs[base + slot] = make_float2(in ? z : 0.f, __int_as_float(col * LD));
             S.dd[lo + slot] = d;
@@ -422,8 +421,9 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
         float dl[PP], z2[PP];               // distances from the origin of the root, squares of z
         {
             const float2* const pz = S.dz + base;
-            const int unit = valid ? __float_as_int(S.za[mid - 1]) : 0;
-            const float rho = valid ? ldexpf(S.rho[mid - 1], -unit) : 1.f;
+            const float weight = valid ? S.rho[mid - 1] : 1.f;
+            const int unit = __builtin_amdgcn_frexp_expf(weight);
+            const float rho = __builtin_amdgcn_frexp_mantf(weight);
             const float rinv = __builtin_amdgcn_rcpf(rho);
             const bool many = root && K > 1;
             const int i1 = many ? min(k, K - 2) : 0;

@@ -1,4 +1,4 @@
-"""Merges of the divide and conquer whose block is far smaller than the matrix: a root's iteration runs in units of the block, so the
+"""Merges of the divide and conquer whose block is far smaller than the matrix: a root's iteration runs in units of the merge (its rho), so the
 smallest distance that deflation leaves (about 1e-17 of the matrix) has a third power, and a block's size costs no evaluations."""
 import numpy as np
 import pytest
