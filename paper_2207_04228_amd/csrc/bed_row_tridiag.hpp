@@ -35,13 +35,16 @@ struct Spread {
 
 // The multiply-adds with an entry of a Spread for one factor, columns FIRST .. N-1, as assembly: the compiler folds no DPP move into a
 // multiply-add.  FIRST selects the columns while the text is assembled.  The s_nop is the wait between a write of lo or hi and its
-// use by another lane, which the compiler cannot see to here.
+// use by another lane, which the compiler cannot see to here.  Nor can it see how far in front of the block's end an x[c] was written, and what
+// another lane reads next is x[FIRST] (a move between halves, a v_readlane: two waits at most): the columns behind it stand in between, and the
+// last block, which has one, ends with the wait.
 #define BED_COL(c, insn) ".if %c[first] <= " #c "\n\t" insn " row_newbcast:" #c "-16*(" #c "/16) row_mask:0xf bank_mask:0xf\n\t.endif\n\t"
 #define BED_AXPY(c, half) BED_COL(c, "v_fmac_f32_dpp %[x" #c "], %[" #half "], %[f]")
 #define BED_DOT(c, half, p)                                                       \
     ".if %c[first] <= " #c " && " #c " < %c[first]+4 && %c[first]+4 <= %c[n]\n\t" \
     "v_mul_f32_dpp %[p" #p "], %[" #half "], %[x" #c "] row_newbcast:" #c "-16*(" #c "/16) row_mask:0xf bank_mask:0xf\n\t.else\n\t" \
     BED_COL(c, "v_fmac_f32_dpp %[p" #p "], %[" #half "], %[x" #c "]") ".endif\n\t"
+#define BED_LAST ".if %c[first]+2 == %c[n]\n\ts_nop 1\n\t.endif\n\t"
 #define BED_FOUR(op_, a, b, c, d) op_(a) op_(b) op_(c) op_(d)
 #define BED_AL(c) BED_AXPY(c, lo)
 #define BED_AH(c) BED_AXPY(c, hi)
@@ -75,7 +78,9 @@ struct Spread {
     template <int FIRST>                                                                                                         \
     __device__ __forceinline__ void row_axpy(float (&x)[N_], const Spread<N_>& s, float f) {                                     \
         static_assert(FIRST + 2 <= N_, "");                                                                                      \
-        asm("s_nop 1\n\t" BED_AXPY##N_ : BED_X##N_("+v") : [lo] "v"(s.lo), [hi] "v"(s.hi), [f] "v"(f), [first] "n"(FIRST));      \
+        asm("s_nop 1\n\t" BED_AXPY##N_ BED_LAST                                                                                  \
+            : BED_X##N_("+v")                                                                                                    \
+            : [lo] "v"(s.lo), [hi] "v"(s.hi), [f] "v"(f), [first] "n"(FIRST), [n] "n"(N_));                                      \
     }                                                                                                                            \
     template <int FIRST>                                                                                                         \
     __device__ __forceinline__ float row_dot(const float (&x)[N_], const Spread<N_>& s) {                                        \
