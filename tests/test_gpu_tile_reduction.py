@@ -46,19 +46,25 @@ def test_both_ways_of_the_reduction(n):
         assert (lam[:copies].reshape(-1, len(A), n) == lam[:len(A)]).all() and (V[:copies].reshape(-1, len(A), n, n) == V[:len(A)]).all()
 
 
-@pytest.mark.parametrize("n", [33, 64])
-def test_non_finite_entries(n):
-    """A matrix with a NaN or an infinity is all NaN, its neighbours are untouched."""
+@pytest.mark.parametrize("batch", [4, 260])
+@pytest.mark.parametrize("n", [33, 48, 64])
+def test_non_finite_entries(n, batch):
+    """A matrix with a NaN or an infinity is all NaN, its neighbours are untouched; in the first columns and in the last tile."""
     import torch
 
     import paper_2207_04228_amd as bed
 
-    A = np.repeat(_matrices(n)[:1], 4, axis=0)
-    A[1, n - 1, 0] = np.nan
-    A[2, 33 if n > 33 else 32, 32] = np.inf
-    lam, V = (x.cpu().numpy() for x in bed.bed_syevd(torch.from_numpy(A).cuda()))
-    assert np.isnan(lam[1:3]).all() and np.isnan(V[1:3]).all()
-    assert np.isfinite(lam[[0, 3]]).all() and (lam[0] == lam[3]).all() and (V[0] == V[3]).all()
+    A = np.repeat(_matrices(n)[:1], batch, axis=0)
+    A[1::4, n - 1, 0] = np.nan
+    A[2::4, 33 if n > 33 else 32, 32] = np.inf
+    At = torch.from_numpy(A).cuda()
+    lam, V = (x.cpu().numpy() for x in bed.bed_syevd(At))
+    info = bed.bed_syevd_info(At, want_rotations=False)[2].cpu().numpy()
+    lost = np.isin(np.arange(batch) % 4, (1, 2))
+    assert np.isnan(lam[lost]).all() and np.isnan(V[lost]).all() and (info[lost] == n).all()
+    assert np.isfinite(lam[~lost]).all() and (lam[~lost] == lam[0]).all() and (V[~lost] == V[0]).all() and (info[~lost] == 0).all()
+    alone = bed.bed_syevd(At, want_vectors=False)[0].cpu().numpy()
+    assert np.array_equal(alone, lam, equal_nan=True)
 
 
 @pytest.mark.parametrize("n", [65, 79, 95, 96, 97, 127])
