@@ -82,7 +82,6 @@ struct DcShared {
     float rho[N], za[N], zb[N];          // per coupling: weight of the rank-one term, its two sides in z
     float rn[N + 2 * kTail];             // reciprocal norm of a column of U
     int perm[N];                         // sorted position -> column
-    int src[N];                          // slot -> column
     int nrot[N];                         // rotations of the block that starts here
     int unresolved;                      // T > 64: sum of the wavefronts' counts
 };
@@ -215,7 +214,6 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
     if (part == 0) {
         S.rn[e] = 1.f;
         S.perm[e] = e;
-        S.src[e] = e;
         if (!valid) S.first[e] = S.last[e] = 0.f;
     }
     sync();
@@ -403,7 +401,6 @@ __device__ __forceinline__ int dc_solve(DcShared<N, T / N, WANT_V>& S, const int
             S.dz[base + slot] = in ? make_float2(ldexpf(d, -unit), z * z) : make_float2(kDcFar, 0.f);
             S.zs[base + slot] = make_float2(in ? z : 0.f, __int_as_float(col * LD));
             S.dd[lo + slot] = d;
-            S.src[lo + slot] = col;
             S.fl[base + slot] = make_float2(S.first[col], S.last[col]);
             for (int i = k + m; i < Mp; i += m) {
                 S.dz[base + i] = make_float2(kDcFar, 0.f);

@@ -147,10 +147,6 @@ __device__ __forceinline__ float dpp_full(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 
-// The value of lane K of each row of 16 lanes, in that row.
-template <int K>
-__device__ __forceinline__ float row_newbcast(float x) { return dpp_full<0x150 + K>(x); }
-
 // Every lane receives the value lane (i & 31) holds.
 __device__ __forceinline__ float lower_to_both(float x) {
     const unsigned u = __float_as_uint(x);
