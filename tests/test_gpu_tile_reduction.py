@@ -5,6 +5,8 @@ import pytest
 from oracle import jacobi
 from oracle.acceptance import evaluate
 
+from test_gpu_divide_and_conquer import _structured
+
 pytestmark = pytest.mark.gpu
 
 
@@ -24,13 +26,13 @@ def _matrices(n):
     return np.stack(out).astype(np.float32)
 
 
-@pytest.mark.parametrize("n", [33, 34, 40, 47, 48, 63, 64])
+@pytest.mark.parametrize("n", range(33, 65))
 def test_both_ways_of_the_reduction(n):
     import torch
 
     import paper_2207_04228_amd as bed
 
-    A = _matrices(n)
+    A = np.concatenate([_matrices(n), _structured(n, n)])
     lam_o, V_o = jacobi.syevd(A)
     for batch in (256, 257):
         many = np.resize(A, (batch, n, n))
