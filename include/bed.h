@@ -75,6 +75,10 @@ typedef enum {
  * per row; the root finder of divide and conquer is capped too), a NaN/Inf
  * input yields NaNs for that matrix only.  bed_syevd_info reports both: with
  * rotations = NULL it runs the kernel that bed_syevd runs.
+ *
+ * A call repeated gives the same bits, and so do equal matrices of one call.  The kernel, and the order of its
+ * sums, are chosen from n, batch and what is asked for (bed_syevd_kernel; 33 to 64 rows also turn at batch 256
+ * within one kernel), so the last bits of a matrix's result may depend on how many others are in the call.
  */
 int bed_syevd(const float* A, int batch, int n, float* evals, float* evecs,
               void* stream);

@@ -11,9 +11,9 @@ namespace bed {
 
 namespace {
 
-// Up to 64 rows the first 32 columns of the reduction, by four wavefronts up to this batch, by one beyond: as many matrices as there are
-// compute units.  Then each SIMD has one of the four to itself; with more workgroups on a compute unit what all four repeat
-// competes with the other matrices.  us per launch, one wavefront / four: 256 x 64x64 64.2 / 60.0, eigenvalues 52.6 / 48.1, 256 x 36x36 eigenvalues
+// Up to 64 rows the first 32 columns of the reduction, by four wavefronts up to this batch, by one beyond: as many matrices as this chip
+// has compute units (a number measured here, not asked of the device).  Then each SIMD has one of the four to itself; with more workgroups on
+// a compute unit what all four repeat competes with the other matrices.  The two add the tiles' shares of A u in different orders: other last bits.  us per launch, one wavefront / four: 256 x 64x64 64.2 / 60.0, eigenvalues 52.6 / 48.1, 256 x 36x36 eigenvalues
 // 41.1 / 36.5; 384 x 64x64 71.0 / 72.0, 512 x 36x36 55.6 / 56.7, 768 x 36x36 61.6 / 71.4, 768 x 64x64 79.1 / 89.7.
 constexpr int kTilesUpToBatch = 256;
 

@@ -156,6 +156,8 @@ Choice wave_choice(int n) {
 //   4096: 0.70 0.90 0.95   6144: 0.78 0.96 1.07   16384: 1.07 1.36 1.42   n = 18: batch 4096: 0.84 1.00 1.07   n = 20: batch 4096: 0.74 0.91 0.93
 //   n = 24: batch 6144: 0.62 0.78 0.82   8192: 0.79 0.99 1.04   n = 26: batch 16384: 0.82 0.99 1.06   n = 40: batch 1536: 0.75 0.96 1.06
 //   n = 48: batch 1536: 0.58 0.78 0.84   2048: 0.78 1.01 1.13   n = 8 (registers for 8 rows): batch 512: 0.77 0.95 1.00   2560: 0.89 1.06 1.09
+// Their means are below one, but for n = 12 at 4096 (1.04) and n = 16 at 16384 (1.20): the two sides turn beyond the lines, above batch 6144 for
+// 16 rows, 8192 for 24, 2048 for 48.  The lines below are those of the first figures and have not been moved.
 bool divide_and_conquer(const KernelArgs& args, int stage, bool want_v, int forced) {
     if (forced != kFamilyAuto || (stage != kFull && stage != kSpectral)) return false;
     if (args.rotations || args.abs_eps > 0.f || args.sweep_cap) return false;

@@ -15,8 +15,8 @@
 // The reflectors stay behind as the rows of R and are applied to the eigenvectors of T after the divide and conquer,
 // sixteen at a time (compact WY form I - Y T Y^T, Schreiber and Van Loan 1989).
 // The form before this one updated P beside A, in half of the wavefronts, with two barriers a column.
-// Cycles from load to the end of the reduction, one matrix per compute unit: 64x64 130 k, 128x128 364 k; now 73 k and 174 k, and 5 k and
-// 8 k for the blocks of T.  A column costs 850 cycles with one tile left, 1270 with four (n <= 64) or in strips (128): 130 to 170
+// Cycles from load to the end of the reduction, one matrix per compute unit: 64x64 130 k, 128x128 364 k; now 62 k (four wavefronts; one alone,
+// two matrices per compute unit: 75 k) and 171 k, and 5 k and 8 k for the blocks of T.  A column costs 850 cycles with one tile left, 1270 with four (n <= 64) or in strips (128): 130 to 170
 // instructions at 7.4 cycles, two sums over the wavefront, one LDS round trip and the matrix instructions in a chain.
 #ifndef BED_TILE_TRIDIAG_HPP
 #define BED_TILE_TRIDIAG_HPP
