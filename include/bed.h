@@ -76,9 +76,9 @@ typedef enum {
  * input yields NaNs for that matrix only.  bed_syevd_info reports both: with
  * rotations = NULL it runs the kernel that bed_syevd runs.
  *
- * A call repeated gives the same bits, and so do equal matrices of one call.  The kernel, and the order of its
- * sums, are chosen from n, batch and what is asked for (bed_syevd_kernel; 33 to 64 rows also turn at batch 256
- * within one kernel), so the last bits of a matrix's result may depend on how many others are in the call.
+ * A call repeated gives the same bits.  The kernel, and the order of its sums, are chosen from n, batch and what
+ * is asked for (bed_syevd_kernel; 33 to 64 rows also turn at batch 256 within one kernel), so the last bits of a
+ * matrix's result may depend on how many others are in the call.
  */
 int bed_syevd(const float* A, int batch, int n, float* evals, float* evecs,
               void* stream);
